@@ -204,11 +204,14 @@ int hk_read_par(const char* path, int64_t first, int32_t molecule, const hk_line
  * floor((nu0' + cutoff - nu_min)/dnu)].  H_V(a,u) uses the series form of
  * the Faddeeva function for a^2+u^2 < 100 and 3-node / 1-node Gauss-Hermite
  * quadrature for a^2+u^2 < 1e6 / >= 1e6 (§2.4).  Each point sums its
- * Gauss-Hermite terms, then its series terms, each in ascending (nu, input
- * index) order, with no atomics; where the lines crowd into few grid tiles
- * (a wavenumber-ordered piece of a list, a dense band) the Gauss-Hermite sum
- * is split at fixed line-index segments whose ordered sums are then added in
- * segment order.  Results are bitwise reproducible, do not depend on the
+ * Gauss-Hermite terms, then its series terms, each in an order fixed by the
+ * list and the grid (binary32, and the series: ascending (nu, input index)),
+ * with no atomics; where the lines crowd into few grid tiles (a
+ * wavenumber-ordered piece of a list, a dense band) the Gauss-Hermite sum is
+ * split at fixed line-index segments whose sums are then added in segment
+ * order.  In binary64 a line's Gauss-Hermite terms over a tile of points far
+ * from it are interpolated from Chebyshev nodes of the tile, to below 4e-17
+ * of each term.  Results are bitwise reproducible, do not depend on the
  * tuning options, and agree bit for bit with hk_tables.
  *
  * kappa is [device] double[n_points] for both precisions.  comp must be
@@ -319,9 +322,9 @@ int hk_kdist_noalloc(hk_ctx* ctx, const void* kappa, int precision, int64_t n_po
  * (0, the default) as many as fit in "tables_mem_mib".  Each batch's work
  * plan is read back once to size its launches (one stream synchronisation
  * per batch).  On the first call for a (precision, line count, grid size,
- * cutoff/dnu) the wing tile shape is chosen by timing 2, 4 and 8 points per
- * lane on up to four states ("tables_autotune", synchronises the stream
- * once); the shapes give identical results.  precision: HK_F64 or
+ * cutoff/dnu) the binary32 wing tile shape is chosen by timing 2, 4 and 8
+ * points per lane on up to four states ("tables_autotune", synchronises the
+ * stream once); the shapes give identical results.  precision: HK_F64 or
  * HK_F32_KAHAN (cutoff/dnu < 2^23).  Errors: HK_EINVAL (argument, with the
  * index of a bad state), HK_ENOTREADY (no line list), HK_ENOMEM/HK_EDEVICE.
  * hk_stats afterwards reports the evaluation counts summed over the states. */
@@ -444,9 +447,8 @@ int hk_surrogate_load(hk_ctx* ctx, const void* blob, size_t size);
 int hk_gauss_legendre(int32_t n, double* g, double* w);
 
 /* Tuning knobs (results do not depend on them; only speed and memory do):
- *   "f64_points_per_lane"  4 or 8 grid points per lane in the binary64
- *                          opacity kernel (default 4; its points form groups
- *                          of four that share one reciprocal).
+ *   "f64_points_per_lane"  4 (default) or 8; kept for callers that set it:
+ *                          the binary64 kernel has one shape per grid size.
  *   "f32_points_per_lane"  2, 4 or 8 for the binary32 kernel (default 4).
  *   "tables_batch"         states per hk_tables launch, 0 = automatic
  *                          (default).
@@ -455,7 +457,7 @@ int hk_gauss_legendre(int32_t n, double* g, double* w);
  *   "tables_autotune"      1 (default): hk_tables times the tile shapes;
  *                          0: it uses the *_points_per_lane setting and the
  *                          cached choices are dropped.
- *   "wing_edge_paths"      1 (default): the Gauss-Hermite kernels take a
+ *   "wing_edge_paths"      1 (default): the binary32 Gauss-Hermite kernel takes a
  *                          wavefront's run that a line's window covers only
  *                          in part on that rule's own path with a window
  *                          mask, and runs that hold series points or both

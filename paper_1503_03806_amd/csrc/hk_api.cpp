@@ -94,6 +94,7 @@ struct hk_ctx {
     int64_t lds_bytes = kSortLdsBytes;  // LDS a sort workgroup may use
     int64_t lds_max = 65536;            // the device's LDS per workgroup (the radix sorts)
     void* noalloc_scratch = nullptr;    // this device's hk_kdist_noalloc array
+    DevBuf wing_tab;                    // the binary64 wing's interpolation matrices
     std::string err;
     // line list, ascending (nu, index)
     int64_t n_lines = 0;
@@ -134,7 +135,7 @@ struct hk_ctx {
     int tables_overlap = 0;       // 1: tables run the series beside the wing on the second stream
     // batched tables: per-state records, ranges and sums of one batch, the
     // per-state evaluation counters of the last call, and the tile shapes
-    // chosen by timing, per (precision, lines, points, cutoff/dnu)
+    // chosen by timing, per (lines, points, cutoff/dnu)
     DevBuf tb_idx, tb_wing, tb_core, tb_w32, tb_c32, tb_ranges, tb_ranges_c, tb_out, tb_comp, tb_scale, tb_kappa,
         tb_counts, tb_series, tb_prep;
     int64_t tables_batch = 0;  // states per launch; 0 = as many as fit in tables_mem
@@ -142,8 +143,7 @@ struct hk_ctx {
     int tables_autotune = 1;
     int32_t last_tables_states = 0;  // > 0: hk_stats reports that hk_tables call
     int tables_ppl_used = 0;          // tile shape of the last hk_tables call
-    struct Tuned {
-        int precision;
+    struct Tuned {  // binary32
         int64_t n_lines, n_points, cut_steps;
         int ppl;
     };
@@ -657,8 +657,8 @@ constexpr int64_t kPlanBoundBytes = (int64_t)1 << 30;
 // kPlanBoundBytes: read the totals back (one host synchronisation) for
 // *items and the partial sums; else their bounds.
 int make_plan(hk_ctx* ctx, PlanBufs& pb, const int64_t* ranges, int64_t n_tiles, int32_t n_states,
-              const double* reach, int32_t tp, int64_t min_seg, const hk_grid* grid, bool exact, WorkPlan* wp,
-              hipStream_t strm, const double* reach_dev = nullptr)
+              const double* reach, int32_t tp, int64_t min_seg, int64_t busy_min, const hk_grid* grid, bool exact,
+              WorkPlan* wp, hipStream_t strm, const double* reach_dev = nullptr)
 {
     const int64_t n = ctx->n_lines;
     const int32_t np = (int32_t)grid->n_points;
@@ -686,7 +686,7 @@ int make_plan(hk_ctx* ctx, PlanBufs& pb, const int64_t* ranges, int64_t n_tiles,
             HK_HIP(ctx, launch_tile_ranges(nu, n, n_ref, kRefTilePoints, grid->nu_min, grid->dnu, np, reach[s],
                                            ref + (int64_t)s * 2 * n_ref, strm),
                    "tile_ranges");
-    HK_HIP(ctx, launch_seg_length(ref, n_ref, n_states, np, n, min_seg, seg, strm), "seg_length");
+    HK_HIP(ctx, launch_seg_length(ref, n_ref, n_states, np, n, min_seg, busy_min, seg, strm), "seg_length");
     HK_HIP(ctx, launch_work_plan(ranges, n_tiles, n_states, seg, first, slot, static_cast<int64_t*>(pb.bsum.p), total,
                                  strm),
            "work_plan");
@@ -704,34 +704,23 @@ int make_plan(hk_ctx* ctx, PlanBufs& pb, const int64_t* ranges, int64_t n_tiles,
     return HK_OK;
 }
 
-// The wing stage of n_states states whose records lie n_lines apart: the
-// plan, then the wing items and the reduction of cut tiles.  ranges: tile
+// The binary32 wing stage of n_states states whose records lie n_lines apart:
+// the plan, then the wing items and the reduction of cut tiles.  ranges: tile
 // ranges for tiles of `ppl` points per lane; reach[s]: state s's wing reach;
-// out: kappa (binary64) or the Kahan sums (binary32, with comp), n_points
-// per state.
-int wing_stage(hk_ctx* ctx, int precision, int ppl, const void* recs, const WingIdx* idx, const int64_t* ranges,
-               int64_t n_tiles, int32_t n_states, const double* reach, const hk_grid* grid, void* out, float* comp,
-               int accumulate, bool exact)
+// sum, comp: the Kahan pairs, n_points per state.
+int wing_stage_f32(hk_ctx* ctx, int ppl, const WingRec32* recs, const WingIdx* idx, const int64_t* ranges,
+                   int64_t n_tiles, int32_t n_states, const double* reach, const hk_grid* grid, float* sum,
+                   float* comp)
 {
-    const bool f64 = precision == HK_F64;
-    const int32_t tp = f64 ? opacity_f64_tile_points(ppl) : opacity_f32_tile_points(ppl);
     WorkPlan wp;
-    // binary32: segments of whole 256-line compensation blocks
-    if (int rc = make_plan(ctx, ctx->ln.wplan, ranges, n_tiles, n_states, reach, tp, f64 ? 64 : 256, grid, exact, &wp,
-                           ctx->stream))
+    // segments of whole 256-line compensation blocks
+    if (int rc = make_plan(ctx, ctx->ln.wplan, ranges, n_tiles, n_states, reach, opacity_f32_tile_points(ppl), 256,
+                           kBusyMin, grid, false, &wp, ctx->stream))
         return rc;
-    const int64_t n = ctx->n_lines;
-    const int32_t np = (int32_t)grid->n_points;
-    if (f64)
-        HK_HIP(ctx, launch_wing_f64(ppl, static_cast<const WingRec*>(recs), idx, ranges, n, n_tiles, n_states, wp,
-                                    grid->nu_min, grid->dnu, np, static_cast<double*>(out),
-                                    static_cast<double*>(ctx->ln.wplan.partial.p), accumulate, ctx->wing_edge_paths, ctx->stream),
-               "wing_f64");
-    else
-        HK_HIP(ctx, launch_wing_f32(ppl, static_cast<const WingRec32*>(recs), idx, ranges, n, n_tiles, n_states, wp,
-                                    np, static_cast<float*>(out), comp,
-                                    static_cast<float2*>(ctx->ln.wplan.partial.p), ctx->wing_edge_paths, ctx->stream),
-               "wing_f32");
+    HK_HIP(ctx, launch_wing_f32(ppl, recs, idx, ranges, ctx->n_lines, n_tiles, n_states, wp, (int32_t)grid->n_points,
+                                sum, comp, static_cast<float2*>(ctx->ln.wplan.partial.p), ctx->wing_edge_paths,
+                                ctx->stream),
+           "wing_f32");
     return HK_OK;
 }
 
@@ -755,12 +744,11 @@ int reset_surrogate_count(hk_ctx* ctx)
     return HK_OK;
 }
 
-// Times the batched wing kernel at 2, 4 and 8 points per lane on the first
-// states of a batch (one untimed launch, then one timed launch each) and
-// returns the fastest shape.  The shapes give identical results, so the
-// choice affects time only.
-int autotune_wing(hk_ctx* ctx, int precision, const hk_state* states, int32_t n_try, const hk_grid* grid,
-                  int* best_out)
+// Times the batched binary32 wing kernel at 2, 4 and 8 points per lane on
+// the first states of a batch (one untimed launch, then one timed launch
+// each) and returns the fastest shape.  The shapes give identical results,
+// so the choice affects time only.  (The binary64 wing has one shape.)
+int autotune_wing(hk_ctx* ctx, const hk_state* states, int32_t n_try, const hk_grid* grid, int* best_out)
 {
     const int64_t n = ctx->n_lines;
     const int32_t np = (int32_t)grid->n_points;
@@ -777,8 +765,7 @@ int autotune_wing(hk_ctx* ctx, int precision, const hk_state* states, int32_t n_
     std::vector<double> reach((size_t)n_try);
     for (int32_t s = 0; s < n_try; ++s) reach[(size_t)s] = wing_reach(ctx, &states[s], grid);
     for (int cand : {2, 4, 8}) {
-        if (precision == HK_F64 && cand == 2) continue;  // binary64 groups points by four
-        const int32_t tp = precision == HK_F64 ? opacity_f64_tile_points(cand) : opacity_f32_tile_points(cand);
+        const int32_t tp = opacity_f32_tile_points(cand);
         const int64_t n_tiles = ((int64_t)np + tp - 1) / tp;
         err = ctx->tb_ranges.ensure((size_t)std::max<int64_t>(n_tiles * n_try, 1) * 2 * sizeof(int64_t));
         if (err != hipSuccess) break;
@@ -791,10 +778,10 @@ int autotune_wing(hk_ctx* ctx, int precision, const hk_state* states, int32_t n_
         for (int rep = 0; rep < 2 && err == hipSuccess; ++rep) {
             if (rep == 1) err = hipEventRecord(e0, ctx->stream);
             if (err != hipSuccess) break;
-            const void* recs = precision == HK_F64 ? ctx->tb_wing.p : ctx->tb_w32.p;
-            if (int rc = wing_stage(ctx, precision, cand, recs, static_cast<WingIdx*>(ctx->tb_idx.p), ranges, n_tiles,
-                                    n_try, reach.data(), grid, ctx->tb_out.p, static_cast<float*>(ctx->tb_comp.p), 0,
-                                    false)) {
+            if (int rc = wing_stage_f32(ctx, cand, static_cast<WingRec32*>(ctx->tb_w32.p),
+                                        static_cast<WingIdx*>(ctx->tb_idx.p), ranges, n_tiles, n_try, reach.data(),
+                                        grid, static_cast<float*>(ctx->tb_out.p),
+                                        static_cast<float*>(ctx->tb_comp.p))) {
                 (void)hipEventDestroy(e0);
                 (void)hipEventDestroy(e1);
                 return rc;
@@ -937,6 +924,21 @@ int hk_create(int device, hk_ctx** out)
         delete ctx;
         return rc;
     }
+    // the binary64 wing's interpolation matrices
+    static const WingTables tab = [] {
+        WingTables t;
+        wing_tables(&t);
+        return t;
+    }();
+    e = ctx->wing_tab.ensure(sizeof tab);
+    if (e == hipSuccess) e = hipMemcpy(ctx->wing_tab.p, &tab, sizeof tab, hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+        int rc = hip_fail(nullptr, e, "hk_create: the wing's interpolation matrices");
+        ctx->wing_tab.release();
+        (void)hipStreamDestroy(ctx->own);
+        delete ctx;
+        return rc;
+    }
     int lds = 0;
     if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device) == hipSuccess && lds > 0) {
         ctx->lds_bytes = std::min<int64_t>(lds, kSortLdsBytes);
@@ -968,6 +970,7 @@ int hk_destroy(hk_ctx* ctx)
         if (x) (void)hipStreamDestroy(x);
     ctx->partial.release();
     ctx->kscratch.release();
+    ctx->wing_tab.release();
     for (DevBuf* b : {&ctx->tb_idx, &ctx->tb_wing, &ctx->tb_core, &ctx->tb_w32, &ctx->tb_c32, &ctx->tb_ranges,
                       &ctx->tb_ranges_c, &ctx->tb_out, &ctx->tb_comp, &ctx->tb_scale, &ctx->tb_kappa,
                       &ctx->tb_counts, &ctx->tb_series, &ctx->tb_prep})
@@ -1248,10 +1251,10 @@ static int launch_f32_pass(hk_ctx* ctx, const hk_grid* grid, double reach, doubl
     {
         StageTimer tm(ctx, HK_STAGE_LINE_PREP, s);
         // segments of whole 256-line compensation blocks for the wing
-        if (int rc = make_plan(ctx, ctx->ln.wplan, ranges, n_tiles, 1, &reach, tp, 256, grid, false, &wwp, s))
+        if (int rc = make_plan(ctx, ctx->ln.wplan, ranges, n_tiles, 1, &reach, tp, 256, kBusyMin, grid, false, &wwp, s))
             return rc;
         if (int rc = make_plan(ctx, ctx->ln.cplan, ranges_c, n_tiles_c, 1, &reach_core, core_f32_tile_points(), 64,
-                               grid, false, &cwp, s))
+                               kBusyMin, grid, false, &cwp, s))
             return rc;
         tm.stop();
     }
@@ -1332,8 +1335,7 @@ static int opacity_launch(hk_ctx* ctx, const hk_state* st, const hk_grid* grid, 
     HK_HIP(ctx, ctx->ln.wing.ensure(nb * sizeof(WingRec)), "allocating line records");
     HK_HIP(ctx, ctx->ln.widx.ensure(nb * sizeof(WingIdx)), "allocating line records");
     HK_HIP(ctx, ctx->ln.core.ensure(nb * sizeof(CoreRec)), "allocating line records");
-    const int ppl = ctx->f64_points_per_lane;
-    const int32_t tp = opacity_f64_tile_points(ppl);
+    const int32_t tp = opacity_f64_tile_points(np);
     const int64_t n_tiles = ((int64_t)np + tp - 1) / tp;
     const int32_t tpc = precision == HK_F64 ? core_f64_tile_points() : core_f32_tile_points();
     const int64_t n_tiles_c = ((int64_t)np + tpc - 1) / tpc;
@@ -1376,10 +1378,10 @@ static int opacity_launch(hk_ctx* ctx, const hk_state* st, const hk_grid* grid, 
     WorkPlan wwp, cwp;
     {
         StageTimer tm(ctx, HK_STAGE_LINE_PREP, s);
-        if (int rc = make_plan(ctx, ctx->ln.wplan, ranges, n_tiles, 1, &reach, tp, 64, grid, false, &wwp, s))
+        if (int rc = make_plan(ctx, ctx->ln.wplan, ranges, n_tiles, 1, &reach, tp, 64, kBusyMinWing64, grid, false, &wwp, s))
             return rc;
-        if (int rc = make_plan(ctx, ctx->ln.cplan, ranges_c, n_tiles_c, 1, &reach_core, tpc, 64, grid, false, &cwp,
-                               s))
+        if (int rc = make_plan(ctx, ctx->ln.cplan, ranges_c, n_tiles_c, 1, &reach_core, tpc, 64, kBusyMin, grid, false,
+                               &cwp, s))
             return rc;
         tm.stop();
     }
@@ -1394,7 +1396,6 @@ static int opacity_launch(hk_ctx* ctx, const hk_state* st, const hk_grid* grid, 
         tm.stop();
     }
     HK_HIP(ctx, hipEventRecord(core_done, f->cs), "hipEventRecord");
-    f->ppl = ppl;
     f->recs = wing;
     f->ranges = ranges;
     f->n_tiles = n_tiles;
@@ -1413,9 +1414,9 @@ static int flight_wing(hk_ctx* ctx, const Flight& f, hipStream_t w, hipEvent_t k
     if (kappa_ready) HK_HIP(ctx, hipStreamWaitEvent(w, kappa_ready, 0), "hipStreamWaitEvent");
     StageTimer tm(ctx, HK_STAGE_OPACITY, w);
     if (f.precision == HK_F64)
-        HK_HIP(ctx, launch_wing_f64(f.ppl, static_cast<const WingRec*>(f.recs), f.widx, f.ranges, f.n, f.n_tiles, 1,
-                                    f.wwp, f.nu_min, f.dnu, f.np, f.kappa, static_cast<double*>(f.wpartial),
-                                    f.accumulate ? 1 : 0, ctx->wing_edge_paths, w),
+        HK_HIP(ctx, launch_wing_f64(static_cast<const WingRec*>(f.recs), f.widx, f.ranges, f.n, f.n_tiles, 1, f.wwp,
+                                    static_cast<const WingTables*>(ctx->wing_tab.p), f.nu_min, f.dnu, f.np, f.kappa,
+                                    static_cast<double*>(f.wpartial), f.accumulate ? 1 : 0, w),
                "wing_f64");
     else
         HK_HIP(ctx, launch_wing_f32(f.ppl, static_cast<const WingRec32*>(f.recs), f.widx, f.ranges, f.n, f.n_tiles,
@@ -1727,9 +1728,9 @@ int hk_tables(hk_ctx* ctx, const hk_state* states, int32_t n_states, const hk_gr
     const LinesDev L = lines_dev(ctx);
     const int32_t tpc = f64 ? core_f64_tile_points() : core_f32_tile_points();
     const int64_t n_tiles_c = ((int64_t)np + tpc - 1) / tpc;
-    const int64_t n_tiles_max = ((int64_t)np + opacity_f64_tile_points(2) - 1) / opacity_f64_tile_points(2);
-    const int64_t n_tiles_max32 = ((int64_t)np + opacity_f32_tile_points(2) - 1) / opacity_f32_tile_points(2);
-    const int64_t ranges_per_state = 2 * std::max(n_tiles_max, n_tiles_max32);
+    // wing tile ranges per state (binary32: of the smallest shape)
+    const int32_t tp_min = f64 ? opacity_f64_tile_points(np) : opacity_f32_tile_points(2);
+    const int64_t ranges_per_state = 2 * (((int64_t)np + tp_min - 1) / tp_min);
 
     // states per launch: the option, or as many as the memory budget holds
     const int64_t rec_bytes = f64 ? (int64_t)(sizeof(WingRec) + sizeof(WingIdx) + sizeof(CoreRec))
@@ -1774,15 +1775,16 @@ int hk_tables(hk_ctx* ctx, const hk_state* states, int32_t n_states, const hk_gr
     int64_t* rc_all = static_cast<int64_t*>(ctx->tb_ranges_c.p);
     int64_t* counts = static_cast<int64_t*>(ctx->tb_counts.p);
 
-    // tile shape: cached, or timed on the first batch
+    // tile shape: cached, or timed on the first batch (the binary64 wing has
+    // one shape)
     const int64_t cut_steps = grid->cutoff_lorentz > 0.0 ? -(int64_t)std::llround(grid->cutoff_lorentz * 1e3)
                                                          : (int64_t)std::llround(grid->cutoff / grid->dnu);
     int ppl = f64 ? ctx->f64_points_per_lane : ctx->f32_points_per_lane;
     bool tune = false;
-    if (ctx->tables_autotune) {
+    if (ctx->tables_autotune && !f64) {
         tune = true;
         for (const auto& t : ctx->tuned)
-            if (t.precision == precision && t.n_lines == n && t.n_points == np && t.cut_steps == cut_steps) {
+            if (t.n_lines == n && t.n_points == np && t.cut_steps == cut_steps) {
                 ppl = t.ppl;
                 tune = false;
             }
@@ -1841,11 +1843,11 @@ int hk_tables(hk_ctx* ctx, const hk_state* states, int32_t n_states, const hk_gr
         }
         if (tune) {
             const int32_t n_try = std::min<int32_t>(nbat, 4);
-            if (int rc = autotune_wing(ctx, precision, &states[b0], n_try, grid, &ppl)) return rc;
-            ctx->tuned.push_back({precision, n, np, cut_steps, ppl});
+            if (int rc = autotune_wing(ctx, &states[b0], n_try, grid, &ppl)) return rc;
+            ctx->tuned.push_back({n, np, cut_steps, ppl});
             tune = false;
         }
-        const int32_t tp = f64 ? opacity_f64_tile_points(ppl) : opacity_f32_tile_points(ppl);
+        const int32_t tp = f64 ? opacity_f64_tile_points(np) : opacity_f32_tile_points(ppl);
         const int64_t n_tiles = ((int64_t)np + tp - 1) / tp;
         int64_t* rw = static_cast<int64_t*>(ctx->tb_ranges.p);
         WorkPlan wwp, cwp;
@@ -1855,10 +1857,10 @@ int hk_tables(hk_ctx* ctx, const hk_state* states, int32_t n_states, const hk_gr
                                            d_reach, nbat),
                    "tile_ranges");
             // the plans of the whole batch, read back to size the launches
-            if (int rc = make_plan(ctx, ctx->ln.wplan, rw, n_tiles, nbat, reach.data(), tp, f64 ? 64 : 256, grid, true,
-                                   &wwp, ctx->stream, d_reach))
+            if (int rc = make_plan(ctx, ctx->ln.wplan, rw, n_tiles, nbat, reach.data(), tp, f64 ? 64 : 256,
+                                   f64 ? kBusyMinWing64 : kBusyMin, grid, true, &wwp, ctx->stream, d_reach))
                 return rc;
-            if (int rc = make_plan(ctx, ctx->ln.cplan, rc_all, n_tiles_c, nbat, reach_c.data(), tpc, 64, grid, true, &cwp,
+            if (int rc = make_plan(ctx, ctx->ln.cplan, rc_all, n_tiles_c, nbat, reach_c.data(), tpc, 64, kBusyMin, grid, true, &cwp,
                                    ctx->stream, d_reach_c))
                 return rc;
             tm.stop();
@@ -1894,9 +1896,10 @@ int hk_tables(hk_ctx* ctx, const hk_state* states, int32_t n_states, const hk_gr
         {
             StageTimer tm(ctx, HK_STAGE_OPACITY);
             if (f64)
-                HK_HIP(ctx, launch_wing_f64(ppl, static_cast<WingRec*>(ctx->tb_wing.p), tidx, rw, n, n_tiles, nbat, wwp,
-                                            grid->nu_min, grid->dnu, np, static_cast<double*>(ctx->tb_out.p),
-                                            static_cast<double*>(ctx->ln.wplan.partial.p), 0, ctx->wing_edge_paths, ctx->stream),
+                HK_HIP(ctx, launch_wing_f64(static_cast<WingRec*>(ctx->tb_wing.p), tidx, rw, n, n_tiles, nbat, wwp,
+                                            static_cast<const WingTables*>(ctx->wing_tab.p), grid->nu_min, grid->dnu,
+                                            np, static_cast<double*>(ctx->tb_out.p),
+                                            static_cast<double*>(ctx->ln.wplan.partial.p), 0, ctx->stream),
                        "wing_f64");
             else
                 HK_HIP(ctx, launch_wing_f32(ppl, static_cast<WingRec32*>(ctx->tb_w32.p), tidx, rw, n, n_tiles, nbat,

@@ -59,8 +59,8 @@ struct alignas(16) WingIdx {
     int32_t wlo, whi;
     int32_t g3lo, g3hi;
     int32_t clo, chi;
-    int32_t flags;  // kGroupSafe
-    int32_t jc;     // nearest grid index to the centre (binary32 path)
+    int32_t flags;  // kGroupSafe and the slack (kSlackShift)
+    int32_t jc;     // nearest grid index to the centre
 };
 static_assert(sizeof(WingIdx) == 32, "WingIdx layout");
 // Products of four denominators stay in binary64 range: alpha^2 >= 1e-22 and
@@ -68,6 +68,9 @@ static_assert(sizeof(WingIdx) == 32, "WingIdx layout");
 // grid) put each 3-node denominator m = D P within about 1e-60 .. 1e60 (D >=
 // 100 alpha^2 outside the core region).  Otherwise points are not grouped.
 constexpr int32_t kGroupSafe = 1;
+// The flags' other bits: the slack of a line's poles in whole grid points,
+// sqrt(3/2) alpha / dnu rounded up, plus one for the rounding of jc.
+constexpr int kSlackShift = 1;
 
 // Per-line record of the core-region series, read only for lines whose
 // a^2+u^2 < 100 interval meets a wavefront's points.
@@ -187,9 +190,15 @@ int64_t plan_scratch_count(int64_t n_pairs);  // int64 values of the plan's bloc
 // seg[s] from the reference ranges (tiles of kRefTilePoints points, 2 n_ref
 // values per state) of n_states states; min_seg: the shortest segment, a
 // power of two (256 for the binary32 wing, whose compensated sums run over
-// 256-line blocks aligned to global line indices).
+// 256-line blocks aligned to global line indices).  busy_min: a state is cut
+// when fewer reference tiles than that hold lines (or very unevenly many).
+constexpr int64_t kBusyMin = 4096;
+// The binary64 wing, a wavefront of which holds 64 points on small grids: 512
+// workgroups already give every SIMD two wavefronts, and a cut item repeats
+// the tiles' reductions and interpolation.
+constexpr int64_t kBusyMinWing64 = 256;
 hipError_t launch_seg_length(const int64_t* ref_ranges, int64_t n_ref, int32_t n_states, int64_t n_points,
-                             int64_t n_lines, int64_t min_seg, int64_t* seg, hipStream_t s);
+                             int64_t n_lines, int64_t min_seg, int64_t busy_min, int64_t* seg, hipStream_t s);
 // first, slot and total from the tile ranges (2 n_tiles per state) and seg.
 hipError_t launch_work_plan(const int64_t* ranges, int64_t n_tiles, int32_t n_states, const int64_t* seg,
                             int64_t* first, int64_t* slot, int64_t* block_sums, int64_t* total, hipStream_t s);
@@ -269,9 +278,19 @@ hipError_t launch_tile_ranges(const double* nu_sorted, int64_t n_lines, int64_t 
                               int32_t tile_points, double nu_min, double dnu, int32_t n_points,
                               double reach, int64_t* ranges, hipStream_t s, const double* reach_of = nullptr,
                               int32_t n_states = 1);
-// Binary64 opacity: the wing kernel writes kappa (points_per_lane 2, 4 or
-// 8), the core kernel then adds the series terms.
-int32_t opacity_f64_tile_points(int points_per_lane);
+// Binary64 opacity: the wing kernel writes kappa, the core kernel its
+// series terms.
+int32_t opacity_f64_tile_points(int64_t n_points);  // points per work item on such a grid
+// The wing's interpolation matrices (opacity_f64.hip), filled on the host:
+// cheb[m][k]: Chebyshev coefficient k per node value m; child[c][m][k]: node
+// m's weight at node k of child tile c of four; child_cheb: the two in turn.
+constexpr int kWingNodes = 24;
+struct WingTables {
+    double cheb[kWingNodes][kWingNodes];
+    double child[4][kWingNodes][kWingNodes];
+    double child_cheb[4][kWingNodes][kWingNodes];
+};
+void wing_tables(WingTables* out);
 int32_t core_f64_tile_points();
 int32_t core_f32_tile_points();  // points per work item of the binary32 series
 // The wing items of n_states states (records n_lines apart, ranges 2 n_tiles
@@ -279,10 +298,10 @@ int32_t core_f32_tile_points();  // points per work item of the binary32 series
 // tile_points per slot), which the reduction then adds into kappa.  With
 // accumulate, kappa += the wing sum (single state).  One workgroup per item
 // (wp.launch_items workgroups).
-hipError_t launch_wing_f64(int points_per_lane, const WingRec* wing, const WingIdx* idx, const int64_t* ranges,
-                           int64_t n_lines, int64_t n_tiles, int32_t n_states, const WorkPlan& wp, double nu_min,
-                           double dnu, int32_t n_points, double* kappa, double* partial, int accumulate,
-                           int edge_paths, hipStream_t s);
+hipError_t launch_wing_f64(const WingRec* wing, const WingIdx* idx, const int64_t* ranges, int64_t n_lines,
+                           int64_t n_tiles, int32_t n_states, const WorkPlan& wp, const WingTables* tab,
+                           double nu_min, double dnu, int32_t n_points, double* kappa, double* partial,
+                           int accumulate, hipStream_t s);
 // The series items of n_states states (tiles of core_f64_tile_points(),
 // their own plan): series = the series sums, every point written (a grid of
 // its own, n_points per state, added to the wing's afterwards, so that the

@@ -115,6 +115,12 @@ __device__ __forceinline__ double line_peak(const LineScaled& ls)
     return fmin(doppler, lorentz);
 }
 
+// The grid point nearest to a line centre, clamped to int32 range.
+__device__ inline int32_t nearest_point(double nu0, double nu_min, double dnu)
+{
+    return (int32_t)fmin(fmax(rint((nu0 - nu_min) / dnu), -1.0e9), 1.0e9);
+}
+
 // The records of line i for one state (constants pp), in registers.
 __device__ __forceinline__ void line_prep_vals(const LinesDev& L, const PrepParams& pp, int64_t i, WingRec& w,
                                                WingIdx& x, CoreRec& c)
@@ -132,12 +138,14 @@ __device__ __forceinline__ void line_prep_vals(const LinesDev& L, const PrepPara
         w.M0 = w.G2 * (GH * GH);
         w.Bn = 2.0 * w.G2 - 1.5 * a2;
         w.Cn = GH * (2.0 * GH + w.G2) * (1.0 / 3.0);
-        x.jc = 0;
     }
+    x.jc = nearest_point(nu0, pp.nu_min, pp.dnu);
     const int32_t n = pp.n_points;
     {
         const double span = fmax(fabs(nu0 - pp.nu_min), fabs(fma((double)(n - 1), pp.dnu, pp.nu_min) - nu0));
-        x.flags = (alpha * alpha >= 1e-22 && fma(span, span, w.G2) <= 1e20) ? kGroupSafe : 0;
+        const bool safe = alpha * alpha >= 1e-22 && fma(span, span, w.G2) <= 1e20;
+        const double slack = fmin(ceil(1.2247448713915890 * alpha / pp.dnu) + 1.0, 268435456.0);
+        x.flags = ((int32_t)slack << kSlackShift) | (safe ? kGroupSafe : 0);
     }
     {
         // the cutoff: absolute, or a multiple of the line's Lorentz HWHM
@@ -344,10 +352,7 @@ __device__ __forceinline__ void to_f32(const WingRec& w, const CoreRec& c, doubl
     const bool use_alpha = c.y2 < kGH1R2;  // the line has 3-node or core points
     const double lam = use_alpha ? alpha : (G > 0.0 ? G : alpha);
     const double il = 1.0 / lam;
-    // nearest grid point to the centre, clamped to int32 range
-    double fjc = rint((w.nu0 - nu_min) / dnu);
-    fjc = fmin(fmax(fjc, -1.0e9), 1.0e9);
-    const int32_t jc = (int32_t)fjc;
+    const int32_t jc = nearest_point(w.nu0, nu_min, dnu);
     const double f = w.nu0 - fma((double)jc, dnu, nu_min);  // |f| <~ dnu/2
     r.du = (float)(dnu * il);
     r.fu = (float)(f * il);

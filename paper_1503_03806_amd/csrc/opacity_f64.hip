@@ -1,25 +1,25 @@
 // opacity_f64.hip -- the "kappa(nu)" stage in binary64 (§2.4, §2.5).
 //
 // The paper's GPU scheme is a serial loop over lines with the grid spread
-// over threads, kappa held in a register (§2.5).  Here each wavefront owns a
-// contiguous run of 64*P grid points (lane l holds points run0 + l + 64 p),
-// a workgroup's waves share an LDS tile of line records (lines sorted by
-// wavenumber, §2.5's global-to-shared staging), and every wavefront walks the
-// lines of its tile in order, so each point sums its lines in ascending
-// (nu, index) order without atomics.
+// over threads, kappa held in a register (§2.5).  Here a workgroup owns a
+// block of consecutive grid points and the lines (sorted by wavenumber) that
+// reach it.
 //
 // Two kernels per call:
 //  wing: the 3-node and 1-node Gauss-Hermite rules (a^2+u^2 >= 100) for
 //        every line and point; it writes kappa (over the work items of
-//        work_plan.hip: a tile, or the part of its lines in one segment,
-//        whose partial sums a reduction adds in segment order).
+//        work_plan.hip: a block, or the part of its lines in one segment,
+//        whose partial sums a reduction adds in segment order).  Most lines
+//        are far from most blocks and smooth there, and are evaluated at a
+//        few nodes per tile instead of at every point.
 //  core: the series for a^2+u^2 < 100, a few hundred times rarer but ~30
 //        times dearer per point and heavy in registers; it writes its own
 //        ordered sums into a grid of their own (so the two kernels can run
 //        at the same time, on two streams), added to kappa afterwards.
-// So kappa_j = sum_wing + sum_core, each in line order: reproducible bit for
-// bit, independent of the tile shape.
+// So kappa_j = sum_wing + sum_core, each in an order fixed by the lines and
+// the grid alone, without atomics: reproducible bit for bit.
 #include <algorithm>
+#include <cmath>
 
 #include "hk_internal.h"
 
@@ -27,15 +27,8 @@ namespace hk {
 namespace {
 
 constexpr int kWaves = 4;            // wavefronts per workgroup
-constexpr int kTL = 64 * kWaves;     // line records per LDS tile: one per thread
 constexpr int kMaxTerms = 2 * 10 + 14;  // series terms: n = 1 .. 2 ceil(x) + 14, x < 10
 static_assert(kMaxTerms <= 64, "one lane per series term builds the tables");
-
-// Per-(line, wavefront) path, decided once per LDS tile.
-// (kGH1Edge, kGH3Edge: a run wholly in one rule's region that the line's
-// window covers in part; kGH3Core: a run wholly in the 3-node region and the
-// window that holds series points)
-enum : uint32_t { kSkip = 0, kGH1 = 1, kGH3 = 2, kGeneral = 3, kGH1Edge = 4, kGH3Edge = 5, kGH3Core = 6 };
 
 // num / den to about 2^-48 relative: the hardware reciprocal (relative
 // error below 2^-24 on gfx950) and one Newton correction of the quotient.
@@ -61,46 +54,71 @@ __device__ inline double qrcp(double den)
 // (xcd_rank), so an XCD's neighbouring tiles, which read mostly the same
 // lines, share its L2 while every XCD gets a mix of dear and cheap chunks.
 
-// The path of one line for the points [run0, run1] of a wavefront; run_end
-// is the run's nominal last point.  A run cut short by the grid end takes
-// the general path, which evaluates points whose group reaches beyond the
-// grid one by one, and so do lines outside the grouping range.  A run
-// wholly in one rule's region that the line's window covers only in part
-// takes the rule's own path with a window mask (kGH1Edge, kGH3Edge); a run
-// in the window and the 3-node region that holds series points takes the
-// 3-node path with the series points masked (kGH3Core).  edges == false
-// sends these down the general path instead (a check: both give the same
-// bits).
-__device__ inline uint32_t classify(const WingIdx& r, int32_t run0, int32_t run1, int32_t run_end, bool edges)
-{
-    if (run0 > run1 || r.whi < run0 || r.wlo > run1) return kSkip;
-    if (run1 < run_end || !(r.flags & kGroupSafe)) return kGeneral;
-    const bool full = r.wlo <= run0 && r.whi >= run1;
-    const bool nocore = run1 < r.clo || run0 > r.chi;
-    const bool out3 = run1 < r.g3lo || run0 > r.g3hi;  // wholly 1-node
-    const bool in3 = r.g3lo <= run0 && r.g3hi >= run1;  // wholly 3-node
-    if (!edges) {
-        if (!full || !nocore) return kGeneral;
-        return out3 ? kGH1 : in3 ? kGH3 : kGeneral;
-    }
-    if (!nocore) return (full && in3) ? kGH3Core : kGeneral;
-    if (out3) return full ? kGH1 : kGH1Edge;
-    if (in3) return full ? kGH3 : kGH3Edge;
-    return kGeneral;
-}
+// ---- the wing: far lines at Chebyshev nodes, near lines point by point ----
+//
+// A line's wing over a tile of points that it covers whole, on one rule and
+// far enough away, is smooth there: its value at every point of the tile
+// follows from its values at kFarNodes Chebyshev nodes of the tile.  So such
+// a line is evaluated at the nodes only, the nodes' sums over all such lines
+// are kept per tile, and one polynomial per tile gives the sums at its
+// points.  The tiles form three levels (a work item's block of 4 kSub points,
+// its four wavefronts' kSub, their four kLeaf) or, with kSub = kLeaf, two; a
+// line is taken at the largest
+// tile that admits it (far_at is inherited: a tile inside an admitting one
+// admits the line too), and point by point only in the leaves that do not:
+// those near its centre, or where its window, or its boundary between the
+// two rules or with the series, ends inside the leaf.
+//
+// The error of interpolating 1/(x - p) at the roots of T_N is
+// T_N(x)/T_N(p) of the value, pointwise.  The rules' poles (nu0 -+ i Gamma_L,
+// and for the 3-node rule nu0 -+ sqrt(3/2) alpha -+ i Gamma_L) lie at least
+// kFarRatio half-widths of the tile from its centre, where
+// |1/T_24| <= 2 (3 + sqrt 8)^-24 = 8.5e-19; a Lorentzian is a difference of
+// two such terms over Gamma_L, which costs a factor up to ~1.5 N: below
+// 4e-17 of each line's value in every case.
+//
+// Bound: VALU (binary64; 85% of its cycles busy).  On 1e6 lines x 3e6 points
+// with 2e4 points per window a line costs ~1000 node evaluations and ~500
+// point evaluations in place of 2e4, and the kernel alone takes 1.26 ms
+// against 6.9 ms with every line at every point; 3e6 lines x 1e6 points with
+// 5e3 points per window 2.8 against 9.7 ms, 1e5 lines x 4e5 points 0.17
+// against 0.49 ms.
+constexpr int kFarNodes = kWingNodes;  // 24
+constexpr int kFarRatio = 3;
+constexpr int kLeaf = 64;
+static_assert(kFarNodes == 24, "far_eval and wave_reduce are written for 24 nodes");
+// Lines of a work item up to which all of them are taken point by point:
+// there the reductions and the interpolation cost more than the points.
+constexpr int64_t kFewLines = 24;
+// Grids of up to this many points take blocks of 256 points (two levels of
+// tiles): a quarter of the serial work per wavefront, four times the
+// workgroups; larger grids fill the chip with blocks of 1024, which take far
+// lines at fewer nodes.  (500 lines x 6e3 points: 16 us in blocks of 256, 47
+// in blocks of 1024; 1e5 lines x 4e5 points 0.20 against 0.26 ms; 1e6 lines x
+// 3e6 points 2.1 against 1.4 ms.)
+constexpr int64_t kSmallGrid = 400000;
+// Entries of a wavefront's list of lines that its sub-tile does not admit.
+constexpr int kNearCap = 768;
+// A rest of up to this many lines of a leaf's is taken with a point per lane:
+// ~27 issue slots a line, against ~1900 for a batch of a line per lane.
+constexpr int kFewDirect = 48;
+// Points of a leaf evaluated at a time.
+constexpr int kPoints = 16;
 
-// An index interval [lo, hi] relative to a tile's first point t0, each end
-// clipped to [-1, tp] (tp = the tile's points), packed as two int16: for the
-// tile's points 0 .. tp-1 every comparison with an end comes out as with the
-// unclipped interval.
-__device__ inline uint32_t bnd_pack(int32_t lo, int32_t hi, int32_t t0, int32_t tp)
+// cos((2k + 1) pi / 48), k = 0 .. 11; node 23 - k is the negative of node k
+constexpr double kNode[kFarNodes / 2] = {
+    0.99785892323860348, 0.98078528040323043, 0.94693012949510569, 0.89687274153268826,
+    0.83146961230254524, 0.75183980747897738, 0.65934581510006884, 0.55557023301960218,
+    0.44228869021900125, 0.32143946530316159, 0.19509032201612828, 0.065403129230143055};
+
+// 1 / den to full precision: the hardware reciprocal (relative error e below
+// 2^-24) times 1 + e + e^2.
+__device__ inline double qrcp3(double den)
 {
-    const int64_t l = min<int64_t>(max<int64_t>((int64_t)lo - t0, -1), tp);
-    const int64_t h = min<int64_t>(max<int64_t>((int64_t)hi - t0, -1), tp);
-    return ((uint32_t)l & 0xffffu) | ((uint32_t)h << 16);
+    const double r = __builtin_amdgcn_rcp(den);
+    const double e = fma(-den, r, 1.0);
+    return fma(r, fma(e, e, e), r);
 }
-__device__ inline int32_t bnd_lo(uint32_t w) { return (int32_t)(int16_t)(w & 0xffffu); }
-__device__ inline int32_t bnd_hi(uint32_t w) { return (int32_t)w >> 16; }
 
 // 3-node rule of one point: S Phi = Lg n / m with q = dv^2,
 // n = q (q + Bn) + Cn, m = (q + G2)(q (q + B) + C) = ((q + M2) q + M1) q + M0.
@@ -112,319 +130,626 @@ __device__ inline void gh3_nm(double dv, double M2, double M1, double M0, double
     m = fma(fma(q + M2, q, M1), q, M0);
 }
 
-// Points form groups of four that share one reciprocal (the binary64
-// reciprocal issues at a quarter of the FMA rate): with d_0 .. d_3 the
-// group's denominators, P01 = d_0 d_1, P23 = d_2 d_3, c = rcp(P01 P23) Lg,
-// 1/d_0 = (c P23) d_1 / Lg and so on.  Point j groups with j + 64, j + 128
-// and j + 192 when floor(j / 64) is a multiple of 4 (runs start at multiples
-// of 256), and each group type has one fixed sequence of operations, so a
-// point's value has the same bits whichever path or tile shape computes it:
-//   all 1-node:  acc_0 += (c P23) * d_1   (one fma; likewise for the others)
-//   otherwise:   acc_0 += ((c P23) d_1) * num_0
-// (num = 1 for a 1-node point, n of the 3-node rule otherwise).
-// Lines [L0, L1) at the points of grid tile t of one state (record
-// pointers already offset to the state): out[j - obase] = the ordered sum,
-// or += it with accumulate.
-template <int kP>
-__device__ __forceinline__ void wing_f64_tile(int64_t t, int64_t L0, int64_t L1, const WingRec* __restrict__ wing,
-                                              const WingIdx* __restrict__ idx, double nu_min, double dnu, int32_t n,
-                                              double* __restrict__ out, int64_t obase, int accumulate, bool edges)
+// How a line meets the tile of W points from t0 (t1: its last point on the
+// grid).  touches: its window does.  far: the tile admits it at its nodes --
+// the window covers the tile, one rule serves all of it (three: the 3-node
+// rule) and no series point lies in it, the poles are kFarRatio half-widths
+// from its centre (in whole points: jc is the grid point nearest nu0, the
+// slack sqrt(3/2) alpha in points, rounded up, plus one), and the products
+// of four denominators stay in range.  Each condition holds for every tile
+// inside one for which it holds, in these integers exactly.
+struct Meets {
+    bool touches, far, three;
+};
+__device__ inline Meets meets(const WingIdx& r, int32_t t0, int32_t t1, int32_t W, bool far_ok)
 {
-    static_assert(kP % 4 == 0, "points are processed in groups of four");
-    constexpr int kTilePoints = 64 * kP * kWaves;
-    __shared__ WingRec tile[kTL];
-    __shared__ uint8_t code[kWaves][kTL];  // path of each staged line, per wavefront
-    // each staged line's window, 3-node and series intervals and flags,
-    // relative to the tile (bnd_pack), for the window-edge and general paths
-    __shared__ uint4 bnd[kTL];
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    const int32_t tile0 = (int32_t)(t * kTilePoints);
-    const int32_t run0 = tile0 + wave * 64 * kP;
-    const int32_t rel0 = wave * 64 * kP;  // run0 relative to the tile
+    Meets m;
+    m.touches = t0 <= t1 && r.whi >= t0 && r.wlo <= t1;
+    const bool full = r.wlo <= t0 && r.whi >= t1;
+    const bool nocore = t1 < r.clo || t0 > r.chi;
+    const bool out3 = t1 < r.g3lo || t0 > r.g3hi;  // wholly 1-node
+    m.three = r.g3lo <= t0 && r.g3hi >= t1;        // wholly 3-node
+    const bool away = abs(t0 + W / 2 - r.jc) >= kFarRatio * (W / 2) + (r.flags >> kSlackShift);
+    m.far = m.touches && full && nocore && (out3 || m.three) && away && far_ok && (r.flags & kGroupSafe);
+    return m;
+}
 
-    double nuj[kP], acc[kP];
+// acc[k] += the line (one per lane) at the nodes dvc + h kNode[k] (dvc: the
+// tile's centre less nu0).  Lanes without a line have Lg = 0.  The 3-node
+// rule's coefficients are those of WingRec, from G2 and alpha^2; with
+// alpha^2 = 0 it is the 1-node rule, so lanes of both rules can share a
+// call; with any3 false (uniform) every lane takes the 1-node rule.  Four
+// nodes share one reciprocal (the binary64 reciprocal issues at a quarter of
+// the FMA rate): with P01 = d_0 d_1, P23 = d_2 d_3, c = Lg / (P01 P23),
+// Lg/d_0 = (c P23) d_1 and so on.
+__device__ __forceinline__ void far_eval(double (&acc)[kFarNodes], double dvc, double h, double Lg, double G2,
+                                         double a2, bool any3)
+{
+    const double GH = fma(1.5, a2, G2);
+    const double M2 = 3.0 * (G2 - a2), M1 = fma(3.0 * G2, G2, 2.25 * a2 * a2), M0 = G2 * (GH * GH);
+    const double Bn = fma(2.0, G2, -1.5 * a2), Cn = GH * fma(2.0, GH, G2) * (1.0 / 3.0);
 #pragma unroll
-    for (int p = 0; p < kP; ++p) {
-        const int32_t j = run0 + lane + 64 * p;
-        nuj[p] = fma((double)j, dnu, nu_min);
-        acc[p] = 0.0;
-    }
-
-    for (int64_t base = L0; base < L1; base += kTL) {
-        const int cnt = (int)min((int64_t)kTL, L1 - base);
-        // stage one record per thread and decide its path for each wavefront
-        if ((int)threadIdx.x < cnt) {
-            tile[threadIdx.x] = wing[base + threadIdx.x];
-            const WingIdx r = idx[base + threadIdx.x];
-            bnd[threadIdx.x] = make_uint4(bnd_pack(r.wlo, r.whi, tile0, kTilePoints),
-                                          bnd_pack(r.g3lo, r.g3hi, tile0, kTilePoints),
-                                          bnd_pack(r.clo, r.chi, tile0, kTilePoints), (uint32_t)r.flags);
+    for (int g = 0; g < kFarNodes / 4; ++g) {
+        double nn[4], mm[4];
 #pragma unroll
-            for (int w = 0; w < kWaves; ++w) {
-                const int32_t r0 = tile0 + w * 64 * kP;
-                const int32_t r1 = min(r0 + 64 * kP, n) - 1;
-                code[w][threadIdx.x] = (uint8_t)classify(r, r0, r1, r0 + 64 * kP - 1, edges);
-            }
+        for (int e = 0; e < 4; ++e) {
+            const double t = (e & 2) ? -kNode[2 * g + (e & 1)] : kNode[2 * g + (e & 1)];
+            gh3_nm(fma(t, h, dvc), M2, M1, M0, Bn, Cn, nn[e], mm[e]);
         }
-        __syncthreads();
-        // Maximal runs of consecutive lines on one path: a run's end is found
-        // once, 64 codes at a time by a wavefront ballot, and the 1-node and
-        // 3-node runs are looped over with nothing but a counter (few scalar
-        // instructions per line beside the path's own work; the accumulators
-        // stay in place)
-        const uint8_t* cw = code[wave];
-        // The 1-node and 3-node loops read each record by uniform (scalar)
-        // loads, its values then scalar operands of the VALU work, from the
-        // caches that the staging loads above have just filled: no LDS reads
-        // and no VGPRs for them (binary64 step 7.62 -> 7.20 ms; reading the
-        // records only that way, without the staging, measured slower: the
-        // scalar loads then miss).  The rarer paths read the LDS copy.
-        const WingRec* grec = wing + base;
-        int k = 0;
-        while (k < cnt) {
-            const uint32_t path = (uint32_t)__builtin_amdgcn_readfirstlane((int)cw[k]);
-            int kend = k + 1;
-            for (;;) {
-                const int kk = kend + lane;
-                const uint64_t m = __ballot(kk >= cnt || cw[min(kk, kTL - 1)] != path);
-                if (m) {
-                    kend += (int)__builtin_ctzll(m);
-                    break;
-                }
-                kend += 64;
-            }
-            if (path == kSkip) {
-                k = kend;
-                continue;
-            }
-            if (path == kGH1) {
-                do {
-                    const double nu0 = grec[k].nu0, Lg = grec[k].Lg, G2 = grec[k].G2;
-#pragma unroll
-                    for (int p = 0; p < kP; p += 4) {
-                        double D[4];
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const double dv = nuj[p + e] - nu0;
-                            D[e] = fma(dv, dv, G2);
-                        }
-                        const double P01 = D[0] * D[1], P23 = D[2] * D[3];
-                        const double c = qrcp(P01 * P23) * Lg;
-                        const double c01 = c * P23, c23 = c * P01;
-                        acc[p] = fma(c01, D[1], acc[p]);
-                        acc[p + 1] = fma(c01, D[0], acc[p + 1]);
-                        acc[p + 2] = fma(c23, D[3], acc[p + 2]);
-                        acc[p + 3] = fma(c23, D[2], acc[p + 3]);
-                    }
-                    ++k;
-                } while (k < kend);
-                continue;
-            }
-            if (path == kGH3) {
-                do {
-                    const double nu0 = grec[k].nu0, Lg = grec[k].Lg;
-                    const double M2 = grec[k].M2, M1 = grec[k].M1, M0 = grec[k].M0, Bn = grec[k].Bn, Cn = grec[k].Cn;
-#pragma unroll
-                    for (int p = 0; p < kP; p += 4) {
-                        double nn[4], mm[4];
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) gh3_nm(nuj[p + e] - nu0, M2, M1, M0, Bn, Cn, nn[e], mm[e]);
-                        const double P01 = mm[0] * mm[1], P23 = mm[2] * mm[3];
-                        const double c = qrcp(P01 * P23) * Lg;
-                        const double c01 = c * P23, c23 = c * P01;
-                        acc[p] = fma(c01 * mm[1], nn[0], acc[p]);
-                        acc[p + 1] = fma(c01 * mm[0], nn[1], acc[p + 1]);
-                        acc[p + 2] = fma(c23 * mm[3], nn[2], acc[p + 2]);
-                        acc[p + 3] = fma(c23 * mm[2], nn[3], acc[p + 3]);
-                    }
-                    ++k;
-                } while (k < kend);
-                continue;
-            }
-            if (path == kGH1Edge || path == kGH3Edge) {
-                do {
-                    // the rule's own sequence, points outside the window adding
-                    // zero: the general path's sequence for these groups, bit
-                    // for bit, without evaluating the other rule
-                    const uint32_t wb = (uint32_t)__builtin_amdgcn_readfirstlane((int)bnd[k].x);
-                    const int32_t wlo = bnd_lo(wb), whi = bnd_hi(wb);
-                    const double nu0 = tile[k].nu0, Lg = tile[k].Lg;
-                    bool take[kP];
-#pragma unroll
-                    for (int p = 0; p < kP; ++p) {
-                        const int32_t jr = rel0 + lane + 64 * p;
-                        take[p] = jr >= wlo && jr <= whi;
-                    }
-                    if (path == kGH1Edge) {
-                        const double G2 = tile[k].G2;
-#pragma unroll
-                        for (int p = 0; p < kP; p += 4) {
-                            double D[4];
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                const double dv = nuj[p + e] - nu0;
-                                D[e] = fma(dv, dv, G2);
-                            }
-                            const double P01 = D[0] * D[1], P23 = D[2] * D[3];
-                            const double c = qrcp(P01 * P23) * Lg;
-                            const double c01 = c * P23, c23 = c * P01;
-                            acc[p] = fma(take[p] ? c01 : 0.0, D[1], acc[p]);
-                            acc[p + 1] = fma(take[p + 1] ? c01 : 0.0, D[0], acc[p + 1]);
-                            acc[p + 2] = fma(take[p + 2] ? c23 : 0.0, D[3], acc[p + 2]);
-                            acc[p + 3] = fma(take[p + 3] ? c23 : 0.0, D[2], acc[p + 3]);
-                        }
-                    } else {
-                        const double M2 = tile[k].M2, M1 = tile[k].M1, M0 = tile[k].M0, Bn = tile[k].Bn,
-                                     Cn = tile[k].Cn;
-#pragma unroll
-                        for (int p = 0; p < kP; p += 4) {
-                            double nn[4], mm[4];
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) gh3_nm(nuj[p + e] - nu0, M2, M1, M0, Bn, Cn, nn[e], mm[e]);
-                            const double P01 = mm[0] * mm[1], P23 = mm[2] * mm[3];
-                            const double c = qrcp(P01 * P23) * Lg;
-                            const double c01 = c * P23, c23 = c * P01;
-                            const double x0 = c01 * mm[1], x1 = c01 * mm[0], x2 = c23 * mm[3], x3 = c23 * mm[2];
-                            acc[p] = fma(take[p] ? x0 : 0.0, nn[0], acc[p]);
-                            acc[p + 1] = fma(take[p + 1] ? x1 : 0.0, nn[1], acc[p + 1]);
-                            acc[p + 2] = fma(take[p + 2] ? x2 : 0.0, nn[2], acc[p + 2]);
-                            acc[p + 3] = fma(take[p + 3] ? x3 : 0.0, nn[3], acc[p + 3]);
-                        }
-                    }
-                    ++k;
-                } while (k < kend);
-                continue;
-            }
-            if (path == kGH3Core) {
-                do {
-                    // the general path's sequences for these groups: a group
-                    // without series points the 3-node path's, one with them a
-                    // division per point, the series points adding zero
-                    const uint32_t cb = (uint32_t)__builtin_amdgcn_readfirstlane((int)bnd[k].z);
-                    const int32_t clo = bnd_lo(cb), chi = bnd_hi(cb);
-                    const double nu0 = tile[k].nu0, Lg = tile[k].Lg;
-                    const double M2 = tile[k].M2, M1 = tile[k].M1, M0 = tile[k].M0, Bn = tile[k].Bn, Cn = tile[k].Cn;
-#pragma unroll
-                    for (int p = 0; p < kP; p += 4) {
-                        double nn[4], mm[4];
-                        bool cp[4];
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            gh3_nm(nuj[p + e] - nu0, M2, M1, M0, Bn, Cn, nn[e], mm[e]);
-                            const int32_t jr = rel0 + lane + 64 * (p + e);
-                            cp[e] = jr >= clo && jr <= chi;
-                        }
-                        if (!cp[0] && !cp[1] && !cp[2] && !cp[3]) {
-                            const double P01 = mm[0] * mm[1], P23 = mm[2] * mm[3];
-                            const double c = qrcp(P01 * P23) * Lg;
-                            const double c01 = c * P23, c23 = c * P01;
-                            acc[p] = fma(c01 * mm[1], nn[0], acc[p]);
-                            acc[p + 1] = fma(c01 * mm[0], nn[1], acc[p + 1]);
-                            acc[p + 2] = fma(c23 * mm[3], nn[2], acc[p + 2]);
-                            acc[p + 3] = fma(c23 * mm[2], nn[3], acc[p + 3]);
-                        } else {
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                const double v = qdiv(Lg * nn[e], mm[e]);
-                                acc[p + e] += cp[e] ? 0.0 : v;
-                            }
-                        }
-                    }
-                    ++k;
-                } while (k < kend);
-                continue;
-            }
-            do {
-                const double nu0 = tile[k].nu0, Lg = tile[k].Lg, G2 = tile[k].G2;
-                const double M2 = tile[k].M2, M1 = tile[k].M1, M0 = tile[k].M0, Bn = tile[k].Bn, Cn = tile[k].Cn;
-                // general path: window edges (with edges == false), region edges,
-                // core points (left to the core kernel), the grid end, lines
-                // outside the grouping range (rare)
-                const uint4 b4 = bnd[k];
-                const uint32_t b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b4.x);
-                const uint32_t b1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b4.y);
-                const uint32_t b2 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b4.z);
-                const uint32_t b3 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b4.w);
-                const int32_t wlo = bnd_lo(b0), whi = bnd_hi(b0);
-                const int32_t g3lo = bnd_lo(b1), g3hi = bnd_hi(b1);
-                const int32_t clo = bnd_lo(b2), chi = bnd_hi(b2);
-                const bool safe = (b3 & kGroupSafe) != 0;
-#pragma unroll
-                for (int p = 0; p < kP; p += 4) {
-                    double num[4], den[4];
-                    bool take[4], one[4], core_pt[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int32_t jr = rel0 + lane + 64 * (p + e);
-                        const double dv = nuj[p + e] - nu0;
-                        double n3, m3;
-                        gh3_nm(dv, M2, M1, M0, Bn, Cn, n3, m3);
-                        one[e] = jr < g3lo || jr > g3hi;
-                        core_pt[e] = jr >= clo && jr <= chi;
-                        take[e] = jr >= wlo && jr <= whi && !core_pt[e];
-                        num[e] = one[e] ? 1.0 : n3;
-                        den[e] = one[e] ? fma(dv, dv, G2) : m3;
-                    }
-                    if (safe && !core_pt[0] && !core_pt[1] && !core_pt[2] && !core_pt[3] &&
-                        run0 + lane + 64 * (p + 3) < n) {
-                        const double P01 = den[0] * den[1], P23 = den[2] * den[3];
-                        const double c = qrcp(P01 * P23) * Lg;
-                        const double c01 = c * P23, c23 = c * P01;
-                        double xs[4], ys[4];
-                        if (one[0] && one[1] && one[2] && one[3]) {
-                            xs[0] = c01; ys[0] = den[1];
-                            xs[1] = c01; ys[1] = den[0];
-                            xs[2] = c23; ys[2] = den[3];
-                            xs[3] = c23; ys[3] = den[2];
-                        } else {
-                            xs[0] = c01 * den[1]; ys[0] = num[0];
-                            xs[1] = c01 * den[0]; ys[1] = num[1];
-                            xs[2] = c23 * den[3]; ys[2] = num[2];
-                            xs[3] = c23 * den[2]; ys[3] = num[3];
-                        }
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) acc[p + e] = fma(take[e] ? xs[e] : 0.0, ys[e], acc[p + e]);
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const double v = qdiv(Lg * num[e], den[e]);
-                            acc[p + e] += take[e] ? v : 0.0;
-                        }
-                    }
-                }
-                ++k;
-            } while (k < kend);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int p = 0; p < kP; ++p) {
-        const int32_t j = run0 + lane + 64 * p;
-        if (j < n) out[j - obase] = accumulate ? out[j - obase] + acc[p] : acc[p];
+        const double P01 = mm[0] * mm[1], P23 = mm[2] * mm[3];
+        const double c = qrcp3(P01 * P23) * Lg;
+        const double c01 = c * P23, c23 = c * P01;
+        acc[2 * g] = fma(c01 * mm[1], nn[0], acc[2 * g]);
+        acc[2 * g + 1] = fma(c01 * mm[0], nn[1], acc[2 * g + 1]);
+        acc[23 - 2 * g] = fma(c23 * mm[3], nn[2], acc[23 - 2 * g]);
+        acc[22 - 2 * g] = fma(c23 * mm[2], nn[3], acc[22 - 2 * g]);
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
 
-// One workgroup per work item (a grid tile of a state, or its lines in one
-// segment), wp.launch_items of them (the plan's item count or its bound:
-// workgroups past the last item exit at once; a loop over several items per
-// workgroup measured slower, it costs registers).  Per-state arrays lie n_lines records, 2 n_tiles ranges
-// and n points apart; a cut item writes its slot of partial (kTilePoints
-// values).
-template <int kP>
-__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(kP == 4 ? 7 : 1))) void wing_f64_kernel(
-    const WingRec* __restrict__ wing, const WingIdx* __restrict__ idx, const int64_t* __restrict__ ranges,
-    int64_t n_lines, int64_t n_tiles, int32_t n_states, WorkPlan wp, double nu_min, double dnu, int32_t n,
-    double* __restrict__ kappa, double* __restrict__ partial, int accumulate, int edges)
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+// x and y with the upper half of x and the lower half of y exchanged (kHalf
+// 32: 32-lane halves; 16: odd and even rows of 16), added.
+template <int kHalf>
+__device__ inline double swap_add(double x, double y)
 {
-    constexpr int64_t kTilePoints = 64 * kP * kWaves;
+    const uint64_t a = (uint64_t)__double_as_longlong(x), b = (uint64_t)__double_as_longlong(y);
+    u32x2 lo, hi;
+    if constexpr (kHalf == 32) {
+        lo = __builtin_amdgcn_permlane32_swap((uint32_t)a, (uint32_t)b, false, false);
+        hi = __builtin_amdgcn_permlane32_swap((uint32_t)(a >> 32), (uint32_t)(b >> 32), false, false);
+    } else {
+        lo = __builtin_amdgcn_permlane16_swap((uint32_t)a, (uint32_t)b, false, false);
+        hi = __builtin_amdgcn_permlane16_swap((uint32_t)(a >> 32), (uint32_t)(b >> 32), false, false);
+    }
+    const double p = __longlong_as_double((long long)(((uint64_t)hi.x << 32) | lo.x));
+    const double q = __longlong_as_double((long long)(((uint64_t)hi.y << 32) | lo.y));
+    return p + q;
+}
+
+// v plus v rotated by kRor lanes within each row of 16.
+template <int kRor>
+__device__ inline double row_add(double v)
+{
+    const uint64_t a = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)a, 0x120 | kRor, 0xf, 0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(a >> 32), 0x120 | kRor, 0xf, 0xf, false);
+    return v + __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// Adds a row's (16 lanes') values; every lane of the row holds the sum.
+__device__ inline double row_sum(double v) { return row_add<1>(row_add<2>(row_add<4>(row_add<8>(v)))); }
+
+// dst[k] += the wavefront's sum of acc[k].  Two halving steps leave
+// row r of 16 lanes with the partial sums of nodes 6 r .. 6 r + 5.
+__device__ __forceinline__ void wave_reduce(double (&acc)[kFarNodes], double* dst, int lane)
+{
+    double a[12], b[6];
+#pragma unroll
+    for (int i = 0; i < 12; ++i) a[i] = swap_add<32>(acc[i], acc[i + 12]);
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+        b[i] = row_sum(swap_add<16>(a[i], a[i + 6]));
+    }
+    if ((lane & 15) == 0) {
+        double* d = dst + 6 * (lane >> 4);
+#pragma unroll
+        for (int i = 0; i < 6; ++i) d[i] += b[i];
+    }
+}
+
+__device__ inline void clear(double (&acc)[kFarNodes])
+{
+#pragma unroll
+    for (int i = 0; i < kFarNodes; ++i) acc[i] = 0.0;
+}
+
+// A value that every lane holds alike, in scalar registers.
+__device__ inline uint64_t uniform_bits(uint64_t a)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
+    return ((uint64_t)hi << 32) | lo;
+}
+__device__ inline double uniform(double v)
+{
+    return __longlong_as_double((long long)uniform_bits((uint64_t)__double_as_longlong(v)));
+}
+
+// The points of the closed index interval [lo, hi] (empty: lo > hi) among the
+// kPoints from q0, or the kLeaf from q0, as bits.
+__device__ inline uint32_t point_bits(int32_t lo, int32_t hi, int32_t q0)
+{
+    const int32_t a = max(lo, q0), b = min(hi, q0 + kPoints - 1);
+    return a > b ? 0u : (0xffffffffu >> (31 - (b - a))) << (a - q0);
+}
+__device__ inline uint64_t leaf_bits(int32_t lo, int32_t hi, int32_t q0)
+{
+    const int32_t a = max(lo, q0), b = min(hi, q0 + kLeaf - 1);
+    return a > b ? 0ull : (~0ull >> (63 - (b - a))) << (a - q0);
+}
+
+__device__ inline uint64_t readlane64(uint64_t v, int lane)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane);
+    return ((uint64_t)hi << 32) | lo;
+}
+
+// dacc += four lines at this lane's point x of a leaf: line e's record by
+// uniform (scalar) loads, take[e] the points that its window holds outside
+// the series, one[e] the points of the 1-node rule (uniform masks over the
+// leaf's points).  Points not taken have numerator 0 and denominator 1.
+__device__ __forceinline__ double direct_four(const WingRec* const (&r)[4], const uint64_t (&take)[4],
+                                              const uint64_t (&one)[4], double x, double dacc)
+{
+    double num[4], den[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const bool tk = __builtin_amdgcn_inverse_ballot_w64(take[e]);
+        const bool on = __builtin_amdgcn_inverse_ballot_w64(one[e]);
+        const double dv = x - r[e]->nu0;
+        double n, m;
+        gh3_nm(dv, r[e]->M2, r[e]->M1, r[e]->M0, r[e]->Bn, r[e]->Cn, n, m);
+        m = on ? fma(dv, dv, r[e]->G2) : m;
+        n = (on ? 1.0 : n) * r[e]->Lg;
+        num[e] = tk ? n : 0.0;
+        den[e] = tk ? m : 1.0;
+    }
+    const double P01 = den[0] * den[1], P23 = den[2] * den[3];
+    const double c = qrcp3(P01 * P23);
+    const double c01 = c * P23, c23 = c * P01;
+    dacc = fma(c01 * den[1], num[0], dacc);
+    dacc = fma(c01 * den[0], num[1], dacc);
+    dacc = fma(c23 * den[3], num[2], dacc);
+    return fma(c23 * den[2], num[3], dacc);
+}
+
+// v where m is all ones, 0 where it is 0.
+__device__ inline double masked(double v, int32_t m)
+{
+    return __longlong_as_double(__double_as_longlong(v) & (int64_t)m);
+}
+// v where m is all ones, a value in [1, 2) where it is 0 (v's low word under
+// the exponent of 1).
+__device__ inline double one_to_two(double v, int32_t m)
+{
+    const uint64_t a = (uint64_t)__double_as_longlong(v);
+    const uint32_t hi = ((uint32_t)(a >> 32) & (uint32_t)m) | (0x3ff00000u & ~(uint32_t)m);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | (uint32_t)a));
+}
+
+// acc[p] += the line (one per lane) at points x[p] of a leaf where bit p of
+// tk is set (its window holds the point outside the series); bit p of on:
+// the 1-node rule, else the 3-node rule.  Points not taken have numerator 0
+// and a denominator of about 1 (a series point's may be 0 or negative).  kOne, kThree: some lane takes points of that rule.
+// Four points share one reciprocal, as at the nodes.
+template <bool kOne, bool kThree>
+__device__ __forceinline__ void point_eval(double (&acc)[kPoints], const double (&x)[kPoints], uint32_t tk,
+                                           uint32_t on, double nu0, double Lg, double G2, double M2, double M1,
+                                           double M0, double Bn, double Cn)
+{
+#pragma unroll
+    for (int g = 0; g < kPoints; g += 4) {
+        double num[4], den[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int p = g + e;
+            const int32_t take = (int32_t)(tk << (31 - p)) >> 31;  // all ones where the point is taken
+            const double dv = x[p] - nu0;
+            double nn, dd;
+            if constexpr (kThree) gh3_nm(dv, M2, M1, M0, Bn, Cn, nn, dd);
+            if constexpr (kOne) {
+                const bool one = !kThree || ((on >> p) & 1u);
+                dd = one ? fma(dv, dv, G2) : dd;
+                nn = one ? 1.0 : nn;
+            }
+            num[e] = masked(nn, take);
+            den[e] = one_to_two(dd, take);
+        }
+        const double P01 = den[0] * den[1], P23 = den[2] * den[3];
+        const double c = qrcp3(P01 * P23) * Lg;
+        const double c01 = c * P23, c23 = c * P01;
+        acc[g] = fma(c01 * den[1], num[0], acc[g]);
+        acc[g + 1] = fma(c01 * den[0], num[1], acc[g + 1]);
+        acc[g + 2] = fma(c23 * den[3], num[2], acc[g + 2]);
+        acc[g + 3] = fma(c23 * den[2], num[3], acc[g + 3]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// The same with a division per point, for lines outside the grouping range.
+__device__ __forceinline__ void point_eval_single(double (&acc)[kPoints], const double (&x)[kPoints], uint32_t tk,
+                                                  uint32_t on, double nu0, double Lg, double G2, double M2,
+                                                  double M1, double M0, double Bn, double Cn)
+{
+#pragma unroll
+    for (int p = 0; p < kPoints; ++p) {
+        const double dv = x[p] - nu0;
+        double nn, mm;
+        gh3_nm(dv, M2, M1, M0, Bn, Cn, nn, mm);
+        const bool one = (on >> p) & 1u;
+        const double v = qdiv(Lg * (one ? 1.0 : nn), one ? fma(dv, dv, G2) : mm);
+        acc[p] += (tk >> p) & 1u ? v : 0.0;
+    }
+}
+
+// The node sums of one work item: of the block per wavefront (summed at the
+// end), of each sub-tile and of each leaf, then each leaf's polynomial.
+template <int kSub>
+struct WingLds {
+    double block[kWaves][kFarNodes], sub[kWaves][kFarNodes];
+    double leaf[kWaves * kSub / kLeaf][kFarNodes], coef[kWaves * kSub / kLeaf][kFarNodes];
+    double point[kWaves][kSub];        // the lines taken point by point
+    uint32_t near[kWaves][kNearCap];   // lines (offsets from lo) the sub-tile does not admit
+    uint16_t direct[kWaves][kNearCap]; // of those, the ones the current leaf does not admit either
+    uint32_t queue[kWaves][2][128];    // rings of lines for the nodes of the sub-tile, of a leaf
+    uint64_t done[kWaves];             // bit b: batch 4 b + wave needs nothing below the block
+};
+
+__device__ inline void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Lines [L0, L1) at the points of block t of one state (record pointers
+// already offset to the state): out[j - obase] = the sum, or += it with
+// accumulate.  Each wavefront takes every fourth batch of 64 lines (one per
+// lane) for the block's nodes, then walks all batches for its own sub-tile:
+// admitted lines go through a ring to full 64-lane evaluations, the others
+// to a list that is walked once per leaf in the same way, and lines that a
+// leaf does not admit are evaluated at its points.  A lane holds one line
+// throughout, so the records are read by coalesced vector loads; its sums
+// are added across the wavefront at the end.  The order of every sum is
+// fixed by (L0, L1) and the lines alone.
+template <int kSub>
+__device__ __forceinline__ void wing_f64_tile(int64_t t, int64_t L0, int64_t L1, const WingRec* __restrict__ wing,
+                                              const WingIdx* __restrict__ idx, const WingTables* __restrict__ tab,
+                                              double nu_min, double dnu, int32_t n, double* __restrict__ out,
+                                              int64_t obase, int accumulate, bool far_ok)
+{
+    constexpr int kBlock = kWaves * kSub, kLeaves = kSub / kLeaf;  // leaves per wavefront
+    constexpr bool kThreeLevels = kLeaves > 1;
+    static_assert(kLeaves == 1 || kLeaves == 4, "tiles have four children each");
+    __shared__ WingLds<kSub> S;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int32_t b0 = (int32_t)(t * kBlock);
+    const int32_t s0 = b0 + wave * kSub;
+    const int32_t b1 = min(b0 + kBlock, n) - 1, s1 = min(s0 + kSub, n) - 1;
+    const double xref = fma((double)b0, dnu, nu_min);  // positions are taken relative to the block's first point
+    const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    far_ok = far_ok && L1 - L0 > kFewLines;
+    wing += L0;
+    idx += L0;
+    const int32_t nl = (int32_t)(L1 - L0);
+
+    for (int k = threadIdx.x; k < kWaves * kFarNodes; k += 64 * kWaves) (&S.sub[0][0])[k] = (&S.block[0][0])[k] = 0.0;
+    for (int k = threadIdx.x; k < kLeaves * kWaves * kFarNodes; k += 64 * kWaves) (&S.leaf[0][0])[k] = 0.0;
+    for (int k = threadIdx.x; k < kBlock; k += 64 * kWaves) (&S.point[0][0])[k] = 0.0;
+    __syncthreads();
+
+    // ---- the block's nodes ----
+    const double hs = 0.5 * (double)kSub * dnu, hl = 0.5 * (double)kLeaf * dnu, hb = 0.5 * (double)kBlock * dnu;
+    if (far_ok) {
+        double acc[kFarNodes];
+        clear(acc);
+        bool any_block = false;
+        uint64_t done = 0;  // (of the first 64 batches: longer items test the others twice)
+        for (int32_t base = 64 * wave, b = 0; base < nl; base += 64 * kWaves, ++b) {
+            const int32_t i = base + lane;
+            bool far = false, three = false, rest = false;
+            if (i < nl) {
+                const Meets m = meets(idx[i], b0, b1, kBlock, true);
+                far = m.far;
+                three = m.far && m.three;
+                rest = m.touches && !m.far;
+            }
+            if (b < 64 && !__ballot(rest)) done |= 1ull << b;
+            if (!__ballot(far)) continue;
+            any_block = true;
+            double dvc = 1.0, Lg = 0.0, G2 = 1.0, a2 = 0.0;
+            if (far) {
+                const WingRec& r = wing[i];
+                dvc = (xref - r.nu0) + hb;
+                Lg = r.Lg;
+                G2 = r.G2;
+                a2 = three ? fma(r.M2, -1.0 / 3.0, G2) : 0.0;
+            }
+            far_eval(acc, dvc, hb, Lg, G2, a2, __ballot(three) != 0);
+        }
+        if (any_block) wave_reduce(acc, S.block[wave], lane);
+        if (lane == 0) S.done[wave] = done;
+        __syncthreads();
+    }
+
+    // ---- the sub-tile ----
+    if (s0 <= s1) {
+        uint32_t* near = S.near[wave];
+        uint32_t* qs = S.queue[wave][0];
+        uint32_t* ql = S.queue[wave][1];
+        uint16_t* dir = S.direct[wave];
+        const double cs = (double)(wave * kSub + kSub / 2) * dnu;  // the sub-tile's centre from xref
+        int n_near = 0, q_head = 0, q_n = 0;
+        double acc[kFarNodes];  // of the sub-tile's nodes
+        clear(acc);
+        uint64_t done[kWaves] = {};
+        if (far_ok) {
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) done[w] = uniform_bits(S.done[w]);
+        }
+        for (int32_t base = 0, b = 0;; base += 64, ++b) {
+            const bool last = base >= nl;
+            if (!last && b < 64 * kWaves) {
+                const uint64_t dn = (b & 3) == 0 ? done[0] : (b & 3) == 1 ? done[1] : (b & 3) == 2 ? done[2] : done[3];
+                if ((dn >> (b >> 2)) & 1) continue;
+            }
+            if (!last) {
+                const int32_t i = base + lane;
+                bool far = false, keep = false;
+                if (i < nl) {
+                    const WingIdx r = idx[i];
+                    const Meets m = meets(r, s0, s1, kSub, far_ok);
+                    const bool up = meets(r, b0, b1, kBlock, far_ok).far;
+                    far = kThreeLevels && m.far && !up;
+                    keep = m.touches && !far && !up;
+                }
+                const uint64_t fm = __ballot(far), km = __ballot(keep);
+                if (far) qs[(q_head + q_n + __builtin_popcountll(fm & below)) & 127] = (uint32_t)i;
+                if (keep) near[n_near + __builtin_popcountll(km & below)] = (uint32_t)i;
+                q_n += __builtin_popcountll(fm);
+                n_near += __builtin_popcountll(km);
+                wave_fence();
+            }
+            while (q_n >= (last ? 1 : 64)) {  // full batches; what is left at the end
+                double dvc = 1.0, Lg = 0.0, G2 = 1.0, a2 = 0.0;
+                bool three = false;
+                if (lane < q_n) {
+                    const uint32_t i = qs[(q_head + lane) & 127];
+                    const WingRec& r = wing[i];
+                    dvc = (xref - r.nu0) + cs;
+                    Lg = r.Lg;
+                    G2 = r.G2;
+                    three = idx[i].g3lo <= s0 && idx[i].g3hi >= s1;
+                    a2 = three ? fma(r.M2, -1.0 / 3.0, G2) : 0.0;
+                }
+                far_eval(acc, dvc, hs, Lg, G2, a2, __ballot(three) != 0);
+                const int done = min(q_n, 64);
+                q_head = (q_head + done) & 127;
+                q_n -= done;
+            }
+            if (n_near > kNearCap - 64 || (last && n_near > 0)) {
+                // the list is full, or complete: walk it once per leaf
+                if constexpr (kThreeLevels) wave_reduce(acc, S.sub[wave], lane);
+                for (int lf = 0; lf < kLeaves; ++lf) {
+                    const int32_t l0 = s0 + lf * kLeaf, l1 = min(l0 + kLeaf, n) - 1;
+                    if (l0 > l1) break;
+                    const double cl = (double)(l0 - b0 + kLeaf / 2) * dnu;
+                    int h_l = 0, n_l = 0, n_d = 0;
+                    bool any_leaf = false;
+                    double la[kFarNodes];
+                    clear(la);
+                    for (int k = 0;; k += 64) {
+                        const bool lastk = k >= n_near;
+                        if (!lastk) {
+                            bool far = false, direct = false;
+                            uint32_t i = 0;
+                            if (k + lane < n_near) {
+                                i = near[k + lane];
+                                const WingIdx w = idx[i];
+                                const Meets m = meets(w, l0, l1, kLeaf, far_ok);
+                                far = m.far;
+                                // (a leaf wholly inside the series is the series kernel's)
+                                direct = m.touches && !m.far && !(w.clo <= l0 && w.chi >= l1);
+                            }
+                            const uint64_t fm = __ballot(far), dm = __ballot(direct);
+                            if (far) ql[(h_l + n_l + __builtin_popcountll(fm & below)) & 127] = i;
+                            if (direct) dir[n_d + __builtin_popcountll(dm & below)] = (uint16_t)(k + lane);
+                            n_l += __builtin_popcountll(fm);
+                            n_d += __builtin_popcountll(dm);
+                            wave_fence();
+                        }
+                        while (n_l >= (lastk ? 1 : 64)) {
+                            double dvc = 1.0, Lg = 0.0, G2 = 1.0, a2 = 0.0;
+                            bool three = false;
+                            if (lane < n_l) {
+                                const uint32_t i = ql[(h_l + lane) & 127];
+                                const WingRec& r = wing[i];
+                                dvc = (xref - r.nu0) + cl;
+                                Lg = r.Lg;
+                                G2 = r.G2;
+                                three = idx[i].g3lo <= l0 && idx[i].g3hi >= l1;
+                                a2 = three ? fma(r.M2, -1.0 / 3.0, G2) : 0.0;
+                            }
+                            far_eval(la, dvc, hl, Lg, G2, a2, __ballot(three) != 0);
+                            any_leaf = true;
+                            const int done = min(n_l, 64);
+                            h_l = (h_l + done) & 127;
+                            n_l -= done;
+                        }
+                        if (lastk) break;
+                    }
+                    if (any_leaf) wave_reduce(la, S.leaf[wave * kLeaves + lf], lane);
+                    // the others point by point: whole batches of 64 with a
+                    // line per lane, kPoints points at a time, and a rest of
+                    // up to kFewDirect with a point per lane, four lines at a
+                    // time (a batch costs the same whatever its lanes hold)
+                    const int rest = n_d & 63;
+                    const int n_few = rest <= kFewDirect ? rest : 0;
+                    const int n_batch = n_d - n_few;
+                    if (n_few) {
+                        const double x = fma((double)(l0 + lane), dnu, nu_min);
+                        double dacc = 0.0;
+                        uint32_t i = 0;
+                        uint64_t take = 0, one = 0;
+                        bool safe = true;
+                        if (lane < n_few) {
+                            i = near[dir[n_batch + lane]];
+                            const WingIdx w = idx[i];
+                            take = leaf_bits(w.wlo, w.whi, l0) & ~leaf_bits(w.clo, w.chi, l0);
+                            one = ~leaf_bits(w.g3lo, w.g3hi, l0);
+                            safe = (w.flags & kGroupSafe) != 0;
+                        }
+                        for (uint64_t m = __ballot(take != 0 && safe); m;) {
+                            const WingRec* r4[4];
+                            uint64_t t4[4], o4[4];
+                            const int e0 = (int)__builtin_ctzll(m);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                const int at = m ? (int)__builtin_ctzll(m) : e0;
+                                r4[e] = wing + (uint32_t)__builtin_amdgcn_readlane((int)i, at);
+                                t4[e] = m ? readlane64(take, at) : 0ull;
+                                o4[e] = readlane64(one, at);
+                                m &= m - 1;
+                            }
+                            dacc = direct_four(r4, t4, o4, x, dacc);
+                        }
+                        for (uint64_t m = __ballot(take != 0 && !safe); m; m &= m - 1) {
+                            const int at = (int)__builtin_ctzll(m);
+                            const WingRec* r = wing + (uint32_t)__builtin_amdgcn_readlane((int)i, at);
+                            const bool tk = __builtin_amdgcn_inverse_ballot_w64(readlane64(take, at));
+                            const bool on = __builtin_amdgcn_inverse_ballot_w64(readlane64(one, at));
+                            const double dv = x - r->nu0;
+                            double nn, mm;
+                            gh3_nm(dv, r->M2, r->M1, r->M0, r->Bn, r->Cn, nn, mm);
+                            const double v = qdiv(r->Lg * (on ? 1.0 : nn), on ? fma(dv, dv, r->G2) : mm);
+                            dacc += tk ? v : 0.0;
+                        }
+                        S.point[wave][lf * kLeaf + lane] += dacc;
+                    }
+                    for (int p0 = 0; n_batch > 0 && p0 < kLeaf; p0 += kPoints) {
+                        double x[kPoints], pa[kPoints];
+#pragma unroll
+                        for (int p = 0; p < kPoints; ++p) {
+                            x[p] = uniform(fma((double)(l0 + p0 + p), dnu, nu_min));
+                            pa[p] = 0.0;
+                        }
+                        for (int k = 0; k < n_batch; k += 64) {
+                            uint32_t tk = 0, on = 0;
+                            bool safe = true;
+                            WingRec r = {};
+                            if (k + lane < n_batch) {
+                                const uint32_t i = near[dir[k + lane]];
+                                const WingIdx w = idx[i];
+                                const int32_t q0 = l0 + p0;
+                                tk = point_bits(w.wlo, w.whi, q0) & ~point_bits(w.clo, w.chi, q0);
+                                on = ~point_bits(w.g3lo, w.g3hi, q0);
+                                safe = (w.flags & kGroupSafe) != 0;
+                                r = wing[i];
+                            }
+                            if (!__ballot(tk != 0)) continue;
+                            const bool any1 = __ballot((tk & on) != 0) != 0, any3 = __ballot((tk & ~on) != 0) != 0;
+                            if (__ballot(!safe))
+                                point_eval_single(pa, x, tk, on, r.nu0, r.Lg, r.G2, r.M2, r.M1, r.M0, r.Bn, r.Cn);
+                            else if (!any1)
+                                point_eval<false, true>(pa, x, tk, on, r.nu0, r.Lg, r.G2, r.M2, r.M1, r.M0, r.Bn,
+                                                        r.Cn);
+                            else if (!any3)
+                                point_eval<true, false>(pa, x, tk, on, r.nu0, r.Lg, r.G2, r.M2, r.M1, r.M0, r.Bn,
+                                                        r.Cn);
+                            else
+                                point_eval<true, true>(pa, x, tk, on, r.nu0, r.Lg, r.G2, r.M2, r.M1, r.M0, r.Bn,
+                                                       r.Cn);
+                        }
+                        double* dst = &S.point[wave][lf * kLeaf + p0 + 4 * (lane >> 4)];
+                        double h8[8];
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) h8[q] = swap_add<32>(pa[q], pa[q + 8]);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const double v = row_sum(swap_add<16>(h8[q], h8[q + 4]));
+                            if ((lane & 15) == 0) dst[q] += v;
+                        }
+                    }
+                }
+                n_near = 0;
+                clear(acc);
+            }
+            if (last) break;
+        }
+        if constexpr (kThreeLevels) wave_reduce(acc, S.sub[wave], lane);
+    }
+
+    // ---- down the levels, then each leaf's polynomial at its points ----
+    wave_fence();
+    if (far_ok) {
+        __syncthreads();
+        // the parent's sums at this wavefront's nodes: the block's (two
+        // levels), or the block's interpolated and added to the sub-tile's
+        if (lane < kFarNodes) {
+            double v = 0.0;
+            if constexpr (kThreeLevels) {
+                v = S.sub[wave][lane];
+#pragma unroll
+                for (int m = 0; m < kFarNodes; ++m) {
+                    double b = S.block[0][m];
+#pragma unroll
+                    for (int w = 1; w < kWaves; ++w) b += S.block[w][m];
+                    v = fma(tab->child[wave][m][lane], b, v);
+                }
+            } else {
+#pragma unroll
+                for (int w = 0; w < kWaves; ++w) v += S.block[w][lane];
+            }
+            S.sub[wave][lane] = v;
+        }
+        wave_fence();
+        for (int o = lane; o < kLeaves * kFarNodes; o += 64) {  // Chebyshev coefficients of the leaves
+            const int lf = o / kFarNodes, k = o % kFarNodes, c = kThreeLevels ? lf : wave;
+            double v = 0.0;
+#pragma unroll
+            for (int m = 0; m < kFarNodes; ++m) v = fma(tab->cheb[m][k], S.leaf[wave * kLeaves + lf][m], v);
+#pragma unroll
+            for (int m = 0; m < kFarNodes; ++m) v = fma(tab->child_cheb[c][m][k], S.sub[wave][m], v);
+            S.coef[wave * kLeaves + lf][k] = v;
+        }
+        wave_fence();
+    }
+#pragma unroll
+    for (int lf = 0; lf < kLeaves; ++lf) {
+        const int32_t j = s0 + lf * kLeaf + lane;
+        if (j < n) {
+            double v = S.point[wave][lf * kLeaf + lane];
+            if (far_ok) {  // Clenshaw's recurrence
+                const double x = fma((double)j, dnu, nu_min) - xref;
+                const double tt = (x - (double)(wave * kSub + lf * kLeaf + kLeaf / 2) * dnu) / hl;
+                const double* c = S.coef[wave * kLeaves + lf];
+                double u1 = 0.0, u2 = 0.0;
+#pragma unroll
+                for (int k = kFarNodes - 1; k >= 1; --k) {
+                    const double u = fma(2.0 * tt, u1, c[k] - u2);
+                    u2 = u1;
+                    u1 = u;
+                }
+                v += fma(tt, u1, c[0] - u2);
+            }
+            out[j - obase] = accumulate ? out[j - obase] + v : v;
+        }
+    }
+}
+
+// One workgroup per work item (a block of a state, or its lines in one
+// segment), wp.launch_items of them (the plan's item count or its bound:
+// workgroups past the last item exit at once).  Per-state arrays lie n_lines
+// records, 2 n_tiles ranges and n points apart; a cut item writes its slot of
+// partial (kBlock values).
+template <int kSub>
+__global__ __launch_bounds__(64 * kWaves) void wing_f64_kernel(
+    const WingRec* __restrict__ wing, const WingIdx* __restrict__ idx, const int64_t* __restrict__ ranges,
+    int64_t n_lines, int64_t n_tiles, int32_t n_states, WorkPlan wp, const WingTables* __restrict__ tab,
+    double nu_min, double dnu, int32_t n, double* __restrict__ kappa, double* __restrict__ partial, int accumulate,
+    int far_ok)
+{
+    constexpr int64_t kBlock = kWaves * kSub;
     WorkItem it;
     if (work_item(xcd_rank(blockIdx.x), wp, ranges, n_tiles, n_states, it)) {
         const int64_t o = it.st * n_lines;
         const bool direct = it.slot < 0;
-        double* out = direct ? kappa + it.st * (int64_t)n : partial + it.slot * kTilePoints;
-        wing_f64_tile<kP>(it.tile, it.lo, it.hi, wing + o, idx + o, nu_min, dnu, n, out,
-                          direct ? 0 : it.tile * kTilePoints, direct ? accumulate : 0, edges != 0);
+        double* out = direct ? kappa + it.st * (int64_t)n : partial + it.slot * kBlock;
+        wing_f64_tile<kSub>(it.tile, it.lo, it.hi, wing + o, idx + o, tab, nu_min, dnu, n, out,
+                      direct ? 0 : it.tile * kBlock, direct ? accumulate : 0, far_ok != 0);
     }
 }
 
@@ -735,41 +1060,75 @@ __global__ __launch_bounds__(256) void core_f64_reduce_kernel(WorkPlan wp, int64
     }
 }
 
-template <int kP>
-hipError_t launch_wing(const WingRec* wing, const WingIdx* idx, const int64_t* ranges, int64_t n_lines,
-                       int64_t n_tiles, int32_t n_states, const WorkPlan& wp, double nu_min, double dnu, int32_t n,
-                       double* kappa, double* partial, int accumulate, int edges, hipStream_t s)
-{
-    const int64_t nb = plan_blocks(wp.launch_items);
-    if (nb > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
-    wing_f64_kernel<kP><<<dim3((unsigned)nb), dim3(64 * kWaves), 0, s>>>(
-        wing, idx, ranges, n_lines, n_tiles, n_states, wp, nu_min, dnu, n, kappa, partial, accumulate, edges);
-    const int64_t nr = std::min<int64_t>(wp.n_pairs, 8192);
-    wing_f64_reduce_kernel<<<dim3((unsigned)nr), dim3(256), 0, s>>>(wp, n_tiles, n_states, 64 * kP * kWaves, n,
-                                                                    partial, kappa, accumulate);
-    return hipGetLastError();
-}
-
-
-
 }  // namespace
 
-int32_t opacity_f64_tile_points(int points_per_lane) { return 64 * points_per_lane * kWaves; }
+namespace {
+// Points of a wavefront's sub-tile on a grid of n points (see launch_wing_f64).
+int32_t sub_points(int64_t n) { return n <= kSmallGrid ? kLeaf : 4 * kLeaf; }
+}  // namespace
+
+int32_t opacity_f64_tile_points(int64_t n_points) { return kWaves * sub_points(n_points); }
 int32_t core_f64_tile_points() { return kCoreTilePoints; }
 
-hipError_t launch_wing_f64(int points_per_lane, const WingRec* wing, const WingIdx* idx, const int64_t* ranges,
-                           int64_t n_lines, int64_t n_tiles, int32_t n_states, const WorkPlan& wp, double nu_min,
-                           double dnu, int32_t n_points, double* kappa, double* partial, int accumulate, int edges,
-                           hipStream_t s)
+// The interpolation matrices of the wing's tiles, from the closed forms of
+// the Chebyshev nodes t_m = cos((2m + 1) pi / (2N)): a function's Chebyshev
+// coefficients are c_k = (2 - [k = 0]) / N sum_m f_m T_k(t_m), its value at
+// x is sum_k c_k T_k(x); the nodes of child c of four lie at
+// (2c - 3)/4 + t/4 of the parent.
+void wing_tables(WingTables* out)
+{
+    constexpr int N = kFarNodes;
+    const long double pi = 3.14159265358979323846264338327950288L;
+    long double cheb[N][N];  // [m][k]
+    for (int m = 0; m < N; ++m)
+        for (int k = 0; k < N; ++k) {
+            cheb[m][k] = (k == 0 ? 1.0L : 2.0L) / N * std::cos((long double)(k * (2 * m + 1)) * pi / (2 * N));
+            out->cheb[m][k] = (double)cheb[m][k];
+        }
+    for (int c = 0; c < 4; ++c) {
+        long double lag[N][N];  // [m][k]: node m's weight at the child's node k
+        for (int k = 0; k < N; ++k) {
+            const long double t = k < N / 2 ? kNode[k] : -kNode[N - 1 - k];
+            const long double x = 0.25L * ((2 * c - 3) + t);
+            long double T[N] = {1.0L, x};
+            for (int q = 2; q < N; ++q) T[q] = 2.0L * x * T[q - 1] - T[q - 2];
+            for (int m = 0; m < N; ++m) {
+                long double v = 0.0L;
+                for (int q = 0; q < N; ++q) v += cheb[m][q] * T[q];
+                lag[m][k] = v;
+                out->child[c][m][k] = (double)v;
+            }
+        }
+        for (int m = 0; m < N; ++m)
+            for (int k = 0; k < N; ++k) {
+                long double v = 0.0L;
+                for (int q = 0; q < N; ++q) v += cheb[q][k] * lag[m][q];
+                out->child_cheb[c][m][k] = (double)v;
+            }
+    }
+}
+
+hipError_t launch_wing_f64(const WingRec* wing, const WingIdx* idx, const int64_t* ranges, int64_t n_lines,
+                           int64_t n_tiles, int32_t n_states, const WorkPlan& wp, const WingTables* tab,
+                           double nu_min, double dnu, int32_t n_points, double* kappa, double* partial,
+                           int accumulate, hipStream_t s)
 {
     if (n_tiles == 0 || n_states == 0) return hipSuccess;
-    switch (points_per_lane) {
-    case 4: return launch_wing<4>(wing, idx, ranges, n_lines, n_tiles, n_states, wp, nu_min, dnu, n_points, kappa,
-                                  partial, accumulate, edges, s);
-    case 8: return launch_wing<8>(wing, idx, ranges, n_lines, n_tiles, n_states, wp, nu_min, dnu, n_points, kappa,
-                                  partial, accumulate, edges, s);
-    default: return hipErrorInvalidValue;
-    }
+    const int64_t nb = plan_blocks(wp.launch_items);
+    if (nb > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
+    // far lines are interpolated where the grid points' own rounding (half
+    // an ulp of the wavenumber) is below 2^-10 of a leaf's half-width; on
+    // finer grids every line is taken point by point
+    const double top = std::max(std::fabs(nu_min), std::fabs(nu_min + (double)n_points * dnu));
+    const int far_ok = dnu * 281474976710656.0 >= top ? 1 : 0;  // 2^48
+    const int32_t sub = sub_points(n_points);
+    auto kernel = sub == kLeaf ? wing_f64_kernel<kLeaf> : wing_f64_kernel<4 * kLeaf>;
+    kernel<<<dim3((unsigned)nb), dim3(64 * kWaves), 0, s>>>(wing, idx, ranges, n_lines, n_tiles, n_states, wp, tab,
+                                                            nu_min, dnu, n_points, kappa, partial, accumulate, far_ok);
+    const int64_t nr = std::min<int64_t>(wp.n_pairs, 8192);
+    wing_f64_reduce_kernel<<<dim3((unsigned)nr), dim3(256), 0, s>>>(wp, n_tiles, n_states, kWaves * sub, n_points,
+                                                                    partial, kappa, accumulate);
+    return hipGetLastError();
 }
 
 hipError_t launch_core_f64(const WingRec* wing, const WingIdx* idx, const CoreRec* core, const int64_t* ranges,

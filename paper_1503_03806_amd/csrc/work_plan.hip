@@ -13,9 +13,8 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kPerThread = 4;
 constexpr int64_t kPerBlock = (int64_t)kThreads * kPerThread;
-// A state's tiles are cut when fewer than kBusyMin reference tiles hold
+// A state's tiles are cut when fewer than busy_min reference tiles hold
 // lines, or when the fullest holds more than kUneven times the mean.
-constexpr int64_t kBusyMin = 4096;
 constexpr int64_t kUneven = 3;
 
 // One workgroup per state.  Segment length: the smallest power of two >=
@@ -27,7 +26,7 @@ constexpr int64_t kUneven = 3;
 // + 2) <= 6 n_tiles and the partial points <= 6 n_points + 2 tile points.
 __global__ __launch_bounds__(kThreads) void seg_length_kernel(const int64_t* __restrict__ ref, int64_t n_ref,
                                                               int64_t n_points, int64_t n_lines, int64_t min_seg,
-                                                              int64_t* __restrict__ seg)
+                                                              int64_t busy_min, int64_t* __restrict__ seg)
 {
     __shared__ int64_t red[3][kThreads];
     const int64_t* rg = ref + (int64_t)blockIdx.x * 2 * n_ref;
@@ -55,7 +54,7 @@ __global__ __launch_bounds__(kThreads) void seg_length_kernel(const int64_t* __r
         mx = red[1][0];
         sum = red[2][0];
         int64_t L = kNoSplit;
-        if (sum > 0 && (busy < kBusyMin || mx * busy > kUneven * sum)) {
+        if (sum > 0 && (busy < busy_min || mx * busy > kUneven * sum)) {
             const double W = 512.0 * (double)sum + 4096.0 * (double)n_lines;
             const double need = W / (4.0 * (double)n_points);
             L = min_seg;
@@ -181,12 +180,12 @@ __global__ __launch_bounds__(kThreads) void plan_offset_kernel(int64_t n_pairs, 
 int64_t plan_scratch_count(int64_t n_pairs) { return 2 * std::max<int64_t>(1, (n_pairs + kPerBlock - 1) / kPerBlock); }
 
 hipError_t launch_seg_length(const int64_t* ref_ranges, int64_t n_ref, int32_t n_states, int64_t n_points,
-                             int64_t n_lines, int64_t min_seg, int64_t* seg, hipStream_t s)
+                             int64_t n_lines, int64_t min_seg, int64_t busy_min, int64_t* seg, hipStream_t s)
 {
     if (n_states <= 0) return hipSuccess;
     if (min_seg < 1 || (min_seg & (min_seg - 1)) != 0) return hipErrorInvalidValue;
     seg_length_kernel<<<dim3((unsigned)n_states), dim3(kThreads), 0, s>>>(ref_ranges, n_ref, n_points, n_lines,
-                                                                         min_seg, seg);
+                                                                         min_seg, busy_min, seg);
     return hipGetLastError();
 }
 
