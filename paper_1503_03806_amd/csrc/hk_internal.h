@@ -81,7 +81,8 @@ struct alignas(16) CoreRec {
     double ex;    // erfcx(y)
     double norm;  // S(T) / (alpha sqrt(pi))
     double T1;    // sum_{n>=1} e^{-n^2/4} / (n^2/4 + y^2)
-    double pad0, pad1;
+    double ypi;   // y / pi
+    double ipy;   // 1 / (pi y); 0 for y < 1e-100
 };
 static_assert(sizeof(CoreRec) == 64, "CoreRec layout");
 

@@ -184,8 +184,8 @@ __device__ __forceinline__ void line_prep_vals(const LinesDev& L, const PrepPara
         c.ex = 0.0;
         c.T1 = 0.0;
     }
-    c.pad0 = 0.0;
-    c.pad1 = 0.0;
+    c.ypi = y * kInvPi;
+    c.ipy = y >= 1e-100 ? kInvPi / y : 0.0;
 }
 
 // The records of line i for one state, to memory.
