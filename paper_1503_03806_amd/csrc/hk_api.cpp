@@ -1201,13 +1201,11 @@ struct Flight {
     int64_t used_n = 0;
 };
 
-// Binary32 profiles with compensated binary32 sums, after the binary64 line
-// preparation: scale, binary32 records, tile ranges and both plans on f->s,
-// then the series on f->cs; the wing and kappa = (sum + comp) 2^-s in
+// Binary32 profiles with compensated binary32 sums: scale, binary32 records,
+// the wing's tile ranges and both plans on f->s, then the series on f->cs; the wing and kappa = (sum + comp) 2^-s in
 // binary64 are left to flight_wing and flight_finish.
-static int launch_f32_pass(hk_ctx* ctx, const hk_grid* grid, double reach, double reach_core, WingRec* wing,
-                           WingIdx* widx, CoreRec* core, const int64_t* ranges_c, int64_t n_tiles_c, bool surrogate,
-                           Flight* f)
+static int launch_f32_pass(hk_ctx* ctx, const PrepParams& pp, const hk_grid* grid, double reach, double reach_core,
+                           WingIdx* widx, const int64_t* ranges_c, int64_t n_tiles_c, bool surrogate, Flight* f)
 {
     const hipStream_t s = f->s;
     const int64_t n = ctx->n_lines;
@@ -1232,10 +1230,10 @@ static int launch_f32_pass(hk_ctx* ctx, const hk_grid* grid, double reach, doubl
     {
         StageTimer tm(ctx, HK_STAGE_LINE_PREP, s);
         if (n > 0) {
-            HK_HIP(ctx, launch_f32_scale(wing, core, n, static_cast<double*>(ctx->ln.f32partial.p), nblk, scale, s),
+            const LinesDev L = lines_dev(ctx);
+            HK_HIP(ctx, launch_f32_scale(L, pp, nullptr, static_cast<double*>(ctx->ln.f32partial.p), nblk, scale, s),
                    "f32_scale");
-            HK_HIP(ctx, launch_line_prep_f32(wing, widx, core, n, grid->nu_min, grid->dnu, scale, w32, c32, s),
-                   "line_prep_f32");
+            HK_HIP(ctx, launch_line_prep_f32(L, pp, nullptr, scale, widx, w32, c32, s), "line_prep_f32");
         } else {
             HK_HIP(ctx, launch_zero(scale, sizeof(int32_t), s), "zero");
         }
@@ -1332,9 +1330,11 @@ static int opacity_launch(hk_ctx* ctx, const hk_state* st, const hk_grid* grid, 
     ctx->last_P = st->P;
 
     const size_t nb = (size_t)std::max<int64_t>(n, 1);
-    HK_HIP(ctx, ctx->ln.wing.ensure(nb * sizeof(WingRec)), "allocating line records");
     HK_HIP(ctx, ctx->ln.widx.ensure(nb * sizeof(WingIdx)), "allocating line records");
-    HK_HIP(ctx, ctx->ln.core.ensure(nb * sizeof(CoreRec)), "allocating line records");
+    if (precision == HK_F64) {
+        HK_HIP(ctx, ctx->ln.wing.ensure(nb * sizeof(WingRec)), "allocating line records");
+        HK_HIP(ctx, ctx->ln.core.ensure(nb * sizeof(CoreRec)), "allocating line records");
+    }
     const int32_t tp = opacity_f64_tile_points(np);
     const int64_t n_tiles = ((int64_t)np + tp - 1) / tp;
     const int32_t tpc = precision == HK_F64 ? core_f64_tile_points() : core_f32_tile_points();
@@ -1356,17 +1356,18 @@ static int opacity_launch(hk_ctx* ctx, const hk_state* st, const hk_grid* grid, 
 
     {
         StageTimer tm(ctx, HK_STAGE_LINE_PREP, s);
-        HK_HIP(ctx, launch_line_prep_f64(L, pp, wing, widx, core, s), "line_prep_f64");
-        if (precision == HK_F64)  // binary32 wing tiles have their own ranges
+        if (precision == HK_F64) {  // binary32 has records and wing tiles of its own
+            HK_HIP(ctx, launch_line_prep_f64(L, pp, wing, widx, core, s), "line_prep_f64");
             HK_HIP(ctx, launch_tile_ranges(L.nu, n, n_tiles, tp, grid->nu_min, grid->dnu, np, reach, ranges, s),
                    "tile_ranges");
+        }
         HK_HIP(ctx, launch_tile_ranges(L.nu, n, n_tiles_c, tpc, grid->nu_min, grid->dnu, np, reach_core,
                                        ranges_c, s),
                "tile_ranges");
         tm.stop();
     }
     if (precision != HK_F64)
-        return launch_f32_pass(ctx, grid, reach, reach_core, wing, widx, core, ranges_c, n_tiles_c,
+        return launch_f32_pass(ctx, pp, grid, reach, reach_core, widx, ranges_c, n_tiles_c,
                                precision == HK_F32_SURROGATE, f);
     // The series runs on a second stream, concurrent with the wing (each
     // leaves the VALU idle ~20% of the time, which the other fills), into a
@@ -1489,10 +1490,11 @@ static int reserve_line_buffers(hk_ctx* ctx, int64_t n, int precision)
 {
     const size_t nb = (size_t)std::max<int64_t>(n, 1);
     for (Lane* l : {&ctx->ln, &ctx->ln_alt}) {
-        HK_HIP(ctx, l->wing.ensure(nb * sizeof(WingRec)), "allocating line records");
         HK_HIP(ctx, l->widx.ensure(nb * sizeof(WingIdx)), "allocating line records");
-        HK_HIP(ctx, l->core.ensure(nb * sizeof(CoreRec)), "allocating line records");
-        if (precision != HK_F64) {
+        if (precision == HK_F64) {
+            HK_HIP(ctx, l->wing.ensure(nb * sizeof(WingRec)), "allocating line records");
+            HK_HIP(ctx, l->core.ensure(nb * sizeof(CoreRec)), "allocating line records");
+        } else {
             HK_HIP(ctx, l->w32.ensure(nb * sizeof(WingRec32)), "allocating binary32 records");
             HK_HIP(ctx, l->c32.ensure(nb * sizeof(CoreRec32)), "allocating binary32 records");
         }
@@ -1823,15 +1825,14 @@ int hk_tables(hk_ctx* ctx, const hk_state* states, int32_t n_states, const hk_gr
                                                        static_cast<CoreRec*>(ctx->tb_core.p), ctx->stream),
                        "line_prep_f64");
             } else {
-                // the binary32 records straight from the line list: the
-                // states' scales from a pass over the peaks, then the records
+                // the states' scales from a pass over the peaks, then the records
                 int32_t* scale = static_cast<int32_t*>(ctx->tb_scale.p);
-                HK_HIP(ctx, launch_f32_scale_lines(L, d_pps, static_cast<double*>(ctx->ln.f32partial.p), 256, scale,
-                                                   ctx->stream, nbat),
+                HK_HIP(ctx, launch_f32_scale(L, pps[0], d_pps, static_cast<double*>(ctx->ln.f32partial.p), 256,
+                                             scale, ctx->stream, nbat),
                        "f32_scale");
-                HK_HIP(ctx, launch_line_prep_f32_direct(L, d_pps, nbat, grid->nu_min, grid->dnu, scale, tidx,
-                                                        static_cast<WingRec32*>(ctx->tb_w32.p),
-                                                        static_cast<CoreRec32*>(ctx->tb_c32.p), ctx->stream),
+                HK_HIP(ctx, launch_line_prep_f32(L, pps[0], d_pps, scale, tidx,
+                                                 static_cast<WingRec32*>(ctx->tb_w32.p),
+                                                 static_cast<CoreRec32*>(ctx->tb_c32.p), ctx->stream, nbat),
                        "line_prep_f32");
             }
             HK_HIP(ctx, launch_eval_counts(tidx, n, counts + b0 * kCountBlocks * 3, kCountBlocks, ctx->stream, nbat),

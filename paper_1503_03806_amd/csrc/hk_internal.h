@@ -33,26 +33,27 @@ constexpr double kGH1R2 = 1.0e6;
 // in line order.  With alpha = Gamma_D / sqrt(ln 2) the Doppler 1/e width,
 // G = Gamma_L, dv = nu_j - nu0 and q = dv^2:
 //   1-node:  S Phi = Lg / (q + G2)                       (a Lorentzian)
-//   3-node:  S Phi = Lg n / (D P),  D = q + G2,
-//            P = q (q + B) + C,  n = q (q + Bn) + Cn,
+//   3-node:  S Phi = Lg n / m,
 // the 3-node Gauss-Hermite sum (weights 2/3, 1/6, 1/6 of the Lorentzians at
-// nu0 and nu0 -+ sqrt(3/2) alpha) over one common denominator, expanded in
-// q: with GH = G2 + 1.5 alpha^2, P = (q + GH)^2 - 6 alpha^2 q is the product
-// of the two shifted Lorentzians' denominators and 3n = 2P + D (q + GH).
-// Coefficients: B = 2 G2 - 3 alpha^2, C = GH^2, Bn = 2 G2 - 1.5 alpha^2,
-// Cn = GH (2 GH + G2) / 3.  The record holds the denominator as one cubic,
-// D P = ((q + M2) q + M1) q + M0 with M2 = G2 + B = 3 (G2 - alpha^2),
-// M1 = C + G2 B = 3 G2^2 + 2.25 alpha^4 (no cancellation) and M0 = G2 C.
-// Where a^2 + u^2 >= 100, q + G2 >= 100 alpha^2, so the negative parts of
-// M2 and Bn never cancel q's terms.
+// nu0 and nu0 -+ sqrt(3/2) alpha) over one common denominator.  With D = q +
+// G2, GH = G2 + 1.5 alpha^2 and P = (q + GH)^2 - 6 alpha^2 q (the product of
+// the two shifted Lorentzians' denominators), m = D P and 3n = 2P + D (q +
+// GH); in x = q + X, X = G2 - alpha^2, where m has no square term,
+//   m = (x^2 + p) x + r,   n = x (x + alpha^2/2) + c,
+//   p = alpha^2 (6 G2 - 0.75 alpha^2),  r = alpha^4 (6 G2 + 0.25 alpha^2),
+//   c = alpha^2 (4 G2 + alpha^2).
+// Where a^2 + u^2 >= 100, x >= 99 alpha^2 and x > G2 - alpha^2: x^2 and x^3
+// dominate and nothing cancels.  With alpha^2 = 0 it is the 1-node rule.  (Six
+// operations per point before the division; seven with m as a general cubic
+// in q: the wing alone 1.28 -> 1.21 ms on 1e6 lines x 3e6 points.)
 // The grid-index intervals (closed; empty when lo > hi) sit in WingIdx: the
 // cutoff window and the points whose a^2+u^2 lies below 1e6 and below 100.
 struct alignas(16) WingRec {
     double nu0;  // pressure-shifted line centre
     double Lg;   // S(T) Gamma_L / pi
     double G2;   // Gamma_L^2
-    double M2, M1, M0;  // the 3-node denominator's cubic
-    double Bn, Cn;      // the 3-node numerator's quadratic
+    double a2;   // alpha^2
+    double X, c, p, r;  // the 3-node rule
 };
 static_assert(sizeof(WingRec) == 64, "WingRec layout");
 struct alignas(16) WingIdx {
@@ -94,10 +95,13 @@ static_assert(sizeof(CoreRec) == 64, "CoreRec layout");
 // For point j: dv/lambda = (j - jc) du - fu, with jc the nearest grid point
 // to the centre (WingIdx.jc), du = dnu/lambda, fu = (nu0 - nu_jc)/lambda.
 //   1-node:  Lg / (q + G2),  3-node:  Lg n / m  with q = (dv/lambda)^2,
-// m = ((q + M2) q + M1) q + M0 and n = q (q + Bn) + Cn, the coefficients of
-// WingRec scaled by powers of 1/lambda.  A line with 3-node points has
-// lambda = alpha, where Bn = 2 G2 - 1.5 exactly: it is formed in the kernel
-// (lines with lambda = Gamma_L never use the 3-node rule).
+// m = (q + G2)(q (q + B) + C) = ((q + M2) q + M1) q + M0 and n = q (q + Bn) +
+// Cn, where with GH = G2 + 1.5 alpha^2: B = 2 G2 - 3 alpha^2, C = GH^2, Bn =
+// 2 G2 - 1.5 alpha^2, Cn = GH (2 GH + G2) / 3, M2 = 3 (G2 - alpha^2), M1 =
+// 3 G2^2 + 2.25 alpha^4, M0 = G2 C, scaled by powers of 1/lambda.  A line
+// with 3-node points has lambda = alpha, where Bn = 2 G2 - 1.5 exactly: it is
+// formed in the kernel (lines with lambda = Gamma_L never use the 3-node
+// rule).
 struct alignas(16) WingRec32 {
     float du, fu, Lg, G2, M2, M1, M0, Cn;
 };
@@ -320,27 +324,15 @@ hipError_t launch_add_f64(double* a, const double* b, int64_t n, hipStream_t s);
 hipError_t launch_eval_counts(const WingIdx* idx, int64_t n_lines, int64_t* partial,
                               int32_t n_blocks, hipStream_t s, int32_t n_states = 1);
 
-// Binary32 path: the state's scale exponent from the lines' peak heights
-// (two reductions into scale[0]), the record conversion, and the kernels.
-// With n_states > 1, the states of a batch in one launch each (records
-// n_lines apart, partial n_blocks apart, one scale per state).
-hipError_t launch_f32_scale(const WingRec* wing, const CoreRec* core, int64_t n_lines,
-                            double* partial, int32_t n_blocks, int32_t* scale, hipStream_t s,
-                            int32_t n_states = 1);
-// Binary32 tables straight from the line list, every state of a batch in
-// one launch each (state blockIdx.y, constants pps[state]): the peak bound's
-// per-block maxima (n_blocks per state) and the scale of each state; then
-// the index records and the binary32 records (n_lines apart per state),
-// equal to those of launch_line_prep_f64 + launch_f32_scale +
-// launch_line_prep_f32.
-hipError_t launch_f32_scale_lines(const LinesDev& L, const PrepParams* pps, double* partial, int32_t n_blocks,
-                                  int32_t* scale, hipStream_t s, int32_t n_states);
-hipError_t launch_line_prep_f32_direct(const LinesDev& L, const PrepParams* pps, int32_t n_states, double nu_min,
-                                       double dnu, const int32_t* scale, WingIdx* idx, WingRec32* w32,
-                                       CoreRec32* c32, hipStream_t s);
-hipError_t launch_line_prep_f32(const WingRec* wing, WingIdx* idx, const CoreRec* core,
-                                int64_t n_lines, double nu_min, double dnu, const int32_t* scale,
-                                WingRec32* w32, CoreRec32* c32, hipStream_t s, int32_t n_states = 1);
+// Binary32 path, straight from the line list: the peak bound's per-block
+// maxima (n_blocks <= 256 per state) and the scale of each state; then the
+// index records and the binary32 records.  One state: its constants pp, pps
+// NULL.  Every state of a batch in one launch each: pps [device] n_states
+// constants (state blockIdx.y), records n_lines apart per state.
+hipError_t launch_f32_scale(const LinesDev& L, const PrepParams& pp, const PrepParams* pps, double* partial,
+                            int32_t n_blocks, int32_t* scale, hipStream_t s, int32_t n_states = 1);
+hipError_t launch_line_prep_f32(const LinesDev& L, const PrepParams& pp, const PrepParams* pps, const int32_t* scale,
+                                WingIdx* idx, WingRec32* w32, CoreRec32* c32, hipStream_t s, int32_t n_states = 1);
 int32_t opacity_f32_tile_points(int points_per_lane);
 // As launch_wing_f64: the Kahan pairs (sum, comp) of n_states states; cut
 // items write (sum, comp) pairs to partial (tile_points float2 per slot).

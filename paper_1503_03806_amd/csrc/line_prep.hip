@@ -106,7 +106,7 @@ __device__ __forceinline__ LineScaled line_scaled(const LinesDev& L, const PrepP
 
 // S Phi bounded above by the smaller of the Doppler and the Lorentz peak
 // heights, S / (alpha sqrt(pi)) and S / (pi Gamma_L): the same products
-// as the records' norm and Lg / G2.
+// as the binary64 records' norm and Lg / G2.
 __device__ __forceinline__ double line_peak(const LineScaled& ls)
 {
     const double doppler = ls.S * (1.0 / ls.alpha) * kInvSqrtPi;
@@ -121,8 +121,13 @@ __device__ inline int32_t nearest_point(double nu0, double nu_min, double dnu)
     return (int32_t)fmin(fmax(rint((nu0 - nu_min) / dnu), -1.0e9), 1.0e9);
 }
 
+// What the wing's records of both precisions are made of.
+struct WingLine {
+    double nu0, Lg, G2, alpha;
+};
+
 // The records of line i for one state (constants pp), in registers.
-__device__ __forceinline__ void line_prep_vals(const LinesDev& L, const PrepParams& pp, int64_t i, WingRec& w,
+__device__ __forceinline__ void line_prep_vals(const LinesDev& L, const PrepParams& pp, int64_t i, WingLine& w,
                                                WingIdx& x, CoreRec& c)
 {
     const LineScaled ls = line_scaled(L, pp, i);
@@ -130,15 +135,7 @@ __device__ __forceinline__ void line_prep_vals(const LinesDev& L, const PrepPara
     w.nu0 = nu0;
     w.Lg = S * GL * kInvPi;
     w.G2 = GL * GL;
-    {
-        const double a2 = alpha * alpha;
-        const double GH = w.G2 + 1.5 * a2;
-        w.M2 = 3.0 * (w.G2 - a2);
-        w.M1 = 3.0 * (w.G2 * w.G2) + 2.25 * (a2 * a2);
-        w.M0 = w.G2 * (GH * GH);
-        w.Bn = 2.0 * w.G2 - 1.5 * a2;
-        w.Cn = GH * (2.0 * GH + w.G2) * (1.0 / 3.0);
-    }
+    w.alpha = alpha;
     x.jc = nearest_point(nu0, pp.nu_min, pp.dnu);
     const int32_t n = pp.n_points;
     {
@@ -193,10 +190,20 @@ __device__ __forceinline__ void line_prep_one(const LinesDev& L, const PrepParam
                                               WingRec* __restrict__ wing, WingIdx* __restrict__ idx,
                                               CoreRec* __restrict__ core)
 {
-    WingRec w;
+    WingLine l;
     WingIdx x;
     CoreRec c;
-    line_prep_vals(L, pp, i, w, x, c);
+    line_prep_vals(L, pp, i, l, x, c);
+    const double a2 = l.alpha * l.alpha;
+    WingRec w;
+    w.nu0 = l.nu0;
+    w.Lg = l.Lg;
+    w.G2 = l.G2;
+    w.a2 = a2;
+    w.X = l.G2 - a2;
+    w.c = a2 * (4.0 * l.G2 + a2);
+    w.p = a2 * (6.0 * l.G2 - 0.75 * a2);
+    w.r = (a2 * a2) * (6.0 * l.G2 + 0.25 * a2);
     wing[i] = w;
     idx[i] = x;
     core[i] = c;
@@ -302,68 +309,48 @@ __global__ __launch_bounds__(256) void eval_counts_kernel(const WingIdx* __restr
     }
 }
 
-// Peak height of a line's profile times S: S min(1/(alpha sqrt(pi)),
-// 1/(pi Gamma_L)) bounds S Phi everywhere; per-block maxima.
-__global__ __launch_bounds__(256) void f32_peak_kernel(const WingRec* __restrict__ wing,
-                                                       const CoreRec* __restrict__ core, int64_t n,
-                                                       double* __restrict__ partial)
-{
-    __shared__ double red[256];
-    // state blockIdx.y of a batch: records n apart, partials gridDim.x apart
-    wing += (int64_t)blockIdx.y * n;
-    core += (int64_t)blockIdx.y * n;
-    partial += (int64_t)blockIdx.y * gridDim.x;
-    double m = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const double doppler = core[i].norm;                     // S / (alpha sqrt(pi))
-        const double lorentz = wing[i].G2 > 0.0 ? wing[i].Lg / wing[i].G2 : doppler;  // S/(pi G)
-        m = fmax(m, fmin(doppler, lorentz));
-    }
-    red[threadIdx.x] = m;
-    __syncthreads();
-    for (int k = 128; k > 0; k >>= 1) {
-        if ((int)threadIdx.x < k) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + k]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
-}
-
 // s = 100 - exponent(max peak): peaks land at or below 2^101, so sums of up
-// to 2^26 of them stay below binary32's 2^128.
-__global__ void f32_scale_kernel(const double* __restrict__ partial, int32_t n_blocks,
-                                 int32_t* __restrict__ scale)
+// to 2^26 of them stay below binary32's 2^128.  One workgroup per state.
+__global__ __launch_bounds__(256) void f32_scale_kernel(const double* __restrict__ partial, int32_t n_blocks,
+                                                        int32_t* __restrict__ scale)
 {
-    if (threadIdx.x != 0) return;
+    __shared__ double wmax[4];
     partial += (int64_t)blockIdx.x * n_blocks;  // state blockIdx.x of a batch
-    scale += blockIdx.x;
-    double m = 0.0;
-    for (int32_t b = 0; b < n_blocks; ++b) m = fmax(m, partial[b]);
-    scale[0] = m > 0.0 ? 100 - ilogb(m) : 0;
+    double m = (int)threadIdx.x < n_blocks ? partial[threadIdx.x] : 0.0;
+    for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
+    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    m = fmax(fmax(wmax[0], wmax[1]), fmax(wmax[2], wmax[3]));
+    scale[blockIdx.x] = m > 0.0 ? 100 - ilogb(m) : 0;
 }
 
-// The binary32 records of one line from its binary64 ones (scale s: peaks
-// times 2^s), and its nearest grid point jc.
-__device__ __forceinline__ void to_f32(const WingRec& w, const CoreRec& c, double nu_min, double dnu, int s,
-                                       WingRec32& r, CoreRec32& k, int32_t& jc_out)
+// The binary32 records of one line from its binary64 values (scale s: peaks
+// times 2^s).
+__device__ __forceinline__ void to_f32(const WingLine& w, const CoreRec& c, int32_t jc, double nu_min, double dnu,
+                                       int s, WingRec32& r, CoreRec32& k)
 {
+    const double a2 = w.alpha * w.alpha;
+    const double GH = w.G2 + 1.5 * a2;
+    const double M2 = 3.0 * (w.G2 - a2);
+    const double M1 = 3.0 * (w.G2 * w.G2) + 2.25 * (a2 * a2);
+    const double M0 = w.G2 * (GH * GH);
+    const double Cn = GH * (2.0 * GH + w.G2) * (1.0 / 3.0);
     const double alpha = 1.0 / c.invA;
     const double G = sqrt(w.G2);
     const bool use_alpha = c.y2 < kGH1R2;  // the line has 3-node or core points
     const double lam = use_alpha ? alpha : (G > 0.0 ? G : alpha);
     const double il = 1.0 / lam;
-    const int32_t jc = nearest_point(w.nu0, nu_min, dnu);
     const double f = w.nu0 - fma((double)jc, dnu, nu_min);  // |f| <~ dnu/2
     r.du = (float)(dnu * il);
     r.fu = (float)(f * il);
     r.Lg = (float)ldexp(w.Lg * il * il, s);
     r.G2 = (float)(w.G2 * il * il);
     const double il2 = il * il;
-    r.M2 = (float)(w.M2 * il2);
-    r.M1 = (float)(w.M1 * il2 * il2);
-    r.M0 = (float)(w.M0 * il2 * il2 * il2);
-    r.Cn = (float)(w.Cn * il2 * il2);
-    jc_out = jc;
+    r.M2 = (float)(M2 * il2);
+    r.M1 = (float)(M1 * il2 * il2);
+    r.M0 = (float)(M0 * il2 * il2 * il2);
+    r.Cn = (float)(Cn * il2 * il2);
     k.dx = (float)(dnu * c.invA);
     k.fx = (float)(f * c.invA);
     k.y = (float)c.y;
@@ -374,68 +361,43 @@ __device__ __forceinline__ void to_f32(const WingRec& w, const CoreRec& c, doubl
     k.pad = 0.0f;
 }
 
-__global__ __launch_bounds__(256) void line_prep_f32_kernel(
-    const WingRec* __restrict__ wing, WingIdx* __restrict__ idx, const CoreRec* __restrict__ core,
-    int64_t n, double nu_min, double dnu, const int32_t* __restrict__ scale,
-    WingRec32* __restrict__ w32, CoreRec32* __restrict__ c32)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    {  // state blockIdx.y of a batch: records n apart
-        const int64_t o = (int64_t)blockIdx.y * n;
-        wing += o;
-        idx += o;
-        core += o;
-        w32 += o;
-        c32 += o;
-        scale += blockIdx.y;
-    }
-    WingRec32 r;
-    CoreRec32 k;
-    to_f32(wing[i], core[i], nu_min, dnu, scale[0], r, k, idx[i].jc);
-    w32[i] = r;
-    c32[i] = k;
-}
-
-// Line prep straight to the binary32 records: the binary64 records of line
-// i for state blockIdx.y (constants pps[blockIdx.y]) in registers, the
-// index record with its centre to idx, the binary32 records to w32 and c32
-// (records n_lines apart per state).  The same values as the binary64 prep
-// followed by line_prep_f32_kernel.
-__global__ __launch_bounds__(256) void line_prep_f32_direct_kernel(LinesDev L, const PrepParams* __restrict__ pps,
-                                                                   double nu_min, double dnu,
-                                                                   const int32_t* __restrict__ scale,
-                                                                   WingIdx* __restrict__ idx,
-                                                                   WingRec32* __restrict__ w32,
-                                                                   CoreRec32* __restrict__ c32)
+// The binary64 values of line i in registers (a peak pass and this one: 95 us
+// on 1e6 lines, against 140 us by way of binary64 records in memory; state
+// blockIdx.y of a batch, constants pps[blockIdx.y], or the one state pp), the index record to idx,
+// the binary32 records to w32 and c32 (records n_lines apart per state).
+__global__ __launch_bounds__(256) void line_prep_f32_kernel(LinesDev L, PrepParams pp,
+                                                            const PrepParams* __restrict__ pps,
+                                                            const int32_t* __restrict__ scale,
+                                                            WingIdx* __restrict__ idx, WingRec32* __restrict__ w32,
+                                                            CoreRec32* __restrict__ c32)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= L.n) return;
     const int64_t o = (int64_t)blockIdx.y * L.n;
-    WingRec w;
+    const PrepParams& q = pps ? pps[blockIdx.y] : pp;
+    WingLine w;
     WingIdx x;
     CoreRec c;
-    line_prep_vals(L, pps[blockIdx.y], i, w, x, c);
+    line_prep_vals(L, q, i, w, x, c);
     WingRec32 r;
     CoreRec32 k;
-    to_f32(w, c, nu_min, dnu, scale[blockIdx.y], r, k, x.jc);
+    to_f32(w, c, x.jc, q.nu_min, q.dnu, scale[blockIdx.y], r, k);
     idx[o + i] = x;
     w32[o + i] = r;
     c32[o + i] = k;
 }
 
-// Per-block maxima of the peak bound over the lines of state blockIdx.y,
-// from the line list (the values f32_peak_kernel takes from the records).
-__global__ __launch_bounds__(256) void f32_peak_lines_kernel(LinesDev L, const PrepParams* __restrict__ pps,
-                                                             double* __restrict__ partial)
+// Per-block maxima of the peak bound over the lines of state blockIdx.y.
+__global__ __launch_bounds__(256) void f32_peak_kernel(LinesDev L, PrepParams pp, const PrepParams* __restrict__ pps,
+                                                       double* __restrict__ partial)
 {
     __shared__ double red[256];
-    const PrepParams& pp = pps[blockIdx.y];
+    const PrepParams& q = pps ? pps[blockIdx.y] : pp;
     partial += (int64_t)blockIdx.y * gridDim.x;
     double m = 0.0;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < L.n;
          i += (int64_t)gridDim.x * blockDim.x)
-        m = fmax(m, line_peak(line_scaled(L, pp, i)));
+        m = fmax(m, line_peak(line_scaled(L, q, i)));
     red[threadIdx.x] = m;
     __syncthreads();
     for (int k = 128; k > 0; k >>= 1) {
@@ -444,8 +406,6 @@ __global__ __launch_bounds__(256) void f32_peak_lines_kernel(LinesDev L, const P
     }
     if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
 }
-
-
 
 // The wing's Kahan pair (sum, comp) of each point; the series sum, when not
 // zero, Kahan-added to it (value = s - c, c the running correction); then
@@ -481,43 +441,22 @@ __global__ __launch_bounds__(256) void f32_finish_kernel(const float* __restrict
 
 }  // namespace
 
-hipError_t launch_f32_scale(const WingRec* wing, const CoreRec* core, int64_t n_lines,
-                            double* partial, int32_t n_blocks, int32_t* scale, hipStream_t s, int32_t n_states)
+hipError_t launch_f32_scale(const LinesDev& L, const PrepParams& pp, const PrepParams* pps, double* partial,
+                            int32_t n_blocks, int32_t* scale, hipStream_t s, int32_t n_states)
 {
     if (n_states <= 0) return hipSuccess;
-    f32_peak_kernel<<<dim3(n_blocks, n_states), dim3(256), 0, s>>>(wing, core, n_lines, partial);
-    f32_scale_kernel<<<dim3(n_states), dim3(64), 0, s>>>(partial, n_blocks, scale);
+    if (n_blocks > 256) return hipErrorInvalidValue;
+    f32_peak_kernel<<<dim3(n_blocks, n_states), dim3(256), 0, s>>>(L, pp, pps, partial);
+    f32_scale_kernel<<<dim3(n_states), dim3(256), 0, s>>>(partial, n_blocks, scale);
     return hipGetLastError();
 }
 
-hipError_t launch_f32_scale_lines(const LinesDev& L, const PrepParams* pps, double* partial, int32_t n_blocks,
-                                  int32_t* scale, hipStream_t s, int32_t n_states)
-{
-    if (n_states <= 0) return hipSuccess;
-    f32_peak_lines_kernel<<<dim3(n_blocks, n_states), dim3(256), 0, s>>>(L, pps, partial);
-    f32_scale_kernel<<<dim3(n_states), dim3(64), 0, s>>>(partial, n_blocks, scale);
-    return hipGetLastError();
-}
-
-hipError_t launch_line_prep_f32_direct(const LinesDev& L, const PrepParams* pps, int32_t n_states, double nu_min,
-                                       double dnu, const int32_t* scale, WingIdx* idx, WingRec32* w32,
-                                       CoreRec32* c32, hipStream_t s)
+hipError_t launch_line_prep_f32(const LinesDev& L, const PrepParams& pp, const PrepParams* pps, const int32_t* scale,
+                                WingIdx* idx, WingRec32* w32, CoreRec32* c32, hipStream_t s, int32_t n_states)
 {
     if (L.n == 0 || n_states <= 0) return hipSuccess;
     const int64_t blocks = (L.n + 255) / 256;
-    line_prep_f32_direct_kernel<<<dim3((unsigned)blocks, n_states), dim3(256), 0, s>>>(L, pps, nu_min, dnu, scale,
-                                                                                        idx, w32, c32);
-    return hipGetLastError();
-}
-
-hipError_t launch_line_prep_f32(const WingRec* wing, WingIdx* idx, const CoreRec* core,
-                                int64_t n_lines, double nu_min, double dnu, const int32_t* scale,
-                                WingRec32* w32, CoreRec32* c32, hipStream_t s, int32_t n_states)
-{
-    if (n_lines == 0 || n_states <= 0) return hipSuccess;
-    const int64_t blocks = (n_lines + 255) / 256;
-    line_prep_f32_kernel<<<dim3((unsigned)blocks, n_states), dim3(256), 0, s>>>(wing, idx, core, n_lines, nu_min,
-                                                                                 dnu, scale, w32, c32);
+    line_prep_f32_kernel<<<dim3((unsigned)blocks, n_states), dim3(256), 0, s>>>(L, pp, pps, scale, idx, w32, c32);
     return hipGetLastError();
 }
 

@@ -102,6 +102,8 @@ constexpr int kNearCap = 768;
 // A rest of up to this many lines of a leaf's is taken with a point per lane:
 // ~27 issue slots a line, against ~1900 for a batch of a line per lane.
 constexpr int kFewDirect = 48;
+// Marks a ring's entry (a line's offset from lo, below 2^31) as 3-node.
+constexpr uint32_t kThree = 0x80000000u;
 // Points of a leaf evaluated at a time.
 constexpr int kPoints = 16;
 
@@ -120,14 +122,12 @@ __device__ inline double qrcp3(double den)
     return fma(r, fma(e, e, e), r);
 }
 
-// 3-node rule of one point: S Phi = Lg n / m with q = dv^2,
-// n = q (q + Bn) + Cn, m = (q + G2)(q (q + B) + C) = ((q + M2) q + M1) q + M0.
-__device__ inline void gh3_nm(double dv, double M2, double M1, double M0, double Bn, double Cn,
-                              double& n, double& m)
+// 3-node rule of one point, S Phi = Lg n / m (WingRec): six operations.
+__device__ inline void gh3_nm(double dv, double X, double a2, double c, double p, double r, double& n, double& m)
 {
-    const double q = dv * dv;
-    n = fma(q, q + Bn, Cn);
-    m = fma(fma(q + M2, q, M1), q, M0);
+    const double x = fma(dv, dv, X);
+    n = fma(x, fma(0.5, a2, x), c);
+    m = fma(fma(x, x, p), x, r);
 }
 
 // How a line meets the tile of W points from t0 (t1: its last point on the
@@ -157,24 +157,23 @@ __device__ inline Meets meets(const WingIdx& r, int32_t t0, int32_t t1, int32_t 
 // acc[k] += the line (one per lane) at the nodes dvc + h kNode[k] (dvc: the
 // tile's centre less nu0).  Lanes without a line have Lg = 0.  The 3-node
 // rule's coefficients are those of WingRec, from G2 and alpha^2; with
-// alpha^2 = 0 it is the 1-node rule, so lanes of both rules can share a
-// call; with any3 false (uniform) every lane takes the 1-node rule.  Four
-// nodes share one reciprocal (the binary64 reciprocal issues at a quarter of
+// alpha^2 = 0 it is the 1-node rule, so lanes of both rules share a call (a
+// path of its own for 1-node lines made the compiler hold the sums twice: 208
+// registers).  Four nodes share one reciprocal (the binary64 reciprocal issues at a quarter of
 // the FMA rate): with P01 = d_0 d_1, P23 = d_2 d_3, c = Lg / (P01 P23),
 // Lg/d_0 = (c P23) d_1 and so on.
 __device__ __forceinline__ void far_eval(double (&acc)[kFarNodes], double dvc, double h, double Lg, double G2,
-                                         double a2, bool any3)
+                                         double a2)
 {
-    const double GH = fma(1.5, a2, G2);
-    const double M2 = 3.0 * (G2 - a2), M1 = fma(3.0 * G2, G2, 2.25 * a2 * a2), M0 = G2 * (GH * GH);
-    const double Bn = fma(2.0, G2, -1.5 * a2), Cn = GH * fma(2.0, GH, G2) * (1.0 / 3.0);
+    const double X = G2 - a2, cc = a2 * fma(4.0, G2, a2), p = a2 * fma(6.0, G2, -0.75 * a2);
+    const double r = a2 * a2 * fma(6.0, G2, 0.25 * a2);
 #pragma unroll
     for (int g = 0; g < kFarNodes / 4; ++g) {
         double nn[4], mm[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const double t = (e & 2) ? -kNode[2 * g + (e & 1)] : kNode[2 * g + (e & 1)];
-            gh3_nm(fma(t, h, dvc), M2, M1, M0, Bn, Cn, nn[e], mm[e]);
+            gh3_nm(fma(t, h, dvc), X, a2, cc, p, r, nn[e], mm[e]);
         }
         const double P01 = mm[0] * mm[1], P23 = mm[2] * mm[3];
         const double c = qrcp3(P01 * P23) * Lg;
@@ -291,7 +290,7 @@ __device__ __forceinline__ double direct_four(const WingRec* const (&r)[4], cons
         const bool on = __builtin_amdgcn_inverse_ballot_w64(one[e]);
         const double dv = x - r[e]->nu0;
         double n, m;
-        gh3_nm(dv, r[e]->M2, r[e]->M1, r[e]->M0, r[e]->Bn, r[e]->Cn, n, m);
+        gh3_nm(dv, r[e]->X, r[e]->a2, r[e]->c, r[e]->p, r[e]->r, n, m);
         m = on ? fma(dv, dv, r[e]->G2) : m;
         n = (on ? 1.0 : n) * r[e]->Lg;
         num[e] = tk ? n : 0.0;
@@ -323,12 +322,11 @@ __device__ inline double one_to_two(double v, int32_t m)
 // acc[p] += the line (one per lane) at points x[p] of a leaf where bit p of
 // tk is set (its window holds the point outside the series); bit p of on:
 // the 1-node rule, else the 3-node rule.  Points not taken have numerator 0
-// and a denominator of about 1 (a series point's may be 0 or negative).  kOne, kThree: some lane takes points of that rule.
+// and a denominator of about 1 (a series point's may be 0 or negative).  kOne, kGh3: some lane takes points of that rule.
 // Four points share one reciprocal, as at the nodes.
-template <bool kOne, bool kThree>
+template <bool kOne, bool kGh3>
 __device__ __forceinline__ void point_eval(double (&acc)[kPoints], const double (&x)[kPoints], uint32_t tk,
-                                           uint32_t on, double nu0, double Lg, double G2, double M2, double M1,
-                                           double M0, double Bn, double Cn)
+                                           uint32_t on, const WingRec& l)
 {
 #pragma unroll
     for (int g = 0; g < kPoints; g += 4) {
@@ -337,19 +335,19 @@ __device__ __forceinline__ void point_eval(double (&acc)[kPoints], const double 
         for (int e = 0; e < 4; ++e) {
             const int p = g + e;
             const int32_t take = (int32_t)(tk << (31 - p)) >> 31;  // all ones where the point is taken
-            const double dv = x[p] - nu0;
+            const double dv = x[p] - l.nu0;
             double nn, dd;
-            if constexpr (kThree) gh3_nm(dv, M2, M1, M0, Bn, Cn, nn, dd);
+            if constexpr (kGh3) gh3_nm(dv, l.X, l.a2, l.c, l.p, l.r, nn, dd);
             if constexpr (kOne) {
-                const bool one = !kThree || ((on >> p) & 1u);
-                dd = one ? fma(dv, dv, G2) : dd;
+                const bool one = !kGh3 || ((on >> p) & 1u);
+                dd = one ? fma(dv, dv, l.G2) : dd;
                 nn = one ? 1.0 : nn;
             }
             num[e] = masked(nn, take);
             den[e] = one_to_two(dd, take);
         }
         const double P01 = den[0] * den[1], P23 = den[2] * den[3];
-        const double c = qrcp3(P01 * P23) * Lg;
+        const double c = qrcp3(P01 * P23) * l.Lg;
         const double c01 = c * P23, c23 = c * P01;
         acc[g] = fma(c01 * den[1], num[0], acc[g]);
         acc[g + 1] = fma(c01 * den[0], num[1], acc[g + 1]);
@@ -361,16 +359,15 @@ __device__ __forceinline__ void point_eval(double (&acc)[kPoints], const double 
 
 // The same with a division per point, for lines outside the grouping range.
 __device__ __forceinline__ void point_eval_single(double (&acc)[kPoints], const double (&x)[kPoints], uint32_t tk,
-                                                  uint32_t on, double nu0, double Lg, double G2, double M2,
-                                                  double M1, double M0, double Bn, double Cn)
+                                                  uint32_t on, const WingRec& l)
 {
 #pragma unroll
     for (int p = 0; p < kPoints; ++p) {
-        const double dv = x[p] - nu0;
+        const double dv = x[p] - l.nu0;
         double nn, mm;
-        gh3_nm(dv, M2, M1, M0, Bn, Cn, nn, mm);
+        gh3_nm(dv, l.X, l.a2, l.c, l.p, l.r, nn, mm);
         const bool one = (on >> p) & 1u;
-        const double v = qdiv(Lg * (one ? 1.0 : nn), one ? fma(dv, dv, G2) : mm);
+        const double v = qdiv(l.Lg * (one ? 1.0 : nn), one ? fma(dv, dv, l.G2) : mm);
         acc[p] += (tk >> p) & 1u ? v : 0.0;
     }
 }
@@ -384,7 +381,7 @@ struct WingLds {
     double point[kWaves][kSub];        // the lines taken point by point
     uint32_t near[kWaves][kNearCap];   // lines (offsets from lo) the sub-tile does not admit
     uint16_t direct[kWaves][kNearCap]; // of those, the ones the current leaf does not admit either
-    uint32_t queue[kWaves][2][128];    // rings of lines for the nodes of the sub-tile, of a leaf
+    uint32_t queue[kWaves][2][128];    // rings of lines (with kThree) for the nodes of the sub-tile, of a leaf
     uint64_t done[kWaves];             // bit b: batch 4 b + wave needs nothing below the block
 };
 
@@ -456,9 +453,9 @@ __device__ __forceinline__ void wing_f64_tile(int64_t t, int64_t L0, int64_t L1,
                 dvc = (xref - r.nu0) + hb;
                 Lg = r.Lg;
                 G2 = r.G2;
-                a2 = three ? fma(r.M2, -1.0 / 3.0, G2) : 0.0;
+                a2 = three ? r.a2 : 0.0;
             }
-            far_eval(acc, dvc, hb, Lg, G2, a2, __ballot(three) != 0);
+            far_eval(acc, dvc, hb, Lg, G2, a2);
         }
         if (any_block) wave_reduce(acc, S.block[wave], lane);
         if (lane == 0) S.done[wave] = done;
@@ -488,16 +485,17 @@ __device__ __forceinline__ void wing_f64_tile(int64_t t, int64_t L0, int64_t L1,
             }
             if (!last) {
                 const int32_t i = base + lane;
-                bool far = false, keep = false;
+                bool far = false, keep = false, three = false;
                 if (i < nl) {
                     const WingIdx r = idx[i];
                     const Meets m = meets(r, s0, s1, kSub, far_ok);
                     const bool up = meets(r, b0, b1, kBlock, far_ok).far;
                     far = kThreeLevels && m.far && !up;
+                    three = m.three;
                     keep = m.touches && !far && !up;
                 }
                 const uint64_t fm = __ballot(far), km = __ballot(keep);
-                if (far) qs[(q_head + q_n + __builtin_popcountll(fm & below)) & 127] = (uint32_t)i;
+                if (far) qs[(q_head + q_n + __builtin_popcountll(fm & below)) & 127] = (uint32_t)i | (three ? kThree : 0u);
                 if (keep) near[n_near + __builtin_popcountll(km & below)] = (uint32_t)i;
                 q_n += __builtin_popcountll(fm);
                 n_near += __builtin_popcountll(km);
@@ -505,17 +503,15 @@ __device__ __forceinline__ void wing_f64_tile(int64_t t, int64_t L0, int64_t L1,
             }
             while (q_n >= (last ? 1 : 64)) {  // full batches; what is left at the end
                 double dvc = 1.0, Lg = 0.0, G2 = 1.0, a2 = 0.0;
-                bool three = false;
                 if (lane < q_n) {
-                    const uint32_t i = qs[(q_head + lane) & 127];
-                    const WingRec& r = wing[i];
+                    const uint32_t e = qs[(q_head + lane) & 127];
+                    const WingRec& r = wing[e & ~kThree];
                     dvc = (xref - r.nu0) + cs;
                     Lg = r.Lg;
                     G2 = r.G2;
-                    three = idx[i].g3lo <= s0 && idx[i].g3hi >= s1;
-                    a2 = three ? fma(r.M2, -1.0 / 3.0, G2) : 0.0;
+                    a2 = (e & kThree) ? r.a2 : 0.0;
                 }
-                far_eval(acc, dvc, hs, Lg, G2, a2, __ballot(three) != 0);
+                far_eval(acc, dvc, hs, Lg, G2, a2);
                 const int done = min(q_n, 64);
                 q_head = (q_head + done) & 127;
                 q_n -= done;
@@ -534,18 +530,19 @@ __device__ __forceinline__ void wing_f64_tile(int64_t t, int64_t L0, int64_t L1,
                     for (int k = 0;; k += 64) {
                         const bool lastk = k >= n_near;
                         if (!lastk) {
-                            bool far = false, direct = false;
+                            bool far = false, direct = false, three = false;
                             uint32_t i = 0;
                             if (k + lane < n_near) {
                                 i = near[k + lane];
                                 const WingIdx w = idx[i];
                                 const Meets m = meets(w, l0, l1, kLeaf, far_ok);
                                 far = m.far;
+                                three = m.three;
                                 // (a leaf wholly inside the series is the series kernel's)
                                 direct = m.touches && !m.far && !(w.clo <= l0 && w.chi >= l1);
                             }
                             const uint64_t fm = __ballot(far), dm = __ballot(direct);
-                            if (far) ql[(h_l + n_l + __builtin_popcountll(fm & below)) & 127] = i;
+                            if (far) ql[(h_l + n_l + __builtin_popcountll(fm & below)) & 127] = i | (three ? kThree : 0u);
                             if (direct) dir[n_d + __builtin_popcountll(dm & below)] = (uint16_t)(k + lane);
                             n_l += __builtin_popcountll(fm);
                             n_d += __builtin_popcountll(dm);
@@ -553,17 +550,15 @@ __device__ __forceinline__ void wing_f64_tile(int64_t t, int64_t L0, int64_t L1,
                         }
                         while (n_l >= (lastk ? 1 : 64)) {
                             double dvc = 1.0, Lg = 0.0, G2 = 1.0, a2 = 0.0;
-                            bool three = false;
                             if (lane < n_l) {
-                                const uint32_t i = ql[(h_l + lane) & 127];
-                                const WingRec& r = wing[i];
+                                const uint32_t e = ql[(h_l + lane) & 127];
+                                const WingRec& r = wing[e & ~kThree];
                                 dvc = (xref - r.nu0) + cl;
                                 Lg = r.Lg;
                                 G2 = r.G2;
-                                three = idx[i].g3lo <= l0 && idx[i].g3hi >= l1;
-                                a2 = three ? fma(r.M2, -1.0 / 3.0, G2) : 0.0;
+                                a2 = (e & kThree) ? r.a2 : 0.0;
                             }
-                            far_eval(la, dvc, hl, Lg, G2, a2, __ballot(three) != 0);
+                            far_eval(la, dvc, hl, Lg, G2, a2);
                             any_leaf = true;
                             const int done = min(n_l, 64);
                             h_l = (h_l + done) & 127;
@@ -613,7 +608,7 @@ __device__ __forceinline__ void wing_f64_tile(int64_t t, int64_t L0, int64_t L1,
                             const bool on = __builtin_amdgcn_inverse_ballot_w64(readlane64(one, at));
                             const double dv = x - r->nu0;
                             double nn, mm;
-                            gh3_nm(dv, r->M2, r->M1, r->M0, r->Bn, r->Cn, nn, mm);
+                            gh3_nm(dv, r->X, r->a2, r->c, r->p, r->r, nn, mm);
                             const double v = qdiv(r->Lg * (on ? 1.0 : nn), on ? fma(dv, dv, r->G2) : mm);
                             dacc += tk ? v : 0.0;
                         }
@@ -642,16 +637,13 @@ __device__ __forceinline__ void wing_f64_tile(int64_t t, int64_t L0, int64_t L1,
                             if (!__ballot(tk != 0)) continue;
                             const bool any1 = __ballot((tk & on) != 0) != 0, any3 = __ballot((tk & ~on) != 0) != 0;
                             if (__ballot(!safe))
-                                point_eval_single(pa, x, tk, on, r.nu0, r.Lg, r.G2, r.M2, r.M1, r.M0, r.Bn, r.Cn);
+                                point_eval_single(pa, x, tk, on, r);
                             else if (!any1)
-                                point_eval<false, true>(pa, x, tk, on, r.nu0, r.Lg, r.G2, r.M2, r.M1, r.M0, r.Bn,
-                                                        r.Cn);
+                                point_eval<false, true>(pa, x, tk, on, r);
                             else if (!any3)
-                                point_eval<true, false>(pa, x, tk, on, r.nu0, r.Lg, r.G2, r.M2, r.M1, r.M0, r.Bn,
-                                                        r.Cn);
+                                point_eval<true, false>(pa, x, tk, on, r);
                             else
-                                point_eval<true, true>(pa, x, tk, on, r.nu0, r.Lg, r.G2, r.M2, r.M1, r.M0, r.Bn,
-                                                       r.Cn);
+                                point_eval<true, true>(pa, x, tk, on, r);
                         }
                         double* dst = &S.point[wave][lf * kLeaf + p0 + 4 * (lane >> 4)];
                         double h8[8];
