@@ -239,8 +239,8 @@ int hk_read_par(const char* path, int64_t first, int32_t molecule, const hk_line
  * with the Gauss-Hermite terms, into a grid of their own that is then added
  * on ctx's stream (fork and join by events, so the call stays ordered on
  * ctx's stream; hk_tables does the same per batch).  Asynchronous, except
- * on grids above ~2e7 points, where each stage's work plan is read back once
- * (two stream synchronisations) to size its scratch. */
+ * on grids above ~2e7 points, where the work plans are read back once (a
+ * stream synchronisation) to size their scratch. */
 int hk_opacity(hk_ctx* ctx, const hk_state* state, const hk_grid* grid,
                int precision, void* kappa, void* comp, int accumulate);
 

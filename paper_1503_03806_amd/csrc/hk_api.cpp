@@ -155,6 +155,7 @@ struct hk_ctx {
     // the running total of the points the network evaluated (element 0),
     // over the passes of one hk_opacity / hk_opacity_stream call
     DevBuf sg_used_total;
+    bool sg_counting = false;  // the last call counted
     double sg_budget = 0.0;  // of the current certification
     // resampling: QR factors of the Chebyshev design matrix for the bin
     // sizes of the last call (main and ragged last bin), and the quadrature
@@ -651,18 +652,23 @@ constexpr int32_t kCountBlocks = 256;  // partial sums per evaluation count
 // above ~2e7 points) the plan is read back instead.
 constexpr int64_t kPlanBoundBytes = (int64_t)1 << 30;
 
-// The work plan of n_states states (work_plan.hip): reference tile ranges
-// for reach[s], segment lengths, then the items of the tiles whose ranges
-// (2 n_tiles per state) are given, into pb.  exact, or a bound above
-// kPlanBoundBytes: read the totals back (one host synchronisation) for
-// *items and the partial sums; else their bounds.
-int make_plan(hk_ctx* ctx, PlanBufs& pb, const int64_t* ranges, int64_t n_tiles, int32_t n_states,
-              const double* reach, int32_t tp, int64_t min_seg, int64_t busy_min, const hk_grid* grid, bool exact,
-              WorkPlan* wp, hipStream_t strm, const double* reach_dev = nullptr)
+// A plan being made (work_plan.hip): its job, the range jobs of its tiles and
+// reference tiles, and its tiles' points.
+struct PlanMaking {
+    PlanBufs* pb;
+    PlanJob job;
+    RangeJob tiles, ref;
+    int32_t tp;
+};
+
+// The plan of n_states states' tiles of tp points, n_tiles each, into pb (its
+// buffers sized here); the tiles' line ranges go to ranges (2 n_tiles per
+// state).  The reach: of the one state, or reach_of ([device] n_states).
+int plan_begin(hk_ctx* ctx, PlanBufs& pb, int64_t* ranges, int64_t n_tiles, int32_t n_states, double reach,
+               const double* reach_of, int32_t tp, int64_t min_seg, int64_t busy_min, const hk_grid* grid,
+               PlanMaking* pm)
 {
-    const int64_t n = ctx->n_lines;
-    const int32_t np = (int32_t)grid->n_points;
-    const int64_t n_ref = ((int64_t)np + kRefTilePoints - 1) / kRefTilePoints;
+    const int64_t n_ref = (grid->n_points + kRefTilePoints - 1) / kRefTilePoints;
     const int64_t P = n_tiles * n_states;
     HK_HIP(ctx, pb.ref.ensure((size_t)std::max<int64_t>(n_ref * n_states, 1) * 2 * sizeof(int64_t)),
            "allocating the work plan");
@@ -672,56 +678,72 @@ int make_plan(hk_ctx* ctx, PlanBufs& pb, const int64_t* ranges, int64_t n_tiles,
     HK_HIP(ctx, pb.bsum.ensure((size_t)plan_scratch_count(P) * sizeof(int64_t)), "allocating the work plan");
     HK_HIP(ctx, pb.total.ensure(2 * sizeof(int64_t)), "allocating the work plan");
     int64_t* ref = static_cast<int64_t*>(pb.ref.p);
-    int64_t* seg = static_cast<int64_t*>(pb.seg.p);
-    int64_t* first = static_cast<int64_t*>(pb.first.p);
-    int64_t* slot = static_cast<int64_t*>(pb.slot.p);
-    int64_t* total = static_cast<int64_t*>(pb.total.p);
-    const double* nu = lines_field(ctx, 0);
-    if (reach_dev)  // reach_dev: the same reaches on the device, every state in one launch
-        HK_HIP(ctx, launch_tile_ranges(nu, n, n_ref, kRefTilePoints, grid->nu_min, grid->dnu, np, 0.0, ref, strm,
-                                       reach_dev, n_states),
-               "tile_ranges");
-    else
-        for (int32_t s = 0; s < n_states; ++s)
-            HK_HIP(ctx, launch_tile_ranges(nu, n, n_ref, kRefTilePoints, grid->nu_min, grid->dnu, np, reach[s],
-                                           ref + (int64_t)s * 2 * n_ref, strm),
-                   "tile_ranges");
-    HK_HIP(ctx, launch_seg_length(ref, n_ref, n_states, np, n, min_seg, busy_min, seg, strm), "seg_length");
-    HK_HIP(ctx, launch_work_plan(ranges, n_tiles, n_states, seg, first, slot, static_cast<int64_t*>(pb.bsum.p), total,
-                                 strm),
-           "work_plan");
-    int64_t items = plan_items_bound(P, n_states);
-    int64_t points = n_states * plan_partial_points_bound(np, tp);
-    if (exact || points * 8 > kPlanBoundBytes) {
-        int64_t h[2] = {0, 0};
-        HK_HIP(ctx, hipMemcpyAsync(h, total, sizeof h, hipMemcpyDeviceToHost, strm), "reading the work plan");
-        HK_HIP(ctx, hipStreamSynchronize(strm), "hipStreamSynchronize");
-        items = h[0];
-        points = h[1] * tp;
-    }
-    HK_HIP(ctx, pb.partial.ensure((size_t)std::max<int64_t>(points, 1) * 8), "allocating partial sums");
-    *wp = WorkPlan{seg, first, slot, total, P, items};
+    pm->pb = &pb;
+    pm->tp = tp;
+    pm->tiles = RangeJob{n_tiles, tp, n_states, reach, reach_of, ranges};
+    pm->ref = RangeJob{n_ref, kRefTilePoints, n_states, reach, reach_of, ref};
+    pm->job = PlanJob{ref,      ranges,   n_ref,    n_tiles,
+                      min_seg,  busy_min, n_states, static_cast<int64_t*>(pb.seg.p),
+                      static_cast<int64_t*>(pb.first.p), static_cast<int64_t*>(pb.slot.p),
+                      static_cast<int64_t*>(pb.bsum.p),  static_cast<int64_t*>(pb.total.p)};
     return HK_OK;
 }
 
-// The binary32 wing stage of n_states states whose records lie n_lines apart:
-// the plan, then the wing items and the reduction of cut tiles.  ranges: tile
-// ranges for tiles of `ppl` points per lane; reach[s]: state s's wing reach;
-// sum, comp: the Kahan pairs, n_points per state.
-int wing_stage_f32(hk_ctx* ctx, int ppl, const WingRec32* recs, const WingIdx* idx, const int64_t* ranges,
-                   int64_t n_tiles, int32_t n_states, const double* reach, const hk_grid* grid, float* sum,
-                   float* comp)
+RangeJobs range_jobs(hk_ctx* ctx, const hk_grid* grid)
 {
-    WorkPlan wp;
-    // segments of whole 256-line compensation blocks
-    if (int rc = make_plan(ctx, ctx->ln.wplan, ranges, n_tiles, n_states, reach, opacity_f32_tile_points(ppl), 256,
-                           kBusyMin, grid, false, &wp, ctx->stream))
-        return rc;
-    HK_HIP(ctx, launch_wing_f32(ppl, recs, idx, ranges, ctx->n_lines, n_tiles, n_states, wp, (int32_t)grid->n_points,
-                                sum, comp, static_cast<float2*>(ctx->ln.wplan.partial.p), ctx->wing_edge_paths,
-                                ctx->stream),
-           "wing_f32");
+    RangeJobs rj{};
+    rj.nu = lines_field(ctx, 0);
+    rj.n_lines = ctx->n_lines;
+    rj.nu_min = grid->nu_min;
+    rj.dnu = grid->dnu;
+    rj.n_points = (int32_t)grid->n_points;
+    return rj;
+}
+
+// The items and partial sums of n made plans.  exact, or a bound above
+// kPlanBoundBytes: read their totals back (one host synchronisation) for
+// both; else their bounds.
+int plans_end(hk_ctx* ctx, const PlanMaking* pm, int n, const hk_grid* grid, bool exact, WorkPlan* const* wp,
+              hipStream_t strm)
+{
+    int64_t items[2], points[2], h[2][2] = {{0, 0}, {0, 0}};
+    bool read[2] = {false, false};
+    for (int k = 0; k < n; ++k) {
+        const PlanJob& j = pm[k].job;
+        items[k] = plan_items_bound(j.n_tiles * j.n_states, j.n_states);
+        points[k] = j.n_states * plan_partial_points_bound(grid->n_points, pm[k].tp);
+        read[k] = exact || points[k] * 8 > kPlanBoundBytes;
+        if (read[k])
+            HK_HIP(ctx, hipMemcpyAsync(h[k], j.total, sizeof h[k], hipMemcpyDeviceToHost, strm),
+                   "reading the work plan");
+    }
+    if (read[0] || read[1]) HK_HIP(ctx, hipStreamSynchronize(strm), "hipStreamSynchronize");
+    for (int k = 0; k < n; ++k) {
+        const PlanJob& j = pm[k].job;
+        if (read[k]) {
+            items[k] = h[k][0];
+            points[k] = h[k][1] * pm[k].tp;
+        }
+        HK_HIP(ctx, pm[k].pb->partial.ensure((size_t)std::max<int64_t>(points[k], 1) * 8), "allocating partial sums");
+        *wp[k] = WorkPlan{j.seg, j.first, j.slot, j.total, j.n_tiles * j.n_states, items[k]};
+    }
     return HK_OK;
+}
+
+// Both plans of a pass from their ranges, on strm.
+int make_plans(hk_ctx* ctx, const PlanMaking& w, const PlanMaking& c, const hk_grid* grid, bool exact, WorkPlan* wwp,
+               WorkPlan* cwp, hipStream_t strm)
+{
+    const PlanMaking pm[2] = {w, c};
+    const PlanJob jobs[2] = {w.job, c.job};
+    WorkPlan* const wp[2] = {wwp, cwp};
+    HK_HIP(ctx, launch_work_plans(jobs, 2, grid->n_points, ctx->n_lines, strm), "work_plan");
+    return plans_end(ctx, pm, 2, grid, exact, wp, strm);
+}
+
+CutTiles cut_tiles(const PlanMaking& pm, const WorkPlan& wp)
+{
+    return CutTiles{wp, pm.job.n_tiles, pm.tp, pm.pb->partial.p};
 }
 
 // The side stream (the series beside the wing) and its fork / join
@@ -736,9 +758,12 @@ int ensure_side(hk_ctx* ctx)
 }
 
 // Clears the running count of surrogate evaluations (stream-ordered, by a
-// fill kernel), at the start of each hk_opacity / hk_opacity_stream call.
-int reset_surrogate_count(hk_ctx* ctx)
+// fill kernel), at the start of each hk_opacity / hk_opacity_stream call that
+// counts them.
+int reset_surrogate_count(hk_ctx* ctx, int precision)
 {
+    ctx->sg_counting = precision == HK_F32_SURROGATE;
+    if (!ctx->sg_counting) return HK_OK;
     HK_HIP(ctx, ctx->sg_used_total.ensure(sizeof(int64_t)), "allocating surrogate counters");
     HK_HIP(ctx, launch_zero(ctx->sg_used_total.p, sizeof(int64_t), ctx->stream), "zero");
     return HK_OK;
@@ -748,11 +773,9 @@ int reset_surrogate_count(hk_ctx* ctx)
 // the first states of a batch (one untimed launch, then one timed launch
 // each) and returns the fastest shape.  The shapes give identical results,
 // so the choice affects time only.  (The binary64 wing has one shape.)
-int autotune_wing(hk_ctx* ctx, const hk_state* states, int32_t n_try, const hk_grid* grid, int* best_out)
+int autotune_wing(hk_ctx* ctx, int32_t n_try, const double* d_reach, const hk_grid* grid, int* best_out)
 {
-    const int64_t n = ctx->n_lines;
     const int32_t np = (int32_t)grid->n_points;
-    const double* nu = lines_field(ctx, 0);
     hipEvent_t e0 = nullptr, e1 = nullptr;
     HK_HIP(ctx, hipEventCreate(&e0), "hipEventCreate");
     if (hipEventCreate(&e1) != hipSuccess) {
@@ -762,30 +785,36 @@ int autotune_wing(hk_ctx* ctx, const hk_state* states, int32_t n_try, const hk_g
     int best = 0;
     float best_ms = 0.0f;
     hipError_t err = hipSuccess;
-    std::vector<double> reach((size_t)n_try);
-    for (int32_t s = 0; s < n_try; ++s) reach[(size_t)s] = wing_reach(ctx, &states[s], grid);
+    int rc = HK_OK;
     for (int cand : {2, 4, 8}) {
         const int32_t tp = opacity_f32_tile_points(cand);
         const int64_t n_tiles = ((int64_t)np + tp - 1) / tp;
         err = ctx->tb_ranges.ensure((size_t)std::max<int64_t>(n_tiles * n_try, 1) * 2 * sizeof(int64_t));
         if (err != hipSuccess) break;
         int64_t* ranges = static_cast<int64_t*>(ctx->tb_ranges.p);
-        for (int32_t s = 0; s < n_try && err == hipSuccess; ++s)
-            err = launch_tile_ranges(nu, n, n_tiles, tp, grid->nu_min, grid->dnu, np,
-                                     wing_reach(ctx, &states[s], grid), ranges + (int64_t)s * 2 * n_tiles,
-                                     ctx->stream);
+        PlanMaking pm;
+        WorkPlan wp;
+        // segments of whole 256-line compensation blocks
+        rc = plan_begin(ctx, ctx->ln.wplan, ranges, n_tiles, n_try, 0.0, d_reach, tp, 256, kBusyMin, grid, &pm);
+        if (rc != HK_OK) break;
+        RangeJobs rj = range_jobs(ctx, grid);
+        rj.job[rj.n++] = pm.tiles;
+        rj.job[rj.n++] = pm.ref;
+        err = launch_tile_ranges(rj, ctx->stream);
+        if (err == hipSuccess) err = launch_work_plans(&pm.job, 1, np, ctx->n_lines, ctx->stream);
+        if (err != hipSuccess) break;
+        WorkPlan* const wps[1] = {&wp};
+        rc = plans_end(ctx, &pm, 1, grid, false, wps, ctx->stream);
+        if (rc != HK_OK) break;
         float ms = 0.0f;
         for (int rep = 0; rep < 2 && err == hipSuccess; ++rep) {
             if (rep == 1) err = hipEventRecord(e0, ctx->stream);
             if (err != hipSuccess) break;
-            if (int rc = wing_stage_f32(ctx, cand, static_cast<WingRec32*>(ctx->tb_w32.p),
-                                        static_cast<WingIdx*>(ctx->tb_idx.p), ranges, n_tiles, n_try, reach.data(),
-                                        grid, static_cast<float*>(ctx->tb_out.p),
-                                        static_cast<float*>(ctx->tb_comp.p))) {
-                (void)hipEventDestroy(e0);
-                (void)hipEventDestroy(e1);
-                return rc;
-            }
+            err = launch_wing_f32(cand, static_cast<WingRec32*>(ctx->tb_w32.p), static_cast<WingIdx*>(ctx->tb_idx.p),
+                                  ranges, ctx->n_lines, n_tiles, n_try, wp, np, static_cast<float*>(ctx->tb_out.p),
+                                  static_cast<float*>(ctx->tb_comp.p), static_cast<float2*>(ctx->ln.wplan.partial.p),
+                                  ctx->wing_edge_paths, ctx->stream);
+            if (err != hipSuccess) break;
             if (rep == 1) {
                 err = hipEventRecord(e1, ctx->stream);
                 if (err == hipSuccess) err = hipEventSynchronize(e1);
@@ -800,6 +829,7 @@ int autotune_wing(hk_ctx* ctx, const hk_state* states, int32_t n_try, const hk_g
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
+    if (rc != HK_OK) return rc;
     if (err != hipSuccess) return hip_fail(ctx, err, "autotuning the opacity tiles");
     *best_out = best;
     return HK_OK;
@@ -1189,8 +1219,7 @@ struct Flight {
     const WingIdx* widx = nullptr;
     const int64_t* ranges = nullptr;
     int64_t n_tiles = 0;
-    WorkPlan wwp{};
-    void* wpartial = nullptr;
+    CutTiles wing{}, core{};  // the launched plans
     double nu_min = 0.0, dnu = 0.0;
     // the finish: the series grid, the binary32 sums and scale
     void* series = nullptr;
@@ -1204,8 +1233,8 @@ struct Flight {
 // Binary32 profiles with compensated binary32 sums: scale, binary32 records,
 // the wing's tile ranges and both plans on f->s, then the series on f->cs; the wing and kappa = (sum + comp) 2^-s in
 // binary64 are left to flight_wing and flight_finish.
-static int launch_f32_pass(hk_ctx* ctx, const PrepParams& pp, const hk_grid* grid, double reach, double reach_core,
-                           WingIdx* widx, const int64_t* ranges_c, int64_t n_tiles_c, bool surrogate, Flight* f)
+static int launch_f32_pass(hk_ctx* ctx, const PrepParams& pp, const hk_grid* grid, double reach, WingIdx* widx,
+                           const PlanMaking& cpm, bool surrogate, Flight* f)
 {
     const hipStream_t s = f->s;
     const int64_t n = ctx->n_lines;
@@ -1227,33 +1256,29 @@ static int launch_f32_pass(hk_ctx* ctx, const PrepParams& pp, const hk_grid* gri
     HK_HIP(ctx, ctx->ln.ranges.ensure((size_t)std::max<int64_t>(n_tiles, 1) * 2 * sizeof(int64_t)),
            "allocating tile ranges");
     int64_t* ranges = static_cast<int64_t*>(ctx->ln.ranges.p);
-    {
-        StageTimer tm(ctx, HK_STAGE_LINE_PREP, s);
-        if (n > 0) {
-            const LinesDev L = lines_dev(ctx);
-            HK_HIP(ctx, launch_f32_scale(L, pp, nullptr, static_cast<double*>(ctx->ln.f32partial.p), nblk, scale, s),
-                   "f32_scale");
-            HK_HIP(ctx, launch_line_prep_f32(L, pp, nullptr, scale, widx, w32, c32, s), "line_prep_f32");
-        } else {
-            HK_HIP(ctx, launch_zero(scale, sizeof(int32_t), s), "zero");
-        }
-        HK_HIP(ctx, launch_tile_ranges(static_cast<double*>(ctx->lines.p), n, n_tiles, tp, grid->nu_min,
-                                       grid->dnu, np, reach, ranges, s),
-               "tile_ranges");
-        tm.stop();
-    }
     // as in binary64: both plans, then the series on its stream into its own
     // grid while the wing runs; the finish adds it
     HK_HIP(ctx, ctx->ln.kc.ensure((size_t)std::max(np, 1) * sizeof(double)), "allocating the series grid");
     WorkPlan wwp, cwp;
+    PlanMaking wpm;
+    // segments of whole 256-line compensation blocks for the wing
+    if (int rc = plan_begin(ctx, ctx->ln.wplan, ranges, n_tiles, 1, reach, nullptr, tp, 256, kBusyMin, grid, &wpm))
+        return rc;
     {
         StageTimer tm(ctx, HK_STAGE_LINE_PREP, s);
-        // segments of whole 256-line compensation blocks for the wing
-        if (int rc = make_plan(ctx, ctx->ln.wplan, ranges, n_tiles, 1, &reach, tp, 256, kBusyMin, grid, false, &wwp, s))
-            return rc;
-        if (int rc = make_plan(ctx, ctx->ln.cplan, ranges_c, n_tiles_c, 1, &reach_core, core_f32_tile_points(), 64,
-                               kBusyMin, grid, false, &cwp, s))
-            return rc;
+        RangeJobs rj = range_jobs(ctx, grid);
+        for (const RangeJob& j : {wpm.tiles, wpm.ref, cpm.tiles, cpm.ref}) rj.job[rj.n++] = j;
+        if (n > 0) {
+            const LinesDev L = lines_dev(ctx);
+            HK_HIP(ctx, launch_f32_scale(L, pp, nullptr, static_cast<double*>(ctx->ln.f32partial.p), nblk, scale, rj,
+                                         s),
+                   "f32_scale");
+            HK_HIP(ctx, launch_line_prep_f32(L, pp, nullptr, scale, widx, w32, c32, s), "line_prep_f32");
+        } else {
+            HK_HIP(ctx, launch_zero(scale, sizeof(int32_t), s), "zero");
+            HK_HIP(ctx, launch_tile_ranges(rj, s), "tile_ranges");
+        }
+        if (int rc = make_plans(ctx, wpm, cpm, grid, false, &wwp, &cwp, s)) return rc;
         tm.stop();
     }
     HK_HIP(ctx, hipEventRecord(f->fork, s), "hipEventRecord");
@@ -1264,7 +1289,8 @@ static int launch_f32_pass(hk_ctx* ctx, const PrepParams& pp, const hk_grid* gri
         if (surrogate)
             HK_HIP(ctx, ctx->ln.sg_used.ensure((size_t)std::max<int64_t>(used_n, 1) * sizeof(int64_t)),
                    "allocating surrogate counters");
-        HK_HIP(ctx, launch_core_f32(widx, c32, ranges_c, n, n_tiles_c, 1, cwp, np, static_cast<float*>(ctx->ln.kc.p),
+        HK_HIP(ctx, launch_core_f32(widx, c32, cpm.job.ranges, n, cpm.job.n_tiles, 1, cwp, np,
+                                    static_cast<float*>(ctx->ln.kc.p),
                                     static_cast<float*>(ctx->ln.cplan.partial.p), surrogate ? ctx->sg_copy.p : nullptr,
                                     surrogate ? static_cast<const uint8_t*>(ctx->sg_mask.p) : nullptr,
                                     surrogate ? static_cast<int64_t*>(ctx->ln.sg_used.p) : nullptr, used_n,
@@ -1277,13 +1303,13 @@ static int launch_f32_pass(hk_ctx* ctx, const PrepParams& pp, const hk_grid* gri
     f->recs = w32;
     f->ranges = ranges;
     f->n_tiles = n_tiles;
-    f->wwp = wwp;
-    f->wpartial = ctx->ln.wplan.partial.p;
+    f->wing = cut_tiles(wpm, wwp);
+    f->core = cut_tiles(cpm, cwp);
     f->series = ctx->ln.kc.p;
     f->fs = static_cast<float*>(ctx->ln.f32sum.p);
     f->fc = static_cast<float*>(ctx->ln.f32comp.p);
     f->scale = scale;
-    if (surrogate && n_tiles_c > 0) {
+    if (surrogate && cpm.job.n_tiles > 0) {
         f->sg_used = static_cast<const int64_t*>(ctx->ln.sg_used.p);
         f->used_n = used_n;
     }
@@ -1354,36 +1380,29 @@ static int opacity_launch(hk_ctx* ctx, const hk_state* st, const hk_grid* grid, 
     int64_t* ranges_c = static_cast<int64_t*>(ctx->ln.ranges_core.p);
     f->widx = widx;
 
-    {
-        StageTimer tm(ctx, HK_STAGE_LINE_PREP, s);
-        if (precision == HK_F64) {  // binary32 has records and wing tiles of its own
-            HK_HIP(ctx, launch_line_prep_f64(L, pp, wing, widx, core, s), "line_prep_f64");
-            HK_HIP(ctx, launch_tile_ranges(L.nu, n, n_tiles, tp, grid->nu_min, grid->dnu, np, reach, ranges, s),
-                   "tile_ranges");
-        }
-        HK_HIP(ctx, launch_tile_ranges(L.nu, n, n_tiles_c, tpc, grid->nu_min, grid->dnu, np, reach_core,
-                                       ranges_c, s),
-               "tile_ranges");
-        tm.stop();
-    }
+    PlanMaking wpm, cpm;
+    if (int rc = plan_begin(ctx, ctx->ln.cplan, ranges_c, n_tiles_c, 1, reach_core, nullptr, tpc, 64, kBusyMin, grid,
+                            &cpm))
+        return rc;
     if (precision != HK_F64)
-        return launch_f32_pass(ctx, pp, grid, reach, reach_core, widx, ranges_c, n_tiles_c,
-                               precision == HK_F32_SURROGATE, f);
+        return launch_f32_pass(ctx, pp, grid, reach, widx, cpm, precision == HK_F32_SURROGATE, f);
     // The series runs on a second stream, concurrent with the wing (each
-    // leaves the VALU idle ~20% of the time, which the other fills), into a
+    // leaves the VALU idle part of the time, which the other fills), into a
     // grid of its own; the finish adds it to the wing's: kappa_j = wing_j +
-    // series_j, the same single addition as adding in place.  Both work plans
-    // are made first, on s, so that only the two big kernels run side by
-    // side (small kernels queued behind a running one wait for CUs).
+    // series_j.  The line records, the tile ranges and both work plans are
+    // made first, on s, so that only the two big kernels run side by side
+    // (small kernels queued behind a running one wait for CUs): the records
+    // and every kind of tile's ranges in one launch, both plans in another.
     HK_HIP(ctx, ctx->ln.kc.ensure((size_t)std::max(np, 1) * sizeof(double)), "allocating the series grid");
     WorkPlan wwp, cwp;
+    if (int rc = plan_begin(ctx, ctx->ln.wplan, ranges, n_tiles, 1, reach, nullptr, tp, 64, kBusyMinWing64, grid, &wpm))
+        return rc;
     {
         StageTimer tm(ctx, HK_STAGE_LINE_PREP, s);
-        if (int rc = make_plan(ctx, ctx->ln.wplan, ranges, n_tiles, 1, &reach, tp, 64, kBusyMinWing64, grid, false, &wwp, s))
-            return rc;
-        if (int rc = make_plan(ctx, ctx->ln.cplan, ranges_c, n_tiles_c, 1, &reach_core, tpc, 64, kBusyMin, grid, false,
-                               &cwp, s))
-            return rc;
+        RangeJobs rj = range_jobs(ctx, grid);
+        for (const RangeJob& j : {wpm.tiles, wpm.ref, cpm.tiles, cpm.ref}) rj.job[rj.n++] = j;
+        HK_HIP(ctx, launch_line_prep_f64(L, pp, wing, widx, core, rj, s), "line_prep_f64");
+        if (int rc = make_plans(ctx, wpm, cpm, grid, false, &wwp, &cwp, s)) return rc;
         tm.stop();
     }
     HK_HIP(ctx, hipEventRecord(fork, s), "hipEventRecord");
@@ -1400,8 +1419,8 @@ static int opacity_launch(hk_ctx* ctx, const hk_state* st, const hk_grid* grid, 
     f->recs = wing;
     f->ranges = ranges;
     f->n_tiles = n_tiles;
-    f->wwp = wwp;
-    f->wpartial = ctx->ln.wplan.partial.p;
+    f->wing = cut_tiles(wpm, wwp);
+    f->core = cut_tiles(cpm, cwp);
     f->series = ctx->ln.kc.p;
     return HK_OK;
 }
@@ -1415,13 +1434,14 @@ static int flight_wing(hk_ctx* ctx, const Flight& f, hipStream_t w, hipEvent_t k
     if (kappa_ready) HK_HIP(ctx, hipStreamWaitEvent(w, kappa_ready, 0), "hipStreamWaitEvent");
     StageTimer tm(ctx, HK_STAGE_OPACITY, w);
     if (f.precision == HK_F64)
-        HK_HIP(ctx, launch_wing_f64(static_cast<const WingRec*>(f.recs), f.widx, f.ranges, f.n, f.n_tiles, 1, f.wwp,
+        HK_HIP(ctx, launch_wing_f64(static_cast<const WingRec*>(f.recs), f.widx, f.ranges, f.n, f.n_tiles, 1, f.wing.wp,
                                     static_cast<const WingTables*>(ctx->wing_tab.p), f.nu_min, f.dnu, f.np, f.kappa,
-                                    static_cast<double*>(f.wpartial), f.accumulate ? 1 : 0, w),
+                                    static_cast<double*>(const_cast<void*>(f.wing.partial)), f.accumulate ? 1 : 0, w),
                "wing_f64");
     else
         HK_HIP(ctx, launch_wing_f32(f.ppl, static_cast<const WingRec32*>(f.recs), f.widx, f.ranges, f.n, f.n_tiles,
-                                    1, f.wwp, f.np, f.fs, f.fc, static_cast<float2*>(f.wpartial),
+                                    1, f.wing.wp, f.np, f.fs, f.fc,
+                                    static_cast<float2*>(const_cast<void*>(f.wing.partial)),
                                     ctx->wing_edge_paths, w),
                "wing_f32");
     tm.stop();
@@ -1431,7 +1451,8 @@ static int flight_wing(hk_ctx* ctx, const Flight& f, hipStream_t w, hipEvent_t k
 
 // The finish of a pass on f.s, after the series (and the wing, when it ran
 // on another stream: wing_done): the surrogate's count added to the running
-// total, then kappa from the binary32 sums, or the series grid added to it.
+// total, then kappa from the binary32 sums, or the series grid added to it
+// (the cut tiles of either from their partials).
 static int flight_finish(hk_ctx* ctx, const Flight& f, hipEvent_t wing_done)
 {
     if (wing_done) HK_HIP(ctx, hipStreamWaitEvent(f.s, wing_done, 0), "hipStreamWaitEvent");
@@ -1440,10 +1461,12 @@ static int flight_finish(hk_ctx* ctx, const Flight& f, hipEvent_t wing_done)
         HK_HIP(ctx, launch_sum_counts(f.sg_used, f.used_n, static_cast<int64_t*>(ctx->sg_used_total.p), 1, f.s),
                "sum_counts");
     if (f.precision == HK_F64)
-        HK_HIP(ctx, launch_add_f64(f.kappa, static_cast<const double*>(f.series), f.np, f.s), "add_f64");
-    else
-        HK_HIP(ctx, launch_f32_finish(f.fs, f.fc, static_cast<const float*>(f.series), f.scale, f.np, f.kappa,
+        HK_HIP(ctx, launch_f64_finish(f.kappa, static_cast<const double*>(f.series), f.np, 1, f.wing, f.core,
                                       f.accumulate, f.s),
+               "f64_finish");
+    else
+        HK_HIP(ctx, launch_f32_finish(f.fs, f.fc, static_cast<const float*>(f.series), f.scale, f.np, f.kappa, f.wing,
+                                      f.core, f.accumulate, f.s),
                "f32_finish");
     ctx->have_run = true;
     return HK_OK;
@@ -1479,7 +1502,7 @@ int hk_opacity(hk_ctx* ctx, const hk_state* st, const hk_grid* grid, int precisi
     HK_HIP(ctx, hipSetDevice(ctx->device), "hipSetDevice");
     ctx->last_tables_states = 0;
     ctx->last_stream_chunks = 0;
-    if (int rc = reset_surrogate_count(ctx)) return rc;
+    if (int rc = reset_surrogate_count(ctx, precision)) return rc;
     return opacity_run(ctx, st, grid, precision, static_cast<double*>(kappa), accumulate);
 }
 
@@ -1568,7 +1591,7 @@ int hk_opacity_stream(hk_ctx* ctx, const hk_lines* chunks, int32_t n_chunks, con
     HK_HIP(ctx, hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
     if (int rc = reserve_line_buffers(ctx, n_max, precision)) return rc;
     if (int rc = stream_resources(ctx, (size_t)8 * (size_t)std::max<int64_t>(n_max, 1))) return rc;
-    if (int rc = reset_surrogate_count(ctx)) return rc;
+    if (int rc = reset_surrogate_count(ctx, precision)) return rc;
     HK_HIP(ctx, ctx->st_counts.ensure((size_t)kCountBlocks * 3 * (size_t)n_chunks * sizeof(int64_t)),
            "allocating counters");
     ctx->species = *sp;
@@ -1817,18 +1840,37 @@ int hk_tables(hk_ctx* ctx, const hk_state* states, int32_t n_states, const hk_gr
                                        ctx->stream),
                    "copying batch constants");
         }
+        // the batch's plans: the series', and (its tile shape known) the
+        // wing's; every state of the batch in one launch per step
+        PlanMaking wpm, cpm;
+        if (int rc = plan_begin(ctx, ctx->ln.cplan, rc_all, n_tiles_c, nbat, 0.0, d_reach_c, tpc, 64, kBusyMin, grid,
+                                &cpm))
+            return rc;
+        int64_t* rw = static_cast<int64_t*>(ctx->tb_ranges.p);
+        auto wing_plan = [&]() -> int {
+            const int32_t tp = f64 ? opacity_f64_tile_points(np) : opacity_f32_tile_points(ppl);
+            return plan_begin(ctx, ctx->ln.wplan, rw, ((int64_t)np + tp - 1) / tp, nbat, 0.0, d_reach, tp,
+                              f64 ? 64 : 256, f64 ? kBusyMinWing64 : kBusyMin, grid, &wpm);
+        };
+        RangeJobs rj = range_jobs(ctx, grid);
+        rj.job[rj.n++] = cpm.tiles;
+        rj.job[rj.n++] = cpm.ref;
+        if (!tune) {
+            if (int rc = wing_plan()) return rc;
+            rj.job[rj.n++] = wpm.tiles;
+            rj.job[rj.n++] = wpm.ref;
+        }
         {
-            // every state of the batch in one launch per step
             StageTimer tm(ctx, HK_STAGE_LINE_PREP);
             if (f64) {
                 HK_HIP(ctx, launch_line_prep_f64_batch(L, d_pps, nbat, static_cast<WingRec*>(ctx->tb_wing.p), tidx,
-                                                       static_cast<CoreRec*>(ctx->tb_core.p), ctx->stream),
+                                                       static_cast<CoreRec*>(ctx->tb_core.p), rj, ctx->stream),
                        "line_prep_f64");
             } else {
                 // the states' scales from a pass over the peaks, then the records
                 int32_t* scale = static_cast<int32_t*>(ctx->tb_scale.p);
                 HK_HIP(ctx, launch_f32_scale(L, pps[0], d_pps, static_cast<double*>(ctx->ln.f32partial.p), 256,
-                                             scale, ctx->stream, nbat),
+                                             scale, rj, ctx->stream, nbat),
                        "f32_scale");
                 HK_HIP(ctx, launch_line_prep_f32(L, pps[0], d_pps, scale, tidx,
                                                  static_cast<WingRec32*>(ctx->tb_w32.p),
@@ -1837,33 +1879,25 @@ int hk_tables(hk_ctx* ctx, const hk_state* states, int32_t n_states, const hk_gr
             }
             HK_HIP(ctx, launch_eval_counts(tidx, n, counts + b0 * kCountBlocks * 3, kCountBlocks, ctx->stream, nbat),
                    "eval_counts");
-            HK_HIP(ctx, launch_tile_ranges(L.nu, n, n_tiles_c, tpc, grid->nu_min, grid->dnu, np, 0.0, rc_all,
-                                           ctx->stream, d_reach_c, nbat),
-                   "tile_ranges");
             tm.stop();
         }
         if (tune) {
             const int32_t n_try = std::min<int32_t>(nbat, 4);
-            if (int rc = autotune_wing(ctx, &states[b0], n_try, grid, &ppl)) return rc;
+            if (int rc = autotune_wing(ctx, n_try, d_reach, grid, &ppl)) return rc;
             ctx->tuned.push_back({n, np, cut_steps, ppl});
             tune = false;
+            if (int rc = wing_plan()) return rc;
+            RangeJobs rt = range_jobs(ctx, grid);
+            rt.job[rt.n++] = wpm.tiles;
+            rt.job[rt.n++] = wpm.ref;
+            HK_HIP(ctx, launch_tile_ranges(rt, ctx->stream), "tile_ranges");
         }
-        const int32_t tp = f64 ? opacity_f64_tile_points(np) : opacity_f32_tile_points(ppl);
-        const int64_t n_tiles = ((int64_t)np + tp - 1) / tp;
-        int64_t* rw = static_cast<int64_t*>(ctx->tb_ranges.p);
+        const int64_t n_tiles = wpm.job.n_tiles;
         WorkPlan wwp, cwp;
         {
             StageTimer tm(ctx, HK_STAGE_LINE_PREP);
-            HK_HIP(ctx, launch_tile_ranges(L.nu, n, n_tiles, tp, grid->nu_min, grid->dnu, np, 0.0, rw, ctx->stream,
-                                           d_reach, nbat),
-                   "tile_ranges");
             // the plans of the whole batch, read back to size the launches
-            if (int rc = make_plan(ctx, ctx->ln.wplan, rw, n_tiles, nbat, reach.data(), tp, f64 ? 64 : 256,
-                                   f64 ? kBusyMinWing64 : kBusyMin, grid, true, &wwp, ctx->stream, d_reach))
-                return rc;
-            if (int rc = make_plan(ctx, ctx->ln.cplan, rc_all, n_tiles_c, nbat, reach_c.data(), tpc, 64, kBusyMin, grid, true, &cwp,
-                                   ctx->stream, d_reach_c))
-                return rc;
+            if (int rc = make_plans(ctx, wpm, cpm, grid, true, &wwp, &cwp, ctx->stream)) return rc;
             tm.stop();
         }
         // the series of the batch into its own grids: on the second stream
@@ -1912,9 +1946,9 @@ int hk_tables(hk_ctx* ctx, const hk_state* states, int32_t n_states, const hk_gr
         }
         if (overlap) HK_HIP(ctx, hipStreamWaitEvent(ctx->stream, ctx->ev_join, 0), "hipStreamWaitEvent");
         if (f64)
-            HK_HIP(ctx, launch_add_f64(static_cast<double*>(ctx->tb_out.p), static_cast<double*>(ctx->tb_series.p),
-                                       (int64_t)nbat * np, ctx->stream),
-                   "add_f64");
+            HK_HIP(ctx, launch_f64_finish(static_cast<double*>(ctx->tb_out.p), static_cast<double*>(ctx->tb_series.p),
+                                          np, nbat, cut_tiles(wpm, wwp), cut_tiles(cpm, cwp), 0, ctx->stream),
+                   "f64_finish");
         {
             StageTimer tm(ctx, HK_STAGE_KDIST);
             // the batch's binary64 opacities: the wing grids (binary64), or
@@ -1924,7 +1958,8 @@ int hk_tables(hk_ctx* ctx, const hk_state* states, int32_t n_states, const hk_gr
                 HK_HIP(ctx, launch_f32_finish(static_cast<float*>(ctx->tb_out.p), static_cast<float*>(ctx->tb_comp.p),
                                               static_cast<float*>(ctx->tb_series.p),
                                               static_cast<int32_t*>(ctx->tb_scale.p), np,
-                                              static_cast<double*>(ctx->tb_kappa.p), 0, ctx->stream, nbat),
+                                              static_cast<double*>(ctx->tb_kappa.p), cut_tiles(wpm, wwp),
+                                              cut_tiles(cpm, cwp), 0, ctx->stream, nbat),
                        "f32_finish");
                 kap = static_cast<double*>(ctx->tb_kappa.p);
             }
@@ -2327,7 +2362,7 @@ int hk_stats(hk_ctx* ctx, hk_run_stats* out)
         out->evals_core = c;
         out->evals_gh3 = g - c;
         out->evals_gh1 = e - g;
-        if (!tables && ctx->sg_used_total.p) {  // 0 after hk_tables, which has no surrogate
+        if (!tables && ctx->sg_counting) {  // 0 for calls without the surrogate
             int64_t u = 0;
             HK_HIP(ctx, hipMemcpyAsync(&u, ctx->sg_used_total.p, sizeof u, hipMemcpyDeviceToHost, ctx->stream),
                    "copying counters");

@@ -192,21 +192,27 @@ inline int64_t plan_partial_points_bound(int64_t n_points, int32_t tile_points)
     return 6 * n_points + 2 * (int64_t)tile_points;
 }
 int64_t plan_scratch_count(int64_t n_pairs);  // int64 values of the plan's block sums
-// seg[s] from the reference ranges (tiles of kRefTilePoints points, 2 n_ref
-// values per state) of n_states states; min_seg: the shortest segment, a
-// power of two (256 for the binary32 wing, whose compensated sums run over
-// 256-line blocks aligned to global line indices).  busy_min: a state is cut
-// when fewer reference tiles than that hold lines (or very unevenly many).
+// A state is cut when fewer reference tiles than busy_min hold lines (or very
+// unevenly many).
 constexpr int64_t kBusyMin = 4096;
 // The binary64 wing, a wavefront of which holds 64 points on small grids: 512
 // workgroups already give every SIMD two wavefronts, and a cut item repeats
 // the tiles' reductions and interpolation.
 constexpr int64_t kBusyMinWing64 = 256;
-hipError_t launch_seg_length(const int64_t* ref_ranges, int64_t n_ref, int32_t n_states, int64_t n_points,
-                             int64_t n_lines, int64_t min_seg, int64_t busy_min, int64_t* seg, hipStream_t s);
-// first, slot and total from the tile ranges (2 n_tiles per state) and seg.
-hipError_t launch_work_plan(const int64_t* ranges, int64_t n_tiles, int32_t n_states, const int64_t* seg,
-                            int64_t* first, int64_t* slot, int64_t* block_sums, int64_t* total, hipStream_t s);
+// One plan to make: the segment lengths seg[s] of n_states states from their
+// reference ranges (tiles of kRefTilePoints points, 2 n_ref values per state;
+// min_seg: the shortest segment, a power of two -- 256 for the binary32 wing,
+// whose compensated sums run over 256-line blocks aligned to global line
+// indices), then first, slot and total from the tile ranges (2 n_tiles values
+// per state).
+struct PlanJob {
+    const int64_t *ref, *ranges;
+    int64_t n_ref, n_tiles, min_seg, busy_min;
+    int32_t n_states;
+    int64_t *seg, *first, *slot, *bsum, *total;
+};
+// Both plans of a pass: one launch where they are small (a workgroup each).
+hipError_t launch_work_plans(const PlanJob* jobs, int n_jobs, int64_t n_points, int64_t n_lines, hipStream_t s);
 // Workgroups for `items` items: padded to whole XCD chunks (xcd_rank is a
 // bijection on each multiple of 8 kPlanChunk).
 inline int64_t plan_blocks(int64_t items) { return (items + 8 * kPlanChunk - 1) / (8 * kPlanChunk) * (8 * kPlanChunk); }
@@ -228,6 +234,18 @@ __device__ inline void pair_decode(int64_t p, int64_t n_tiles, int32_t n_states,
     const int64_t rem = p - c * per_chunk;
     st = rem / sz;
     k = c * kPlanChunk + rem % sz;
+}
+// The pair of (state, tile): the inverse of pair_decode.
+__device__ inline int64_t pair_of(int64_t st, int64_t tile, int64_t n_tiles, int32_t n_states)
+{
+    const int64_t k = n_tiles - 1 - tile, c = k / kPlanChunk;
+    const int64_t sz = min((int64_t)kPlanChunk, n_tiles - c * kPlanChunk);
+    return c * kPlanChunk * n_states + st * sz + (k - c * kPlanChunk);
+}
+// Segments of pair p (1: not cut).
+__device__ inline int64_t pair_segments(const WorkPlan& wp, int64_t p)
+{
+    return (p + 1 < wp.n_pairs ? wp.first[p + 1] : wp.total[0]) - wp.first[p];
 }
 struct WorkItem {
     int64_t st, tile;  // state, grid tile
@@ -251,7 +269,7 @@ __device__ inline bool work_item(int64_t r, const WorkPlan& wp, const int64_t* r
         }
         p = a;
     }
-    const int64_t nseg = (p + 1 < wp.n_pairs ? wp.first[p + 1] : total) - wp.first[p];
+    const int64_t nseg = pair_segments(wp, p);
     int64_t k;
     pair_decode(p, n_tiles, n_states, it.st, k);
     it.tile = n_tiles - 1 - k;
@@ -271,18 +289,41 @@ __device__ inline bool work_item(int64_t r, const WorkPlan& wp, const int64_t* r
 }
 
 // ---- launches (stream-ordered, no synchronisation) ----
-hipError_t launch_line_prep_f64(const LinesDev& L, const PrepParams& pp, WingRec* wing,
-                                WingIdx* idx, CoreRec* core, hipStream_t s);
+// Tile line ranges of one kind of tile: n_tiles tiles of tile_points points,
+// the lines within `reach` of each to ranges (2 n_tiles values); or, with
+// reach_of ([device] n_states values), of n_states states, 2 n_tiles apart.
+struct RangeJob {
+    int64_t n_tiles;
+    int32_t tile_points, n_states;
+    double reach;
+    const double* reach_of;
+    int64_t* ranges;
+};
+// The range jobs of one opacity pass (the wing's and the series' tiles and
+// their plans' reference tiles), which share one launch.
+struct RangeJobs {
+    const double* nu;  // sorted line centres
+    int64_t n_lines;
+    double nu_min, dnu;
+    int32_t n_points;
+    int32_t n;
+    RangeJob job[4];
+    int32_t blocks(int k) const { return (int32_t)((job[k].n_tiles * job[k].n_states + 255) / 256); }
+    int64_t blocks() const
+    {
+        int64_t b = 0;
+        for (int k = 0; k < n; ++k) b += blocks(k);
+        return b;
+    }
+};
+hipError_t launch_tile_ranges(const RangeJobs& rj, hipStream_t s);
+// The binary64 records of one state, and the tile ranges, in one launch.
+hipError_t launch_line_prep_f64(const LinesDev& L, const PrepParams& pp, WingRec* wing, WingIdx* idx, CoreRec* core,
+                                const RangeJobs& rj, hipStream_t s);
 // Every state of a batch in one launch: pps [device] n_states constants,
 // records L.n apart per state.
 hipError_t launch_line_prep_f64_batch(const LinesDev& L, const PrepParams* pps, int32_t n_states, WingRec* wing,
-                                      WingIdx* idx, CoreRec* core, hipStream_t s);
-// Tile line ranges for `reach`; or, with reach_of ([device] n_states values),
-// the ranges of n_states states in one launch, 2 n_tiles apart.
-hipError_t launch_tile_ranges(const double* nu_sorted, int64_t n_lines, int64_t n_tiles,
-                              int32_t tile_points, double nu_min, double dnu, int32_t n_points,
-                              double reach, int64_t* ranges, hipStream_t s, const double* reach_of = nullptr,
-                              int32_t n_states = 1);
+                                      WingIdx* idx, CoreRec* core, const RangeJobs& rj, hipStream_t s);
 // Binary64 opacity: the wing kernel writes kappa, the core kernel its
 // series terms.
 int32_t opacity_f64_tile_points(int64_t n_points);  // points per work item on such a grid
@@ -300,9 +341,9 @@ int32_t core_f64_tile_points();
 int32_t core_f32_tile_points();  // points per work item of the binary32 series
 // The wing items of n_states states (records n_lines apart, ranges 2 n_tiles
 // apart, kappa n_points apart); items cut by the plan write partial (binary64,
-// tile_points per slot), which the reduction then adds into kappa.  With
-// accumulate, kappa += the wing sum (single state).  One workgroup per item
-// (wp.launch_items workgroups).
+// tile_points per slot), which the finish adds into kappa.  With accumulate,
+// kappa += the wing sum (single state; cut tiles: by the finish).  One
+// workgroup per item (wp.launch_items workgroups).
 hipError_t launch_wing_f64(const WingRec* wing, const WingIdx* idx, const int64_t* ranges, int64_t n_lines,
                            int64_t n_tiles, int32_t n_states, const WorkPlan& wp, const WingTables* tab,
                            double nu_min, double dnu, int32_t n_points, double* kappa, double* partial,
@@ -317,8 +358,18 @@ hipError_t launch_core_f64(const WingRec* wing, const WingIdx* idx, const CoreRe
 // Zero `bytes` (a multiple of 4) at p with a kernel (unlike hipMemsetAsync,
 // safe to record into a captured graph).
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);
-// a[j] += b[j], j < n.
-hipError_t launch_add_f64(double* a, const double* b, int64_t n, hipStream_t s);
+// A launched plan with its tiles and partial sums, for the finishes: a cut
+// tile's values are the ordered sums of its partials, segment by segment.
+struct CutTiles {
+    WorkPlan wp;
+    int64_t n_tiles;
+    int32_t tile_points;
+    const void* partial;  // double, float2 (binary32 wing) or float (binary32 series)
+};
+// The binary64 finish of n_states grids (n_points apart): kappa = (wing, cut
+// tiles from their partials, + kappa where accumulating) + series.
+hipError_t launch_f64_finish(double* kappa, const double* series, int32_t n_points, int32_t n_states,
+                             const CutTiles& wing, const CutTiles& core, int accumulate, hipStream_t s);
 // n_blocks partial triples per state; n_states states (records n_lines
 // apart, partials 3 n_blocks apart) in one launch.
 hipError_t launch_eval_counts(const WingIdx* idx, int64_t n_lines, int64_t* partial,
@@ -329,8 +380,10 @@ hipError_t launch_eval_counts(const WingIdx* idx, int64_t n_lines, int64_t* part
 // index records and the binary32 records.  One state: its constants pp, pps
 // NULL.  Every state of a batch in one launch each: pps [device] n_states
 // constants (state blockIdx.y), records n_lines apart per state.
+// (The peak pass's launch takes the tile ranges along.)
 hipError_t launch_f32_scale(const LinesDev& L, const PrepParams& pp, const PrepParams* pps, double* partial,
-                            int32_t n_blocks, int32_t* scale, hipStream_t s, int32_t n_states = 1);
+                            int32_t n_blocks, int32_t* scale, const RangeJobs& rj, hipStream_t s,
+                            int32_t n_states = 1);
 hipError_t launch_line_prep_f32(const LinesDev& L, const PrepParams& pp, const PrepParams* pps, const int32_t* scale,
                                 WingIdx* idx, WingRec32* w32, CoreRec32* c32, hipStream_t s, int32_t n_states = 1);
 int32_t opacity_f32_tile_points(int points_per_lane);
@@ -363,9 +416,10 @@ hipError_t launch_sum_counts(const int64_t* used, int64_t n, int64_t* total, int
 // kappa (binary64) = (the Kahan pair (sum, comp) with the series sum, when
 // not zero, Kahan-added) * 2^-s, or += when accumulating; series may be NULL.
 // n_states grids of n_points each (one scale per state) in one launch.
+// Cut tiles of either plan are summed from their partials.
 hipError_t launch_f32_finish(const float* sum, const float* comp, const float* series, const int32_t* scale,
-                             int32_t n_points, double* kappa, int accumulate, hipStream_t s,
-                             int32_t n_states = 1);
+                             int32_t n_points, double* kappa, const CutTiles& wing, const CutTiles& core,
+                             int accumulate, hipStream_t s, int32_t n_states = 1);
 
 // k-distribution.  elem_bytes 8 (binary64 keys) or 4 (binary32 keys).
 int64_t kdist_lds_max_points(int elem_bytes, int64_t lds_bytes);

@@ -209,65 +209,67 @@ __device__ __forceinline__ void line_prep_one(const LinesDev& L, const PrepParam
     core[i] = c;
 }
 
-__global__ __launch_bounds__(256) void line_prep_f64_kernel(LinesDev L, PrepParams pp,
-                                                            WingRec* __restrict__ wing,
-                                                            WingIdx* __restrict__ idx,
-                                                            CoreRec* __restrict__ core)
+// Line index range [first, last) of every tile of the jobs: the lines whose
+// unshifted centre lies within the reach of the tile's points.  Each line in
+// the range is still tested against its exact window by the opacity kernel.
+// Block b of the jobs' blocks; a thread per (state, tile).
+__device__ void tile_ranges_block(const RangeJobs& rj, int64_t b)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < L.n) line_prep_one(L, pp, i, wing, idx, core);
+    int k = 0;
+    for (; k < rj.n; ++k) {
+        const int64_t nb = (rj.job[k].n_tiles * rj.job[k].n_states + 255) / 256;
+        if (b < nb) break;
+        b -= nb;
+    }
+    if (k == rj.n) return;
+    const RangeJob& j = rj.job[k];
+    const int64_t e = b * 256 + threadIdx.x;
+    if (e >= j.n_tiles * j.n_states) return;
+    const int64_t st = e / j.n_tiles, t = e - st * j.n_tiles;
+    const double reach = j.reach_of ? j.reach_of[st] : j.reach;
+    const double* nu = rj.nu;
+    const int64_t j0 = t * j.tile_points;
+    int64_t j1 = j0 + j.tile_points;
+    if (j1 > rj.n_points) j1 = rj.n_points;
+    const double lo_nu = fma((double)j0, rj.dnu, rj.nu_min) - reach;
+    const double hi_nu = fma((double)(j1 - 1), rj.dnu, rj.nu_min) + reach;
+    // both ends by binary search, side by side: first nu >= lo_nu, first nu > hi_nu
+    int64_t a = 0, b2 = rj.n_lines, c = 0, d = rj.n_lines;
+    while (a < b2 || c < d) {
+        const int64_t m = a + ((b2 - a) >> 1), q = c + ((d - c) >> 1);
+        const double vm = a < b2 ? nu[m] : 0.0, vq = c < d ? nu[q] : 0.0;
+        if (a < b2) {
+            if (vm < lo_nu) a = m + 1;
+            else b2 = m;
+        }
+        if (c < d) {
+            if (vq <= hi_nu) c = q + 1;
+            else d = q;
+        }
+    }
+    int64_t* out = j.ranges + 2 * e;
+    out[0] = a;
+    out[1] = max(a, c);
 }
 
-// Every state of a batch in one launch: state blockIdx.y, constants pps[st],
-// records n_lines apart per state.
-__global__ __launch_bounds__(256) void line_prep_f64_batch_kernel(LinesDev L, const PrepParams* __restrict__ pps,
-                                                                  WingRec* __restrict__ wing,
-                                                                  WingIdx* __restrict__ idx,
-                                                                  CoreRec* __restrict__ core)
+__global__ __launch_bounds__(256) void tile_ranges_kernel(RangeJobs rj) { tile_ranges_block(rj, blockIdx.x); }
+
+// One state (constants pp), or every state of a batch (state blockIdx.y,
+// constants pps[st], records n_lines apart per state); the workgroups past
+// the lines (of the first state) take the tile ranges.
+__global__ __launch_bounds__(256) void line_prep_f64_kernel(LinesDev L, PrepParams pp,
+                                                            const PrepParams* __restrict__ pps,
+                                                            WingRec* __restrict__ wing, WingIdx* __restrict__ idx,
+                                                            CoreRec* __restrict__ core, RangeJobs rj)
 {
+    const int64_t nb = (L.n + 255) / 256;
+    if (blockIdx.x >= nb) {
+        if (blockIdx.y == 0) tile_ranges_block(rj, blockIdx.x - nb);
+        return;
+    }
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t o = (int64_t)blockIdx.y * L.n;
-    if (i < L.n) line_prep_one(L, pps[blockIdx.y], i, wing + o, idx + o, core + o);
-}
-
-// Line index range [first, last) of every grid tile: the lines whose
-// unshifted centre lies within `reach` of the tile's points.  Each line in
-// the range is still tested against its exact window by the opacity kernel.
-// reach_of: NULL, or one reach per state (state blockIdx.y, ranges
-// 2 n_tiles apart per state).
-__global__ __launch_bounds__(256) void tile_ranges_kernel(const double* __restrict__ nu, int64_t n,
-                                                          int64_t n_tiles, int32_t tile_points,
-                                                          double nu_min, double dnu,
-                                                          int32_t n_points, double reach,
-                                                          const double* __restrict__ reach_of,
-                                                          int64_t* __restrict__ ranges)
-{
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n_tiles) return;
-    if (reach_of) {
-        reach = reach_of[blockIdx.y];
-        ranges += (int64_t)blockIdx.y * 2 * n_tiles;
-    }
-    int64_t j0 = t * tile_points;
-    int64_t j1 = j0 + tile_points;
-    if (j1 > n_points) j1 = n_points;
-    double lo_nu = fma((double)j0, dnu, nu_min) - reach;
-    double hi_nu = fma((double)(j1 - 1), dnu, nu_min) + reach;
-    int64_t a = 0, b = n;  // first nu >= lo_nu
-    while (a < b) {
-        int64_t m = a + ((b - a) >> 1);
-        if (nu[m] < lo_nu) a = m + 1;
-        else b = m;
-    }
-    int64_t first = a;
-    b = n;  // first nu > hi_nu
-    while (a < b) {
-        int64_t m = a + ((b - a) >> 1);
-        if (nu[m] <= hi_nu) a = m + 1;
-        else b = m;
-    }
-    ranges[2 * t] = first;
-    ranges[2 * t + 1] = a;
+    if (i < L.n) line_prep_one(L, pps ? pps[blockIdx.y] : pp, i, wing + o, idx + o, core + o);
 }
 
 __device__ inline int64_t overlap(int64_t alo, int64_t ahi, int64_t blo, int64_t bhi)
@@ -388,15 +390,20 @@ __global__ __launch_bounds__(256) void line_prep_f32_kernel(LinesDev L, PrepPara
 }
 
 // Per-block maxima of the peak bound over the lines of state blockIdx.y.
+// (n_blocks workgroups per state; those past them, of the first state, take
+// the tile ranges.)
 __global__ __launch_bounds__(256) void f32_peak_kernel(LinesDev L, PrepParams pp, const PrepParams* __restrict__ pps,
-                                                       double* __restrict__ partial)
+                                                       double* __restrict__ partial, int32_t n_blocks, RangeJobs rj)
 {
     __shared__ double red[256];
+    if ((int)blockIdx.x >= n_blocks) {
+        if (blockIdx.y == 0) tile_ranges_block(rj, blockIdx.x - n_blocks);
+        return;
+    }
     const PrepParams& q = pps ? pps[blockIdx.y] : pp;
-    partial += (int64_t)blockIdx.y * gridDim.x;
+    partial += (int64_t)blockIdx.y * n_blocks;
     double m = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < L.n;
-         i += (int64_t)gridDim.x * blockDim.x)
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < L.n; i += (int64_t)n_blocks * blockDim.x)
         m = fmax(m, line_peak(line_scaled(L, q, i)));
     red[threadIdx.x] = m;
     __syncthreads();
@@ -407,46 +414,77 @@ __global__ __launch_bounds__(256) void f32_peak_kernel(LinesDev L, PrepParams pp
     if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
 }
 
-// The wing's Kahan pair (sum, comp) of each point; the series sum, when not
+// The wing's Kahan pair (sum, comp) of each point (a cut tile's: the binary64
+// sum of its partial pairs in segment order, normalised as by an uncut item);
+// the series sum (a cut tile's: its partials in segment order), when not
 // zero, Kahan-added to it (value = s - c, c the running correction); then
 // scaled back into binary64.
 __global__ __launch_bounds__(256) void f32_finish_kernel(const float* __restrict__ sum,
                                                          const float* __restrict__ comp,
                                                          const float* __restrict__ series,
                                                          const int32_t* __restrict__ scale,
-                                                         int32_t n, double* __restrict__ kappa,
-                                                         int accumulate)
+                                                         int32_t n, double* __restrict__ kappa, CutTiles wing,
+                                                         CutTiles core, int accumulate)
 {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= n) return;
-    {  // state blockIdx.y of a batch: grids n apart
-        const int64_t o = (int64_t)blockIdx.y * n;
-        sum += o;
-        comp += o;
-        if (series) series += o;
-        kappa += o;
-        scale += blockIdx.y;
+    const int64_t st = blockIdx.y, o = st * n;  // state of a batch: grids n apart
+    float s, c, x;
+    {
+        int64_t nseg = 1, slot = 0;
+        if (wing.wp.total[0] != wing.wp.n_pairs) {
+            const int64_t p = pair_of(st, j / wing.tile_points, wing.n_tiles, gridDim.y);
+            nseg = pair_segments(wing.wp, p);
+            slot = wing.wp.slot[p];
+        }
+        if (nseg < 2) {
+            s = sum[o + j];
+            c = -comp[o + j];
+        } else {
+            const float2* src = (const float2*)wing.partial + slot * wing.tile_points + j % wing.tile_points;
+            double v = 0.0;
+            for (int64_t sg = 0; sg < nseg; ++sg) {
+                const float2 e = src[sg * wing.tile_points];
+                v += (double)e.x + (double)e.y;
+            }
+            s = (float)v;
+            c = -(float)(v - (double)s);
+        }
     }
-    float s = sum[j], c = -comp[j];
-    const float x = series ? series[j] : 0.0f;
+    {
+        int64_t nseg = 1, slot = 0;
+        if (core.wp.total[0] != core.wp.n_pairs) {
+            const int64_t p = pair_of(st, j / core.tile_points, core.n_tiles, gridDim.y);
+            nseg = pair_segments(core.wp, p);
+            slot = core.wp.slot[p];
+        }
+        if (nseg < 2) {
+            x = series[o + j];
+        } else {
+            const float* src = (const float*)core.partial + slot * core.tile_points + j % core.tile_points;
+            x = 0.0f;
+            for (int64_t sg = 0; sg < nseg; ++sg) x += src[sg * core.tile_points];
+        }
+    }
     if (x != 0.0f) {
         const float y = x - c;
         const float t = s + y;
         c = (t - s) - y;
         s = t;
     }
-    const double v = ldexp((double)s - (double)c, -scale[0]);
-    kappa[j] = accumulate ? kappa[j] + v : v;
+    const double v = ldexp((double)s - (double)c, -scale[st]);
+    kappa[o + j] = accumulate ? kappa[o + j] + v : v;
 }
 
 }  // namespace
 
 hipError_t launch_f32_scale(const LinesDev& L, const PrepParams& pp, const PrepParams* pps, double* partial,
-                            int32_t n_blocks, int32_t* scale, hipStream_t s, int32_t n_states)
+                            int32_t n_blocks, int32_t* scale, const RangeJobs& rj, hipStream_t s, int32_t n_states)
 {
     if (n_states <= 0) return hipSuccess;
-    if (n_blocks > 256) return hipErrorInvalidValue;
-    f32_peak_kernel<<<dim3(n_blocks, n_states), dim3(256), 0, s>>>(L, pp, pps, partial);
+    const int64_t nb = n_blocks + rj.blocks();
+    if (n_blocks > 256 || nb > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
+    f32_peak_kernel<<<dim3((unsigned)nb, n_states), dim3(256), 0, s>>>(L, pp, pps, partial, n_blocks, rj);
     f32_scale_kernel<<<dim3(n_states), dim3(256), 0, s>>>(partial, n_blocks, scale);
     return hipGetLastError();
 }
@@ -461,42 +499,44 @@ hipError_t launch_line_prep_f32(const LinesDev& L, const PrepParams& pp, const P
 }
 
 hipError_t launch_f32_finish(const float* sum, const float* comp, const float* series, const int32_t* scale,
-                             int32_t n_points, double* kappa, int accumulate, hipStream_t s, int32_t n_states)
+                             int32_t n_points, double* kappa, const CutTiles& wing, const CutTiles& core,
+                             int accumulate, hipStream_t s, int32_t n_states)
 {
     if (n_points == 0 || n_states <= 0) return hipSuccess;
     const int64_t blocks = ((int64_t)n_points + 255) / 256;
     f32_finish_kernel<<<dim3((unsigned)blocks, n_states), dim3(256), 0, s>>>(sum, comp, series, scale, n_points,
-                                                                              kappa, accumulate);
+                                                                              kappa, wing, core, accumulate);
     return hipGetLastError();
 }
 
-hipError_t launch_line_prep_f64(const LinesDev& L, const PrepParams& pp, WingRec* wing,
-                                WingIdx* idx, CoreRec* core, hipStream_t s)
+hipError_t launch_line_prep_f64(const LinesDev& L, const PrepParams& pp, WingRec* wing, WingIdx* idx, CoreRec* core,
+                                const RangeJobs& rj, hipStream_t s)
 {
-    if (L.n == 0) return hipSuccess;
-    int64_t blocks = (L.n + 255) / 256;
-    line_prep_f64_kernel<<<dim3((unsigned)blocks), dim3(256), 0, s>>>(L, pp, wing, idx, core);
+    const int64_t blocks = (L.n + 255) / 256 + rj.blocks();
+    if (blocks == 0) return hipSuccess;
+    if (blocks > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
+    line_prep_f64_kernel<<<dim3((unsigned)blocks), dim3(256), 0, s>>>(L, pp, nullptr, wing, idx, core, rj);
     return hipGetLastError();
 }
 
 hipError_t launch_line_prep_f64_batch(const LinesDev& L, const PrepParams* pps, int32_t n_states, WingRec* wing,
-                                      WingIdx* idx, CoreRec* core, hipStream_t s)
+                                      WingIdx* idx, CoreRec* core, const RangeJobs& rj, hipStream_t s)
 {
-    if (L.n == 0 || n_states <= 0) return hipSuccess;
-    int64_t blocks = (L.n + 255) / 256;
-    line_prep_f64_batch_kernel<<<dim3((unsigned)blocks, n_states), dim3(256), 0, s>>>(L, pps, wing, idx, core);
+    if (n_states <= 0) return hipSuccess;
+    const int64_t blocks = (L.n + 255) / 256 + rj.blocks();
+    if (blocks == 0) return hipSuccess;
+    if (blocks > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
+    line_prep_f64_kernel<<<dim3((unsigned)blocks, n_states), dim3(256), 0, s>>>(L, PrepParams{}, pps, wing, idx, core,
+                                                                                rj);
     return hipGetLastError();
 }
 
-hipError_t launch_tile_ranges(const double* nu_sorted, int64_t n_lines, int64_t n_tiles,
-                              int32_t tile_points, double nu_min, double dnu, int32_t n_points,
-                              double reach, int64_t* ranges, hipStream_t s, const double* reach_of,
-                              int32_t n_states)
+hipError_t launch_tile_ranges(const RangeJobs& rj, hipStream_t s)
 {
-    if (n_tiles == 0 || n_states <= 0) return hipSuccess;
-    int64_t blocks = (n_tiles + 255) / 256;
-    tile_ranges_kernel<<<dim3((unsigned)blocks, reach_of ? n_states : 1), dim3(256), 0, s>>>(
-        nu_sorted, n_lines, n_tiles, tile_points, nu_min, dnu, n_points, reach, reach_of, ranges);
+    const int64_t blocks = rj.blocks();
+    if (blocks == 0) return hipSuccess;
+    if (blocks > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
+    tile_ranges_kernel<<<dim3((unsigned)blocks), dim3(256), 0, s>>>(rj);
     return hipGetLastError();
 }
 

@@ -337,36 +337,6 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(kP 
     }
 }
 
-// The cut tiles: each point's value is the binary64 sum of its partial
-// pairs in segment order, stored normalised as by a direct item.
-__global__ __launch_bounds__(256) void wing_f32_reduce_kernel(WorkPlan wp, int64_t n_tiles, int32_t n_states,
-                                                             int32_t tp, int32_t n, const float2* __restrict__ partial,
-                                                             float* __restrict__ sum, float* __restrict__ comp)
-{
-    const int64_t total = wp.total[0];
-    if (total == wp.n_pairs) return;  // nothing cut
-    for (int64_t p = blockIdx.x; p < wp.n_pairs; p += gridDim.x) {
-        const int64_t nseg = (p + 1 < wp.n_pairs ? wp.first[p + 1] : total) - wp.first[p];
-        if (nseg < 2) continue;
-        int64_t st, k;
-        pair_decode(p, n_tiles, n_states, st, k);
-        const int64_t j0 = (n_tiles - 1 - k) * tp;
-        const float2* src = partial + wp.slot[p] * tp;
-        for (int q = threadIdx.x; q < tp; q += blockDim.x) {
-            const int64_t j = j0 + q;
-            if (j >= n) break;
-            double v = 0.0;
-            for (int64_t sg = 0; sg < nseg; ++sg) {
-                const float2 e = src[sg * tp + q];
-                v += (double)e.x + (double)e.y;
-            }
-            const float hi = (float)v;
-            sum[st * (int64_t)n + j] = hi;
-            comp[st * (int64_t)n + j] = (float)(v - (double)hi);
-        }
-    }
-}
-
 // The core series in binary32 (the formula of voigt_core in
 // opacity_f64.hip).  Binary32 cannot hold e^{+-nx} (x up to 10, n up to
 // 34), so the Gaussians are summed directly, each over a fixed window of
@@ -759,31 +729,6 @@ __global__ __launch_bounds__(64 * kWaves) void core_f32_kernel(
     }
 }
 
-// Cut series tiles: series_j = the partials summed in segment order in
-// binary32.
-__global__ __launch_bounds__(256) void core_f32_reduce_kernel(WorkPlan wp, int64_t n_tiles, int32_t n_states,
-                                                             int32_t tp, int32_t n, const float* __restrict__ partial,
-                                                             float* __restrict__ series)
-{
-    const int64_t total = wp.total[0];
-    if (total == wp.n_pairs) return;  // nothing cut
-    for (int64_t p = blockIdx.x; p < wp.n_pairs; p += gridDim.x) {
-        const int64_t nseg = (p + 1 < wp.n_pairs ? wp.first[p + 1] : total) - wp.first[p];
-        if (nseg < 2) continue;
-        int64_t st, k;
-        pair_decode(p, n_tiles, n_states, st, k);
-        const int64_t j0 = (n_tiles - 1 - k) * tp;
-        const float* src = partial + wp.slot[p] * tp;
-        for (int q = threadIdx.x; q < tp; q += blockDim.x) {
-            const int64_t j = j0 + q;
-            if (j >= n) break;
-            float v = 0.0f;
-            for (int64_t sg = 0; sg < nseg; ++sg) v += src[sg * tp + q];
-            series[st * (int64_t)n + j] = v;
-        }
-    }
-}
-
 // total[0] (+)= used[0] + ... + used[n-1], one workgroup (the surrogate's
 // per-workgroup counts of a launch).
 __global__ __launch_bounds__(256) void sum_counts_kernel(const int64_t* __restrict__ used, int64_t n,
@@ -810,9 +755,6 @@ hipError_t launch_wing(const WingRec32* wing, const WingIdx* idx, const int64_t*
     if (nb > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
     wing_f32_kernel<kP><<<dim3((unsigned)nb), dim3(64 * kWaves), 0, s>>>(wing, idx, ranges, n_lines, n_tiles,
                                                                         n_states, wp, n, sum, comp, partial, edges);
-    const int64_t nr = std::min<int64_t>(wp.n_pairs, 8192);
-    wing_f32_reduce_kernel<<<dim3((unsigned)nr), dim3(256), 0, s>>>(wp, n_tiles, n_states, 64 * kP * kWaves, n,
-                                                                    partial, sum, comp);
     return hipGetLastError();
 }
 
@@ -855,9 +797,6 @@ hipError_t launch_core_f32(const WingIdx* idx, const CoreRec32* core, const int6
         core_f32_kernel<false><<<dim3((unsigned)nb), dim3(64 * kWaves), 0, s>>>(
             idx, core, ranges, n_lines, n_tiles, n_states, wp, n_points, series, partial, nullptr, nullptr,
             nullptr);
-    const int64_t nr = std::min<int64_t>(wp.n_pairs, 8192);
-    core_f32_reduce_kernel<<<dim3((unsigned)nr), dim3(256), 0, s>>>(wp, n_tiles, n_states, kCoreTilePoints,
-                                                                    n_points, partial, series);
     return hipGetLastError();
 }
 

@@ -745,32 +745,6 @@ __global__ __launch_bounds__(64 * kWaves) void wing_f64_kernel(
     }
 }
 
-// The cut tiles: kappa_j (+)= the ordered sum of the tile's partials,
-// segment by segment.  Workgroups stride over the (state, tile) pairs.
-__global__ __launch_bounds__(256) void wing_f64_reduce_kernel(WorkPlan wp, int64_t n_tiles, int32_t n_states,
-                                                             int32_t tp, int32_t n, const double* __restrict__ partial,
-                                                             double* __restrict__ kappa, int accumulate)
-{
-    const int64_t total = wp.total[0];
-    if (total == wp.n_pairs) return;  // nothing cut
-    for (int64_t p = blockIdx.x; p < wp.n_pairs; p += gridDim.x) {
-        const int64_t nseg = (p + 1 < wp.n_pairs ? wp.first[p + 1] : total) - wp.first[p];
-        if (nseg < 2) continue;
-        int64_t st, k;
-        pair_decode(p, n_tiles, n_states, st, k);
-        const int64_t j0 = (n_tiles - 1 - k) * tp;
-        const double* src = partial + wp.slot[p] * tp;
-        double* dst = kappa + st * (int64_t)n;
-        for (int q = threadIdx.x; q < tp; q += blockDim.x) {
-            const int64_t j = j0 + q;
-            if (j >= n) break;
-            double v = 0.0;
-            for (int64_t sg = 0; sg < nseg; ++sg) v += src[sg * tp + q];
-            dst[j] = accumulate ? dst[j] + v : v;
-        }
-    }
-}
-
 // H_V(a, u) for a^2 + u^2 < 100 by the series form of the Faddeeva function
 // (Abramowitz & Stegun 7.1.29 applied to w(z) = e^{-z^2} erfc(-iz), step
 // 1/2), the three exponential series summed in one loop (§2.4):
@@ -1076,31 +1050,6 @@ __global__ __launch_bounds__(64 * kWaves) void core_f64_kernel(
     }
 }
 
-// Cut series tiles: series_j = the ordered sum of the tile's partials.
-__global__ __launch_bounds__(256) void core_f64_reduce_kernel(WorkPlan wp, int64_t n_tiles, int32_t n_states,
-                                                             int32_t tp, int32_t n, const double* __restrict__ partial,
-                                                             double* __restrict__ series)
-{
-    const int64_t total = wp.total[0];
-    if (total == wp.n_pairs) return;  // nothing cut
-    for (int64_t p = blockIdx.x; p < wp.n_pairs; p += gridDim.x) {
-        const int64_t nseg = (p + 1 < wp.n_pairs ? wp.first[p + 1] : total) - wp.first[p];
-        if (nseg < 2) continue;
-        int64_t st, k;
-        pair_decode(p, n_tiles, n_states, st, k);
-        const int64_t j0 = (n_tiles - 1 - k) * tp;
-        const double* src = partial + wp.slot[p] * tp;
-        double* dst = series + st * (int64_t)n;
-        for (int q = threadIdx.x; q < tp; q += blockDim.x) {
-            const int64_t j = j0 + q;
-            if (j >= n) break;
-            double v = 0.0;
-            for (int64_t sg = 0; sg < nseg; ++sg) v += src[sg * tp + q];
-            dst[j] = v;
-        }
-    }
-}
-
 }  // namespace
 
 namespace {
@@ -1166,9 +1115,6 @@ hipError_t launch_wing_f64(const WingRec* wing, const WingIdx* idx, const int64_
     auto kernel = sub == kLeaf ? wing_f64_kernel<kLeaf> : wing_f64_kernel<4 * kLeaf>;
     kernel<<<dim3((unsigned)nb), dim3(64 * kWaves), 0, s>>>(wing, idx, ranges, n_lines, n_tiles, n_states, wp, tab,
                                                             nu_min, dnu, n_points, kappa, partial, accumulate, far_ok);
-    const int64_t nr = std::min<int64_t>(wp.n_pairs, 8192);
-    wing_f64_reduce_kernel<<<dim3((unsigned)nr), dim3(256), 0, s>>>(wp, n_tiles, n_states, kWaves * sub, n_points,
-                                                                    partial, kappa, accumulate);
     return hipGetLastError();
 }
 
@@ -1182,27 +1128,47 @@ hipError_t launch_core_f64(const WingRec* wing, const WingIdx* idx, const CoreRe
     core_f64_kernel<<<dim3((unsigned)nb), dim3(64 * kWaves), 0, s>>>(wing, idx, core, ranges, n_lines, n_tiles,
                                                                     n_states, wp, nu_min, dnu, n_points, series,
                                                                     partial);
-    const int64_t nr = std::min<int64_t>(wp.n_pairs, 8192);
-    core_f64_reduce_kernel<<<dim3((unsigned)nr), dim3(256), 0, s>>>(wp, n_tiles, n_states, core_f64_tile_points(),
-                                                                    n_points, partial, series);
     return hipGetLastError();
 }
 
 namespace {
 
-__global__ __launch_bounds__(256) void add_f64_kernel(double* __restrict__ a, const double* __restrict__ b, int64_t n)
+// The ordered sum of point j's partials, if its tile is cut.
+__device__ inline bool cut_sum(const CutTiles& c, int64_t st, int64_t j, int32_t n_states, double& v)
+{
+    if (c.wp.total[0] == c.wp.n_pairs) return false;  // nothing cut
+    const int64_t p = pair_of(st, j / c.tile_points, c.n_tiles, n_states);
+    const int64_t nseg = pair_segments(c.wp, p);
+    if (nseg < 2) return false;
+    const double* src = (const double*)c.partial + c.wp.slot[p] * c.tile_points + j % c.tile_points;
+    v = 0.0;
+    for (int64_t sg = 0; sg < nseg; ++sg) v += src[sg * c.tile_points];
+    return true;
+}
+
+// kappa_j = wing_j + series_j (state blockIdx.y).
+__global__ __launch_bounds__(256) void f64_finish_kernel(double* __restrict__ kappa, const double* __restrict__ series,
+                                                        int64_t n, CutTiles wing, CutTiles core, int accumulate)
 {
     const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (j < n) a[j] += b[j];
+    if (j >= n) return;
+    const int64_t st = blockIdx.y, o = st * n + j;
+    double v, w;
+    if (!cut_sum(wing, st, j, gridDim.y, v)) v = kappa[o];
+    else if (accumulate) v = kappa[o] + v;
+    if (!cut_sum(core, st, j, gridDim.y, w)) w = series[o];
+    kappa[o] = v + w;
 }
 
 }  // namespace
 
-hipError_t launch_add_f64(double* a, const double* b, int64_t n, hipStream_t s)
+hipError_t launch_f64_finish(double* kappa, const double* series, int32_t n_points, int32_t n_states,
+                             const CutTiles& wing, const CutTiles& core, int accumulate, hipStream_t s)
 {
-    if (n <= 0) return hipSuccess;
-    if ((n + 255) / 256 > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
-    add_f64_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s>>>(a, b, n);
+    if (n_points <= 0 || n_states <= 0) return hipSuccess;
+    const int64_t nb = ((int64_t)n_points + 255) / 256;
+    f64_finish_kernel<<<dim3((unsigned)nb, (unsigned)n_states), dim3(256), 0, s>>>(kappa, series, n_points, wing, core,
+                                                                                   accumulate);
     return hipGetLastError();
 }
 

@@ -17,21 +17,31 @@ constexpr int64_t kPerBlock = (int64_t)kThreads * kPerThread;
 // lines, or when the fullest holds more than kUneven times the mean.
 constexpr int64_t kUneven = 3;
 
-// One workgroup per state.  Segment length: the smallest power of two >=
+// Segment length of a state from its reference tiles' statistics: the smallest power of two >=
 // min_seg and >= W / (4 n_points), W = 512 sum_t c_t + 4096 n_lines (c_t:
 // lines of reference tile t).  W bounds the sum over any tiles of <= 2048
 // points of (lines in the tile's range) x (tile points): a line's reach
 // covers |A| grid points, which lie in >= |A| / 512 reference tiles and meet
 // <= |A| / tp + 2 tiles of tp points.  So the items stay <= sum_t (c_t / L
 // + 2) <= 6 n_tiles and the partial points <= 6 n_points + 2 tile points.
-__global__ __launch_bounds__(kThreads) void seg_length_kernel(const int64_t* __restrict__ ref, int64_t n_ref,
-                                                              int64_t n_points, int64_t n_lines, int64_t min_seg,
-                                                              int64_t busy_min, int64_t* __restrict__ seg)
+__device__ inline int64_t seg_length(int64_t busy, int64_t mx, int64_t sum, int64_t n_points, int64_t n_lines,
+                                     int64_t min_seg, int64_t busy_min)
+{
+    if (!(sum > 0 && (busy < busy_min || mx * busy > kUneven * sum))) return kNoSplit;
+    const double W = 512.0 * (double)sum + 4096.0 * (double)n_lines;
+    const double need = W / (4.0 * (double)n_points);
+    int64_t L = min_seg;
+    while ((double)L < need && L < kNoSplit) L <<= 1;  // kNoSplit: not cut after all
+    return L;
+}
+
+// One workgroup per state.
+__global__ __launch_bounds__(kThreads) void seg_length_kernel(PlanJob j, int64_t n_points, int64_t n_lines)
 {
     __shared__ int64_t red[3][kThreads];
-    const int64_t* rg = ref + (int64_t)blockIdx.x * 2 * n_ref;
+    const int64_t* rg = j.ref + (int64_t)blockIdx.x * 2 * j.n_ref;
     int64_t busy = 0, mx = 0, sum = 0;
-    for (int64_t t = threadIdx.x; t < n_ref; t += kThreads) {
+    for (int64_t t = threadIdx.x; t < j.n_ref; t += kThreads) {
         const int64_t c = rg[2 * t + 1] - rg[2 * t];
         busy += c > 0;
         mx = max(mx, c);
@@ -49,19 +59,8 @@ __global__ __launch_bounds__(kThreads) void seg_length_kernel(const int64_t* __r
         }
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        busy = red[0][0];
-        mx = red[1][0];
-        sum = red[2][0];
-        int64_t L = kNoSplit;
-        if (sum > 0 && (busy < busy_min || mx * busy > kUneven * sum)) {
-            const double W = 512.0 * (double)sum + 4096.0 * (double)n_lines;
-            const double need = W / (4.0 * (double)n_points);
-            L = min_seg;
-            while ((double)L < need && L < kNoSplit) L <<= 1;  // kNoSplit: not cut after all
-        }
-        seg[blockIdx.x] = L;
-    }
+    if (threadIdx.x == 0)
+        j.seg[blockIdx.x] = seg_length(red[0][0], red[1][0], red[2][0], n_points, n_lines, j.min_seg, j.busy_min);
 }
 
 __device__ inline void pair_counts(int64_t p, int64_t n_pairs, const int64_t* __restrict__ ranges,
@@ -175,29 +174,126 @@ __global__ __launch_bounds__(kThreads) void plan_offset_kernel(int64_t n_pairs, 
     }
 }
 
+// Both plans of a pass in one launch, a workgroup each (plans of up to
+// kSmallPairs pairs): the states' segment lengths (a wavefront per state, in
+// turn), then the pairs kSmallThreads at a time with running totals.
+constexpr int kSmallThreads = 1024;
+constexpr int64_t kSmallPairs = 16384;
+struct PlanJobs {
+    PlanJob job[2];
+};
+__global__ __launch_bounds__(kSmallThreads) void plan_small_kernel(PlanJobs jobs, int64_t n_points, int64_t n_lines)
+{
+    const PlanJob& j = jobs.job[blockIdx.x];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    constexpr int kW = kSmallThreads / 64;
+    __shared__ int64_t wa[kW], wb[kW], part[3][kW];
+    // every wavefront a share of a state's reference tiles
+    for (int32_t st = 0; st < j.n_states; ++st) {
+        const int64_t* rg = j.ref + (int64_t)st * 2 * j.n_ref;
+        int64_t busy = 0, mx = 0, sum = 0;
+        for (int64_t t = threadIdx.x; t < j.n_ref; t += kSmallThreads) {
+            const int64_t c = rg[2 * t + 1] - rg[2 * t];
+            busy += c > 0;
+            mx = max(mx, c);
+            sum += c;
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            busy += __shfl_xor(busy, o, 64);
+            mx = max(mx, (int64_t)__shfl_xor(mx, o, 64));
+            sum += __shfl_xor(sum, o, 64);
+        }
+        if (lane == 0) {
+            part[0][wave] = busy;
+            part[1][wave] = mx;
+            part[2][wave] = sum;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            busy = mx = sum = 0;
+            for (int w = 0; w < kW; ++w) {
+                busy += part[0][w];
+                mx = max(mx, part[1][w]);
+                sum += part[2][w];
+            }
+            j.seg[st] = seg_length(busy, mx, sum, n_points, n_lines, j.min_seg, j.busy_min);
+        }
+        __syncthreads();
+    }
+    const int64_t n_pairs = j.n_tiles * j.n_states;
+    int64_t ra = 0, rb = 0;  // totals of the pairs before
+    for (int64_t base = 0; base < n_pairs; base += kSmallThreads) {
+        const int64_t p = base + threadIdx.x;
+        int64_t it, sl;
+        pair_counts(p, n_pairs, j.ranges, j.n_tiles, j.n_states, j.seg, it, sl);
+        int64_t ia = it, ib = sl;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int64_t va = __shfl_up(ia, o, 64), vb = __shfl_up(ib, o, 64);
+            if (lane >= o) {
+                ia += va;
+                ib += vb;
+            }
+        }
+        if (lane == 63) {
+            wa[wave] = ia;
+            wb[wave] = ib;
+        }
+        __syncthreads();
+        int64_t oa = ra, ob = rb;
+        for (int w = 0; w < kW; ++w) {
+            if (w < wave) {
+                oa += wa[w];
+                ob += wb[w];
+            }
+            ra += wa[w];
+            rb += wb[w];
+        }
+        if (p < n_pairs) {
+            j.first[p] = oa + ia - it;
+            j.slot[p] = ob + ib - sl;
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        j.total[0] = ra;
+        j.total[1] = rb;
+    }
+}
+
 }  // namespace
 
 int64_t plan_scratch_count(int64_t n_pairs) { return 2 * std::max<int64_t>(1, (n_pairs + kPerBlock - 1) / kPerBlock); }
 
-hipError_t launch_seg_length(const int64_t* ref_ranges, int64_t n_ref, int32_t n_states, int64_t n_points,
-                             int64_t n_lines, int64_t min_seg, int64_t busy_min, int64_t* seg, hipStream_t s)
+hipError_t launch_work_plans(const PlanJob* jobs, int n_jobs, int64_t n_points, int64_t n_lines, hipStream_t s)
 {
-    if (n_states <= 0) return hipSuccess;
-    if (min_seg < 1 || (min_seg & (min_seg - 1)) != 0) return hipErrorInvalidValue;
-    seg_length_kernel<<<dim3((unsigned)n_states), dim3(kThreads), 0, s>>>(ref_ranges, n_ref, n_points, n_lines,
-                                                                         min_seg, busy_min, seg);
-    return hipGetLastError();
-}
-
-hipError_t launch_work_plan(const int64_t* ranges, int64_t n_tiles, int32_t n_states, const int64_t* seg,
-                            int64_t* first, int64_t* slot, int64_t* block_sums, int64_t* total, hipStream_t s)
-{
-    const int64_t n_pairs = n_tiles * (int64_t)n_states;
-    const int64_t nb = std::max<int64_t>(1, (n_pairs + kPerBlock - 1) / kPerBlock);
-    plan_count_kernel<<<dim3((unsigned)nb), dim3(kThreads), 0, s>>>(ranges, n_tiles, n_states, seg, n_pairs, first,
-                                                                    slot, block_sums);
-    plan_scan_kernel<<<dim3(1), dim3(kThreads), 0, s>>>(block_sums, nb, total);
-    plan_offset_kernel<<<dim3((unsigned)nb), dim3(kThreads), 0, s>>>(n_pairs, block_sums, first, slot);
+    if (n_jobs < 1 || n_jobs > 2) return hipErrorInvalidValue;
+    // one workgroup per plan walks its pairs 1024 at a time: ~6 us a plan of
+    // 3e3 pairs, against four launches of 2 - 9 us each; beyond kSmallPairs
+    // the launches' parallel passes take less
+    bool small = true;
+    for (int k = 0; k < n_jobs; ++k) {
+        const PlanJob& j = jobs[k];
+        if (j.min_seg < 1 || (j.min_seg & (j.min_seg - 1)) != 0) return hipErrorInvalidValue;
+        if (j.n_states <= 0) return hipSuccess;
+        small = small && j.n_tiles * j.n_states <= kSmallPairs && j.n_ref * j.n_states <= 2 * kSmallPairs &&
+                j.n_states <= 16;
+    }
+    if (small) {
+        PlanJobs pj;
+        for (int k = 0; k < n_jobs; ++k) pj.job[k] = jobs[k];
+        plan_small_kernel<<<dim3((unsigned)n_jobs), dim3(kSmallThreads), 0, s>>>(pj, n_points, n_lines);
+        return hipGetLastError();
+    }
+    for (int k = 0; k < n_jobs; ++k) {
+        const PlanJob& j = jobs[k];
+        const int64_t n_pairs = j.n_tiles * (int64_t)j.n_states;
+        const int64_t nb = std::max<int64_t>(1, (n_pairs + kPerBlock - 1) / kPerBlock);
+        seg_length_kernel<<<dim3((unsigned)j.n_states), dim3(kThreads), 0, s>>>(j, n_points, n_lines);
+        plan_count_kernel<<<dim3((unsigned)nb), dim3(kThreads), 0, s>>>(j.ranges, j.n_tiles, j.n_states, j.seg, n_pairs,
+                                                                        j.first, j.slot, j.bsum);
+        plan_scan_kernel<<<dim3(1), dim3(kThreads), 0, s>>>(j.bsum, nb, j.total);
+        plan_offset_kernel<<<dim3((unsigned)nb), dim3(kThreads), 0, s>>>(n_pairs, j.bsum, j.first, j.slot);
+    }
     return hipGetLastError();
 }
 
