@@ -653,7 +653,7 @@ __device__ __forceinline__ int64_t core_f32_surr_tile(int64_t t, int64_t L0, int
                 const CorePiece32& pp = pc[own[q]];
                 const int32_t j = pp.a + (f0 + q - pp.start);
                 const float x = act ? fabsf(fmaf((float)(j - pp.jc), pp.dx, -pp.fx)) : 0.0f;
-                const float z = surr::mlp_forward<false>(P, mlp_tab[wave], surr::feature_x(x),
+                const float z = surr::mlp_forward(P, mlp_tab[wave], surr::feature_x(x),
                                                          surr::feature_y(act ? pp.y : 1.0f));
                 if (act) val[q] = pp.norm * surr::surrogate_K(x, pp.y, z);
             }

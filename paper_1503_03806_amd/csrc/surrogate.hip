@@ -5,7 +5,7 @@
 //  * labels: the plain method's K in binary64 (series for x^2+y^2 < 100,
 //    3-node rule beyond, §2.4), turned into the target
 //    z = asinh(ln(K/G3)/tau);
-//  * training step: one wavefront per 64 samples runs the forward pass, the
+//  * training step: one workgroup per 64 samples runs the forward pass, the
 //    mean-squared-error gradient and the backward pass (the 64x64 products
 //    dW = dZ^T A and dA = dZ W on the matrix cores) and writes its partial
 //    gradient; the update kernel sums the partials in a fixed order and
@@ -98,173 +98,263 @@ __global__ __launch_bounds__(256) void pack_kernel(const float* __restrict__ the
     if (p < kNParams) write_copy(theta, p, P);
 }
 
-// LDS of the training step (one wavefront per workgroup)
+// LDS of the training step (one workgroup per 64 samples)
 struct alignas(16) TrainLds {
-    float Z[4][kHid][kHid];         // pre-activations of layers 1-4, [s][o]
+    float Z[4][kHid][kHid + 1];     // pre-activations of layers 1-4, [s][o] (padded: layer 1 writes a column per lane)
     uint16_t inT[4][kHid][kLd];   // bfloat16 inputs of layers 2-5, [i][s]
-    uint16_t act[kHid][kLd];      // forward scratch [s][i]
+    uint16_t act[2][kHid][kLd];   // forward activations [s][i], two in turn
     uint16_t dz[kHid][kLd];       // bfloat16 dZ of the current layer, [s][o]
     uint16_t dzT[kHid][kLd];      // the same, [o][s]
     float f1[kHid], f2[kHid], dout[kHid];
 };
+constexpr int kTrainWaves = 4;
 
 // Forward, loss and backward of 64 samples; samples j = (base + 64 w + l)
 // mod n for 64 w + l < batch (other lanes are padding with zero gradient).
 // Loss: mean of w(z) (z_hat - z)^2 with w(z) = 1 / (1 + (z/wscale)^2), or
 // w = 1 when wscale = 0.  part_grad[w][p]; part_loss[w] = the weighted sum.
-__global__ __launch_bounds__(64) void train_kernel(const MlpBf16* __restrict__ P, const float* __restrict__ xs,
-                                                   const float* __restrict__ ys, const float* __restrict__ zs,
-                                                   int64_t n, int64_t base, int32_t batch, float wscale,
-                                                   float* __restrict__ part_grad, float* __restrict__ part_loss)
+//
+// Four wavefronts share the 64 samples, each taking 16 of the 64 outputs of
+// every layer (and inputs, on the way back): a step's batch of 4096 is only
+// 64 groups of samples, so one wavefront a group left a quarter of the CUs
+// with one wavefront each and the rest idle, bound by that wavefront's serial
+// chain.  Every value is the same sequence of operations as with one
+// wavefront, bit for bit.  (Batch 4096: 36 -> 15 us, of which 8 pass before the
+// first layer, in launch and the weights' way from the update of the step
+// before.  Sixteen wavefronts, a tile each: 17 us.)
+__global__ __launch_bounds__(64 * kTrainWaves) void train_kernel(
+    const MlpBf16* __restrict__ P, const float* __restrict__ xs, const float* __restrict__ ys,
+    const float* __restrict__ zs, int64_t n, int64_t base, int32_t batch, float wscale,
+    float* __restrict__ part_grad, float* __restrict__ part_loss)
 {
     __shared__ __align__(16) TrainLds L;
-    const int lane = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int row = lane & 15, kq = 8 * (lane >> 4);
+    const int o = 16 * wave + row;  // this lane's output of the products
+    // every weight this lane needs, asked for before anything waits: the update
+    // of the step before has just written them elsewhere, and each of the
+    // seven layers' passes would wait for its own
+    bf16x8 w0[3], w1[3], t0[3], t1[3];
+    float bias[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        w0[k] = ld8(P->W[k] + o * kHid + kq);
+        w1[k] = ld8(P->W[k] + o * kHid + 32 + kq);
+        t0[k] = ld8(P->WT[k] + o * kHid + kq);
+        t1[k] = ld8(P->WT[k] + o * kHid + 32 + kq);
+        bias[k] = P->b[k + 1][o];
+    }
+    const float w5 = bf2f(P->w5[o]), b5 = P->b5;
     const int64_t b = (int64_t)blockIdx.x * kHid + lane;
     const bool active = b < batch;
-    const int64_t j = (base + b) % n;
+    int64_t j = base + b;
+    if (j >= n) j -= n;
+    if (j >= n) j %= n;  // (rarely: a batch, or a start, beyond 2 n)
     const float x = active ? fabsf(xs[j]) : 0.0f, y = active ? ys[j] : 1.0f;
-    const float f1 = feature_x(x), f2 = feature_y(y);
-    L.f1[lane] = f1;
-    L.f2[lane] = f2;
-    const float out = mlp_forward<true>(P, &L.act[0][0], f1, f2, &L.Z[0][0][0], &L.inT[0][0][0]);
     const float zt = active ? zs[j] : 0.0f;
-    const float res = active ? out - zt : 0.0f;
-    const float q = wscale > 0.0f ? zt / wscale : 0.0f;
-    const float wgt = 1.0f / fmaf(q, q, 1.0f);
-    const float dout = 2.0f * wgt * res / (float)batch;
-    L.dout[lane] = dout;
+    uint4 w5v[kHid / 8];  // the output layer's weights (wavefront 0)
+#pragma unroll
+    for (int q = 0; q < kHid / 8; ++q) w5v[q] = reinterpret_cast<const uint4*>(P->w5)[q];
+    const float f1 = feature_x(x), f2 = feature_y(y);
+    if (wave == 0) {
+        L.f1[lane] = f1;
+        L.f2[lane] = f2;
+    }
+    // layer 1 (2 -> 64), a sample per lane, 16 outputs per wavefront
+#pragma unroll
+    for (int q = 16 * wave; q < 16 * wave + 16; q += 8) {
+        uint16_t hv[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float z = fmaf(bf2f(P->W1[2 * (q + e)]), f1, fmaf(bf2f(P->W1[2 * (q + e) + 1]), f2, P->b[0][q + e]));
+            hv[e] = f2bf(silu(z));
+            L.Z[0][lane][q + e] = z;
+            L.inT[0][q + e][lane] = hv[e];
+        }
+        uint4 pk;
+        pk.x = hv[0] | ((uint32_t)hv[1] << 16);
+        pk.y = hv[2] | ((uint32_t)hv[3] << 16);
+        pk.z = hv[4] | ((uint32_t)hv[5] << 16);
+        pk.w = hv[6] | ((uint32_t)hv[7] << 16);
+        *reinterpret_cast<uint4*>(&L.act[0][lane][q]) = pk;
+    }
+    __syncthreads();
+    // layers 2-4 on the matrix cores: every sample, this wavefront's outputs
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const uint16_t* act = &L.act[k & 1][0][0];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const bf16x8 a0 = ld8(act + (16 * m + row) * kLd + kq);
+            const bf16x8 a1 = ld8(act + (16 * m + row) * kLd + 32 + kq);
+            floatx4 c = {0.0f, 0.0f, 0.0f, 0.0f};
+            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, w0[k], c, 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, w1[k], c, 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int s = 16 * m + 4 * (lane >> 4) + r;
+                const float z = c[r] + bias[k];
+                const uint16_t h = f2bf(silu(z));
+                L.act[(k + 1) & 1][s][o] = h;
+                L.Z[k + 1][s][o] = z;
+                L.inT[k + 1][o][s] = h;
+            }
+        }
+        __syncthreads();
+    }
     float* G = part_grad + (int64_t)blockIdx.x * kNParams;
-    // loss
-    float sq = wgt * res * res;
-    for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
-    if (lane == 0) part_loss[blockIdx.x] = sq;
-    float db5 = dout;
-    for (int o = 32; o > 0; o >>= 1) db5 += __shfl_xor(db5, o, 64);
-    wave_sync();
-    // output layer: dw5[o] = sum_s dout[s] in5[s][o] (lane o), db5
-    {
-        float g = 0.0f;
-        for (int s = 0; s < kHid; ++s) g = fmaf(L.dout[s], bf2f(L.inT[3][lane][s]), g);
-        G[kOffW5 + lane] = g;
+    // output (64 -> 1) and loss, a sample per lane
+    if (wave == 0) {
+        const uint16_t* act = &L.act[1][0][0];
+        float out = b5;
+#pragma unroll
+        for (int q = 0; q < kHid; q += 8) {
+            const uint4 v = *reinterpret_cast<const uint4*>(act + lane * kLd + q);
+            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+            const uint32_t u[4] = {w5v[q / 8].x, w5v[q / 8].y, w5v[q / 8].z, w5v[q / 8].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                out = fmaf(__uint_as_float(u[e] << 16), __uint_as_float(w[e] << 16), out);
+                out = fmaf(__uint_as_float(u[e] & 0xFFFF0000u), __uint_as_float(w[e] & 0xFFFF0000u), out);
+            }
+        }
+        const float res = active ? out - zt : 0.0f;
+        const float q = wscale > 0.0f ? zt / wscale : 0.0f;
+        const float wgt = 1.0f / fmaf(q, q, 1.0f);
+        const float dout = 2.0f * wgt * res / (float)batch;
+        L.dout[lane] = dout;
+        float sq = wgt * res * res;
+        for (int sh = 32; sh > 0; sh >>= 1) sq += __shfl_xor(sq, sh, 64);
+        if (lane == 0) part_loss[blockIdx.x] = sq;
+        float db5 = dout;
+        for (int sh = 32; sh > 0; sh >>= 1) db5 += __shfl_xor(db5, sh, 64);
         if (lane == 0) G[kOffB5] = db5;
     }
+    __syncthreads();
+    // output layer: dw5[o] = sum_s dout[s] in5[s][o], a lane per output
+    if (wave == 3) {
+        float g = 0.0f;
+#pragma unroll 16
+        for (int s = 0; s < kHid; ++s) g = fmaf(L.dout[s], bf2f(L.inT[3][lane][s]), g);
+        G[kOffW5 + lane] = g;
+    }
     // dH4 in the product layout: dH[s][o] = dout[s] w5[o]
-    floatx4 dh[4][4];
+    floatx4 dh[4];
 #pragma unroll
     for (int m = 0; m < 4; ++m)
 #pragma unroll
-        for (int nn = 0; nn < 4; ++nn)
+        for (int r = 0; r < 4; ++r) dh[m][r] = L.dout[16 * m + 4 * (lane >> 4) + r] * w5;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int s = 16 * m + 4 * (lane >> 4) + r, o = 16 * nn + (lane & 15);
-                dh[m][nn][r] = L.dout[s] * bf2f(P->w5[o]);
-            }
-    const int row = lane & 15, kq = 8 * (lane >> 4);
     for (int k = 3; k >= 1; --k) {  // layers 4, 3, 2 (weights P->W[k-1])
         // dZ = dH * SiLU'(Z); bias gradient; bfloat16 dZ in both layouts
-        float bsum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        float bsum = 0.0f;
 #pragma unroll
         for (int m = 0; m < 4; ++m)
 #pragma unroll
-            for (int nn = 0; nn < 4; ++nn)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int s = 16 * m + 4 * (lane >> 4) + r, o = 16 * nn + (lane & 15);
-                    const float dz = dh[m][nn][r] * dsilu(L.Z[k][s][o]);
-                    bsum[nn] += dz;
-                    const uint16_t h = f2bf(dz);
-                    L.dz[s][o] = h;
-                    L.dzT[o][s] = h;
-                }
-#pragma unroll
-        for (int nn = 0; nn < 4; ++nn) {
-            float v = bsum[nn];
-            v += __shfl_xor(v, 16, 64);
-            v += __shfl_xor(v, 32, 64);
-            if (lane < 16) G[kOffB2 + (k - 1) * (kHid * kHid + kHid) + 16 * nn + lane] = v;
-        }
-        wave_sync();
+            for (int r = 0; r < 4; ++r) {
+                const int s = 16 * m + 4 * (lane >> 4) + r;
+                const float dz = dh[m][r] * dsilu(L.Z[k][s][o]);
+                bsum += dz;
+                const uint16_t h = f2bf(dz);
+                L.dz[s][o] = h;
+                L.dzT[o][s] = h;
+            }
+        bsum += __shfl_xor(bsum, 16, 64);
+        bsum += __shfl_xor(bsum, 32, 64);
+        if (lane < 16) G[kOffB2 + (k - 1) * (kHid * kHid + kHid) + 16 * wave + lane] = bsum;
+        __syncthreads();
         // dW[o][i] = sum_s dZ[s][o] in[s][i]:  A = dZ^T (rows o), B = in^T rows i
         {
             const uint16_t* inT = &L.inT[k - 1][0][0];
-            bf16x8 a[4][2], bb[4][2];
-#pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                a[m][0] = ld8(&L.dzT[16 * m + row][kq]);
-                a[m][1] = ld8(&L.dzT[16 * m + row][32 + kq]);
-                bb[m][0] = ld8(inT + (16 * m + row) * kLd + kq);
-                bb[m][1] = ld8(inT + (16 * m + row) * kLd + 32 + kq);
-            }
+            const bf16x8 a0 = ld8(&L.dzT[o][kq]);
+            const bf16x8 a1 = ld8(&L.dzT[o][32 + kq]);
             float* GW = G + kOffW2 + (k - 1) * (kHid * kHid + kHid);
 #pragma unroll
-            for (int m = 0; m < 4; ++m)
+            for (int nn = 0; nn < 4; ++nn) {
+                const bf16x8 b0 = ld8(inT + (16 * nn + row) * kLd + kq);
+                const bf16x8 b1 = ld8(inT + (16 * nn + row) * kLd + 32 + kq);
+                floatx4 c = {0.0f, 0.0f, 0.0f, 0.0f};
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, b0, c, 0, 0, 0);
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b1, c, 0, 0, 0);
 #pragma unroll
-                for (int nn = 0; nn < 4; ++nn) {
-                    floatx4 c = {0.0f, 0.0f, 0.0f, 0.0f};
-                    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m][0], bb[nn][0], c, 0, 0, 0);
-                    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m][1], bb[nn][1], c, 0, 0, 0);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        GW[(16 * m + 4 * (lane >> 4) + r) * kHid + 16 * nn + (lane & 15)] = c[r];
-                }
+                for (int r = 0; r < 4; ++r)
+                    GW[(16 * wave + 4 * (lane >> 4) + r) * kHid + 16 * nn + row] = c[r];
+            }
         }
         // dH_prev[s][i] = sum_o dZ[s][o] W[o][i]:  A = dZ (rows s), B = W^T rows i
         {
-            bf16x8 a[4][2];
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
-                a[m][0] = ld8(&L.dz[16 * m + row][kq]);
-                a[m][1] = ld8(&L.dz[16 * m + row][32 + kq]);
-            }
-            const uint16_t* WT = P->WT[k - 1];
-#pragma unroll
-            for (int nn = 0; nn < 4; ++nn) {
-                const bf16x8 b0 = ld8(WT + (16 * nn + row) * kHid + kq);
-                const bf16x8 b1 = ld8(WT + (16 * nn + row) * kHid + 32 + kq);
-#pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    floatx4 c = {0.0f, 0.0f, 0.0f, 0.0f};
-                    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m][0], b0, c, 0, 0, 0);
-                    dh[m][nn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m][1], b1, c, 0, 0, 0);
-                }
+                const bf16x8 a0 = ld8(&L.dz[16 * m + row][kq]);
+                const bf16x8 a1 = ld8(&L.dz[16 * m + row][32 + kq]);
+                floatx4 c = {0.0f, 0.0f, 0.0f, 0.0f};
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, t0[k - 1], c, 0, 0, 0);
+                dh[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, t1[k - 1], c, 0, 0, 0);
             }
         }
-        wave_sync();  // dz / dzT are rewritten by the next layer
+        __syncthreads();  // dz / dzT are rewritten by the next layer
     }
     // layer 1: dZ1 = dH1 SiLU'(Z1), kept in place of Z1
 #pragma unroll
     for (int m = 0; m < 4; ++m)
 #pragma unroll
-        for (int nn = 0; nn < 4; ++nn)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int s = 16 * m + 4 * (lane >> 4) + r, o = 16 * nn + (lane & 15);
-                L.Z[0][s][o] = dh[m][nn][r] * dsilu(L.Z[0][s][o]);
-            }
-    wave_sync();
-    {
-        float g0 = 0.0f, g1 = 0.0f, gb = 0.0f;
-        for (int s = 0; s < kHid; ++s) {
-            const float dz = L.Z[0][s][lane];
-            g0 = fmaf(dz, L.f1[s], g0);
-            g1 = fmaf(dz, L.f2[s], g1);
-            gb += dz;
+        for (int r = 0; r < 4; ++r) {
+            const int s = 16 * m + 4 * (lane >> 4) + r;
+            L.Z[0][s][o] = dh[m][r] * dsilu(L.Z[0][s][o]);
         }
-        G[kOffW1 + 2 * lane] = g0;
-        G[kOffW1 + 2 * lane + 1] = g1;
-        G[kOffB1 + lane] = gb;
+    __syncthreads();
+    if (wave == 0) {
+        float g = 0.0f;
+#pragma unroll 16
+        for (int s = 0; s < kHid; ++s) g = fmaf(L.Z[0][s][lane], L.f1[s], g);
+        G[kOffW1 + 2 * lane] = g;
+    } else if (wave == 1) {
+        float g = 0.0f;
+#pragma unroll 16
+        for (int s = 0; s < kHid; ++s) g = fmaf(L.Z[0][s][lane], L.f2[s], g);
+        G[kOffW1 + 2 * lane + 1] = g;
+    } else if (wave == 2) {
+        float g = 0.0f;
+#pragma unroll 16
+        for (int s = 0; s < kHid; ++s) g += L.Z[0][s][lane];
+        G[kOffB1 + lane] = g;
     }
 }
 
 // Sum of the per-workgroup partials in workgroup order; thread per parameter.
+// (Sixteen loads are in flight before the first is added: one at a time, the
+// 64 partials of a batch of 4096 took a memory latency each.)
 __device__ inline float sum_partials(const float* __restrict__ part, int32_t n_wg, int p)
 {
     float g = 0.0f;
-    for (int w = 0; w < n_wg; ++w) g += part[(int64_t)w * kNParams + p];
+    int w = 0;
+    for (; w + 16 <= n_wg; w += 16) {
+        float v[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) v[e] = part[(int64_t)(w + e) * kNParams + p];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) g += v[e];
+    }
+    for (; w < n_wg; ++w) g += part[(int64_t)w * kNParams + p];
     return g;
 }
+// The losses of the workgroups, summed in workgroup order by one lane (the
+// other lanes of its wavefront load them).
+__device__ inline float sum_losses(const float* __restrict__ part_loss, int32_t n_wg)
+{
+    const int lane = threadIdx.x & 63;
+    float s = 0.0f;
+    for (int w0 = 0; w0 < n_wg; w0 += 64) {
+        const float v = w0 + lane < n_wg ? part_loss[w0 + lane] : 0.0f;
+        for (int e = 0; e < min(64, n_wg - w0); ++e)
+            s += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), e));
+    }
+    return s;
+}
+constexpr int kUpdateThreads = 64;  // a wavefront per workgroup: 200 of them, spread over the CUs
 
-__global__ __launch_bounds__(256) void adam_kernel(float* __restrict__ theta, float* __restrict__ m,
+__global__ __launch_bounds__(kUpdateThreads) void adam_kernel(float* __restrict__ theta, float* __restrict__ m,
                                                    float* __restrict__ v, const float* __restrict__ part,
                                                    int32_t n_wg, float lr, float beta1, float beta2, float eps,
                                                    float c1, float c2, MlpBf16* __restrict__ P,
@@ -272,10 +362,9 @@ __global__ __launch_bounds__(256) void adam_kernel(float* __restrict__ theta, fl
                                                    float* __restrict__ loss_out)
 {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p == 0 && loss_out) {
-        float s = 0.0f;
-        for (int w = 0; w < n_wg; ++w) s += part_loss[w];
-        *loss_out = s / (float)batch;
+    if (blockIdx.x == 0 && loss_out) {
+        const float s = sum_losses(part_loss, n_wg);
+        if (p == 0) *loss_out = s / (float)batch;
     }
     if (p >= kNParams) return;
     const float g = sum_partials(part, n_wg, p);
@@ -287,15 +376,14 @@ __global__ __launch_bounds__(256) void adam_kernel(float* __restrict__ theta, fl
     write_copy(theta, p, P);
 }
 
-__global__ __launch_bounds__(256) void reduce_kernel(const float* __restrict__ part, int32_t n_wg,
+__global__ __launch_bounds__(kUpdateThreads) void reduce_kernel(const float* __restrict__ part, int32_t n_wg,
                                                      float* __restrict__ grad, const float* __restrict__ part_loss,
                                                      int32_t batch, float* __restrict__ loss_out)
 {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p == 0 && loss_out) {
-        float s = 0.0f;
-        for (int w = 0; w < n_wg; ++w) s += part_loss[w];
-        *loss_out = s / (float)batch;
+    if (blockIdx.x == 0 && loss_out) {
+        const float s = sum_losses(part_loss, n_wg);
+        if (p == 0) *loss_out = s / (float)batch;
     }
     if (p < kNParams) grad[p] = sum_partials(part, n_wg, p);
 }
@@ -309,7 +397,7 @@ __global__ __launch_bounds__(256) void eval_kernel(const MlpBf16* __restrict__ P
     const int wave = threadIdx.x >> 6;
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const float x = i < n ? fabsf(xs[i]) : 0.0f, y = i < n ? ys[i] : 1.0f;
-    const float z = mlp_forward<false>(P, act[wave], feature_x(x), feature_y(y));
+    const float z = mlp_forward(P, act[wave], feature_x(x), feature_y(y));
     if (i < n) {
         z_out[i] = z;
         if (K_out) K_out[i] = surrogate_K(x, y, z);
@@ -334,7 +422,7 @@ __global__ __launch_bounds__(256) void certify_kernel(const MlpBf16* __restrict_
     const float x = ((float)ix + (float)i / (float)(kCertSide - 1)) * kCellW;
     const float ly = -4.0f + ((float)iy + (float)j / (float)(kCertSide - 1)) * kCellH;
     const float y = exp10f(ly);
-    const float z = mlp_forward<false>(P, act[wave], feature_x(x), feature_y(y));
+    const float z = mlp_forward(P, act[wave], feature_x(x), feature_y(y));
     const double K = (double)surrogate_K(x, y, z);
     const double ref = plain_K((double)x, (double)y);
     double e = fabs(K / ref - 1.0);
@@ -370,7 +458,7 @@ hipError_t launch_surrogate_train_step(const void* P, const float* x, const floa
                                        float* part_loss, hipStream_t s)
 {
     const int n_wg = (batch + kHid - 1) / kHid;
-    train_kernel<<<dim3(n_wg), dim3(64), 0, s>>>(static_cast<const MlpBf16*>(P), x, y, z, n, base, batch, wscale,
+    train_kernel<<<dim3(n_wg), dim3(64 * kTrainWaves), 0, s>>>(static_cast<const MlpBf16*>(P), x, y, z, n, base, batch, wscale,
                                                  part_grad, part_loss);
     return hipGetLastError();
 }
@@ -380,7 +468,7 @@ hipError_t launch_surrogate_adam(float* theta, float* m, float* v, const float* 
                                  const float* part_loss, float* loss_out, hipStream_t s)
 {
     const int n_wg = (batch + kHid - 1) / kHid;
-    adam_kernel<<<dim3((kNParams + 255) / 256), dim3(256), 0, s>>>(theta, m, v, part_grad, n_wg, lr, beta1, beta2,
+    adam_kernel<<<dim3((kNParams + kUpdateThreads - 1) / kUpdateThreads), dim3(kUpdateThreads), 0, s>>>(theta, m, v, part_grad, n_wg, lr, beta1, beta2,
                                                                    eps, c1, c2, static_cast<MlpBf16*>(P),
                                                                    part_loss, batch, loss_out);
     return hipGetLastError();
@@ -390,7 +478,7 @@ hipError_t launch_surrogate_reduce(const float* part_grad, int32_t batch, float*
                                    float* loss_out, hipStream_t s)
 {
     const int n_wg = (batch + kHid - 1) / kHid;
-    reduce_kernel<<<dim3((kNParams + 255) / 256), dim3(256), 0, s>>>(part_grad, n_wg, grad, part_loss, batch,
+    reduce_kernel<<<dim3((kNParams + kUpdateThreads - 1) / kUpdateThreads), dim3(kUpdateThreads), 0, s>>>(part_grad, n_wg, grad, part_loss, batch,
                                                                      loss_out);
     return hipGetLastError();
 }

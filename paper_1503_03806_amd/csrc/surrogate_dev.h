@@ -96,12 +96,8 @@ __device__ __forceinline__ void layer_mfma(const uint16_t* act, const uint16_t* 
 }
 
 // Forward pass of one wavefront (lane = sample): returns z_hat.  act is the
-// wavefront's [64][kLd] bfloat16 scratch.  With kTrain, also keeps the
-// pre-activations Z[layer][s][o] (binary32) and the bfloat16 inputs of
-// layers 2-5 transposed, inT[layer-2][i][s] (row stride kLd).
-template <bool kTrain>
-__device__ __forceinline__ float mlp_forward(const MlpBf16* __restrict__ P, uint16_t* act, float f1, float f2,
-                             float* Z = nullptr, uint16_t* inT = nullptr)
+// wavefront's [64][kLd] bfloat16 scratch.
+__device__ __forceinline__ float mlp_forward(const MlpBf16* __restrict__ P, uint16_t* act, float f1, float f2)
 {
     const int lane = threadIdx.x & 63;
     // layer 1 (2 -> 64) on the vector units, one sample per lane
@@ -112,10 +108,6 @@ __device__ __forceinline__ float mlp_forward(const MlpBf16* __restrict__ P, uint
         for (int e = 0; e < 8; ++e) {
             const float z = fmaf(bf2f(P->W1[2 * (o + e)]), f1, fmaf(bf2f(P->W1[2 * (o + e) + 1]), f2, P->b[0][o + e]));
             hv[e] = f2bf(silu(z));
-            if (kTrain) {
-                Z[lane * kHid + o + e] = z;
-                inT[(o + e) * kLd + lane] = hv[e];
-            }
         }
         uint4 pk;
         pk.x = hv[0] | ((uint32_t)hv[1] << 16);
@@ -139,12 +131,7 @@ __device__ __forceinline__ float mlp_forward(const MlpBf16* __restrict__ P, uint
                 for (int r = 0; r < 4; ++r) {
                     const int s = 16 * m + 4 * (lane >> 4) + r, o = 16 * n + (lane & 15);
                     const float z = acc[m][n][r] + P->b[k + 1][o];
-                    const uint16_t h = f2bf(silu(z));
-                    act[s * kLd + o] = h;
-                    if (kTrain) {
-                        Z[((k + 1) * kHid + s) * kHid + o] = z;
-                        inT[((k + 1) * kHid + o) * kLd + s] = h;
-                    }
+                    act[s * kLd + o] = f2bf(silu(z));
                 }
         wave_sync();
     }
