@@ -159,7 +159,7 @@ struct hk_ctx {
     double sg_budget = 0.0;  // of the current certification
     // resampling: QR factors of the Chebyshev design matrix for the bin
     // sizes of the last call (main and ragged last bin), and the quadrature
-    DevBuf rs_Q, rs_R, rs_Ql, rs_Rl, rs_quad;
+    DevBuf rs_Q, rs_R, rs_Ql, rs_Rl, rs_quad, rs_part;
     int64_t rs_m = -1, rs_ml = -1;
     int rs_nc = 0;
     bool rs_quad_ready = false;
@@ -1007,7 +1007,7 @@ int hk_destroy(hk_ctx* ctx)
         b->release();
     for (DevBuf* b : {&ctx->sg_theta, &ctx->sg_m, &ctx->sg_v, &ctx->sg_copy, &ctx->sg_part, &ctx->sg_ploss,
                       &ctx->sg_err, &ctx->sg_mask, &ctx->sg_used_total, &ctx->rs_Q, &ctx->rs_R, &ctx->rs_Ql, &ctx->rs_Rl,
-                      &ctx->rs_quad})
+                      &ctx->rs_quad, &ctx->rs_part})
         b->release();
     for (auto& p : ctx->pending) {
         (void)hipEventDestroy(p.second.first);
@@ -2273,9 +2273,11 @@ int hk_resample(hk_ctx* ctx, const void* sorted, int precision, int64_t n_points
     }
     const double* Ql = ragged ? static_cast<const double*>(ctx->rs_Ql.p) : static_cast<const double*>(ctx->rs_Q.p);
     const double* Rl = ragged ? static_cast<const double*>(ctx->rs_Rl.p) : static_cast<const double*>(ctx->rs_R.p);
+    HK_HIP(ctx, ctx->rs_part.ensure(std::max<size_t>(resample_scratch_bytes(n_points, points_per_bin), 8)),
+           "allocating partial products");
     HK_HIP(ctx, launch_resample(sorted, precision == HK_F64 ? 8 : 4, n_points, points_per_bin, n_coef,
                                 static_cast<const double*>(ctx->rs_Q.p), static_cast<const double*>(ctx->rs_R.p), Ql,
-                                Rl, coef_out, ctx->stream),
+                                Rl, static_cast<double*>(ctx->rs_part.p), coef_out, ctx->stream),
            "resample");
     return HK_OK;
 }
@@ -2319,8 +2321,11 @@ int hk_transmission_direct(hk_ctx* ctx, const void* sorted, int precision, int64
     if (int rc = check_ctx(ctx)) return rc;
     if (n_points == 0 || n_m == 0) return HK_OK;
     HK_HIP(ctx, hipSetDevice(ctx->device), "hipSetDevice");
+    HK_HIP(ctx, ctx->rs_part.ensure(
+                    std::max<size_t>(transmission_direct_scratch_bytes(n_points, points_per_bin, n_m), 8)),
+           "allocating partial sums");
     HK_HIP(ctx, launch_transmission_direct(sorted, precision == HK_F64 ? 8 : 4, n_points, points_per_bin, m_col, n_m,
-                                           T_out, ctx->stream),
+                                           static_cast<double*>(ctx->rs_part.p), T_out, ctx->stream),
            "transmission_direct");
     return HK_OK;
 }

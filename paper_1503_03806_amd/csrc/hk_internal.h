@@ -466,13 +466,18 @@ hipError_t launch_surrogate_certify(const void* P, double* err, hipStream_t s);
 // Resampling and transmission (resample.hip).
 constexpr int kMaxCoef = 32;   // Chebyshev coefficients per bin
 constexpr int kMaxQuad = 128;  // quadrature nodes of the fitted transmission
+// part: resample_scratch_bytes of device memory (0: none needed).
+size_t resample_scratch_bytes(int64_t n_points, int64_t ppb);
 hipError_t launch_resample(const void* sorted, int key_bytes, int64_t n_points, int64_t ppb, int nc,
-                           const double* Q, const double* R, const double* Ql, const double* Rl, double* coef,
-                           hipStream_t s);
+                           const double* Q, const double* R, const double* Ql, const double* Rl, double* part,
+                           double* coef, hipStream_t s);
 hipError_t launch_transmission_fit(const double* coef, int64_t n_bins, int nc, const double* yq, const double* wq,
                                    int nq, const double* m, int n_m, double* T, hipStream_t s);
+// part: transmission_direct_scratch_bytes of device memory (0: none needed;
+// below 1 MiB).
+size_t transmission_direct_scratch_bytes(int64_t n_points, int64_t ppb, int n_m);
 hipError_t launch_transmission_direct(const void* sorted, int key_bytes, int64_t n_points, int64_t ppb,
-                                      const double* m, int n_m, double* T, hipStream_t s);
+                                      const double* m, int n_m, double* part, double* T, hipStream_t s);
 
 // Sets the message hk_last_error(NULL) returns on this thread (host code
 // outside hk_api.cpp that fails without a context).

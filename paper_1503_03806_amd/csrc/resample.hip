@@ -4,8 +4,12 @@
 //
 // The design matrix A[i][c] = T_c(t_i), t_i = 2 (i + 1/2)/M - 1, is the same
 // for every bin of M points, so its QR factors (A = QR, thin Householder,
-// computed once on the host) are shared: per bin the kernel forms Q^T d
-// (d_i = ln kappa_i of the sorted bin) and solves R C = Q^T d.
+// computed once on the host) are shared: per bin the kernels form Q^T d
+// (d_i = ln kappa_i of the sorted bin) and solve R C = Q^T d.  Over all bins
+// Q^T d is one matrix product, taken by the matrix cores for bins of at least
+// kMfmaRows points.
+#include <algorithm>
+
 #include "hk_internal.h"
 
 namespace hk {
@@ -16,7 +20,7 @@ constexpr int kThreads = 256;
 __device__ inline double key_to_double(const double* s, int64_t i) { return s[i]; }
 __device__ inline double key_to_double(const float* s, int64_t i) { return (double)s[i]; }
 
-// One workgroup per bin.  Q: row-major [M][nc]; R: row-major [nc][nc],
+// Bins of few points, one workgroup per bin.  Q: row-major [M][nc]; R: row-major [nc][nc],
 // upper triangular.  The last bin may use its own factors (Ql, Rl, ml).
 template <typename K>
 __global__ __launch_bounds__(kThreads) void resample_kernel(const K* __restrict__ sorted, int64_t n_points,
@@ -67,101 +71,402 @@ __global__ __launch_bounds__(kThreads) void resample_kernel(const K* __restrict_
     }
 }
 
+// ---- Q^T d on the matrix cores ----
+//
+// Sixteen bins form a group: their Q^T d is the product of Q^T (32 x M, two
+// tiles of 16 coefficients) and the 16 columns d, by v_mfma_f64_16x16x4.  A
+// workgroup takes kChunkRows rows of one group, kWaveRows per wavefront; the
+// partial products of its wavefronts are added in LDS and its sum goes to
+// part; resample_solve_kernel adds a bin's parts in chunk order and solves.
+// Bound: the logarithms (one per point) and reading the bins once; Q (1.6 MB
+// for bins of 1e4 points, 20 coefficients) is read once per group from L2.
+// One workgroup per bin with a dot product per coefficient read Q once per
+// bin and solved the triangle with one lane: 300 bins of 1e4 points took 229
+// us, 37 us (27 + 10) now.
+constexpr int64_t kMfmaRows = 512;  // bins from this size (smaller ones: a workgroup per bin)
+constexpr int kWaveRows = 64, kChunkRows = kWaveRows * kThreads / 64;
+constexpr int kGroupBins = 16;
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+
+// The bins of one size: n_bins of m rows from `sorted` on, ppb points apart,
+// their factors and their coefficients.
+template <typename K>
+struct BinSet {
+    const K* sorted;
+    int64_t n_bins, m;
+    const double *Q, *R;
+    double* coef;
+};
+
+// Group blockIdx.x (of the whole bins, or the last, shorter bin's own), chunk
+// blockIdx.y; part: [group][chunk][32 coefficients][16 bins].
+template <typename K>
+__global__ __launch_bounds__(kThreads) void resample_product_kernel(BinSet<K> whole, BinSet<K> last, int64_t groups,
+                                                                    int64_t ppb, int nc, double* __restrict__ part)
+{
+    __shared__ double sum[kThreads / 64][32 * kGroupBins];
+    const bool is_last = blockIdx.x >= groups;
+    const BinSet<K>& B = is_last ? last : whole;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int col = lane & 15, kk = lane >> 4;
+    const int64_t bin = (is_last ? 0 : (int64_t)blockIdx.x * kGroupBins) + col;
+    const bool have = bin < B.n_bins;
+    const K* __restrict__ d = B.sorted + (have ? bin : 0) * ppb;
+    const double* __restrict__ Q = B.Q;
+    const bool two = nc > 16;
+    const int64_t r0 = (int64_t)blockIdx.y * kChunkRows + wave * kWaveRows;
+    const int64_t r1 = min(r0 + kWaveRows, B.m);
+    doublex4 c0 = {0.0, 0.0, 0.0, 0.0}, c1 = {0.0, 0.0, 0.0, 0.0};
+    // 16 rows at a time, the next 16 loaded while these are taken; lane (col,
+    // kk) takes rows 4 kk .. 4 kk + 3 of its bin's column and of Q's (any
+    // order of the rows will do, as long as both operands have the same)
+    double v[4], q0[4], q1[4], vn[4], q0n[4], q1n[4];
+    auto load = [&](int64_t r, double (&a)[4], double (&x)[4], double (&y)[4]) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int64_t i = r + 4 * kk + e;
+            const bool in = i < r1;
+            a[e] = in && have ? key_to_double(d, i) : 1.0;
+            x[e] = in && col < nc ? Q[i * nc + col] : 0.0;
+            y[e] = two && in && col + 16 < nc ? Q[i * nc + col + 16] : 0.0;
+        }
+    };
+    load(r0, v, q0, q1);
+    for (int64_t r = r0; r < r1; r += 16) {
+        load(r + 16, vn, q0n, q1n);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const double lv = log(fmax(v[e], 2.2250738585072014e-308));
+            c0 = __builtin_amdgcn_mfma_f64_16x16x4f64(q0[e], lv, c0, 0, 0, 0);
+            if (two) c1 = __builtin_amdgcn_mfma_f64_16x16x4f64(q1[e], lv, c1, 0, 0, 0);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            v[e] = vn[e];
+            q0[e] = q0n[e];
+            q1[e] = q1n[e];
+        }
+    }
+    // lane (col, kk) holds coefficients kk + 4 e of bin col
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        sum[wave][(kk + 4 * e) * kGroupBins + col] = c0[e];
+        sum[wave][(16 + kk + 4 * e) * kGroupBins + col] = c1[e];
+    }
+    __syncthreads();
+    double* out = part + ((int64_t)blockIdx.x * gridDim.y + blockIdx.y) * 32 * kGroupBins;
+    for (int t = threadIdx.x; t < 32 * kGroupBins; t += kThreads) {
+        double w = 0.0;
+#pragma unroll
+        for (int k = 0; k < kThreads / 64; ++k) w += sum[k][t];
+        out[t] = w;
+    }
+}
+
+// R C = Q^T d, a wavefront per bin (the last, shorter bin in a workgroup of
+// its own, past `blocks`): lane c adds its coefficient's parts in chunk order;
+// then back substitution by columns, lane c holding row c's right-hand side.
+template <typename K>
+__global__ __launch_bounds__(kThreads) void resample_solve_kernel(BinSet<K> whole, BinSet<K> last, int64_t blocks,
+                                                                  int64_t groups, int chunks, int nc,
+                                                                  const double* __restrict__ part)
+{
+    __shared__ double R[kMaxCoef * kMaxCoef];
+    const bool is_last = blockIdx.x >= blocks;
+    const BinSet<K>& B = is_last ? last : whole;
+    for (int t = threadIdx.x; t < nc * nc; t += kThreads) R[t] = B.R[t];
+    __syncthreads();
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t bin = (is_last ? 0 : (int64_t)blockIdx.x * (kThreads / 64)) + wave;
+    if (bin >= B.n_bins) return;
+    const int c = min(lane, nc - 1);
+    const int n_parts = (int)((B.m + kChunkRows - 1) / kChunkRows);  // the other chunks of a shorter bin are empty
+    const double* p = part + ((is_last ? groups : bin / kGroupBins) * chunks * 32 + c) * kGroupBins + bin % kGroupBins;
+    double s = 0.0;
+#pragma unroll 8
+    for (int k = 0; k < n_parts; ++k) s += p[(int64_t)k * 32 * kGroupBins];
+    double x = 0.0;
+    for (int k = nc - 1; k >= 0; --k) {
+        const double xk = __shfl(s, k, 64) / R[k * nc + k];
+        if (lane == k) x = xk;
+        if (lane < k) s = fma(-R[lane * nc + k], xk, s);
+    }
+    if (lane < nc) B.coef[bin * nc + lane] = x;
+}
+
+// ---- transmission ----
+
+// e^{-t} for t >= 0 (not NaN; beyond 800 it is 0): t = n ln 2 + r, |r| <= ln 2
+// / 2, e^r by the polynomial through the function at Chebyshev nodes (within
+// 2e-17).  ~20 instructions; the library's exp, for any argument, ~40.
+__device__ inline double exp_neg(double t)
+{
+    t = fmin(t, 800.0);
+    const double n = rint(t * 1.4426950408889634);
+    const double r = fma(n, 7.371002565167799e-13, fma(n, 0.6931471805592082, -t));
+    double p = fma(2.5110049204818658e-08, r, 2.763265472252779e-07);
+    p = fma(p, r, 2.755724088722987e-06);
+    p = fma(p, r, 2.4801485441561313e-05);
+    p = fma(p, r, 0.00019841269890076403);
+    p = fma(p, r, 0.0013888888952352863);
+    p = fma(p, r, 0.008333333333319589);
+    p = fma(p, r, 0.04166666666648795);
+    p = fma(p, r, 0.1666666666666668);
+    p = fma(p, r, 0.5000000000000019);
+    p = fma(p, r, 1.0);
+    p = fma(p, r, 1.0);
+    return ldexp(p, -(int)n);
+}
+// e^{-t} is exactly 0 in binary64 above kExpZero and rounds to 1 below
+// kExpOne.
+constexpr double kExpZero = 746.0, kExpOne = 5.5511151231257827e-17;  // 2^-54
+constexpr double kHuge = 1.7976931348623157e308;
+
 // T(m_j) = sum_q w_q exp(-exp(P(t_q)) m_j), P the bin's Chebyshev sum, at the
-// quadrature nodes y_q (t_q = 2 y_q - 1).  One workgroup per bin.
+// quadrature nodes y_q (t_q = 2 y_q - 1).  Block (bin, chunk of 256 column
+// masses).  Four nodes whose exponentials are all 0, or all 1, for every lane
+// of a wavefront need none of them: on column masses over many decades most are.
+// (300 bins x 1000 masses: 48 us with a workgroup per bin and the library's
+// exp throughout, 34 us.)
 __global__ __launch_bounds__(kThreads) void transmission_fit_kernel(const double* __restrict__ coef, int nc,
                                                                     const double* __restrict__ yq,
                                                                     const double* __restrict__ wq, int nq,
                                                                     const double* __restrict__ mcol, int n_m,
                                                                     double* __restrict__ T)
 {
-    __shared__ double kq[kMaxQuad];
+    __shared__ double kq[kMaxQuad], ws[kMaxQuad];
+    __shared__ double cb[kMaxCoef];
     const int64_t b = blockIdx.x;
-    const double* c = coef + b * nc;
+    for (int k = threadIdx.x; k < nc; k += kThreads) cb[k] = coef[b * nc + k];
+    __syncthreads();
+    bool fine = true;
     for (int q = threadIdx.x; q < nq; q += kThreads) {
         const double t = 2.0 * yq[q] - 1.0;
-        double tm = 1.0, tc = t, s = c[0];
-        if (nc > 1) s = fma(c[1], t, s);
+        double tm = 1.0, tc = t, s = cb[0];
+        if (nc > 1) s = fma(cb[1], t, s);
         for (int k = 2; k < nc; ++k) {
             const double tn = fma(2.0 * t, tc, -tm);
             tm = tc;
             tc = tn;
-            s = fma(c[k], tc, s);
+            s = fma(cb[k], tc, s);
         }
-        kq[q] = exp(s);
+        const double v = exp(s);
+        kq[q] = v;
+        ws[q] = wq[q];
+        fine = fine && v <= kHuge;  // finite (>= 0, an exponential), not NaN
     }
+    const bool fine_q = __syncthreads_and(fine);
+    const int j = blockIdx.y * kThreads + threadIdx.x;
+    const double mj = j < n_m ? mcol[j] : 0.0;
+    double s = 0.0;
+    if (fine_q && !__ballot(!(mj >= 0.0 && mj <= kHuge))) {
+        int q = 0;
+        for (; q + 4 <= nq; q += 4) {  // four independent chains
+            double t[4], e[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) t[u] = kq[q + u] * mj;
+            const double lo = fmin(fmin(t[0], t[1]), fmin(t[2], t[3])), hi = fmax(fmax(t[0], t[1]), fmax(t[2], t[3]));
+            if (!__ballot(lo < kExpZero)) continue;
+            const bool one = !__ballot(hi >= kExpOne);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) e[u] = one ? 1.0 : exp_neg(t[u]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) s = fma(ws[q + u], e[u], s);
+        }
+        for (; q < nq; ++q) s = fma(ws[q], exp_neg(kq[q] * mj), s);
+    } else {
+        for (int q = 0; q < nq; ++q) s = fma(ws[q], exp(-kq[q] * mj), s);
+    }
+    if (j < n_m) T[b * n_m + j] = s;
+}
+
+// T(m_j) = (1/M) sum_i exp(-kappa_i m_j) over a bin's values.  Block (bin, 64
+// column masses, segment of the bin), a mass per lane; its wavefronts take the
+// segment's values 64 at a time in turn, each finding the least and the
+// largest of its 64.  Where those and the wavefront's own least and largest
+// mass put all of the 64 values' exponentials at 0, or at 1, none is
+// evaluated.  The wavefronts' sums are added in LDS in order; with more than
+// one segment (few bins and masses would leave the chip idle) the segments'
+// go to part and are added by transmission_sum_kernel.  Bound: the VALU work
+// of the exponentials left.  (100 bins of 1e4 x 500 masses over 48 decades:
+// 680 us with a mass per thread over the whole bin and the library's exp
+// throughout, 240 us; 3 bins of 2.7e4 x 37 masses 1790 -> 29 us.)
+constexpr int kDirectWaves = 8;
+template <typename K>
+__global__ __launch_bounds__(64 * kDirectWaves) void transmission_direct_kernel(const K* __restrict__ sorted,
+                                                                                int64_t n_points, int64_t ppb,
+                                                                                const double* __restrict__ mcol,
+                                                                                int n_m, double* __restrict__ part,
+                                                                                double* __restrict__ T)
+{
+    __shared__ double kb[kDirectWaves][64], sums[kDirectWaves][64];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int64_t b = blockIdx.x;
+    const int j = blockIdx.y * 64 + lane;
+    const int64_t b0 = b * ppb;
+    const int64_t m = min(ppb, n_points - b0);
+    const double mj = mcol[min(j, n_m - 1)];
+    double mlo = mj, mhi = mj;
+    const bool fine_m = !__ballot(!(mj >= 0.0 && mj <= kHuge));
+    for (int o = 32; o > 0; o >>= 1) {
+        mlo = fmin(mlo, __shfl_xor(mlo, o, 64));
+        mhi = fmax(mhi, __shfl_xor(mhi, o, 64));
+    }
+    double s = 0.0;
+    const int64_t step = 64ll * kDirectWaves * gridDim.z;
+    for (int64_t i0 = 64ll * ((int64_t)blockIdx.z * kDirectWaves + wave); i0 < m; i0 += step) {
+        const int64_t i = i0 + lane;
+        const int cnt = (int)min((int64_t)64, m - i0);
+        const double v = i < m ? key_to_double(sorted, b0 + i) : 0.0;
+        const bool fine = !__ballot(!(v >= 0.0 && v <= kHuge));
+        double vlo = i < m ? v : kHuge, vhi = v;
+        for (int o = 32; o > 0; o >>= 1) {
+            vlo = fmin(vlo, __shfl_xor(vlo, o, 64));
+            vhi = fmax(vhi, __shfl_xor(vhi, o, 64));
+        }
+        double* k64 = kb[wave];
+        k64[lane] = v;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (!fine_m || !fine) {
+            for (int k = 0; k < cnt; ++k) s += exp(-k64[k] * mj);
+        } else if (vlo * mlo > kExpZero) {
+            // all 0
+        } else if (vhi * mhi < kExpOne) {
+            s += (double)cnt;
+        } else {
+            int k = 0;
+            for (; k + 4 <= cnt; k += 4) {  // four independent chains
+                double e[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) e[u] = exp_neg(k64[k + u] * mj);
+                s += (e[0] + e[1]) + (e[2] + e[3]);
+            }
+            for (; k < cnt; ++k) s += exp_neg(k64[k] * mj);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    sums[wave][lane] = s;
     __syncthreads();
-    for (int j = threadIdx.x; j < n_m; j += kThreads) {
-        const double mj = mcol[j];
-        double s = 0.0;
-        for (int q = 0; q < nq; ++q) s = fma(wq[q], exp(-kq[q] * mj), s);
-        T[b * n_m + j] = s;
+    if (wave == 0 && j < n_m) {
+        double v = 0.0;
+#pragma unroll
+        for (int w = 0; w < kDirectWaves; ++w) v += sums[w][lane];
+        if (gridDim.z == 1)
+            T[b * n_m + j] = v / (double)m;
+        else
+            part[((int64_t)blockIdx.z * gridDim.x + b) * n_m + j] = v;
     }
 }
 
-// T(m_j) = (1/M) sum_i exp(-kappa_i m_j) over a bin's values.  Block
-// (bin, chunk of 256 column masses); the bin's values pass through LDS.
-template <typename K>
-__global__ __launch_bounds__(kThreads) void transmission_direct_kernel(const K* __restrict__ sorted,
-                                                                       int64_t n_points, int64_t ppb,
-                                                                       const double* __restrict__ mcol, int n_m,
-                                                                       double* __restrict__ T)
+// The segments' sums, in order.
+__global__ __launch_bounds__(256) void transmission_sum_kernel(const double* __restrict__ part, int segs,
+                                                              int64_t n_bins, int64_t n_points, int64_t ppb, int n_m,
+                                                              double* __restrict__ T)
 {
-    __shared__ double kb[kThreads];
-    const int64_t b = blockIdx.x;
-    const int j = blockIdx.y * kThreads + threadIdx.x;
-    const int64_t b0 = b * ppb;
-    const int64_t m = min(ppb, n_points - b0);
-    const double mj = j < n_m ? mcol[j] : 0.0;
-    double s = 0.0;
-    for (int64_t i0 = 0; i0 < m; i0 += kThreads) {
-        const int64_t i = i0 + threadIdx.x;
-        kb[threadIdx.x] = i < m ? key_to_double(sorted, b0 + i) : 0.0;
-        __syncthreads();
-        const int cnt = (int)min((int64_t)kThreads, m - i0);
-        for (int k = 0; k < cnt; ++k) s += exp(-kb[k] * mj);
-        __syncthreads();
-    }
-    if (j < n_m) T[b * n_m + j] = s / (double)m;
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t >= n_bins * n_m) return;
+    double v = 0.0;
+    for (int k = 0; k < segs; ++k) v += part[k * n_bins * n_m + t];
+    const int64_t b = t / n_m;
+    T[t] = v / (double)min(ppb, n_points - b * ppb);
+}
+
+// Segments of each bin: enough for four wavefronts per SIMD, of at least one
+// round of the workgroup's wavefronts each.
+int direct_segments(int64_t n_points, int64_t ppb, int n_m)
+{
+    const int64_t n_bins = (n_points + ppb - 1) / ppb, blocks = n_bins * ((n_m + 63) / 64);
+    const int64_t m = std::min(ppb, n_points);
+    return (int)std::max<int64_t>(1, std::min<int64_t>(512 / blocks, m / (64 * kDirectWaves)));
 }
 
 }  // namespace
 
-hipError_t launch_resample(const void* sorted, int key_bytes, int64_t n_points, int64_t ppb, int nc,
-                           const double* Q, const double* R, const double* Ql, const double* Rl, double* coef,
-                           hipStream_t s)
+namespace {
+
+template <typename K>
+hipError_t run_resample(const K* sorted, int64_t n_points, int64_t ppb, int nc, const double* Q, const double* R,
+                        const double* Ql, const double* Rl, double* part, double* coef, hipStream_t s)
 {
     const int64_t n_bins = (n_points + ppb - 1) / ppb;
-    if (n_bins == 0) return hipSuccess;
-    if (key_bytes == 8)
-        resample_kernel<double><<<dim3((unsigned)n_bins), dim3(kThreads), 0, s>>>(
-            static_cast<const double*>(sorted), n_points, ppb, nc, Q, R, Ql, Rl, coef);
-    else
-        resample_kernel<float><<<dim3((unsigned)n_bins), dim3(kThreads), 0, s>>>(
-            static_cast<const float*>(sorted), n_points, ppb, nc, Q, R, Ql, Rl, coef);
+    const int64_t m = std::min(ppb, n_points), last = n_points - (n_bins - 1) * ppb;
+    if (!resample_scratch_bytes(n_points, ppb)) {
+        resample_kernel<K><<<dim3((unsigned)n_bins), dim3(kThreads), 0, s>>>(sorted, n_points, ppb, nc, Q, R, Ql, Rl,
+                                                                             coef);
+        return hipGetLastError();
+    }
+    // the whole bins, and a shorter last one with its own factors
+    const int64_t n_whole = last < m ? n_bins - 1 : n_bins, n_last = n_bins - n_whole;
+    const BinSet<K> whole{sorted, n_whole, m, Q, R, coef};
+    const BinSet<K> short_bin{sorted + n_whole * ppb, n_last, last, Ql, Rl, coef + n_whole * nc};
+    const int64_t groups = (n_whole + kGroupBins - 1) / kGroupBins;
+    const int64_t chunks = (m + kChunkRows - 1) / kChunkRows;
+    if (groups + n_last > (int64_t)INT32_MAX) return hipErrorInvalidValue;
+    resample_product_kernel<K><<<dim3((unsigned)(groups + n_last), (unsigned)chunks), dim3(kThreads), 0, s>>>(
+        whole, short_bin, groups, ppb, nc, part);
+    const int64_t blocks = (n_whole + kThreads / 64 - 1) / (kThreads / 64);
+    resample_solve_kernel<K><<<dim3((unsigned)(blocks + n_last)), dim3(kThreads), 0, s>>>(whole, short_bin, blocks,
+                                                                                         groups, (int)chunks, nc, part);
     return hipGetLastError();
+}
+
+}  // namespace
+
+// (Bins whose rows would need more than 65535 chunks, 1.6e7 points, also go
+// one workgroup per bin.)
+size_t resample_scratch_bytes(int64_t n_points, int64_t ppb)
+{
+    const int64_t m = std::min(ppb, n_points);
+    const int64_t chunks = (m + kChunkRows - 1) / kChunkRows;
+    if (m < kMfmaRows || chunks > 65535) return 0;
+    const int64_t groups = ((n_points + ppb - 1) / ppb + kGroupBins - 1) / kGroupBins + 1;
+    return (size_t)(groups * chunks) * 32 * kGroupBins * sizeof(double);
+}
+
+hipError_t launch_resample(const void* sorted, int key_bytes, int64_t n_points, int64_t ppb, int nc,
+                           const double* Q, const double* R, const double* Ql, const double* Rl, double* part,
+                           double* coef, hipStream_t s)
+{
+    if (n_points == 0) return hipSuccess;
+    if (key_bytes == 8)
+        return run_resample(static_cast<const double*>(sorted), n_points, ppb, nc, Q, R, Ql, Rl, part, coef, s);
+    return run_resample(static_cast<const float*>(sorted), n_points, ppb, nc, Q, R, Ql, Rl, part, coef, s);
 }
 
 hipError_t launch_transmission_fit(const double* coef, int64_t n_bins, int nc, const double* yq, const double* wq,
                                    int nq, const double* m, int n_m, double* T, hipStream_t s)
 {
     if (n_bins == 0 || n_m == 0) return hipSuccess;
-    transmission_fit_kernel<<<dim3((unsigned)n_bins), dim3(kThreads), 0, s>>>(coef, nc, yq, wq, nq, m, n_m, T);
+    const dim3 grid((unsigned)n_bins, (unsigned)((n_m + kThreads - 1) / kThreads));
+    transmission_fit_kernel<<<grid, dim3(kThreads), 0, s>>>(coef, nc, yq, wq, nq, m, n_m, T);
     return hipGetLastError();
 }
 
+size_t transmission_direct_scratch_bytes(int64_t n_points, int64_t ppb, int n_m)
+{
+    if (n_points <= 0 || n_m <= 0) return 0;
+    const int segs = direct_segments(n_points, ppb, n_m);
+    return segs == 1 ? 0 : (size_t)segs * (size_t)((n_points + ppb - 1) / ppb) * (size_t)n_m * sizeof(double);
+}
+
 hipError_t launch_transmission_direct(const void* sorted, int key_bytes, int64_t n_points, int64_t ppb,
-                                      const double* m, int n_m, double* T, hipStream_t s)
+                                      const double* m, int n_m, double* part, double* T, hipStream_t s)
 {
     const int64_t n_bins = (n_points + ppb - 1) / ppb;
     if (n_bins == 0 || n_m == 0) return hipSuccess;
-    const dim3 grid((unsigned)n_bins, (unsigned)((n_m + kThreads - 1) / kThreads));
+    const int segs = direct_segments(n_points, ppb, n_m);
+    const dim3 grid((unsigned)n_bins, (unsigned)((n_m + 63) / 64), (unsigned)segs);
     if (key_bytes == 8)
-        transmission_direct_kernel<double><<<grid, dim3(kThreads), 0, s>>>(static_cast<const double*>(sorted),
-                                                                           n_points, ppb, m, n_m, T);
+        transmission_direct_kernel<double><<<grid, dim3(64 * kDirectWaves), 0, s>>>(
+            static_cast<const double*>(sorted), n_points, ppb, m, n_m, part, T);
     else
-        transmission_direct_kernel<float><<<grid, dim3(kThreads), 0, s>>>(static_cast<const float*>(sorted),
-                                                                          n_points, ppb, m, n_m, T);
+        transmission_direct_kernel<float><<<grid, dim3(64 * kDirectWaves), 0, s>>>(static_cast<const float*>(sorted),
+                                                                                   n_points, ppb, m, n_m, part, T);
+    if (segs > 1)
+        transmission_sum_kernel<<<dim3((unsigned)((n_bins * n_m + 255) / 256)), dim3(256), 0, s>>>(
+            part, segs, n_bins, n_points, ppb, n_m, T);
     return hipGetLastError();
 }
 
