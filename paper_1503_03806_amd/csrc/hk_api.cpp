@@ -91,7 +91,6 @@ struct hk_ctx {
     int device = 0;
     hipStream_t own = nullptr;     // created with the context
     hipStream_t stream = nullptr;  // where work is enqueued (may be the null stream)
-    int64_t lds_bytes = kSortLdsBytes;  // LDS a sort workgroup may use
     int64_t lds_max = 65536;            // the device's LDS per workgroup (the radix sorts)
     void* noalloc_scratch = nullptr;    // this device's hk_kdist_noalloc array
     DevBuf wing_tab;                    // the binary64 wing's interpolation matrices
@@ -970,10 +969,8 @@ int hk_create(int device, hk_ctx** out)
         return rc;
     }
     int lds = 0;
-    if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device) == hipSuccess && lds > 0) {
-        ctx->lds_bytes = std::min<int64_t>(lds, kSortLdsBytes);
+    if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device) == hipSuccess && lds > 0)
         ctx->lds_max = lds;
-    }
     *out = ctx;
     return HK_OK;
 }
@@ -1677,11 +1674,11 @@ int hk_kdist(hk_ctx* ctx, const void* kappa, int precision, int64_t n_points, co
     if (int rc = check_ctx(ctx)) return rc;
     HK_HIP(ctx, hipSetDevice(ctx->device), "hipSetDevice");
     const int eb = precision == HK_F64 ? 8 : 4;
-    const size_t sb = kdist_scratch_bytes(eb, n_points, bins->points_per_bin, ctx->lds_bytes, ctx->lds_max);
+    const size_t sb = kdist_scratch_bytes(eb, n_points, bins->points_per_bin, ctx->lds_max);
     if (sb) HK_HIP(ctx, ctx->kscratch.ensure(sb), "allocating sort scratch");
     StageTimer tm(ctx, HK_STAGE_KDIST);
     HK_HIP(ctx, launch_kdist(kappa, eb, n_points, bins->points_per_bin, gv, k_out, sorted_out,
-                             ctx->kscratch.p, ctx->lds_bytes, ctx->lds_max, 1, ctx->stream),
+                             ctx->kscratch.p, ctx->lds_max, 1, ctx->stream),
            "kdist");
     tm.stop();
     return HK_OK;
@@ -1700,7 +1697,7 @@ int hk_kdist_noalloc(hk_ctx* ctx, const void* kappa, int precision, int64_t n_po
     if (n_points > 0 && (!kappa || !k_out)) return fail(ctx, HK_EINVAL, "kappa and k_out must not be NULL");
     if (int rc = check_ctx(ctx)) return rc;
     const int eb = precision == HK_F64 ? 8 : 4;
-    const size_t sb = kdist_scratch_bytes(eb, n_points, bins->points_per_bin, ctx->lds_bytes, ctx->lds_max);
+    const size_t sb = kdist_scratch_bytes(eb, n_points, bins->points_per_bin, ctx->lds_max);
     if (sb > kNoAllocScratchBytes)
         return fail(ctx, HK_EINVAL,
                     "hk_kdist_noalloc: bins of %lld points above one LDS sort need %zu bytes of scratch, more than "
@@ -1709,7 +1706,7 @@ int hk_kdist_noalloc(hk_ctx* ctx, const void* kappa, int precision, int64_t n_po
     if (!ctx->noalloc_scratch) return fail(ctx, HK_EDEVICE, "no fixed sort scratch on this device");
     HK_HIP(ctx, hipSetDevice(ctx->device), "hipSetDevice");
     HK_HIP(ctx, launch_kdist(kappa, eb, n_points, bins->points_per_bin, gv, k_out, sorted_out, ctx->noalloc_scratch,
-                             ctx->lds_bytes, ctx->lds_max, 1, ctx->stream),
+                             ctx->lds_max, 1, ctx->stream),
            "kdist");
     return HK_OK;
 }
@@ -1791,7 +1788,7 @@ int hk_tables(hk_ctx* ctx, const hk_state* states, int32_t n_states, const hk_gr
     HK_HIP(ctx, ctx->tb_ranges_c.ensure((size_t)B * 2 * n_tiles_c * sizeof(int64_t)), "allocating tile ranges");
     HK_HIP(ctx, ctx->tb_counts.ensure((size_t)n_states * kCountBlocks * 3 * sizeof(int64_t)),
            "allocating counters");
-    const size_t sb = kdist_scratch_bytes(8, np, bins->points_per_bin, ctx->lds_bytes, ctx->lds_max);
+    const size_t sb = kdist_scratch_bytes(8, np, bins->points_per_bin, ctx->lds_max);
     if (sb) HK_HIP(ctx, ctx->kscratch.ensure(sb), "allocating sort scratch");
     // bins of one LDS radix sort: every state of a batch in one sort launch
     const bool sort_batched = bins->points_per_bin <= kdist_radix_max_keys(8, ctx->lds_max);
@@ -1965,13 +1962,13 @@ int hk_tables(hk_ctx* ctx, const hk_state* states, int32_t n_states, const hk_gr
             }
             if (sort_batched) {
                 HK_HIP(ctx, launch_kdist(kap, 8, np, bins->points_per_bin, gv, k_out + b0 * n_bins * gv.n, nullptr,
-                                         ctx->kscratch.p, ctx->lds_bytes, ctx->lds_max, nbat, ctx->stream),
+                                         ctx->kscratch.p, ctx->lds_max, nbat, ctx->stream),
                        "kdist");
             } else {
                 for (int32_t s = 0; s < nbat; ++s)
                     HK_HIP(ctx, launch_kdist(kap + (int64_t)s * np, 8, np, bins->points_per_bin, gv,
                                              k_out + (b0 + s) * n_bins * gv.n, nullptr, ctx->kscratch.p,
-                                             ctx->lds_bytes, ctx->lds_max, 1, ctx->stream),
+                                             ctx->lds_max, 1, ctx->stream),
                            "kdist");
             }
             tm.stop();

@@ -422,22 +422,16 @@ hipError_t launch_f32_finish(const float* sum, const float* comp, const float* s
                              int accumulate, hipStream_t s, int32_t n_states = 1);
 
 // k-distribution.  elem_bytes 8 (binary64 keys) or 4 (binary32 keys).
-int64_t kdist_lds_max_points(int elem_bytes, int64_t lds_bytes);
-// LDS per sort workgroup: 32 KB (4096 binary64 or 8192 binary32 keys);
-// larger bins are sorted in chunks of that size and merged.  Measured: 300
-// bins of 1e4 binary64 keys take 0.18 ms in 32 KB chunks, 0.19 in 16 KB,
-// 0.22 in 64 KB and 0.30 ms in one 128 KB sort each (more, smaller sorts
-// share the CUs; the merges are cheap).
-constexpr int64_t kSortLdsBytes = 32768;
 // Bins of up to kdist_radix_max_keys(lds_max) keys (16384 on gfx950's
 // 160 KB of LDS per workgroup) are sorted by an LDS radix sort, one
 // workgroup per bin, the bins of n_states contiguous grids (each n_points)
-// in one launch; larger bins (one grid per call) by the chunks below.
+// in one launch; larger bins (one grid per call) in sorted chunks that are
+// merged.
 int64_t kdist_radix_max_keys(int elem_bytes, int64_t lds_max);
 hipError_t launch_kdist(const void* kappa, int elem_bytes, int64_t n_points, int64_t ppb,
                         const GValues& g, double* k_out, void* sorted_out, void* scratch,
-                        int64_t lds_bytes, int64_t lds_max, int32_t n_states, hipStream_t s);
-size_t kdist_scratch_bytes(int elem_bytes, int64_t n_points, int64_t ppb, int64_t lds_bytes, int64_t lds_max);
+                        int64_t lds_max, int32_t n_states, hipStream_t s);
+size_t kdist_scratch_bytes(int elem_bytes, int64_t n_points, int64_t ppb, int64_t lds_max);
 // The fixed device array of hk_kdist_noalloc (HK_KDIST_NOALLOC_SCRATCH_BYTES),
 // its address on the current device (call with that device current).
 constexpr size_t kNoAllocScratchBytes = (size_t)64 << 20;

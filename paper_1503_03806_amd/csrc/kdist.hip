@@ -7,20 +7,16 @@
 // (non-negative IEEE values order like their unsigned integer images).  A
 // bin of up to kRadixMaxKeys keys is sorted by one workgroup in registers
 // and LDS, by a radix sort whose ranking uses wavefront ballots (below); a
-// larger bin is cut into LDS-sized chunks, each sorted in LDS by a bitonic
-// network, then merged pairwise in global memory (each element finds its
-// rank in the partner run by binary search; ties keep left-before-right, so
-// the merge is stable).
+// larger bin is cut into chunks, each sorted in that way, then merged eight
+// runs at a time in global memory (each key finds its rank in the other seven
+// by binary searches; ties keep the earlier run first).
+#include <algorithm>
+
 #include "hk_internal.h"
 
 namespace hk {
 size_t radix_lds_bytes(int elem_bytes, int64_t keys);
 namespace {
-
-// threads per chunk-sort workgroup (measured on 300 bins of 1e4 binary64
-// keys sorted this way: 0.177 ms, against 0.185 ms with 1024 threads and
-// 0.188 ms with 256)
-constexpr int kSortThreads = 512;
 
 template <typename K>
 struct KeyMax;
@@ -44,31 +40,6 @@ template <>
 __device__ inline double key_value<uint32_t>(uint32_t k)
 {
     return (double)__uint_as_float(k);
-}
-
-// Sort s[0 .. npad) ascending in LDS; npad is a power of two, all threads of
-// the block take part.
-// Each stage has npad/2 compare-exchange pairs (i, i + j), i with bit j
-// clear; thread t takes pairs t, t + blockDim, ... so that every lane works.
-template <typename K>
-__device__ void bitonic_lds(K* s, int npad)
-{
-    const int half = npad >> 1;
-    for (int k = 2; k <= npad; k <<= 1) {
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int q = threadIdx.x; q < half; q += blockDim.x) {
-                const int i = ((q & ~(j - 1)) << 1) | (q & (j - 1));
-                const int ixj = i + j;
-                const K a = s[i], b = s[ixj];
-                const bool up = (i & k) == 0;
-                if ((a > b) == up) {
-                    s[i] = b;
-                    s[ixj] = a;
-                }
-            }
-            __syncthreads();
-        }
-    }
 }
 
 // k(g) read off a bin's m sorted keys s[0 .. m).  Step rule: the smallest
@@ -269,73 +240,148 @@ __global__ __launch_bounds__(kRadixThreads) void radix_bin_kernel(const K* __res
     if ((int)threadIdx.x < g.n) k_out[bin * g.n + threadIdx.x] = k_of_g<K>(buf, m, g.g[threadIdx.x], g.rule);
 }
 
-// One workgroup per bin (bins <= chunk), or per chunk of a larger bin when
-// `chunk < ppb`: sort in LDS; if `final`, also emit k(g) for the bin.
+// One workgroup per chunk of a larger bin (one grid): the chunk's keys in
+// order to dst, same layout.  `chunk` is a whole number of rounds.
 template <typename K>
-__global__ __launch_bounds__(kSortThreads) void sort_chunk_lds_kernel(
-    const K* __restrict__ src, int64_t n_points, int64_t ppb, int64_t chunk, int npad,
-    int64_t chunks_per_bin, K* __restrict__ dst, GValues g, double* __restrict__ k_out, int final)
+__global__ __launch_bounds__(kRadixThreads) void radix_chunk_kernel(const K* __restrict__ src, int64_t n_points,
+                                                                    int64_t ppb, int chunk, uint32_t chunks_per_bin,
+                                                                    K* __restrict__ dst)
 {
-    extern __shared__ unsigned char lds_raw[];
-    K* s = reinterpret_cast<K*>(lds_raw);
-    const int64_t bin = blockIdx.x / chunks_per_bin;
-    const int64_t c = blockIdx.x - bin * chunks_per_bin;
-    const int64_t b0 = bin * ppb;
-    const int64_t m_bin = min(ppb, n_points - b0);
-    const int64_t j0 = b0 + c * chunk;
-    const int64_t m = min(chunk, b0 + m_bin - j0);
-    for (int i = threadIdx.x; i < npad; i += blockDim.x) s[i] = i < m ? src[j0 + i] : KeyMax<K>::v;
-    __syncthreads();
-    bitonic_lds(s, npad);
-    if (dst) {
-        for (int i = threadIdx.x; i < m; i += blockDim.x) dst[j0 + i] = s[i];
+    extern __shared__ __align__(16) unsigned char radix_lds[];
+    const uint32_t bin = blockIdx.x / chunks_per_bin;
+    const int64_t first = (int64_t)(blockIdx.x - bin * chunks_per_bin) * chunk;  // in the bin
+    const int64_t b0 = bin * ppb + first;
+    const int64_t left = min(ppb - first, n_points - b0);
+    if (left <= 0) return;
+    const int m = (int)min((int64_t)chunk, left);
+    const int rounds = chunk / kRadixThreads;
+    K* buf = reinterpret_cast<K*>(radix_lds);
+    uint32_t* cnt = reinterpret_cast<uint32_t*>(radix_lds + (size_t)chunk * sizeof(K));
+    uint32_t* wsum = cnt + kRadixWaves * 256;
+    K key[kRadixMaxRounds];
+    const int base_p = (int)(threadIdx.x >> 6) * 64 * rounds + (int)(threadIdx.x & 63);
+#pragma unroll
+    for (int r = 0; r < kRadixMaxRounds; ++r) {
+        const int p = base_p + r * 64;
+        key[r] = (r < rounds && p < m) ? src[b0 + p] : KeyMax<K>::v;
     }
-    if (final && (int)threadIdx.x < g.n) {
-        k_out[bin * g.n + threadIdx.x] = k_of_g<K>(s, m, g.g[threadIdx.x], g.rule);
-    }
+    radix_sort_block<K>(key, rounds, m, buf, cnt, wsum);
+    for (int p = (int)threadIdx.x; p < m; p += kRadixThreads) dst[b0 + p] = buf[p];
 }
 
-// One pass of pairwise merging of sorted runs of length `run` inside each
-// bin.  One thread per element.
-template <typename K>
-__global__ __launch_bounds__(256) void merge_pass_kernel(const K* __restrict__ src,
-                                                         K* __restrict__ dst, int64_t n_points,
-                                                         int64_t ppb, int64_t run)
+// One pass of merging groups of kWays sorted runs of `run` keys (a
+// multiple of kMergeThreads, so a workgroup's keys are of one run) inside
+// each bin; src and dst differ.  One thread per key, which goes to its place
+// in its own run plus its ranks in the others (keys of earlier runs count when
+// equal).  Bound: latency on few keys, the probes on many.  The workgroup's
+// first and last keys bound the windows of the other runs that its keys fall
+// into: two searches per run of 16 lanes each, 16 probes a step (a run of 16384 keys
+// in 4 dependent loads, not 14).  The windows, about kMergeThreads keys each,
+// then are searched in LDS; where the runs' ranges differ so much that they
+// do not fit there, in global memory.  The runs of a group are 8, or 4 or 2
+// where no more are left to merge (each further run costs every key a search).
+// Measured, binary64, the whole sort against chunks of 4096 keys by a bitonic
+// network and merges of two runs with a search per key: 3 bins of 1e5 keys 95
+// -> 52 us (16 chunks, 16 a merge), one of 3e6 493 -> 289, 150 of 2e4 189 ->
+// 129, one of 2e7 4.5 -> 2.5 ms.
+constexpr int kMergeWays = 8, kMergeThreads = 256, kMergeWindow = 3072;
+static_assert(kMergeThreads == 2 * kMergeWays * 16, "a search of 16 lanes per bound");
+template <typename K, int kWays>
+__global__ __launch_bounds__(kMergeThreads) void merge_runs_kernel(const K* __restrict__ src, K* __restrict__ dst,
+                                                                   int64_t n_points, int64_t ppb,
+                                                                   uint32_t blocks_per_bin, int64_t run)
 {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n_points) return;
-    const int64_t bin = e / ppb;
+    __shared__ K win[kMergeWindow + 1];
+    __shared__ uint32_t bound[2 * kMergeWays];
+    const uint32_t bin = blockIdx.x / blocks_per_bin;
     const int64_t b0 = bin * ppb;
     const int64_t m = min(ppb, n_points - b0);
-    const int64_t i = e - b0;
-    const int64_t r = i / run;
-    const int64_t pair0 = (r & ~(int64_t)1) * run;
-    const int64_t own0 = r * run;
-    const K key = src[e];
-    int64_t p0, p1;
-    if ((r & 1) == 0) {
-        p0 = own0 + run;
-        p1 = min(own0 + 2 * run, m);
-    } else {
-        p0 = own0 - run;
-        p1 = own0;
-    }
-    int64_t lo = p0, hi = p1 > p0 ? p1 : p0;
-    if ((r & 1) == 0) {  // left run: count partner keys < key
-        while (lo < hi) {
-            int64_t mid = lo + ((hi - lo) >> 1);
-            if (src[b0 + mid] < key) lo = mid + 1;
-            else hi = mid;
+    const int64_t i0 = (int64_t)(blockIdx.x - bin * blocks_per_bin) * kMergeThreads;
+    if (i0 >= m) return;
+    const int t = threadIdx.x;
+    const int64_t r = i0 / run;
+    const int own = (int)(r % kWays);
+    const int64_t g0 = (r - own) * run;  // the group's first key in the bin
+    const K* grp = src + b0 + g0;
+    // no key after the run's end: runs end at multiples of kMergeThreads or at m
+    const int n_own = (int)min((int64_t)kMergeThreads, m - i0);
+    const K key = src[b0 + i0 + min(t, n_own - 1)];
+    {
+        const int j = t >> 5;
+        const K bk = src[b0 + i0 + ((t >> 4) & 1 ? n_own - 1 : 0)];
+        const int64_t left = m - g0 - j * run;
+        const K* rj = grp + j * run;
+        uint32_t lo = 0u, hi = j >= kWays || j == own || left <= 0 ? 0u : (uint32_t)min(left, run);
+        for (uint32_t size = (uint32_t)run; size; size = (size + 15u) / 16u - 1u) {
+            // 16 lanes probe the ends of the 16 parts of [lo, hi)
+            const uint32_t part = (hi - lo + 15u) / 16u;
+            const uint32_t p = lo + ((t & 15) + 1u) * part;
+            const bool in = part && p <= hi;
+            const K v = in ? rj[p - 1] : K(0);
+            const uint64_t before = __ballot(in && (v < bk || (v == bk && j < own)));
+            const uint32_t c = __builtin_popcount((uint32_t)(before >> (t & 48)) & 0xffffu);
+            if (part) {
+                lo += c * part;
+                hi = min(hi, lo + part - 1u);
+            }
         }
-    } else {  // right run: count partner keys <= key
-        while (lo < hi) {
-            int64_t mid = lo + ((hi - lo) >> 1);
-            if (src[b0 + mid] <= key) lo = mid + 1;
-            else hi = mid;
-        }
+        if ((t & 15) == 0) bound[t >> 4] = lo;
     }
-    const int64_t partner_rank = lo - p0;
-    dst[b0 + pair0 + (i - own0) + partner_rank] = key;
+    __syncthreads();
+    uint32_t from[kWays], len[kWays], off[kWays], total = 0u, most = 0u;
+#pragma unroll
+    for (int j = 0; j < kWays; ++j) {
+        from[j] = __builtin_amdgcn_readfirstlane(bound[2 * j]);
+        len[j] = __builtin_amdgcn_readfirstlane(bound[2 * j + 1]) - from[j];
+        off[j] = total;
+        total += len[j];
+        most = max(most, len[j]);
+    }
+    uint32_t lo[kWays] = {};
+    const bool staged = total <= (uint32_t)kMergeWindow;
+    if (staged) {
+        for (uint32_t q0 = 0; q0 < total; q0 += 8 * kMergeThreads) {
+            K v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const uint32_t q = min(q0 + u * kMergeThreads + t, total - 1u);
+                int64_t at = from[0] + (int64_t)q;
+#pragma unroll
+                for (int j = 1; j < kWays; ++j)
+                    at = q >= off[j] ? j * run + from[j] + (int64_t)(q - off[j]) : at;
+                v[u] = grp[at];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const uint32_t q = q0 + u * kMergeThreads + t;
+                if (q < total) win[q] = v[u];
+            }
+        }
+        __syncthreads();
+    }
+    uint32_t step = most ? 1u << (31 - __builtin_clz(most)) : 0u;
+    // the searches side by side, their loads in flight together (an empty
+    // window reads some key and takes none)
+    auto search = [&](auto at) {
+        for (; step; step >>= 1) {
+#pragma unroll
+            for (int j = 0; j < kWays; ++j) {
+                const uint32_t p = lo[j] + step;
+                const K v = at(j, max(min(p, len[j]), 1u) - 1u);
+                const bool take = (p <= len[j]) & ((v < key) | ((v == key) & (j < own)));
+                lo[j] = take ? p : lo[j];
+            }
+        }
+    };
+    if (staged)
+        search([&](int j, uint32_t q) { return win[off[j] + q]; });
+    else
+        search([&](int j, uint32_t q) { return grp[len[j] ? j * run + from[j] + (int64_t)q : 0]; });
+    if (t >= n_own) return;
+    int64_t at = i0 - r * run + t;
+#pragma unroll
+    for (int j = 0; j < kWays; ++j) at += from[j] + lo[j];
+    dst[b0 + g0 + at] = key;
 }
 
 template <typename K>
@@ -350,16 +396,14 @@ __global__ __launch_bounds__(64) void kdist_pick_kernel(const K* __restrict__ so
         k_out[bin * g.n + threadIdx.x] = k_of_g<K>(sorted + b0, m, g.g[threadIdx.x], g.rule);
 }
 
-int pow2_at_least(int64_t m)
-{
-    int p = 1;
-    while (p < m) p <<= 1;
-    return p;
-}
+// Chunks of a large bin: as short as gives each CU one, in steps of two
+// rounds (a merge's workgroups that write to the same lines then are a
+// multiple of 8 apart, so on one XCD).
+constexpr int64_t kChunkShare = 256 * kRadixThreads;
 
 template <typename K>
 hipError_t run_kdist(const K* kappa, int64_t n_points, int64_t ppb, const GValues& g,
-                     double* k_out, K* sorted_out, K* scratch, int64_t lds_bytes, int64_t radix_keys,
+                     double* k_out, K* sorted_out, K* scratch, int64_t radix_keys,
                      int32_t n_states, hipStream_t s)
 {
     const int64_t n_bins = (n_points + ppb - 1) / ppb;
@@ -376,43 +420,29 @@ hipError_t run_kdist(const K* kappa, int64_t n_points, int64_t ppb, const GValue
         return hipGetLastError();
     }
     if (n_states != 1) return hipErrorInvalidValue;  // bins above one LDS sort: one grid per call
-    const int64_t cap = kdist_lds_max_points(sizeof(K), lds_bytes);
-    if (ppb <= cap) {
-        const int npad = pow2_at_least(ppb);
-        const size_t shm = (size_t)npad * sizeof(K);
-        hipError_t e = hipFuncSetAttribute(
-            reinterpret_cast<const void*>(&sort_chunk_lds_kernel<K>),
-            hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
-        if (e != hipSuccess) return e;
-        sort_chunk_lds_kernel<K><<<dim3((unsigned)n_bins), dim3(kSortThreads), shm, s>>>(
-            kappa, n_points, ppb, ppb, npad, 1, sorted_out, g, k_out, 1);
-        return hipGetLastError();
-    }
-    // chunked: sort chunks of `cap` points, then merge runs until one run
-    // covers the bin.  Ping-pong between scratch halves; the last pass
-    // lands in sorted_out when given.
-    const int64_t chunk = cap;
-    const int64_t cpb = (ppb + chunk - 1) / chunk;
-    const int npad = pow2_at_least(chunk);
-    const size_t shm = (size_t)npad * sizeof(K);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&sort_chunk_lds_kernel<K>),
+    // chunks, then merges until one run covers the bin.  Ping-pong between the
+    // scratch halves; the last step lands in sorted_out when given.
+    const int64_t span = std::min(ppb, n_points);
+    const int64_t rounds =
+        std::min((n_points + 2 * kChunkShare - 1) / (2 * kChunkShare) * 2, radix_keys / kRadixThreads);
+    const int64_t chunk = rounds * kRadixThreads;
+    const int64_t cpb = (span + chunk - 1) / chunk, bpb = (span + kMergeThreads - 1) / kMergeThreads;
+    const size_t shm = radix_lds_bytes(sizeof(K), chunk);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&radix_chunk_kernel<K>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
     if (e != hipSuccess) return e;
-    K* bufA = scratch;
-    K* bufB = scratch + n_points;
-    sort_chunk_lds_kernel<K><<<dim3((unsigned)(n_bins * cpb)), dim3(kSortThreads), shm, s>>>(
-        kappa, n_points, ppb, chunk, npad, cpb, bufA, g, k_out, 0);
+    if (n_bins * bpb > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
+    K* cur = chunk >= span && sorted_out ? sorted_out : scratch;
+    K* nxt = scratch + n_points;
+    radix_chunk_kernel<K><<<dim3((unsigned)(n_bins * cpb)), dim3(kRadixThreads), shm, s>>>(
+        kappa, n_points, ppb, (int)chunk, (uint32_t)cpb, cur);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    K* cur = bufA;
-    K* nxt = bufB;
-    int passes = 0;
-    for (int64_t run = chunk; run < ppb; run *= 2) ++passes;
-    int done = 0;
-    for (int64_t run = chunk; run < ppb; run *= 2) {
-        ++done;
-        K* out = (done == passes && sorted_out) ? sorted_out : nxt;
-        const int64_t blocks = (n_points + 255) / 256;
-        merge_pass_kernel<K><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(cur, out, n_points, ppb, run);
+    for (int64_t run = chunk; run < span; run *= kMergeWays) {
+        K* out = run * kMergeWays >= span && sorted_out ? sorted_out : nxt;
+        const int64_t runs = (span + run - 1) / run;  // (the last pass may have fewer than kMergeWays left)
+        auto* merge = runs > 4 ? &merge_runs_kernel<K, 8> : runs > 2 ? &merge_runs_kernel<K, 4> : &merge_runs_kernel<K, 2>;
+        merge<<<dim3((unsigned)(n_bins * bpb)), dim3(kMergeThreads), 0, s>>>(cur, out, n_points, ppb, (uint32_t)bpb,
+                                                                              run);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         nxt = cur;
         cur = out;
@@ -436,34 +466,25 @@ int64_t kdist_radix_max_keys(int elem_bytes, int64_t lds_max)
     return r * kRadixThreads;
 }
 
-int64_t kdist_lds_max_points(int elem_bytes, int64_t lds_bytes)
+size_t kdist_scratch_bytes(int elem_bytes, int64_t n_points, int64_t ppb, int64_t lds_max)
 {
-    // largest power of two whose keys fit in the workgroup's LDS
-    int64_t p = 1;
-    while (p * 2 * elem_bytes <= lds_bytes && p * 2 <= (1 << 16)) p *= 2;
-    return p;
-}
-
-size_t kdist_scratch_bytes(int elem_bytes, int64_t n_points, int64_t ppb, int64_t lds_bytes, int64_t lds_max)
-{
-    if (ppb <= kdist_radix_max_keys(elem_bytes, lds_max) || ppb <= kdist_lds_max_points(elem_bytes, lds_bytes))
-        return 0;
+    if (ppb <= kdist_radix_max_keys(elem_bytes, lds_max)) return 0;
     return (size_t)2 * (size_t)n_points * (size_t)elem_bytes;
 }
 
 hipError_t launch_kdist(const void* kappa, int elem_bytes, int64_t n_points, int64_t ppb,
                         const GValues& g, double* k_out, void* sorted_out, void* scratch,
-                        int64_t lds_bytes, int64_t lds_max, int32_t n_states, hipStream_t s)
+                        int64_t lds_max, int32_t n_states, hipStream_t s)
 {
     if (n_points == 0 || n_states == 0) return hipSuccess;
     const int64_t rk = kdist_radix_max_keys(elem_bytes, lds_max);
     if (elem_bytes == 8)
         return run_kdist<uint64_t>(static_cast<const uint64_t*>(kappa), n_points, ppb, g, k_out,
                                    static_cast<uint64_t*>(sorted_out),
-                                   static_cast<uint64_t*>(scratch), lds_bytes, rk, n_states, s);
+                                   static_cast<uint64_t*>(scratch), rk, n_states, s);
     return run_kdist<uint32_t>(static_cast<const uint32_t*>(kappa), n_points, ppb, g, k_out,
                                static_cast<uint32_t*>(sorted_out), static_cast<uint32_t*>(scratch),
-                               lds_bytes, rk, n_states, s);
+                               rk, n_states, s);
 }
 
 // The fixed sort scratch of hk_kdist_noalloc: one array per device, made
