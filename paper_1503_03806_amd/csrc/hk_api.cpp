@@ -91,7 +91,7 @@ struct hk_ctx {
     int device = 0;
     hipStream_t own = nullptr;     // created with the context
     hipStream_t stream = nullptr;  // where work is enqueued (may be the null stream)
-    int64_t lds_max = 65536;            // the device's LDS per workgroup (the radix sorts)
+    int64_t lds_max = 65536;          // the device's LDS per workgroup (the radix sorts)
     void* noalloc_scratch = nullptr;    // this device's hk_kdist_noalloc array
     DevBuf wing_tab;                    // the binary64 wing's interpolation matrices
     std::string err;
@@ -127,6 +127,7 @@ struct hk_ctx {
                ev_cwing[2] = {nullptr, nullptr}, ev_kappa = nullptr;
     DevBuf partial;  // evaluation counters of hk_stats
     DevBuf kscratch;
+    DevBuf line_scratch;  // the last unordered list's sort, up to kKeepSortScratch
     bool have_run = false;
     int f64_points_per_lane = 4;  // tile shape of the binary64 opacity kernel (4 or 8)
     int f32_points_per_lane = 4;  // tile shape of the binary32 opacity kernel
@@ -997,6 +998,7 @@ int hk_destroy(hk_ctx* ctx)
         if (x) (void)hipStreamDestroy(x);
     ctx->partial.release();
     ctx->kscratch.release();
+    ctx->line_scratch.release();
     ctx->wing_tab.release();
     for (DevBuf* b : {&ctx->tb_idx, &ctx->tb_wing, &ctx->tb_core, &ctx->tb_w32, &ctx->tb_c32, &ctx->tb_ranges,
                       &ctx->tb_ranges_c, &ctx->tb_out, &ctx->tb_comp, &ctx->tb_scale, &ctx->tb_kappa,
@@ -1121,6 +1123,9 @@ int check_lines_device(hk_ctx* ctx, const hk_lines* L, ListInfo* li, bool* sorte
 
 }  // namespace
 
+// (scratch for 2.8 million lines)
+constexpr size_t kKeepSortScratch = (size_t)64 << 20;
+
 extern "C" {
 
 int hk_load_lines(hk_ctx* ctx, const hk_lines* L, const hk_species* sp, int lines_on_device)
@@ -1165,7 +1170,7 @@ int hk_load_lines(hk_ctx* ctx, const hk_lines* L, const hk_species* sp, int line
                        "copying the line list");
     } else {
         // ordered on the device: a host list is first copied as it is
-        DevBuf staging, scratch;
+        DevBuf staging;
         hipError_t e = hipSuccess;
         const double* dsrc[8] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
         if (lines_on_device) {
@@ -1180,14 +1185,19 @@ int hk_load_lines(hk_ctx* ctx, const hk_lines* L, const hk_species* sp, int line
                 }
         }
         const uint32_t* perm = nullptr;
-        if (e == hipSuccess) e = scratch.ensure(line_sort_scratch_bytes(n));
-        if (e == hipSuccess) e = launch_line_order(dsrc[0], n, scratch.p, &perm, ctx->stream);
+        GatherFields gf;
         for (const auto& f : fields)
-            for (size_t k = f.first; k < f.first + f.second && e == hipSuccess; ++k)
-                e = launch_gather(dsrc[k], perm, n, dst + k * n, ctx->stream);
+            for (size_t k = f.first; k < f.first + f.second; ++k) {
+                gf.src[gf.n] = dsrc[k];
+                gf.dst[gf.n++] = dst + k * n;
+            }
+        if (e == hipSuccess) e = ctx->line_scratch.ensure(line_sort_scratch_bytes(n));
+        if (e == hipSuccess) e = launch_line_order(dsrc[0], n, ctx->line_scratch.p, ctx->lds_max, &perm, ctx->stream);
+        if (e == hipSuccess) e = launch_gather(gf, perm, n, ctx->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
         staging.release();
-        scratch.release();
+        // (kept for the next list while it is small)
+        if (ctx->line_scratch.cap > kKeepSortScratch) ctx->line_scratch.release();
         if (e != hipSuccess) return hip_fail(ctx, e, "ordering the line list");
     }
     HK_HIP(ctx, hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");

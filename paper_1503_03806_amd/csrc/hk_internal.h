@@ -404,8 +404,16 @@ hipError_t launch_core_f32(const WingIdx* idx, const CoreRec32* core, const int6
 // check of a list in device memory.
 size_t line_sort_scratch_bytes(int64_t n);
 // perm_out: points into scratch, the input indices in (nu, index) order
-hipError_t launch_line_order(const double* nu, int64_t n, void* scratch, const uint32_t** perm_out, hipStream_t s);
-hipError_t launch_gather(const double* src, const uint32_t* perm, int64_t n, double* dst, hipStream_t s);
+hipError_t launch_line_order(const double* nu, int64_t n, void* scratch, int64_t lds_max, const uint32_t** perm_out,
+                             hipStream_t s);
+constexpr int kLineFields = 8;
+struct GatherFields {
+    int n = 0;
+    const double* src[kLineFields] = {};
+    double* dst[kLineFields] = {};
+};
+// dst[k][i] = src[k][perm[i]], k < f.n
+hipError_t launch_gather(const GatherFields& f, const uint32_t* perm, int64_t n, hipStream_t s);
 int32_t check_lines_blocks(int64_t n);  // CheckPart results launch_check_lines writes
 hipError_t launch_check_lines(const LinesDev& L, void* part, hipStream_t s);
 
