@@ -27,7 +27,8 @@ namespace hk {
 namespace {
 
 constexpr int kWaves = 4;            // wavefronts per workgroup
-constexpr int kMaxTerms = 2 * 10 + 14;  // series terms: n = 1 .. 2 ceil(x) + 14, x < 10
+constexpr int kMaxTerms = 32;  // series terms: n = 1 .. 2 x + 12, x < 10
+constexpr int kTermStride = kMaxTerms + 2;  // between tables in LDS (other banks)
 static_assert(kMaxTerms <= 64, "one lane per series term builds the tables");
 
 // num / den to about 2^-48 relative: the hardware reciprocal (relative
@@ -755,8 +756,8 @@ __global__ __launch_bounds__(64 * kWaves) void wing_f64_kernel(
 //         = 2 e^{-x^2} sum_n w_n cosh(n x),  w_n = e^{-n^2/4} / (n^2/4 + y^2),
 // so that H = e^{-x^2} [erfcx(y) cos 2xy + sin^2(xy)/(pi y)
 //                        + (y/pi) (sum_n w_n cosh(nx) - cos(2xy) T1)].
-// cosh(nx) comes from a three-term recurrence in n (at most e^{340}/2,
-// x < 10, n <= 34); w[n-1] is the line's table (same y for all its points),
+// The powers of e^x and of e^-x are summed by Horner's rule (at most e^{320},
+// x < 10, n <= 32); w[n-1] is the line's table (same y for all its points),
 // read from LDS.
 // e^{-n^2/4}, n = 1 .. kMaxTerms
 __constant__ double kGauss[kMaxTerms] = {
@@ -792,8 +793,6 @@ __constant__ double kGauss[kMaxTerms] = {
     1.9219477278238491e-98,
     4.5787899692915775e-105,
     6.6162610567094853e-112,
-    5.7986554185640377e-119,
-    3.0824406969490981e-126,
 };
 
 // cosh(r) and sinh(r)/r as polynomials in r^2 (interpolated at Chebyshev
@@ -819,7 +818,7 @@ constexpr double kPiHi = 3.141592653589214, kPiLo = 5.792147943243964e-13;
 // exp, exp and sincos, with their ranges' tests, took 65 instructions more of
 // 298 per evaluation: the kernel alone 1.10 -> 0.91 ms on 1e6 lines x 3e6
 // points.  Against 113-bit arithmetic over x in [0, 10), y from 1e-6 to 9.5
-// the error is 1.1e-15 rms and 5.8e-15 at most, against 2.3e-15 and 1.0e-14
+// the error is 1.0e-15 rms and 5.4e-15 at most, against 2.3e-15 and 1.0e-14
 // with the library's functions of the rounded x^2 and xy.)
 __device__ double voigt_core(double x, double y, double ex, double T1, double ypi, double ipy, const double* w)
 {
@@ -830,41 +829,44 @@ __device__ double voigt_core(double x, double y, double ex, double T1, double yp
     double C, Sr;
     cosh_sinh(re * re, C, Sr);
     const double E = ldexp(fma(re, Sr, C), (int)ke);
-    // 2 cosh x = e^x + e^{-x}
+    // X = e^x and e^{-x}
     const double kx = rint(x * kLog2e);
     const double rx = fma(-kx, kLn2Lo, fma(-kx, kLn2Hi, x));
     cosh_sinh(rx * rx, C, Sr);
-    const double c1 = ldexp(fma(rx, Sr, C), (int)kx) + ldexp(fma(-rx, Sr, C), -(int)kx);
-    // all kMaxTerms terms for every point (x < 10, so at least the
-    // 2 ceil(x) + 14 terms the series needs; the rest are below 1e-20 of the
-    // sum): a fixed trip count, the same for every lane.  2 cosh(n x) by the
-    // three-term recurrence c_{n+1} = c_1 c_n - c_{n-1}, c_0 = 2, which
-    // follows the growing solution e^{nx} stably (relative error ~n eps).
-    // (w is read a pair of terms at a time, each pair one pair ahead of its
-    // use, so that a read is in flight while the previous pair is summed;
-    // the loop is unrolled twice, which saves the register moves of the
-    // pairs' hand-over)
-    static_assert(kMaxTerms % 4 == 2, "8 double pairs in the loop, one after it");
+    const double X = ldexp(fma(rx, Sr, C), (int)kx), Xi = ldexp(fma(-rx, Sr, C), -(int)kx);
+    // sc = sum w_n (X^n + X^-n) by Horner's rule: kMaxTerms positive powers
+    // for every point (x < 10: the rest are below 5e-19 of the sum; a fixed
+    // trip count, the same for every lane) and 13 negative ones, which fall as
+    // e^{-n^2/4}; odd and even powers apart, so that four chains run side by
+    // side.  w is read a pair of terms at a time.  (2 cosh(n x) by its
+    // three-term recurrence took 68 operations in place of 49: the kernel
+    // alone 0.91 -> 0.75 ms on 1e6 lines x 3e6 points, 1.90 -> 1.65 ms on 3e6
+    // lines x 1e6 points; with one chain each 0.78 and 1.66.)
+    static_assert(kMaxTerms == 32, "16 pairs, the last 6 with the negative powers");
     const double2* w2 = reinterpret_cast<const double2*>(w);
-    double cm = 2.0, cc = c1, sc = 0.0;
-    auto term = [&](double wn) {
-        sc = fma(wn, cc, sc);
-        const double cn = fma(c1, cc, -cm);
-        cm = cc;
-        cc = cn;
-    };
-    double2 wa = w2[0];
-#pragma unroll 2
-    for (int h = 0; h < kMaxTerms / 2 - 1; h += 2) {
-        const double2 wb = w2[h + 1];
-        term(wa.x);
-        term(wa.y);
-        wa = w2[h + 2];
-        term(wb.x);
-        term(wb.y);
+    const double X2 = X * X, Xi2 = Xi * Xi;
+    double po = w2[15].x, pe = w2[15].y;  // odd and even powers
+#pragma unroll
+    for (int h = 14; h > 6; --h) {
+        const double2 wh = w2[h];
+        po = fma(po, X2, wh.x);
+        pe = fma(pe, X2, wh.y);
     }
-    term(wa.x);
-    term(wa.y);
+    double no = w2[6].x, ne = w2[5].y;
+    po = fma(po, X2, no);
+    pe = fma(pe, X2, w2[6].y);
+    no = fma(no, Xi2, w2[5].x);
+    po = fma(po, X2, w2[5].x);
+    pe = fma(pe, X2, ne);
+#pragma unroll
+    for (int h = 4; h >= 0; --h) {
+        const double2 wh = w2[h];
+        po = fma(po, X2, wh.x);
+        pe = fma(pe, X2, wh.y);
+        no = fma(no, Xi2, wh.x);
+        ne = fma(ne, Xi2, wh.y);
+    }
+    const double sc = fma(X, fma(pe, X, po), Xi * fma(ne, Xi, no));
     // s2 = sin^2(xy): r = xy - k pi, |r| <= pi / 2; sin(r)/r interpolated at
     // Chebyshev nodes, within 3e-17
     const double p = x * y, dp = fma(x, y, -p);
@@ -927,7 +929,7 @@ __device__ __forceinline__ void core_f64_tile(int64_t t, int64_t L0, int64_t L1,
 {
     __shared__ double acc_tab[kWaves][kCoreRun];
     __shared__ CorePiece piece_tab[kWaves][kCoreBatch];
-    __shared__ __align__(16) double w_tab[kWaves][kChunkPieces * kMaxTerms];
+    __shared__ __align__(16) double w_tab[kWaves][kChunkPieces * kTermStride];
     const int wave = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
     // lane nn < kMaxTerms builds term nn + 1 of each piece's table
@@ -988,7 +990,7 @@ __device__ __forceinline__ void core_f64_tile(int64_t t, int64_t L0, int64_t L1,
             // the 1 / (n^2/4 + y^2) e^{-n^2/4} tables of pieces s_lo .. s_end-1
             for (int k = s_lo; k < s_end; ++k) {
                 const double y2 = pc[k].y2;
-                if (lane < kMaxTerms) wt[(k - s_lo) * kMaxTerms + lane] = g_lane * qrcp(fma(m_lane, m_lane, y2));
+                if (lane < kMaxTerms) wt[(k - s_lo) * kTermStride + lane] = g_lane * qrcp(fma(m_lane, m_lane, y2));
             }
             __builtin_amdgcn_wave_barrier();
             // this lane's point f and its piece
@@ -1004,7 +1006,7 @@ __device__ __forceinline__ void core_f64_tile(int64_t t, int64_t L0, int64_t L1,
                 jr = j - run0;
                 const double dv = fma((double)j, dnu, nu_min) - pp.nu0;
                 v = pp.norm * voigt_core(fabs(dv) * pp.invA, pp.y, pp.ex, pp.T1, pp.ypi, pp.ipy,
-                                         wt + (my - s_lo) * kMaxTerms);
+                                         wt + (my - s_lo) * kTermStride);
             }
             // add in line order: one LDS add instruction per piece, whose
             // lanes hold distinct points; a wavefront's LDS operations are
