@@ -1388,8 +1388,8 @@ static int opacity_launch(hk_ctx* ctx, const hk_state* st, const hk_grid* grid, 
     f->widx = widx;
 
     PlanMaking wpm, cpm;
-    if (int rc = plan_begin(ctx, ctx->ln.cplan, ranges_c, n_tiles_c, 1, reach_core, nullptr, tpc, 64, kBusyMin, grid,
-                            &cpm))
+    if (int rc = plan_begin(ctx, ctx->ln.cplan, ranges_c, n_tiles_c, 1, reach_core, nullptr, tpc, 64,
+                            precision == HK_F64 ? kBusyMinCore64 : kBusyMin, grid, &cpm))
         return rc;
     if (precision != HK_F64)
         return launch_f32_pass(ctx, pp, grid, reach, widx, cpm, precision == HK_F32_SURROGATE, f);
@@ -1850,8 +1850,8 @@ int hk_tables(hk_ctx* ctx, const hk_state* states, int32_t n_states, const hk_gr
         // the batch's plans: the series', and (its tile shape known) the
         // wing's; every state of the batch in one launch per step
         PlanMaking wpm, cpm;
-        if (int rc = plan_begin(ctx, ctx->ln.cplan, rc_all, n_tiles_c, nbat, 0.0, d_reach_c, tpc, 64, kBusyMin, grid,
-                                &cpm))
+        if (int rc = plan_begin(ctx, ctx->ln.cplan, rc_all, n_tiles_c, nbat, 0.0, d_reach_c, tpc, 64,
+                                f64 ? kBusyMinCore64 : kBusyMin, grid, &cpm))
             return rc;
         int64_t* rw = static_cast<int64_t*>(ctx->tb_ranges.p);
         auto wing_plan = [&]() -> int {

@@ -199,6 +199,12 @@ constexpr int64_t kBusyMin = 4096;
 // workgroups already give every SIMD two wavefronts, and a cut item repeats
 // the tiles' reductions and interpolation.
 constexpr int64_t kBusyMinWing64 = 256;
+// The binary64 series: a wavefront has work only from the lines near its own
+// 256 points, so the halves of a cut tile's lines leave half its wavefronts
+// idle; from 256 workgroups on whole tiles are the better split.  (3e6 lines x
+// 1e6 points 4.9 -> 4.4 ms a step, 3e5 x 1e6 twice 1.13 -> 1.08, nine states
+// of 1e5 x 4e5 1.33 -> 1.28; with 1024 here the latter two stay.)
+constexpr int64_t kBusyMinCore64 = 512;
 // One plan to make: the segment lengths seg[s] of n_states states from their
 // reference ranges (tiles of kRefTilePoints points, 2 n_ref values per state;
 // min_seg: the shortest segment, a power of two -- 256 for the binary32 wing,
