@@ -53,6 +53,7 @@ struct ListInfo {
     // bounds of the width parameters, for the reach of Lorentz-width cutoffs
     double max_gamma_air = 0.0, max_gamma_self = 0.0, max_A21 = 0.0, min_n_air = 0.0, max_n_air = 0.0;
     double nu_max = 0.0;  // largest line centre (bounds the Doppler core widths)
+    double nu_low = 0.0;  // smallest line centre
 };
 
 // Device buffers of one work plan (work_plan.hip) and its partial sums.
@@ -358,6 +359,16 @@ double max_cutoff(const hk_ctx* ctx, const hk_state* st, const hk_grid* grid)
 {
     return max_cutoff(ctx->li, ctx->species.T_ref, st, grid);
 }
+// Grid points from the first line's centre to the last's (the same for every
+// state), 0 without lines there.
+int64_t covered_points(const hk_ctx* ctx, const hk_grid* grid)
+{
+    if (ctx->n_lines <= 0) return 0;
+    const double n = (double)grid->n_points;
+    const double lo = std::clamp((ctx->li.nu_low - grid->nu_min) / grid->dnu, 0.0, n);
+    const double hi = std::clamp((ctx->li.nu_max - grid->nu_min) / grid->dnu, 0.0, n);
+    return (int64_t)(hi - lo);
+}
 double wing_reach(const hk_ctx* ctx, const hk_state* st, const hk_grid* grid)
 {
     return max_cutoff(ctx, st, grid) + ctx->li.max_abs_delta * st->P + 2.0 * grid->dnu;
@@ -491,10 +502,11 @@ std::vector<ListScan> scan_lists(const hk_lines* L, int64_t k)
             ListInfo& b = p.b;
             p.any = true;
             int ok = 1, up = 1;
-            double nu_max = 0.0;
+            double nu_max = 0.0, nu_low = l->nu[i0];
             for (int64_t i = i0; i < i1; ++i) {
                 ok &= (l->nu[i] > 0.0) & (l->nu[i] <= kMax);
                 nu_max = l->nu[i] > nu_max ? l->nu[i] : nu_max;
+                nu_low = l->nu[i] < nu_low ? l->nu[i] : nu_low;
             }
             for (int64_t i = std::max<int64_t>(i0, 1); i < i1; ++i) up &= !(l->nu[i] < l->nu[i - 1]);
             double s_max = 0.0;
@@ -522,6 +534,7 @@ std::vector<ListScan> scan_lists(const hk_lines* L, int64_t k)
             }
             if (l->A21) ok &= nonneg(l->A21, i0, i1, b.max_A21);
             b.nu_max = nu_max;
+            b.nu_low = nu_low;
             b.min_n_air = n_lo;
             b.max_n_air = n_hi;
             p.bad = !ok;
@@ -557,6 +570,7 @@ std::vector<ListScan> scan_lists(const hk_lines* L, int64_t k)
             li.min_n_air = first ? b.min_n_air : std::min(li.min_n_air, b.min_n_air);
             li.max_n_air = first ? b.max_n_air : std::max(li.max_n_air, b.max_n_air);
             li.nu_max = std::max(li.nu_max, b.nu_max);
+            li.nu_low = first ? b.nu_low : std::min(li.nu_low, b.nu_low);
             first = false;
         }
     }
@@ -1099,6 +1113,7 @@ int check_lines_device(hk_ctx* ctx, const hk_lines* L, ListInfo* li, bool* sorte
         c.min_n_air = std::min(c.min_n_air, b.min_n_air);
         c.max_n_air = std::max(c.max_n_air, b.max_n_air);
         c.nu_max = std::max(c.nu_max, b.nu_max);
+        c.nu_low = std::min(c.nu_low, b.nu_low);
     }
     if (c.first_bad < n) {  // read that line back for the message
         const int64_t i = c.first_bad;
@@ -1117,6 +1132,7 @@ int check_lines_device(hk_ctx* ctx, const hk_lines* L, ListInfo* li, bool* sorte
     li->min_n_air = c.min_n_air;
     li->max_n_air = c.max_n_air;
     li->nu_max = c.nu_max;
+    li->nu_low = c.nu_low;
     *sorted = c.first_unordered >= n;
     return HK_OK;
 }
@@ -1368,7 +1384,7 @@ static int opacity_launch(hk_ctx* ctx, const hk_state* st, const hk_grid* grid, 
         HK_HIP(ctx, ctx->ln.wing.ensure(nb * sizeof(WingRec)), "allocating line records");
         HK_HIP(ctx, ctx->ln.core.ensure(nb * sizeof(CoreRec)), "allocating line records");
     }
-    const int32_t tp = opacity_f64_tile_points(np);
+    const int32_t tp = opacity_f64_tile_points(covered_points(ctx, grid));
     const int64_t n_tiles = ((int64_t)np + tp - 1) / tp;
     const int32_t tpc = precision == HK_F64 ? core_f64_tile_points() : core_f32_tile_points();
     const int64_t n_tiles_c = ((int64_t)np + tpc - 1) / tpc;
@@ -1442,7 +1458,8 @@ static int flight_wing(hk_ctx* ctx, const Flight& f, hipStream_t w, hipEvent_t k
     StageTimer tm(ctx, HK_STAGE_OPACITY, w);
     if (f.precision == HK_F64)
         HK_HIP(ctx, launch_wing_f64(static_cast<const WingRec*>(f.recs), f.widx, f.ranges, f.n, f.n_tiles, 1, f.wing.wp,
-                                    static_cast<const WingTables*>(ctx->wing_tab.p), f.nu_min, f.dnu, f.np, f.kappa,
+                                    static_cast<const WingTables*>(ctx->wing_tab.p), f.nu_min, f.dnu, f.np,
+                                    f.wing.tile_points, f.kappa,
                                     static_cast<double*>(const_cast<void*>(f.wing.partial)), f.accumulate ? 1 : 0, w),
                "wing_f64");
     else
@@ -1761,7 +1778,8 @@ int hk_tables(hk_ctx* ctx, const hk_state* states, int32_t n_states, const hk_gr
     const int32_t tpc = f64 ? core_f64_tile_points() : core_f32_tile_points();
     const int64_t n_tiles_c = ((int64_t)np + tpc - 1) / tpc;
     // wing tile ranges per state (binary32: of the smallest shape)
-    const int32_t tp_min = f64 ? opacity_f64_tile_points(np) : opacity_f32_tile_points(2);
+    const int32_t tp64 = opacity_f64_tile_points(covered_points(ctx, grid));
+    const int32_t tp_min = f64 ? tp64 : opacity_f32_tile_points(2);
     const int64_t ranges_per_state = 2 * (((int64_t)np + tp_min - 1) / tp_min);
 
     // states per launch: the option, or as many as the memory budget holds
@@ -1855,7 +1873,7 @@ int hk_tables(hk_ctx* ctx, const hk_state* states, int32_t n_states, const hk_gr
             return rc;
         int64_t* rw = static_cast<int64_t*>(ctx->tb_ranges.p);
         auto wing_plan = [&]() -> int {
-            const int32_t tp = f64 ? opacity_f64_tile_points(np) : opacity_f32_tile_points(ppl);
+            const int32_t tp = f64 ? tp64 : opacity_f32_tile_points(ppl);
             return plan_begin(ctx, ctx->ln.wplan, rw, ((int64_t)np + tp - 1) / tp, nbat, 0.0, d_reach, tp,
                               f64 ? 64 : 256, f64 ? kBusyMinWing64 : kBusyMin, grid, &wpm);
         };
@@ -1940,7 +1958,7 @@ int hk_tables(hk_ctx* ctx, const hk_state* states, int32_t n_states, const hk_gr
             if (f64)
                 HK_HIP(ctx, launch_wing_f64(static_cast<WingRec*>(ctx->tb_wing.p), tidx, rw, n, n_tiles, nbat, wwp,
                                             static_cast<const WingTables*>(ctx->wing_tab.p), grid->nu_min, grid->dnu,
-                                            np, static_cast<double*>(ctx->tb_out.p),
+                                            np, tp64, static_cast<double*>(ctx->tb_out.p),
                                             static_cast<double*>(ctx->ln.wplan.partial.p), 0, ctx->stream),
                        "wing_f64");
             else

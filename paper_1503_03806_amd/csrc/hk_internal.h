@@ -132,7 +132,7 @@ struct LinesDev {
 // valid lines that size the launches.
 struct CheckPart {
     int64_t first_bad, first_unordered;
-    double max_abs_delta, max_gamma_air, max_gamma_self, max_A21, min_n_air, max_n_air, nu_max;
+    double max_abs_delta, max_gamma_air, max_gamma_self, max_A21, min_n_air, max_n_air, nu_max, nu_low;
 };
 
 // State-dependent constants of the line preparation, computed on the host.
@@ -195,16 +195,18 @@ int64_t plan_scratch_count(int64_t n_pairs);  // int64 values of the plan's bloc
 // A state is cut when fewer reference tiles than busy_min hold lines (or very
 // unevenly many).
 constexpr int64_t kBusyMin = 4096;
-// The binary64 wing, a wavefront of which holds 64 points on small grids: 512
-// workgroups already give every SIMD two wavefronts, and a cut item repeats
-// the tiles' reductions and interpolation.
-constexpr int64_t kBusyMinWing64 = 256;
+// The binary64 wing, a wavefront of which holds 64 points on small grids: 256
+// workgroups on whole tiles are better than twice the items, each of which
+// repeats the tiles' reductions and interpolation.  (Whole steps, with 256 /
+// with 128 here: 9e4 lines x 9e4 points 213 / 195 us, 1.2e4 x 1.2e5 87 / 73,
+// 1.2e5 x 1.2e5 239 / 208; with 64 the same but 4e3 x 4e4 67 -> 69.)
+constexpr int64_t kBusyMinWing64 = 128;
 // The binary64 series: a wavefront has work only from the lines near its own
 // 256 points, so the halves of a cut tile's lines leave half its wavefronts
-// idle; from 256 workgroups on whole tiles are the better split.  (3e6 lines x
-// 1e6 points 4.9 -> 4.4 ms a step, 3e5 x 1e6 twice 1.13 -> 1.08, nine states
-// of 1e5 x 4e5 1.33 -> 1.28; with 1024 here the latter two stay.)
-constexpr int64_t kBusyMinCore64 = 512;
+// idle.  (3e6 lines x 1e6 points 4.9 ms a step with 4096 here, 4.4 with 1024
+// and below; nine states of 1e5 x 4e5 1.33 -> 1.28 with 512; 4e5 lines x 1.2e5
+// points 584 us with 256 and 553 with 128.)
+constexpr int64_t kBusyMinCore64 = 128;
 // One plan to make: the segment lengths seg[s] of n_states states from their
 // reference ranges (tiles of kRefTilePoints points, 2 n_ref values per state;
 // min_seg: the shortest segment, a power of two -- 256 for the binary32 wing,
@@ -332,7 +334,7 @@ hipError_t launch_line_prep_f64_batch(const LinesDev& L, const PrepParams* pps, 
                                       WingIdx* idx, CoreRec* core, const RangeJobs& rj, hipStream_t s);
 // Binary64 opacity: the wing kernel writes kappa, the core kernel its
 // series terms.
-int32_t opacity_f64_tile_points(int64_t n_points);  // points per work item on such a grid
+int32_t opacity_f64_tile_points(int64_t covered);  // points per work item, lines across that many points
 // The wing's interpolation matrices (opacity_f64.hip), filled on the host:
 // cheb[m][k]: Chebyshev coefficient k per node value m; child[c][m][k]: node
 // m's weight at node k of child tile c of four; child_cheb: the two in turn.
@@ -352,8 +354,8 @@ int32_t core_f32_tile_points();  // points per work item of the binary32 series
 // workgroup per item (wp.launch_items workgroups).
 hipError_t launch_wing_f64(const WingRec* wing, const WingIdx* idx, const int64_t* ranges, int64_t n_lines,
                            int64_t n_tiles, int32_t n_states, const WorkPlan& wp, const WingTables* tab,
-                           double nu_min, double dnu, int32_t n_points, double* kappa, double* partial,
-                           int accumulate, hipStream_t s);
+                           double nu_min, double dnu, int32_t n_points, int32_t tile_points, double* kappa,
+                           double* partial, int accumulate, hipStream_t s);
 // The series items of n_states states (tiles of core_f64_tile_points(),
 // their own plan): series = the series sums, every point written (a grid of
 // its own, n_points per state, added to the wing's afterwards, so that the

@@ -217,6 +217,7 @@ __global__ __launch_bounds__(256) void check_lines_kernel(LinesDev L, CheckPart*
     c.min_n_air = __builtin_inf();
     c.max_n_air = -__builtin_inf();
     c.nu_max = 0.0;
+    c.nu_low = __builtin_inf();
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < L.n; i += (int64_t)gridDim.x * 256) {
         const double nu = L.nu[i], S = L.S_ref[i], E = L.E_lower[i], ga = L.gamma_air[i], na = L.n_air[i];
         const double gs = L.gamma_self ? L.gamma_self[i] : ga;
@@ -237,6 +238,7 @@ __global__ __launch_bounds__(256) void check_lines_kernel(LinesDev L, CheckPart*
         c.min_n_air = fmin(c.min_n_air, na);
         c.max_n_air = fmax(c.max_n_air, na);
         c.nu_max = fmax(c.nu_max, nu);
+        c.nu_low = fmin(c.nu_low, nu);
     }
     sh[threadIdx.x] = c;
     __syncthreads();
@@ -253,6 +255,7 @@ __global__ __launch_bounds__(256) void check_lines_kernel(LinesDev L, CheckPart*
             a.min_n_air = fmin(a.min_n_air, b.min_n_air);
             a.max_n_air = fmax(a.max_n_air, b.max_n_air);
             a.nu_max = fmax(a.nu_max, b.nu_max);
+            a.nu_low = fmin(a.nu_low, b.nu_low);
         }
         __syncthreads();
     }

@@ -91,12 +91,14 @@ static_assert(kFarNodes == 24, "far_eval and wave_reduce are written for 24 node
 // Lines of a work item up to which all of them are taken point by point:
 // there the reductions and the interpolation cost more than the points.
 constexpr int64_t kFewLines = 24;
-// Grids of up to this many points take blocks of 256 points (two levels of
-// tiles): a quarter of the serial work per wavefront, four times the
-// workgroups; larger grids fill the chip with blocks of 1024, which take far
-// lines at fewer nodes.  (500 lines x 6e3 points: 16 us in blocks of 256, 47
-// in blocks of 1024; 1e5 lines x 4e5 points 0.20 against 0.26 ms; 1e6 lines x
-// 3e6 points 2.1 against 1.4 ms.)
+// Lists whose centres lie on up to this many grid points take blocks of 256
+// points (two levels of tiles): a quarter of the serial work per wavefront,
+// four times the workgroups; wider lists fill the chip with blocks of 1024,
+// which take far lines at fewer nodes.  (500 lines x 6e3 points: 16 us in
+// blocks of 256, 47 in blocks of 1024; 1e5 lines x 4e5 points 0.20 against
+// 0.26 ms; whole steps of 1.2e5 lines x 6e5 points 255 against 248 us, 1.25e5
+// x 1e6 283 / 239, 8 times 1.25e5 lines on an eighth each of 1e6 points 2.8 /
+// 4.0 ms; 1e6 lines x 3e6 points 2.1 / 1.4 ms.)
 constexpr int64_t kSmallGrid = 400000;
 // Entries of a wavefront's list of lines that its sub-tile does not admit.
 constexpr int kNearCap = 768;
@@ -1055,11 +1057,9 @@ __global__ __launch_bounds__(64 * kWaves) void core_f64_kernel(
 }  // namespace
 
 namespace {
-// Points of a wavefront's sub-tile on a grid of n points (see launch_wing_f64).
-int32_t sub_points(int64_t n) { return n <= kSmallGrid ? kLeaf : 4 * kLeaf; }
 }  // namespace
 
-int32_t opacity_f64_tile_points(int64_t n_points) { return kWaves * sub_points(n_points); }
+int32_t opacity_f64_tile_points(int64_t covered) { return kWaves * (covered <= kSmallGrid ? kLeaf : 4 * kLeaf); }
 int32_t core_f64_tile_points() { return kCoreTilePoints; }
 
 // The interpolation matrices of the wing's tiles, from the closed forms of
@@ -1102,8 +1102,8 @@ void wing_tables(WingTables* out)
 
 hipError_t launch_wing_f64(const WingRec* wing, const WingIdx* idx, const int64_t* ranges, int64_t n_lines,
                            int64_t n_tiles, int32_t n_states, const WorkPlan& wp, const WingTables* tab,
-                           double nu_min, double dnu, int32_t n_points, double* kappa, double* partial,
-                           int accumulate, hipStream_t s)
+                           double nu_min, double dnu, int32_t n_points, int32_t tile_points, double* kappa,
+                           double* partial, int accumulate, hipStream_t s)
 {
     if (n_tiles == 0 || n_states == 0) return hipSuccess;
     const int64_t nb = plan_blocks(wp.launch_items);
@@ -1113,8 +1113,7 @@ hipError_t launch_wing_f64(const WingRec* wing, const WingIdx* idx, const int64_
     // finer grids every line is taken point by point
     const double top = std::max(std::fabs(nu_min), std::fabs(nu_min + (double)n_points * dnu));
     const int far_ok = dnu * 281474976710656.0 >= top ? 1 : 0;  // 2^48
-    const int32_t sub = sub_points(n_points);
-    auto kernel = sub == kLeaf ? wing_f64_kernel<kLeaf> : wing_f64_kernel<4 * kLeaf>;
+    auto kernel = tile_points == kWaves * kLeaf ? wing_f64_kernel<kLeaf> : wing_f64_kernel<4 * kLeaf>;
     kernel<<<dim3((unsigned)nb), dim3(64 * kWaves), 0, s>>>(wing, idx, ranges, n_lines, n_tiles, n_states, wp, tab,
                                                             nu_min, dnu, n_points, kappa, partial, accumulate, far_ok);
     return hipGetLastError();
