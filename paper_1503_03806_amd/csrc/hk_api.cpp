@@ -856,6 +856,7 @@ namespace {
 // Thin QR of the m x nc Chebyshev design matrix A[i][c] = T_c(t_i),
 // t_i = 2 (i + 1/2)/m - 1, by Householder reflections (Golub & Van Loan,
 // Alg. 5.2.1): Q row-major [m][nc], R row-major [nc][nc] upper triangular.
+// (For bins of few points; larger ones' factors are made on the device.)
 void chebyshev_qr(int64_t m, int nc, std::vector<double>& Q, std::vector<double>& R)
 {
     std::vector<double> A((size_t)m * nc);
@@ -912,12 +913,21 @@ void chebyshev_qr(int64_t m, int nc, std::vector<double>& Q, std::vector<double>
     }
 }
 
-int upload_qr(hk_ctx* ctx, int64_t m, int nc, DevBuf& dQ, DevBuf& dR)
+int make_qr(hk_ctx* ctx, int64_t m, int nc, DevBuf& dQ, DevBuf& dR)
 {
+    HK_HIP(ctx, dQ.ensure((size_t)m * nc * sizeof(double)), "allocating QR factors");
+    HK_HIP(ctx, dR.ensure((size_t)nc * nc * sizeof(double)), "allocating QR factors");
+    if (m >= design_factor_min_rows()) {
+        HK_HIP(ctx, ctx->rs_part.ensure(design_factor_scratch_bytes()), "allocating QR scratch");
+        HK_HIP(ctx, launch_design_factors(m, nc, static_cast<double*>(dQ.p), static_cast<double*>(dR.p), ctx->rs_part.p,
+                                          ctx->stream),
+               "design_factors");
+        // (a later call may use them on another stream)
+        HK_HIP(ctx, hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
+        return HK_OK;
+    }
     std::vector<double> Q, R;
     chebyshev_qr(m, nc, Q, R);
-    HK_HIP(ctx, dQ.ensure(Q.size() * sizeof(double)), "allocating QR factors");
-    HK_HIP(ctx, dR.ensure(R.size() * sizeof(double)), "allocating QR factors");
     HK_HIP(ctx, hipMemcpy(dQ.p, Q.data(), Q.size() * sizeof(double), hipMemcpyHostToDevice), "copying QR factors");
     HK_HIP(ctx, hipMemcpy(dR.p, R.data(), R.size() * sizeof(double), hipMemcpyHostToDevice), "copying QR factors");
     return HK_OK;
@@ -2285,7 +2295,8 @@ int hk_resample(hk_ctx* ctx, const void* sorted, int precision, int64_t n_points
     const int64_t m = std::min(points_per_bin, n_points);
     if (ctx->rs_m != m || ctx->rs_nc != n_coef) {
         HK_HIP(ctx, hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
-        if (int rc = upload_qr(ctx, m, n_coef, ctx->rs_Q, ctx->rs_R)) return rc;
+        ctx->rs_m = ctx->rs_ml = -1;
+        if (int rc = make_qr(ctx, m, n_coef, ctx->rs_Q, ctx->rs_R)) return rc;
         ctx->rs_m = m;
         ctx->rs_ml = -1;
         ctx->rs_nc = n_coef;
@@ -2293,7 +2304,8 @@ int hk_resample(hk_ctx* ctx, const void* sorted, int precision, int64_t n_points
     const bool ragged = n_points > points_per_bin && ml > 0;
     if (ragged && ctx->rs_ml != ml) {
         HK_HIP(ctx, hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
-        if (int rc = upload_qr(ctx, ml, n_coef, ctx->rs_Ql, ctx->rs_Rl)) return rc;
+        ctx->rs_ml = -1;
+        if (int rc = make_qr(ctx, ml, n_coef, ctx->rs_Ql, ctx->rs_Rl)) return rc;
         ctx->rs_ml = ml;
     }
     const double* Ql = ragged ? static_cast<const double*>(ctx->rs_Ql.p) : static_cast<const double*>(ctx->rs_Q.p);

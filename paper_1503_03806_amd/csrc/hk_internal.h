@@ -477,6 +477,11 @@ hipError_t launch_surrogate_certify(const void* P, double* err, hipStream_t s);
 constexpr int kMaxCoef = 32;   // Chebyshev coefficients per bin
 constexpr int kMaxQuad = 128;  // quadrature nodes of the fitted transmission
 // part: resample_scratch_bytes of device memory (0: none needed).
+// launch_design_factors makes Q and R of bins of m >= design_factor_min_rows()
+// points (scratch: design_factor_scratch_bytes()).
+int64_t design_factor_min_rows();
+size_t design_factor_scratch_bytes();
+hipError_t launch_design_factors(int64_t m, int nc, double* Q, double* R, void* scratch, hipStream_t s);
 size_t resample_scratch_bytes(int64_t n_points, int64_t ppb);
 hipError_t launch_resample(const void* sorted, int key_bytes, int64_t n_points, int64_t ppb, int nc,
                            const double* Q, const double* R, const double* Ql, const double* Rl, double* part,
