@@ -65,22 +65,24 @@ def kernel_digest() -> str:
     return h.hexdigest()[:16]
 
 
-def measured_traffic():
-    """HBM bytes per launch of the dominant kernel (fetch + write) from the
-    committed counter summary, or None if the kernel's sources changed since
-    the counters were taken."""
+def measured_counters() -> dict:
+    """Per launch, from the committed counter summary: the dominant kernel's
+    HBM bytes (fetch + write) and its and the series' executed binary64
+    operations.  Empty if the kernels' sources changed since the counters
+    were taken."""
     try:
         kv = dict(line.split(":", 1) for line in open(TRAFFIC_FILE)
                   if ":" in line and not line.startswith("#"))
     except OSError:
-        return None
+        return {}
     kv = {k.strip(): v.strip() for k, v in kv.items()}
     if kv.get("kernel_sources_sha256_16") != kernel_digest():
-        return None
+        return {}
     try:
-        return int(kv["fetch_bytes_per_launch"]) + int(kv["write_bytes_per_launch"])
+        return {"traffic": int(kv["fetch_bytes_per_launch"]) + int(kv["write_bytes_per_launch"]),
+                "wing_flops": int(kv["wing_flops_per_launch"]), "core_flops": int(kv["core_flops_per_launch"])}
     except (KeyError, ValueError):
-        return None
+        return {}
 
 
 def synth_conditions(T, P):
@@ -485,13 +487,21 @@ def main(argv=None):
     ms_step = 1e3 * elapsed / a.steps
     # the dominant kernel: the Gauss-Hermite wing kernel (stage "opacity")
     op_ms = tm["opacity"][0] / max(tm["opacity"][1], 1)
-    flops = FLOPS_PER_EVAL["gh1"] * st["evals_gh1"] + FLOPS_PER_EVAL["gh3"] * st["evals_gh3"]
-    achieved = flops / (op_ms * 1e-3) / 1e12
-    step_flops = flops + FLOPS_PER_EVAL["core"] * st["evals_core"]
+    # The wing evaluates most lines at a few nodes of a tile of points, not at
+    # every point, so the line-point work it stands for (line_point_flops)
+    # exceeds what any kernel executes; the roofline takes the operations the
+    # counters saw.
+    line_point_flops = FLOPS_PER_EVAL["gh1"] * st["evals_gh1"] + FLOPS_PER_EVAL["gh3"] * st["evals_gh3"]
+    counted = measured_counters()
+    default_work = w.name == WORKLOAD  # that of the counters
+    flops = counted.get("wing_flops") if default_work else None
+    achieved = flops / (op_ms * 1e-3) / 1e12 if flops else None
+    step_flops = flops + counted["core_flops"] if flops else None
+    step_rate = step_flops / (ms_step * 1e-3) / 1e12 if flops else None
     # the wing's algorithmic bytes: each line record (64 B) read once, each
     # grid value (8 B) written once
     alg_bytes = 64 * len(lines["nu"]) + 8 * N
-    traffic = measured_traffic()
+    traffic = counted.get("traffic") if default_work else None
     rec = {
         "metric": "Voigt line-point evals/s (opacity + k(g) wall time per step in ms_per_step)",
         "value": evals * a.steps / elapsed,
@@ -511,16 +521,19 @@ def main(argv=None):
                       "on two streams and overlap; 'line_prep' includes tile ranges and work plans",
         "roofline": {"bound": "alu", "kernel": DOMINANT_KERNEL,
                      "achieved": achieved, "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
-                     "frac": achieved / PEAK_FP64_TFLOPS, "traffic": traffic,
+                     "frac": achieved / PEAK_FP64_TFLOPS if flops else None, "traffic": traffic,
                      "flops_per_launch": flops, "launch_ms": op_ms,
-                     "flops_per_eval": FLOPS_PER_EVAL,
+                     "flops_note": "binary64 operations executed, from the committed counters",
+                     "line_point_flops": line_point_flops, "flops_per_eval": FLOPS_PER_EVAL,
+                     "line_point_note": "the work of every line at every point of its window; the kernel takes "
+                                        "far lines at the Chebyshev nodes of tiles instead",
                      "algorithmic_bytes": alg_bytes,
                      "traffic_over_algorithmic": (traffic / alg_bytes) if traffic else None,
                      "concurrent_with": "core_f64_kernel on a second stream (launch_ms includes "
                                         "the time the two share the device)",
-                     "step": {"flops": step_flops, "achieved": step_flops / (ms_step * 1e-3) / 1e12,
-                              "frac": step_flops / (ms_step * 1e-3) / 1e12 / PEAK_FP64_TFLOPS,
-                              "what": "wing + series algorithmic work over the whole step's wall time"}},
+                     "step": {"flops": step_flops, "achieved": step_rate,
+                              "frac": step_rate / PEAK_FP64_TFLOPS if flops else None,
+                              "what": "wing + series operations executed over the whole step's wall time"}},
     }
     if f32_tm is not None:
         f32_steps = max(1, a.steps // 2)

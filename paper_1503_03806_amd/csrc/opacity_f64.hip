@@ -80,9 +80,9 @@ __device__ inline double qrcp(double den)
 //
 // Bound: VALU (binary64; 85% of its cycles busy).  On 1e6 lines x 3e6 points
 // with 2e4 points per window a line costs ~1000 node evaluations and ~500
-// point evaluations in place of 2e4, and the kernel alone takes 1.26 ms
+// point evaluations in place of 2e4, and the kernel alone takes 1.22 ms
 // against 6.9 ms with every line at every point; 3e6 lines x 1e6 points with
-// 5e3 points per window 2.8 against 9.7 ms, 1e5 lines x 4e5 points 0.17
+// 5e3 points per window 2.6 against 9.7 ms, 1e5 lines x 4e5 points 0.16
 // against 0.49 ms.
 constexpr int kFarNodes = kWingNodes;  // 24
 constexpr int kFarRatio = 3;
