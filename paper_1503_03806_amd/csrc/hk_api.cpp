@@ -128,6 +128,7 @@ struct hk_ctx {
                ev_cwing[2] = {nullptr, nullptr}, ev_kappa = nullptr;
     DevBuf partial;  // evaluation counters of hk_stats
     DevBuf kscratch;
+    DevBuf check_part;    // of a list in device memory
     DevBuf line_scratch;  // the last unordered list's sort, up to kKeepSortScratch
     bool have_run = false;
     int f64_points_per_lane = 4;  // tile shape of the binary64 opacity kernel (4 or 8)
@@ -1023,6 +1024,7 @@ int hk_destroy(hk_ctx* ctx)
     ctx->partial.release();
     ctx->kscratch.release();
     ctx->line_scratch.release();
+    ctx->check_part.release();
     ctx->wing_tab.release();
     for (DevBuf* b : {&ctx->tb_idx, &ctx->tb_wing, &ctx->tb_core, &ctx->tb_w32, &ctx->tb_c32, &ctx->tb_ranges,
                       &ctx->tb_ranges_c, &ctx->tb_out, &ctx->tb_comp, &ctx->tb_scale, &ctx->tb_kappa,
@@ -1103,28 +1105,13 @@ int check_lines_device(hk_ctx* ctx, const hk_lines* L, ListInfo* li, bool* sorte
     D.A21 = L->A21;
     D.n = n;
     const int32_t nb = check_lines_blocks(n);
-    DevBuf part;
-    std::vector<CheckPart> h((size_t)nb);
-    hipError_t e = part.ensure((size_t)nb * sizeof(CheckPart));
-    if (e == hipSuccess) e = launch_check_lines(D, part.p, ctx->stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(h.data(), part.p, h.size() * sizeof(CheckPart), hipMemcpyDeviceToHost, ctx->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-    part.release();
-    if (e != hipSuccess) return hip_fail(ctx, e, "checking the line list on the device");
-    CheckPart c = h[0];
-    for (const CheckPart& b : h) {
-        c.first_bad = std::min(c.first_bad, b.first_bad);
-        c.first_unordered = std::min(c.first_unordered, b.first_unordered);
-        c.max_abs_delta = std::max(c.max_abs_delta, b.max_abs_delta);
-        c.max_gamma_air = std::max(c.max_gamma_air, b.max_gamma_air);
-        c.max_gamma_self = std::max(c.max_gamma_self, b.max_gamma_self);
-        c.max_A21 = std::max(c.max_A21, b.max_A21);
-        c.min_n_air = std::min(c.min_n_air, b.min_n_air);
-        c.max_n_air = std::max(c.max_n_air, b.max_n_air);
-        c.nu_max = std::max(c.nu_max, b.nu_max);
-        c.nu_low = std::min(c.nu_low, b.nu_low);
-    }
+    CheckPart c;
+    HK_HIP(ctx, ctx->check_part.ensure((size_t)(nb + 1) * sizeof(CheckPart)), "allocating the list's check");
+    HK_HIP(ctx, launch_check_lines(D, ctx->check_part.p, ctx->stream), "checking the line list on the device");
+    HK_HIP(ctx, hipMemcpyAsync(&c, static_cast<CheckPart*>(ctx->check_part.p) + nb, sizeof c, hipMemcpyDeviceToHost,
+                               ctx->stream),
+           "reading the list's check");
+    HK_HIP(ctx, hipStreamSynchronize(ctx->stream), "checking the line list on the device");
     if (c.first_bad < n) {  // read that line back for the message
         const int64_t i = c.first_bad;
         double v[8] = {0, 0, 0, 0, 0, 0, 0, 0};

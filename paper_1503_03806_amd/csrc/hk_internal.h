@@ -422,7 +422,7 @@ struct GatherFields {
 };
 // dst[k][i] = src[k][perm[i]], k < f.n
 hipError_t launch_gather(const GatherFields& f, const uint32_t* perm, int64_t n, hipStream_t s);
-int32_t check_lines_blocks(int64_t n);  // CheckPart results launch_check_lines writes
+int32_t check_lines_blocks(int64_t n);  // launch_check_lines writes as many CheckParts, then their total
 hipError_t launch_check_lines(const LinesDev& L, void* part, hipStream_t s);
 
 // total[0] = (add ? total[0] : 0) + used[0] + ... + used[n-1]

@@ -78,7 +78,7 @@ __device__ inline double qrcp(double den)
 // two such terms over Gamma_L, which costs a factor up to ~1.5 N: below
 // 4e-17 of each line's value in every case.
 //
-// Bound: VALU (binary64; 85% of its cycles busy).  On 1e6 lines x 3e6 points
+// Bound: VALU (binary64; 81% of its cycles busy).  On 1e6 lines x 3e6 points
 // with 2e4 points per window a line costs ~1000 node evaluations and ~500
 // point evaluations in place of 2e4, and the kernel alone takes 1.22 ms
 // against 6.9 ms with every line at every point; 3e6 lines x 1e6 points with
