@@ -346,7 +346,10 @@ int hk_tables(hk_ctx* ctx, const hk_state* states, int32_t n_states, const hk_gr
  *            (double for HK_F64, float for HK_F32_KAHAN keys)
  *   coef_out [device] double [n_bins][n_coef]
  * Values <= 0 are clamped to the smallest positive normal double before
- * the logarithm.  Every bin needs at least n_coef points (HK_EINVAL). */
+ * the logarithm.  Every bin needs at least n_coef points (HK_EINVAL).
+ * Partial products go through scratch of the context; calls on different
+ * streams wait for each other's use of it.  While the stream is captured into
+ * a graph no scratch is used: a workgroup per bin, slower, equal to rounding. */
 int hk_resample(hk_ctx* ctx, const void* sorted, int precision, int64_t n_points,
                 int64_t points_per_bin, int32_t n_coef, double* coef_out);
 
@@ -359,7 +362,9 @@ int hk_transmission(hk_ctx* ctx, const double* coef, int64_t n_bins, int32_t n_c
                     const double* m_col, int32_t n_m, double* T_out);
 
 /* The same from the sorted values themselves: T(m) = (1/M) sum_i
- * exp(-kappa_i m) per bin (the reference for the resampling error). */
+ * exp(-kappa_i m) per bin (the reference for the resampling error).  Few bins
+ * are summed in segments, through scratch as in hk_resample; while the stream
+ * is captured in one segment each, equal to rounding. */
 int hk_transmission_direct(hk_ctx* ctx, const void* sorted, int precision, int64_t n_points,
                            int64_t points_per_bin, const double* m_col, int32_t n_m, double* T_out);
 

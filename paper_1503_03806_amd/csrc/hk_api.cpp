@@ -45,6 +45,47 @@ struct DevBuf {
     }
 };
 
+// Scratch of calls that a program may issue on different streams with no order
+// between them: the stream of each use first waits for the use before it (by
+// an event, which stays valid when the stream it was recorded on is gone).
+struct StreamScratch {
+    DevBuf buf;
+    hipEvent_t used = nullptr;  // after the last use
+    bool recorded = false;
+    void release()
+    {
+        buf.release();
+        if (used) (void)hipEventDestroy(used);
+        used = nullptr;
+        recorded = false;
+    }
+    // `bytes` of it, for work enqueued on s until end()
+    hipError_t begin(size_t bytes, hipStream_t s)
+    {
+        hipError_t e = hipSuccess;
+        if (!used) e = hipEventCreateWithFlags(&used, hipEventDisableTiming);
+        if (e == hipSuccess && recorded)
+            e = bytes > buf.cap ? hipEventSynchronize(used) : hipStreamWaitEvent(s, used, 0);
+        return e == hipSuccess ? buf.ensure(bytes) : e;
+    }
+    hipError_t end(hipStream_t s)
+    {
+        recorded = true;
+        return hipEventRecord(used, s);
+    }
+};
+
+// Whether s is being captured into a graph.  A graph may be replayed at any
+// later time and on any stream, so calls under capture take no scratch of the
+// context.
+bool is_capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
+}
+
 // What the launches need to know of a line list besides its values: which
 // optional fields it has, and bounds that size the tile ranges.
 struct ListInfo {
@@ -161,7 +202,8 @@ struct hk_ctx {
     double sg_budget = 0.0;  // of the current certification
     // resampling: QR factors of the Chebyshev design matrix for the bin
     // sizes of the last call (main and ragged last bin), and the quadrature
-    DevBuf rs_Q, rs_R, rs_Ql, rs_Rl, rs_quad, rs_part;
+    DevBuf rs_Q, rs_R, rs_Ql, rs_Rl, rs_quad;
+    StreamScratch rs_part, td_part;  // partial products of the fit, segment sums of the direct transmission
     int64_t rs_m = -1, rs_ml = -1;
     int rs_nc = 0;
     bool rs_quad_ready = false;
@@ -919,10 +961,11 @@ int make_qr(hk_ctx* ctx, int64_t m, int nc, DevBuf& dQ, DevBuf& dR)
     HK_HIP(ctx, dQ.ensure((size_t)m * nc * sizeof(double)), "allocating QR factors");
     HK_HIP(ctx, dR.ensure((size_t)nc * nc * sizeof(double)), "allocating QR factors");
     if (m >= design_factor_min_rows()) {
-        HK_HIP(ctx, ctx->rs_part.ensure(design_factor_scratch_bytes()), "allocating QR scratch");
-        HK_HIP(ctx, launch_design_factors(m, nc, static_cast<double*>(dQ.p), static_cast<double*>(dR.p), ctx->rs_part.p,
-                                          ctx->stream),
+        HK_HIP(ctx, ctx->rs_part.begin(design_factor_scratch_bytes(), ctx->stream), "allocating QR scratch");
+        HK_HIP(ctx, launch_design_factors(m, nc, static_cast<double*>(dQ.p), static_cast<double*>(dR.p),
+                                          ctx->rs_part.buf.p, ctx->stream),
                "design_factors");
+        HK_HIP(ctx, ctx->rs_part.end(ctx->stream), "hipEventRecord");
         // (a later call may use them on another stream)
         HK_HIP(ctx, hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
         return HK_OK;
@@ -1032,8 +1075,10 @@ int hk_destroy(hk_ctx* ctx)
         b->release();
     for (DevBuf* b : {&ctx->sg_theta, &ctx->sg_m, &ctx->sg_v, &ctx->sg_copy, &ctx->sg_part, &ctx->sg_ploss,
                       &ctx->sg_err, &ctx->sg_mask, &ctx->sg_used_total, &ctx->rs_Q, &ctx->rs_R, &ctx->rs_Ql, &ctx->rs_Rl,
-                      &ctx->rs_quad, &ctx->rs_part})
+                      &ctx->rs_quad})
         b->release();
+    ctx->rs_part.release();
+    ctx->td_part.release();
     for (auto& p : ctx->pending) {
         (void)hipEventDestroy(p.second.first);
         (void)hipEventDestroy(p.second.second);
@@ -2297,12 +2342,13 @@ int hk_resample(hk_ctx* ctx, const void* sorted, int precision, int64_t n_points
     }
     const double* Ql = ragged ? static_cast<const double*>(ctx->rs_Ql.p) : static_cast<const double*>(ctx->rs_Q.p);
     const double* Rl = ragged ? static_cast<const double*>(ctx->rs_Rl.p) : static_cast<const double*>(ctx->rs_R.p);
-    HK_HIP(ctx, ctx->rs_part.ensure(std::max<size_t>(resample_scratch_bytes(n_points, points_per_bin), 8)),
-           "allocating partial products");
+    const size_t sb = is_capturing(ctx->stream) ? 0 : resample_scratch_bytes(n_points, points_per_bin);
+    if (sb) HK_HIP(ctx, ctx->rs_part.begin(sb, ctx->stream), "allocating partial products");
     HK_HIP(ctx, launch_resample(sorted, precision == HK_F64 ? 8 : 4, n_points, points_per_bin, n_coef,
                                 static_cast<const double*>(ctx->rs_Q.p), static_cast<const double*>(ctx->rs_R.p), Ql,
-                                Rl, static_cast<double*>(ctx->rs_part.p), coef_out, ctx->stream),
+                                Rl, sb ? static_cast<double*>(ctx->rs_part.buf.p) : nullptr, coef_out, ctx->stream),
            "resample");
+    if (sb) HK_HIP(ctx, ctx->rs_part.end(ctx->stream), "hipEventRecord");
     return HK_OK;
 }
 
@@ -2345,12 +2391,14 @@ int hk_transmission_direct(hk_ctx* ctx, const void* sorted, int precision, int64
     if (int rc = check_ctx(ctx)) return rc;
     if (n_points == 0 || n_m == 0) return HK_OK;
     HK_HIP(ctx, hipSetDevice(ctx->device), "hipSetDevice");
-    HK_HIP(ctx, ctx->rs_part.ensure(
-                    std::max<size_t>(transmission_direct_scratch_bytes(n_points, points_per_bin, n_m), 8)),
-           "allocating partial sums");
+    const size_t sb =
+        is_capturing(ctx->stream) ? 0 : transmission_direct_scratch_bytes(n_points, points_per_bin, n_m);
+    if (sb) HK_HIP(ctx, ctx->td_part.begin(sb, ctx->stream), "allocating partial sums");
     HK_HIP(ctx, launch_transmission_direct(sorted, precision == HK_F64 ? 8 : 4, n_points, points_per_bin, m_col, n_m,
-                                           static_cast<double*>(ctx->rs_part.p), T_out, ctx->stream),
+                                           sb ? static_cast<double*>(ctx->td_part.buf.p) : nullptr, T_out,
+                                           ctx->stream),
            "transmission_direct");
+    if (sb) HK_HIP(ctx, ctx->td_part.end(ctx->stream), "hipEventRecord");
     return HK_OK;
 }
 

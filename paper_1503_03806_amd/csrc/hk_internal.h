@@ -476,7 +476,8 @@ hipError_t launch_surrogate_certify(const void* P, double* err, hipStream_t s);
 // Resampling and transmission (resample.hip).
 constexpr int kMaxCoef = 32;   // Chebyshev coefficients per bin
 constexpr int kMaxQuad = 128;  // quadrature nodes of the fitted transmission
-// part: resample_scratch_bytes of device memory (0: none needed).
+// part: resample_scratch_bytes of device memory (0: none needed), or NULL for
+// a workgroup per bin, which needs none.
 // launch_design_factors makes Q and R of bins of m >= design_factor_min_rows()
 // points (scratch: design_factor_scratch_bytes()).
 int64_t design_factor_min_rows();
@@ -489,7 +490,7 @@ hipError_t launch_resample(const void* sorted, int key_bytes, int64_t n_points, 
 hipError_t launch_transmission_fit(const double* coef, int64_t n_bins, int nc, const double* yq, const double* wq,
                                    int nq, const double* m, int n_m, double* T, hipStream_t s);
 // part: transmission_direct_scratch_bytes of device memory (0: none needed;
-// below 1 MiB).
+// below 1 MiB), or NULL for bins in one segment each, which need none.
 size_t transmission_direct_scratch_bytes(int64_t n_points, int64_t ppb, int n_m);
 hipError_t launch_transmission_direct(const void* sorted, int key_bytes, int64_t n_points, int64_t ppb,
                                       const double* m, int n_m, double* part, double* T, hipStream_t s);

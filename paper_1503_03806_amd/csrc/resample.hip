@@ -21,8 +21,9 @@ constexpr int kThreads = 256;
 __device__ inline double key_to_double(const double* s, int64_t i) { return s[i]; }
 __device__ inline double key_to_double(const float* s, int64_t i) { return (double)s[i]; }
 
-// Bins of few points, one workgroup per bin.  Q: row-major [M][nc]; R: row-major [nc][nc],
-// upper triangular.  The last bin may use its own factors (Ql, Rl, ml).
+// Bins of few points, and calls without scratch: one workgroup per bin.  Q:
+// row-major [M][nc]; R: row-major [nc][nc], upper triangular.  The last bin may
+// use its own factors (Ql, Rl, ml).
 template <typename K>
 __global__ __launch_bounds__(kThreads) void resample_kernel(const K* __restrict__ sorted, int64_t n_points,
                                                             int64_t ppb, int nc, const double* __restrict__ Q,
@@ -529,7 +530,7 @@ hipError_t run_resample(const K* sorted, int64_t n_points, int64_t ppb, int nc, 
 {
     const int64_t n_bins = (n_points + ppb - 1) / ppb;
     const int64_t m = std::min(ppb, n_points), last = n_points - (n_bins - 1) * ppb;
-    if (!resample_scratch_bytes(n_points, ppb)) {
+    if (!part || !resample_scratch_bytes(n_points, ppb)) {
         resample_kernel<K><<<dim3((unsigned)n_bins), dim3(kThreads), 0, s>>>(sorted, n_points, ppb, nc, Q, R, Ql, Rl,
                                                                              coef);
         return hipGetLastError();
@@ -613,7 +614,7 @@ hipError_t launch_transmission_direct(const void* sorted, int key_bytes, int64_t
 {
     const int64_t n_bins = (n_points + ppb - 1) / ppb;
     if (n_bins == 0 || n_m == 0) return hipSuccess;
-    const int segs = direct_segments(n_points, ppb, n_m);
+    const int segs = part ? direct_segments(n_points, ppb, n_m) : 1;
     const dim3 grid((unsigned)n_bins, (unsigned)((n_m + 63) / 64), (unsigned)segs);
     if (key_bytes == 8)
         transmission_direct_kernel<double><<<grid, dim3(64 * kDirectWaves), 0, s>>>(
