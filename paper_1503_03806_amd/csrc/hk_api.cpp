@@ -2326,7 +2326,8 @@ int hk_resample(hk_ctx* ctx, const void* sorted, int precision, int64_t n_points
     HK_HIP(ctx, hipSetDevice(ctx->device), "hipSetDevice");
     const int64_t m = std::min(points_per_bin, n_points);
     if (ctx->rs_m != m || ctx->rs_nc != n_coef) {
-        HK_HIP(ctx, hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
+        // (fits in flight on any stream read the factors that are replaced)
+        HK_HIP(ctx, hipDeviceSynchronize(), "hipDeviceSynchronize");
         ctx->rs_m = ctx->rs_ml = -1;
         if (int rc = make_qr(ctx, m, n_coef, ctx->rs_Q, ctx->rs_R)) return rc;
         ctx->rs_m = m;
@@ -2335,7 +2336,7 @@ int hk_resample(hk_ctx* ctx, const void* sorted, int precision, int64_t n_points
     }
     const bool ragged = n_points > points_per_bin && ml > 0;
     if (ragged && ctx->rs_ml != ml) {
-        HK_HIP(ctx, hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
+        HK_HIP(ctx, hipDeviceSynchronize(), "hipDeviceSynchronize");
         ctx->rs_ml = -1;
         if (int rc = make_qr(ctx, ml, n_coef, ctx->rs_Ql, ctx->rs_Rl)) return rc;
         ctx->rs_ml = ml;

@@ -61,6 +61,28 @@ def test_calls_on_two_streams(ctx, first, second):
         assert torch.equal(g, alone[i % 2]), i
 
 
+@pytest.mark.parametrize("default_first", [True, False])
+def test_fits_of_two_sizes_on_two_streams(ctx, default_first):
+    """A bin size of its own has factors of its own: making them must not
+    disturb a fit that is still reading the others'."""
+    size = [20000, 9000]
+    k = [bins(200, 5, size[0]), bins(300, 6, size[1])]
+    ctx.use_current_stream()
+    alone = [ctx.resample(k[x], size[x], 20) for x in range(2)]
+    s = [torch.cuda.default_stream() if default_first else torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    got = []
+    for _ in range(10):
+        for x in range(2):
+            with torch.cuda.stream(s[x]):
+                ctx.use_current_stream()
+                got.append(ctx.resample(k[x], size[x], 20))
+    torch.cuda.synchronize()
+    ctx.use_current_stream()
+    for i, g in enumerate(got):
+        assert torch.equal(g, alone[i % 2]), i
+
+
 def close(kind, a, b):
     if kind == "fit":
         return bool(((a - b).abs() <= 1e-9 * b.abs().amax(dim=1, keepdim=True)).all())
