@@ -72,6 +72,7 @@ constexpr int32_t kGroupSafe = 1;
 // The flags' other bits: the slack of a line's poles in whole grid points,
 // sqrt(3/2) alpha / dnu rounded up, plus one for the rounding of jc.
 constexpr int kSlackShift = 1;
+constexpr double kMaxSlack = 268435456.0;  // (wider lines: series points, or a Lorentz width, far beyond a tile)
 
 // Per-line record of the core-region series, read only for lines whose
 // a^2+u^2 < 100 interval meets a wavefront's points.

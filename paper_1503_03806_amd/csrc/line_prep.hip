@@ -4,6 +4,7 @@
 // evaluation counts by region.
 #include <algorithm>
 
+#include "hk.h"
 #include "hk_internal.h"
 
 #include <climits>
@@ -115,10 +116,17 @@ __device__ __forceinline__ double line_peak(const LineScaled& ls)
     return fmin(doppler, lorentz);
 }
 
-// The grid point nearest to a line centre, clamped to int32 range.
+// The grid point nearest to a line centre.  Centres off the grid are clamped
+// where no tile is near them and differences with grid indexes fit int32: the
+// true point for every centre on the largest grid, and beyond it by more than
+// any distance that the wing's tiles admit lines from (kMaxSlack).
+constexpr double kLowestPoint = -1.0e9, kHighestPoint = 1.6e9;
+static_assert(kHighestPoint - (double)HK_MAX_POINTS > kMaxSlack + 4096.0 && -kLowestPoint > kMaxSlack + 4096.0 &&
+                  (double)HK_MAX_POINTS + 4096.0 - kLowestPoint < 2147483647.0,
+              "the centre's index decides which tiles are far from it");
 __device__ inline int32_t nearest_point(double nu0, double nu_min, double dnu)
 {
-    return (int32_t)fmin(fmax(rint((nu0 - nu_min) / dnu), -1.0e9), 1.0e9);
+    return (int32_t)fmin(fmax(rint((nu0 - nu_min) / dnu), kLowestPoint), kHighestPoint);
 }
 
 // What the wing's records of both precisions are made of.
@@ -141,7 +149,7 @@ __device__ __forceinline__ void line_prep_vals(const LinesDev& L, const PrepPara
     {
         const double span = fmax(fabs(nu0 - pp.nu_min), fabs(fma((double)(n - 1), pp.dnu, pp.nu_min) - nu0));
         const bool safe = alpha * alpha >= 1e-22 && fma(span, span, w.G2) <= 1e20;
-        const double slack = fmin(ceil(1.2247448713915890 * alpha / pp.dnu) + 1.0, 268435456.0);
+        const double slack = fmin(ceil(1.2247448713915890 * alpha / pp.dnu) + 1.0, kMaxSlack);
         x.flags = ((int32_t)slack << kSlackShift) | (safe ? kGroupSafe : 0);
     }
     {
