@@ -67,7 +67,10 @@ static_assert(sizeof(WingIdx) == 32, "WingIdx layout");
 // Products of four denominators stay in binary64 range: alpha^2 >= 1e-22 and
 // dv^2 + Gamma_L^2 <= 1e20 at every grid point (every physical line and
 // grid) put each 3-node denominator m = D P within about 1e-60 .. 1e60 (D >=
-// 100 alpha^2 outside the core region).  Otherwise points are not grouped.
+// 100 alpha^2 outside the core region), and with Lg <= 1e60 (infinite or NaN
+// where S(T) is out of range) the group's quotients are finite, so that a point
+// that takes nothing adds 0.  Otherwise points are not grouped, and no tile
+// takes the line at its nodes.
 constexpr int32_t kGroupSafe = 1;
 // The flags' other bits: the slack of a line's poles in whole grid points,
 // sqrt(3/2) alpha / dnu rounded up, plus one for the rounding of jc.

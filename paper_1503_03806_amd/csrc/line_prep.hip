@@ -148,7 +148,7 @@ __device__ __forceinline__ void line_prep_vals(const LinesDev& L, const PrepPara
     const int32_t n = pp.n_points;
     {
         const double span = fmax(fabs(nu0 - pp.nu_min), fabs(fma((double)(n - 1), pp.dnu, pp.nu_min) - nu0));
-        const bool safe = alpha * alpha >= 1e-22 && fma(span, span, w.G2) <= 1e20;
+        const bool safe = alpha * alpha >= 1e-22 && fma(span, span, w.G2) <= 1e20 && w.Lg <= 1e60;
         const double slack = fmin(ceil(1.2247448713915890 * alpha / pp.dnu) + 1.0, kMaxSlack);
         x.flags = ((int32_t)slack << kSlackShift) | (safe ? kGroupSafe : 0);
     }

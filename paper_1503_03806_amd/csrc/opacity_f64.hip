@@ -32,14 +32,15 @@ constexpr int kTermStride = kMaxTerms + 2;  // between tables in LDS (other bank
 static_assert(kMaxTerms <= 64, "one lane per series term builds the tables");
 
 // num / den to about 2^-48 relative: the hardware reciprocal (relative
-// error below 2^-24 on gfx950) and one Newton correction of the quotient.
-// Callers discard the result (by select) wherever den may be 0.
+// error below 2^-24 on gfx950) and one Newton correction of the quotient,
+// which is none where num is infinite.  Callers discard the result (by select)
+// wherever den may be 0.
 __device__ inline double qdiv(double num, double den)
 {
     const double r = __builtin_amdgcn_rcp(den);
     const double q = num * r;
     const double e = fma(-den, q, num);
-    return fma(e, r, q);
+    return e == e ? fma(e, r, q) : q;
 }
 
 // 1 / den to about 2^-48 relative (one Newton step on the reciprocal).
