@@ -180,8 +180,8 @@ __device__ __forceinline__ void far_eval(double (&acc)[kFarNodes], double dvc, d
             gh3_nm(fma(t, h, dvc), X, a2, cc, p, r, nn[e], mm[e]);
         }
         const double P01 = mm[0] * mm[1], P23 = mm[2] * mm[3];
-        const double c = qrcp3(P01 * P23) * Lg;
-        const double c01 = c * P23, c23 = c * P01;
+        const double c = qrcp3(P01 * P23);
+        const double c01 = (c * P23) * Lg, c23 = (c * P01) * Lg;
         acc[2 * g] = fma(c01 * mm[1], nn[0], acc[2 * g]);
         acc[2 * g + 1] = fma(c01 * mm[0], nn[1], acc[2 * g + 1]);
         acc[23 - 2 * g] = fma(c23 * mm[3], nn[2], acc[23 - 2 * g]);

@@ -1,7 +1,7 @@
 """Line strengths at the ends of binary64's range in the binary64 opacity: a
 line whose strength overflows (or is NaN) at the state makes the points of its
-own window infinite (or NaN) and changes no other.  Every point against the
-oracle.
+own window infinite (or NaN) and changes no other; lists so weak that kappa lies
+near 1e-285 keep their precision.  Every point against the oracle.
 
 Tolerance: as for the wing's nodes elsewhere, 400 * 2^-53 of each (positive)
 term on both sides together: 1e-13.  The grids are dyadic."""
@@ -52,4 +52,16 @@ def test_one_line_out_of_range(n_lines, special):
     lines["S_ref"][at], lines["E_lower"][at] = {"inf": (1e300, 0.0), "nan": (0.0, -1e8), "1e200": (1e188, 0.0)}[special]
     got, ref = both(lines, cond, dict(GRID, cutoff=2.0 if special == "nan" else 9.0))
     assert special == "1e200" or 0 < (~np.isfinite(ref)).sum() < 4000
+    compare(got, ref)
+
+
+@pytest.mark.parametrize("cutoff", [9.0, 25.0])
+@pytest.mark.parametrize("scale", [1e-258, 1e-264])
+def test_weak_lists(cutoff, scale):
+    """Strengths of cold states' highest levels: kappa near 1e-280 and 1e-286."""
+    lines = synth.line_list(2500, 60.0, seed=9)
+    lines["nu"] = lines["nu"] + 1992.0
+    lines["S_ref"] = lines["S_ref"] * scale
+    lines["E_lower"] = np.zeros(2500)
+    got, ref = both(lines, synth.conditions(1500.0, 0.5), dict(GRID, cutoff=cutoff))
     compare(got, ref)
