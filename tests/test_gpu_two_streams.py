@@ -40,14 +40,15 @@ def ctx():
 
 
 @pytest.mark.parametrize("first,second", [("direct", "direct"), ("direct", "fit"), ("fit", "direct"), ("fit", "fit")])
-def test_calls_on_two_streams(ctx, first, second):
+@pytest.mark.parametrize("default_first", [True, False])
+def test_calls_on_two_streams(ctx, first, second, default_first):
     m = [torch.logspace(15, 27, 37, dtype=torch.float64, device="cuda"),
          torch.logspace(18, 24, 40, dtype=torch.float64, device="cuda")]
     k = [bins(3, 1), bins(5, 2)]
     f = [CALLS[first], CALLS[second]]
     ctx.use_current_stream()
     alone = [f[x](ctx, k[x], m[x]) for x in range(2)]  # (also makes the factors)
-    s = [torch.cuda.Stream(), torch.cuda.Stream()]
+    s = [torch.cuda.default_stream() if default_first else torch.cuda.Stream(), torch.cuda.Stream()]
     torch.cuda.synchronize()
     got = []
     for _ in range(20):
