@@ -334,14 +334,14 @@ __global__ __launch_bounds__(kQrThreads) void design_q_kernel(int64_t m, int nc,
 
 // ---- transmission ----
 
-// e^{-t} for t >= 0 (not NaN; beyond 800 it is 0): t = n ln 2 + r, |r| <= ln 2
-// / 2, e^r by the polynomial through the function at Chebyshev nodes (within
-// 2e-17).  ~20 instructions; the library's exp, for any argument, ~40.
+// e^{-t} for 0 <= t <= kExpMost (there 0): t = -n ln 2 - r, |r| <= ln 2 / 2, e^r
+// by the polynomial through the function at Chebyshev nodes (within 2e-17).  18
+// instructions; the library's exp, for any argument, 22.
+constexpr double kExpMost = 800.0;
 __device__ inline double exp_neg(double t)
 {
-    t = fmin(t, 800.0);
-    const double n = rint(t * 1.4426950408889634);
-    const double r = fma(n, 7.371002565167799e-13, fma(n, 0.6931471805592082, -t));
+    const double n = rint(t * -1.4426950408889634);
+    const double r = fma(n, -7.371002565167799e-13, fma(n, -0.6931471805592082, -t));
     double p = fma(2.5110049204818658e-08, r, 2.763265472252779e-07);
     p = fma(p, r, 2.755724088722987e-06);
     p = fma(p, r, 2.4801485441561313e-05);
@@ -353,7 +353,7 @@ __device__ inline double exp_neg(double t)
     p = fma(p, r, 0.5000000000000019);
     p = fma(p, r, 1.0);
     p = fma(p, r, 1.0);
-    return ldexp(p, -(int)n);
+    return ldexp(p, (int)n);
 }
 // e^{-t} is exactly 0 in binary64 above kExpZero and rounds to 1 below
 // kExpOne.
@@ -361,74 +361,141 @@ constexpr double kExpZero = 746.0, kExpOne = 5.5511151231257827e-17;  // 2^-54
 constexpr double kHuge = 1.7976931348623157e308;
 
 // T(m_j) = sum_q w_q exp(-exp(P(t_q)) m_j), P the bin's Chebyshev sum, at the
-// quadrature nodes y_q (t_q = 2 y_q - 1).  Block (bin, chunk of 256 column
-// masses).  Four nodes whose exponentials are all 0, or all 1, for every lane
-// of a wavefront need none of them: on column masses over many decades most are.
-// (300 bins x 1000 masses: 48 us with a workgroup per bin and the library's
-// exp throughout, 34 us.)
-__global__ __launch_bounds__(kThreads) void transmission_fit_kernel(const double* __restrict__ coef, int nc,
-                                                                    const double* __restrict__ yq,
+// quadrature nodes y_q (t_q = 2 y_q - 1).  A wavefront per bin and 64 column
+// masses: the nodes' exp(P) a node per lane, kept in LDS, then a mass per lane.
+// kStep nodes whose exponentials are all 0, or all 1, for every lane need none
+// of them: on column masses over many decades most are. (300 bins x 1000
+// masses: 23 us, 44 with a workgroup per bin and the library's exp throughout;
+// 1e5 bins x 10 masses 415 and 500.)
+constexpr int kStep = 4;
+__global__ __launch_bounds__(kThreads) void transmission_fit_kernel(const double* __restrict__ coef, int64_t n_bins,
+                                                                    int nc, const double* __restrict__ yq,
                                                                     const double* __restrict__ wq, int nq,
                                                                     const double* __restrict__ mcol, int n_m,
                                                                     double* __restrict__ T)
 {
-    __shared__ double kq[kMaxQuad], ws[kMaxQuad];
-    __shared__ double cb[kMaxCoef];
-    const int64_t b = blockIdx.x;
-    for (int k = threadIdx.x; k < nc; k += kThreads) cb[k] = coef[b * nc + k];
-    __syncthreads();
-    bool fine = true;
-    for (int q = threadIdx.x; q < nq; q += kThreads) {
+    __shared__ double2 node[kThreads / 64][kMaxQuad];  // exp(P(t_q)), w_q
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int64_t b = (int64_t)blockIdx.x * (kThreads / 64) + wave;
+    if (b >= n_bins) return;
+    double2* nd = node[wave];
+    const double* c = coef + b * nc;
+    const int j = blockIdx.y * 64 + lane;
+    const double mj = mcol[min(j, n_m - 1)];
+    bool fine = mj >= 0.0 && mj <= kHuge;
+    for (int q = lane; q < nq; q += 64) {
         const double t = 2.0 * yq[q] - 1.0;
-        double tm = 1.0, tc = t, s = cb[0];
-        if (nc > 1) s = fma(cb[1], t, s);
+        double tm = 1.0, tc = t, s = c[0];
+        if (nc > 1) s = fma(c[1], t, s);
         for (int k = 2; k < nc; ++k) {
             const double tn = fma(2.0 * t, tc, -tm);
             tm = tc;
             tc = tn;
-            s = fma(cb[k], tc, s);
+            s = fma(c[k], tc, s);
         }
         const double v = exp(s);
-        kq[q] = v;
-        ws[q] = wq[q];
+        nd[q] = make_double2(v, wq[q]);
         fine = fine && v <= kHuge;  // finite (>= 0, an exponential), not NaN
     }
-    const bool fine_q = __syncthreads_and(fine);
-    const int j = blockIdx.y * kThreads + threadIdx.x;
-    const double mj = j < n_m ? mcol[j] : 0.0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
     double s = 0.0;
-    if (fine_q && !__ballot(!(mj >= 0.0 && mj <= kHuge))) {
+    if (!__ballot(!fine)) {
         int q = 0;
-        for (; q + 4 <= nq; q += 4) {  // four independent chains
-            double t[4], e[4];
+        for (; q + kStep <= nq; q += kStep) {  // independent chains
+            double t[kStep], w[kStep], e[kStep];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) t[u] = kq[q + u] * mj;
-            const double lo = fmin(fmin(t[0], t[1]), fmin(t[2], t[3])), hi = fmax(fmax(t[0], t[1]), fmax(t[2], t[3]));
+            for (int u = 0; u < kStep; ++u) {
+                const double2 n = nd[q + u];
+                t[u] = fmin(n.x * mj, kExpMost);
+                w[u] = n.y;
+            }
+            double lo = t[0], hi = t[0];
+#pragma unroll
+            for (int u = 1; u < kStep; ++u) {
+                lo = fmin(lo, t[u]);
+                hi = fmax(hi, t[u]);
+            }
             if (!__ballot(lo < kExpZero)) continue;
-            const bool one = !__ballot(hi >= kExpOne);
+            if (__ballot(hi >= kExpOne)) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) e[u] = one ? 1.0 : exp_neg(t[u]);
+                for (int u = 0; u < kStep; ++u) e[u] = exp_neg(t[u]);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) s = fma(ws[q + u], e[u], s);
+                for (int u = 0; u < kStep; ++u) s = fma(w[u], e[u], s);
+            } else {
+#pragma unroll
+                for (int u = 0; u < kStep; ++u) s += w[u];
+            }
         }
-        for (; q < nq; ++q) s = fma(ws[q], exp_neg(kq[q] * mj), s);
+        for (; q < nq; ++q) s = fma(nd[q].y, exp_neg(fmin(nd[q].x * mj, kExpMost)), s);
     } else {
-        for (int q = 0; q < nq; ++q) s = fma(ws[q], exp(-kq[q] * mj), s);
+        for (int q = 0; q < nq; ++q) s = fma(nd[q].y, exp(-nd[q].x * mj), s);
     }
     if (j < n_m) T[b * n_m + j] = s;
 }
 
-// T(m_j) = (1/M) sum_i exp(-kappa_i m_j) over a bin's values.  Block (bin, 64
-// column masses, segment of the bin), a mass per lane; its wavefronts take the
-// segment's values 64 at a time in turn, each finding the least and the
-// largest of its 64.  Where those and the wavefront's own least and largest
-// mass put all of the 64 values' exponentials at 0, or at 1, none is
-// evaluated.  The wavefronts' sums are added in LDS in order; with more than
-// one segment (few bins and masses would leave the chip idle) the segments'
-// go to part and are added by transmission_sum_kernel.  Bound: the VALU work
-// of the exponentials left.  (100 bins of 1e4 x 500 masses over 48 decades:
-// 680 us with a mass per thread over the whole bin and the library's exp
-// throughout, 240 us; 3 bins of 2.7e4 x 37 masses 1790 -> 29 us.)
+// T(m_j) = (1/M) sum_i exp(-kappa_i m_j) over a bin's values, by two kernels.
+//
+// Bins of up to kShortBin values, and of up to kMidBin where there are at least
+// 4 m^2 outputs for m values: a thread per bin and mass, over all outputs in
+// turn, so that lanes stay full whatever the counts are.  Bound: the
+// exponentials.  (Against the kernel below, whose wavefronts take 64 values of
+// a bin each: 1e6 bins of 1 x 10 masses 30 / 3700 us, 15625 of 64 x 200 133 /
+// 640, 3000 of 100 x 300 62 / 156, 1560 of 192 x 300 69 / 94, 1170 of 256 x 300
+// 70 / 75.  Fewer outputs leave a thread's chain of m exponentials bare: 656 of
+// 100 x 100 12.6 / 19.3, but 640 of 250 x 106 30 / 19 and 30 of 100 x 100 10.9 /
+// 7.4.  A workgroup of 256 masses per bin, with the library's exp: 620, 171,
+// 104, 108, 112, 16.6, 38 and 8.9 us.)
+constexpr int64_t kShortBin = 64, kMidBin = 256;
+template <typename K>
+__global__ __launch_bounds__(kThreads) void transmission_short_kernel(const K* __restrict__ sorted, int64_t n_points,
+                                                                      int ppb, uint32_t n_out,
+                                                                      const double* __restrict__ mcol, uint32_t n_m,
+                                                                      double* __restrict__ T)
+{
+    const uint32_t o = blockIdx.x * kThreads + threadIdx.x;
+    if (o >= n_out) return;
+    const uint32_t b = o / n_m, j = o - b * n_m;
+    const K* __restrict__ k = sorted + (int64_t)b * ppb;
+    const int m = (int)min((int64_t)ppb, n_points - (int64_t)b * ppb);
+    const double mj = mcol[j];
+    double s = 0.0;
+    int i = 0;
+    for (; i + 4 <= m; i += 4) {  // four independent chains
+        double t[4], c[4], e[4];
+        uint64_t other = 0;  // lanes with a negative t, or NaN
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            t[u] = key_to_double(k, i + u) * mj;
+            c[u] = fmin(t[u], kExpMost);
+            other |= __ballot(!(t[u] >= 0.0));
+        }
+        if (!other) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) e[u] = exp_neg(c[u]);
+        } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) e[u] = exp(-t[u]);
+        }
+        s += (e[0] + e[1]) + (e[2] + e[3]);
+    }
+    for (; i < m; ++i) {
+        const double t = key_to_double(k, i) * mj, c = fmin(t, kExpMost);
+        s += __ballot(!(t >= 0.0)) ? exp(-t) : exp_neg(c);
+    }
+    T[o] = s / (double)m;
+}
+
+// Longer bins: block (bin, 64 column masses, segment of the bin), a mass per
+// lane; its wavefronts take the segment's values 64 at a time in turn, each
+// finding the least and the largest of its 64.  Where those and the wavefront's
+// own least and largest mass put all of the 64 values' exponentials at 0, or at
+// 1, none is evaluated.  The wavefronts' sums are added in LDS in order; with
+// more than one segment (few bins and masses would leave the chip idle) the
+// segments' go to part and are added by transmission_sum_kernel.  Bound: the
+// VALU work of the exponentials left.  (100 bins of 1e4 x 500 masses over 48
+// decades: 680 us with a mass per thread over the whole bin and the library's
+// exp throughout, 240 us; 3 bins of 2.7e4 x 37 masses 1790 -> 29 us.)
 constexpr int kDirectWaves = 8;
 template <typename K>
 __global__ __launch_bounds__(64 * kDirectWaves) void transmission_direct_kernel(const K* __restrict__ sorted,
@@ -477,10 +544,10 @@ __global__ __launch_bounds__(64 * kDirectWaves) void transmission_direct_kernel(
             for (; k + 4 <= cnt; k += 4) {  // four independent chains
                 double e[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) e[u] = exp_neg(k64[k + u] * mj);
+                for (int u = 0; u < 4; ++u) e[u] = exp_neg(fmin(k64[k + u] * mj, kExpMost));
                 s += (e[0] + e[1]) + (e[2] + e[3]);
             }
-            for (; k < cnt; ++k) s += exp_neg(k64[k] * mj);
+            for (; k < cnt; ++k) s += exp_neg(fmin(k64[k] * mj, kExpMost));
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -597,8 +664,15 @@ hipError_t launch_transmission_fit(const double* coef, int64_t n_bins, int nc, c
                                    int nq, const double* m, int n_m, double* T, hipStream_t s)
 {
     if (n_bins == 0 || n_m == 0) return hipSuccess;
-    const dim3 grid((unsigned)n_bins, (unsigned)((n_m + kThreads - 1) / kThreads));
-    transmission_fit_kernel<<<grid, dim3(kThreads), 0, s>>>(coef, nc, yq, wq, nq, m, n_m, T);
+    constexpr int64_t per_block = kThreads / 64;
+    // (a launch holds less than 2^32 threads along its blocks)
+    const int64_t most = ((int64_t)1 << 23) * per_block;
+    for (int64_t b = 0; b < n_bins; b += most) {
+        const int64_t nb = std::min(most, n_bins - b);
+        const dim3 grid((unsigned)((nb + per_block - 1) / per_block), (unsigned)((n_m + 63) / 64));
+        transmission_fit_kernel<<<grid, dim3(kThreads), 0, s>>>(coef + b * nc, nb, nc, yq, wq, nq, m, n_m,
+                                                                T + b * n_m);
+    }
     return hipGetLastError();
 }
 
@@ -614,6 +688,24 @@ hipError_t launch_transmission_direct(const void* sorted, int key_bytes, int64_t
 {
     const int64_t n_bins = (n_points + ppb - 1) / ppb;
     if (n_bins == 0 || n_m == 0) return hipSuccess;
+    const int64_t span = std::min(ppb, n_points);
+    if (span <= kShortBin || (span <= kMidBin && n_bins * n_m >= 4 * span * span)) {
+        // (outputs of a launch counted in 32 bits; less than 2^32 threads)
+        const int64_t most = std::max<int64_t>(1, ((int64_t)1 << 30) / n_m);
+        for (int64_t b = 0; b < n_bins; b += most) {
+            const int64_t n_out = std::min(most, n_bins - b) * n_m, o = b * ppb;
+            const dim3 grid((unsigned)((n_out + kThreads - 1) / kThreads));
+            if (key_bytes == 8)
+                transmission_short_kernel<double><<<grid, dim3(kThreads), 0, s>>>(
+                    static_cast<const double*>(sorted) + o, n_points - o, (int)span, (uint32_t)n_out, m, (uint32_t)n_m,
+                    T + b * n_m);
+            else
+                transmission_short_kernel<float><<<grid, dim3(kThreads), 0, s>>>(
+                    static_cast<const float*>(sorted) + o, n_points - o, (int)span, (uint32_t)n_out, m, (uint32_t)n_m,
+                    T + b * n_m);
+        }
+        return hipGetLastError();
+    }
     const int segs = part ? direct_segments(n_points, ppb, n_m) : 1;
     const dim3 grid((unsigned)n_bins, (unsigned)((n_m + 63) / 64), (unsigned)segs);
     if (key_bytes == 8)
