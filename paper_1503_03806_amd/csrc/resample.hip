@@ -322,13 +322,17 @@ __global__ __launch_bounds__(kQrThreads) void design_q_kernel(int64_t m, int nc,
     __shared__ Pair w[kMaxCoef][kMaxCoef + 1];
     __shared__ double a[kQrTile][kMaxCoef + 1];
     w[threadIdx.x / kMaxCoef][threadIdx.x % kMaxCoef] = W[threadIdx.x];
-    const int64_t r0 = (int64_t)blockIdx.x * kQrTile, n = min((int64_t)kQrTile, m - r0) * nc;
-    design_rows(r0, m, m, nc, a);
-    for (int e = threadIdx.x; e < n; e += kQrThreads) {
-        const int r = e / nc, c = e % nc;
-        Pair s = {0.0, 0.0};
-        for (int k = 0; k <= c; ++k) s = add(s, mul({a[r][k], 0.0}, w[k][c]));
-        Q[r0 * nc + e] = s.h;
+    // (tiles in turn: a grid of one each would pass 2^32 threads from 2^28 rows)
+    for (int64_t r0 = (int64_t)blockIdx.x * kQrTile; r0 < m; r0 += (int64_t)gridDim.x * kQrTile) {
+        const int64_t n = min((int64_t)kQrTile, m - r0) * nc;
+        design_rows(r0, m, m, nc, a);
+        for (int e = threadIdx.x; e < n; e += kQrThreads) {
+            const int r = e / nc, c = e % nc;
+            Pair s = {0.0, 0.0};
+            for (int k = 0; k <= c; ++k) s = add(s, mul({a[r][k], 0.0}, w[k][c]));
+            Q[r0 * nc + e] = s.h;
+        }
+        __syncthreads();
     }
 }
 
@@ -631,8 +635,7 @@ hipError_t launch_design_factors(int64_t m, int nc, double* Q, double* R, void* 
     const int64_t per = (m + kQrMaxChunks - 1) / kQrMaxChunks;
     const int64_t rows = (per + kQrTile - 1) / kQrTile * kQrTile;
     const int chunks = (int)((m + rows - 1) / rows);
-    const int64_t tiles = (m + kQrTile - 1) / kQrTile;
-    if (tiles > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
+    const int64_t tiles = std::min<int64_t>((m + kQrTile - 1) / kQrTile, (int64_t)1 << 16);
     Pair* W = static_cast<Pair*>(scratch);
     Pair* part = W + kQrThreads;
     gram_kernel<<<dim3((unsigned)chunks), dim3(kQrThreads), 0, s>>>(m, nc, rows, part);
