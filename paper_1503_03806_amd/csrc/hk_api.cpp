@@ -1437,7 +1437,7 @@ static int opacity_launch(hk_ctx* ctx, const hk_state* st, const hk_grid* grid, 
         HK_HIP(ctx, ctx->ln.wing.ensure(nb * sizeof(WingRec)), "allocating line records");
         HK_HIP(ctx, ctx->ln.core.ensure(nb * sizeof(CoreRec)), "allocating line records");
     }
-    const int32_t tp = opacity_f64_tile_points(covered_points(ctx, grid));
+    const int32_t tp = opacity_f64_tile_points(covered_points(ctx, grid), np);
     const int64_t n_tiles = ((int64_t)np + tp - 1) / tp;
     const int32_t tpc = precision == HK_F64 ? core_f64_tile_points() : core_f32_tile_points();
     const int64_t n_tiles_c = ((int64_t)np + tpc - 1) / tpc;
@@ -1831,7 +1831,7 @@ int hk_tables(hk_ctx* ctx, const hk_state* states, int32_t n_states, const hk_gr
     const int32_t tpc = f64 ? core_f64_tile_points() : core_f32_tile_points();
     const int64_t n_tiles_c = ((int64_t)np + tpc - 1) / tpc;
     // wing tile ranges per state (binary32: of the smallest shape)
-    const int32_t tp64 = opacity_f64_tile_points(covered_points(ctx, grid));
+    const int32_t tp64 = opacity_f64_tile_points(covered_points(ctx, grid), np);
     const int32_t tp_min = f64 ? tp64 : opacity_f32_tile_points(2);
     const int64_t ranges_per_state = 2 * (((int64_t)np + tp_min - 1) / tp_min);
 
@@ -1842,7 +1842,9 @@ int hk_tables(hk_ctx* ctx, const hk_state* states, int32_t n_states, const hk_gr
     // sums, compensations and series in binary32)
     const int64_t per_state = n * rec_bytes + (ranges_per_state + 2 * n_tiles_c) * 8 + (int64_t)np * (f64 ? 16 : 20);
     int64_t B = ctx->tables_batch > 0 ? ctx->tables_batch : std::max<int64_t>(1, ctx->tables_mem / per_state);
-    B = std::min<int64_t>(B, n_states);
+    // (and as one launch holds; states are also a grid's second dimension)
+    B = std::min({B, (int64_t)n_states, plan_states_most((np + std::min(tp_min, tpc) - 1) / std::min(tp_min, tpc)),
+                  (int64_t)65535});
     const int64_t n_batches = (n_states + B - 1) / B;
     B = (n_states + n_batches - 1) / n_batches;
 

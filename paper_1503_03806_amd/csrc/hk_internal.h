@@ -191,6 +191,13 @@ struct WorkPlan {
 // + 2 per state (launches of n_pairs = n_tiles n_states pairs), partial
 // points <= 6 n_points + 2 tile_points per state.
 inline int64_t plan_items_bound(int64_t n_pairs, int32_t n_states) { return 6 * n_pairs + 2 * (int64_t)n_states; }
+// States whose items a launch holds (workgroups of 256 threads, below 2^32
+// threads; of one state it holds any grid's).
+inline int64_t plan_states_most(int64_t n_tiles)
+{
+    const int64_t items = (int64_t)UINT32_MAX / 256 - 8 * kPlanChunk;
+    return items / plan_items_bound(n_tiles, 1) > 1 ? items / plan_items_bound(n_tiles, 1) : 1;
+}
 inline int64_t plan_partial_points_bound(int64_t n_points, int32_t tile_points)
 {
     return 6 * n_points + 2 * (int64_t)tile_points;
@@ -338,7 +345,8 @@ hipError_t launch_line_prep_f64_batch(const LinesDev& L, const PrepParams* pps, 
                                       WingIdx* idx, CoreRec* core, const RangeJobs& rj, hipStream_t s);
 // Binary64 opacity: the wing kernel writes kappa, the core kernel its
 // series terms.
-int32_t opacity_f64_tile_points(int64_t covered);  // points per work item, lines across that many points
+// points per work item, lines across `covered` of n_points points
+int32_t opacity_f64_tile_points(int64_t covered, int64_t n_points);
 // The wing's interpolation matrices (opacity_f64.hip), filled on the host:
 // cheb[m][k]: Chebyshev coefficient k per node value m; child[c][m][k]: node
 // m's weight at node k of child tile c of four; child_cheb: the two in turn.

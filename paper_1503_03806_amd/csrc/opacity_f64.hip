@@ -101,6 +101,9 @@ constexpr int64_t kFewLines = 24;
 // x 1e6 283 / 239, 8 times 1.25e5 lines on an eighth each of 1e6 points 2.8 /
 // 4.0 ms; 1e6 lines x 3e6 points 2.1 / 1.4 ms.)
 constexpr int64_t kSmallGrid = 400000;
+// (a thread per point of the blocks, up to 6 items a block: 2^32 threads are
+// more than a launch holds)
+constexpr int64_t kSmallTiles = (int64_t)1 << 29;
 // Entries of a wavefront's list of lines that its sub-tile does not admit.
 constexpr int kNearCap = 768;
 // A rest of up to this many lines of a leaf's is taken with a point per lane:
@@ -1060,7 +1063,10 @@ __global__ __launch_bounds__(64 * kWaves) void core_f64_kernel(
 namespace {
 }  // namespace
 
-int32_t opacity_f64_tile_points(int64_t covered) { return kWaves * (covered <= kSmallGrid ? kLeaf : 4 * kLeaf); }
+int32_t opacity_f64_tile_points(int64_t covered, int64_t n_points)
+{
+    return kWaves * (covered <= kSmallGrid && n_points <= kSmallTiles ? kLeaf : 4 * kLeaf);
+}
 int32_t core_f64_tile_points() { return kCoreTilePoints; }
 
 // The interpolation matrices of the wing's tiles, from the closed forms of
