@@ -48,17 +48,17 @@ __device__ inline double k_of_g(const K* s, int64_t m, double g, int rule)
     return a + (u - fl) * (b - a);
 }
 
-// One workgroup per bin: bins of ppb consecutive points of n_states grids
-// of n_points each (grid s at s * n_points; a grid's last bin may be short).
+// One workgroup per bin, from bin0 on: bins of ppb consecutive points of n_states
+// grids of n_points each (grid s at s * n_points; a grid's last bin may be short).
 // Sorted keys to dst (optional, same layout) and k(g) to k_out[bin][g.n].
 template <typename K>
 __global__ __launch_bounds__(kRadixThreads) void radix_bin_kernel(const K* __restrict__ src, int64_t n_points,
-                                                                  int64_t ppb, int64_t bins_per_grid,
+                                                                  int64_t ppb, int64_t bins_per_grid, int64_t bin0,
                                                                   K* __restrict__ dst, GValues g,
                                                                   double* __restrict__ k_out)
 {
     extern __shared__ __align__(16) unsigned char radix_lds[];
-    const int64_t bin = blockIdx.x;
+    const int64_t bin = bin0 + blockIdx.x;
     const int64_t st = bin / bins_per_grid, lb = bin - st * bins_per_grid;
     const int64_t b0 = st * n_points + lb * ppb;
     const int m = (int)min(ppb, n_points - lb * ppb);
@@ -106,10 +106,11 @@ hipError_t run_kdist(const K* kappa, int64_t n_points, int64_t ppb, const GValue
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&radix_bin_kernel<K>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
         if (e != hipSuccess) return e;
-        const int64_t nb = n_bins * n_states;
-        if (nb > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
-        radix_bin_kernel<K><<<dim3((unsigned)nb), dim3(kRadixThreads), shm, s>>>(kappa, n_points, ppb, n_bins,
-                                                                                  sorted_out, g, k_out);
+        // (a launch holds less than 2^32 threads)
+        constexpr int64_t most = (int64_t)1 << 21;
+        for (int64_t b = 0, nb = n_bins * n_states; b < nb; b += most)
+            radix_bin_kernel<K><<<dim3((unsigned)std::min(most, nb - b)), dim3(kRadixThreads), shm, s>>>(
+                kappa, n_points, ppb, n_bins, b, sorted_out, g, k_out);
         return hipGetLastError();
     }
     if (n_states != 1) return hipErrorInvalidValue;  // bins above one LDS sort: one grid per call

@@ -602,8 +602,10 @@ hipError_t run_resample(const K* sorted, int64_t n_points, int64_t ppb, int nc, 
     const int64_t n_bins = (n_points + ppb - 1) / ppb;
     const int64_t m = std::min(ppb, n_points), last = n_points - (n_bins - 1) * ppb;
     if (!part || !resample_scratch_bytes(n_points, ppb)) {
-        resample_kernel<K><<<dim3((unsigned)n_bins), dim3(kThreads), 0, s>>>(sorted, n_points, ppb, nc, Q, R, Ql, Rl,
-                                                                             coef);
+        constexpr int64_t most = (int64_t)1 << 23;  // (a launch holds less than 2^32 threads)
+        for (int64_t b = 0; b < n_bins; b += most)
+            resample_kernel<K><<<dim3((unsigned)std::min(most, n_bins - b)), dim3(kThreads), 0, s>>>(
+                sorted + b * ppb, n_points - b * ppb, ppb, nc, Q, R, Ql, Rl, coef + b * nc);
         return hipGetLastError();
     }
     // the whole bins, and a shorter last one with its own factors
