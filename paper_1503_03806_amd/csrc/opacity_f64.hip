@@ -620,6 +620,7 @@ __device__ __forceinline__ void wing_f64_tile(int64_t t, int64_t L0, int64_t L1,
                             dacc += tk ? v : 0.0;
                         }
                         S.point[wave][lf * kLeaf + lane] += dacc;
+                        wave_fence();  // (other lanes add to these below)
                     }
                     for (int p0 = 0; n_batch > 0 && p0 < kLeaf; p0 += kPoints) {
                         double x[kPoints], pa[kPoints];
@@ -1058,9 +1059,6 @@ __global__ __launch_bounds__(64 * kWaves) void core_f64_kernel(
     }
 }
 
-}  // namespace
-
-namespace {
 }  // namespace
 
 int32_t opacity_f64_tile_points(int64_t covered, int64_t n_points)
