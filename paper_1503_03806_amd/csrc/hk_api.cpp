@@ -415,13 +415,17 @@ double max_cutoff(const hk_ctx* ctx, const hk_state* st, const hk_grid* grid)
 }
 // Grid points from the first line's centre to the last's (the same for every
 // state), 0 without lines there.
+int64_t covered_points(const ListInfo& li, int64_t n_lines, const hk_grid* grid)
+{
+    if (n_lines <= 0) return 0;
+    const double n = (double)grid->n_points;
+    const double lo = std::clamp((li.nu_low - grid->nu_min) / grid->dnu, 0.0, n);
+    const double hi = std::clamp((li.nu_max - grid->nu_min) / grid->dnu, 0.0, n);
+    return (int64_t)(hi - lo);
+}
 int64_t covered_points(const hk_ctx* ctx, const hk_grid* grid)
 {
-    if (ctx->n_lines <= 0) return 0;
-    const double n = (double)grid->n_points;
-    const double lo = std::clamp((ctx->li.nu_low - grid->nu_min) / grid->dnu, 0.0, n);
-    const double hi = std::clamp((ctx->li.nu_max - grid->nu_min) / grid->dnu, 0.0, n);
-    return (int64_t)(hi - lo);
+    return covered_points(ctx->li, ctx->n_lines, grid);
 }
 double wing_reach(const hk_ctx* ctx, const hk_state* st, const hk_grid* grid)
 {
@@ -729,14 +733,11 @@ struct PlanMaking {
     int32_t tp;
 };
 
-// The plan of n_states states' tiles of tp points, n_tiles each, into pb (its
-// buffers sized here); the tiles' line ranges go to ranges (2 n_tiles per
-// state).  The reach: of the one state, or reach_of ([device] n_states).
-int plan_begin(hk_ctx* ctx, PlanBufs& pb, int64_t* ranges, int64_t n_tiles, int32_t n_states, double reach,
-               const double* reach_of, int32_t tp, int64_t min_seg, int64_t busy_min, const hk_grid* grid,
-               PlanMaking* pm)
+// Sizes pb for the plan of n_states states' tiles, n_tiles each (without the
+// partial sums).
+int plan_reserve(hk_ctx* ctx, PlanBufs& pb, int64_t n_points, int64_t n_tiles, int32_t n_states)
 {
-    const int64_t n_ref = (grid->n_points + kRefTilePoints - 1) / kRefTilePoints;
+    const int64_t n_ref = (n_points + kRefTilePoints - 1) / kRefTilePoints;
     const int64_t P = n_tiles * n_states;
     HK_HIP(ctx, pb.ref.ensure((size_t)std::max<int64_t>(n_ref * n_states, 1) * 2 * sizeof(int64_t)),
            "allocating the work plan");
@@ -745,6 +746,18 @@ int plan_begin(hk_ctx* ctx, PlanBufs& pb, int64_t* ranges, int64_t n_tiles, int3
     HK_HIP(ctx, pb.slot.ensure((size_t)std::max<int64_t>(P, 1) * sizeof(int64_t)), "allocating the work plan");
     HK_HIP(ctx, pb.bsum.ensure((size_t)plan_scratch_count(P) * sizeof(int64_t)), "allocating the work plan");
     HK_HIP(ctx, pb.total.ensure(2 * sizeof(int64_t)), "allocating the work plan");
+    return HK_OK;
+}
+
+// The plan of n_states states' tiles of tp points, n_tiles each, into pb (its
+// buffers sized here); the tiles' line ranges go to ranges (2 n_tiles per
+// state).  The reach: of the one state, or reach_of ([device] n_states).
+int plan_begin(hk_ctx* ctx, PlanBufs& pb, int64_t* ranges, int64_t n_tiles, int32_t n_states, double reach,
+               const double* reach_of, int32_t tp, int64_t min_seg, int64_t busy_min, const hk_grid* grid,
+               PlanMaking* pm)
+{
+    const int64_t n_ref = (grid->n_points + kRefTilePoints - 1) / kRefTilePoints;
+    if (int rc = plan_reserve(ctx, pb, grid->n_points, n_tiles, n_states)) return rc;
     int64_t* ref = static_cast<int64_t*>(pb.ref.p);
     pm->pb = &pb;
     pm->tp = tp;
@@ -1583,10 +1596,12 @@ int hk_opacity(hk_ctx* ctx, const hk_state* st, const hk_grid* grid, int precisi
     return opacity_run(ctx, st, grid, precision, static_cast<double*>(kappa), accumulate);
 }
 
-// Sizes every per-line buffer of opacity_run for lists of up to n lines, so
-// that a stream of chunks never reallocates (and so never synchronises) in
-// its loop.
-static int reserve_line_buffers(hk_ctx* ctx, int64_t n, int precision)
+// Sizes the buffers of opacity_run that depend on the list, for lists of up to
+// n lines and (binary64) wing tiles of tp_least to tp_most points, so that a
+// stream of chunks never reallocates (and so never synchronises) once both
+// lanes have been used for its grid.
+static int reserve_line_buffers(hk_ctx* ctx, int64_t n, const hk_grid* grid, int precision, int32_t tp_least,
+                                int32_t tp_most, bool both_lanes)
 {
     const size_t nb = (size_t)std::max<int64_t>(n, 1);
     for (Lane* l : {&ctx->ln, &ctx->ln_alt}) {
@@ -1594,6 +1609,14 @@ static int reserve_line_buffers(hk_ctx* ctx, int64_t n, int precision)
         if (precision == HK_F64) {
             HK_HIP(ctx, l->wing.ensure(nb * sizeof(WingRec)), "allocating line records");
             HK_HIP(ctx, l->core.ensure(nb * sizeof(CoreRec)), "allocating line records");
+            if (l == &ctx->ln_alt && !both_lanes) continue;
+            const int64_t n_tiles = (grid->n_points + tp_least - 1) / tp_least;
+            HK_HIP(ctx, l->ranges.ensure((size_t)std::max<int64_t>(n_tiles, 1) * 2 * sizeof(int64_t)),
+                   "allocating tile ranges");
+            if (int rc = plan_reserve(ctx, l->wplan, grid->n_points, n_tiles, 1)) return rc;
+            const int64_t points = plan_partial_points_bound(grid->n_points, tp_most);
+            if (points * 8 <= kPlanBoundBytes)
+                HK_HIP(ctx, l->wplan.partial.ensure((size_t)points * 8), "allocating partial sums");
         } else {
             HK_HIP(ctx, l->w32.ensure(nb * sizeof(WingRec32)), "allocating binary32 records");
             HK_HIP(ctx, l->c32.ensure(nb * sizeof(CoreRec32)), "allocating binary32 records");
@@ -1641,12 +1664,16 @@ int hk_opacity_stream(hk_ctx* ctx, const hk_lines* chunks, int32_t n_chunks, con
     const std::vector<ListScan> scan = scan_lists(chunks, n_shaped);
     std::vector<ListInfo> info((size_t)n_chunks);
     int64_t n_max = 0, n_total = 0;
+    int32_t tp_least = INT32_MAX, tp_most = 0;  // of the binary64 wing's tiles
     for (int32_t c = 0; c < n_chunks; ++c) {
         if (c == n_shaped || scan[(size_t)c].bad) return check_lines(ctx, &chunks[c], c);
         info[(size_t)c] = scan[(size_t)c].info;
         if (precision != HK_F64 && !(max_cutoff(info[(size_t)c], sp->T_ref, st, grid) / grid->dnu < 8388608.0))
             return fail(ctx, HK_EINVAL, "chunk %d: binary32 profiles need (largest cutoff)/dnu < 2^23 (got %g)", c,
                         max_cutoff(info[(size_t)c], sp->T_ref, st, grid) / grid->dnu);
+        const int32_t tp = opacity_f64_tile_points(covered_points(info[(size_t)c], chunks[c].n, grid), grid->n_points);
+        tp_least = std::min(tp_least, tp);
+        tp_most = std::max(tp_most, tp);
         n_max = std::max(n_max, chunks[c].n);
         n_total += chunks[c].n;
     }
@@ -1666,7 +1693,7 @@ int hk_opacity_stream(hk_ctx* ctx, const hk_lines* chunks, int32_t n_chunks, con
     ctx->last_tables_states = 0;
     ctx->last_stream_chunks = 0;
     HK_HIP(ctx, hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
-    if (int rc = reserve_line_buffers(ctx, n_max, precision)) return rc;
+    if (int rc = reserve_line_buffers(ctx, n_max, grid, precision, tp_least, tp_most, n_chunks > 1)) return rc;
     if (int rc = stream_resources(ctx, (size_t)8 * (size_t)std::max<int64_t>(n_max, 1))) return rc;
     if (int rc = reset_surrogate_count(ctx, precision)) return rc;
     HK_HIP(ctx, ctx->st_counts.ensure((size_t)kCountBlocks * 3 * (size_t)n_chunks * sizeof(int64_t)),
