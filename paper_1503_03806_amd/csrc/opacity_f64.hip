@@ -89,9 +89,15 @@ constexpr int kFarNodes = kWingNodes;  // 24
 constexpr int kFarRatio = 3;
 constexpr int kLeaf = 64;
 static_assert(kFarNodes == 24, "far_eval and wave_reduce are written for 24 nodes");
-// Lines of a work item up to which all of them are taken point by point:
-// there the reductions and the interpolation cost more than the points.
-constexpr int64_t kFewLines = 24;
+// Lines of a work item up to which all of them are taken point by point, in
+// blocks of 1024 and of 256 points: there a block's fixed cost (clearing and
+// reducing the node sums, the interpolation) is more than the points'.  (Steps
+// with 24 lines, through the leaves' lists / with 48, a run of 256 points at a
+// time: 1e4 lines x 3e6 points 182 / 130 us, 10 x 1e7 without a cutoff 356 /
+// 192, 24 x 1e7 477 / 242; with 64 lines 64 x 1e7 330 / 391.  Blocks of 256:
+// tables of 300 states of 300 lines x 6e4 points 2130 / 1616 us; with 96 lines
+// in place of 64 1e3 x 6e4 2424 / 2344, with 192 1e4 x 3e5 74 / 91.)
+constexpr int kFewLines = 48, kFewLinesSmall = 96;
 // Lists whose centres lie on up to this many grid points take blocks of 256
 // points (two levels of tiles): a quarter of the serial work per wavefront,
 // four times the workgroups; wider lists fill the chip with blocks of 1024,
@@ -398,6 +404,79 @@ __device__ inline void wave_fence()
     __builtin_amdgcn_wave_barrier();
 }
 
+// acc[e] += the line at this lane's points x[e] (index j0 + 64 e): a run of 256
+// points, four a lane, that share one reciprocal.  The line's window, rules and
+// series intervals are the same for the wavefront.
+__device__ __forceinline__ void run_eval(double (&acc)[4], const double (&x)[4], int32_t run0, int32_t j0,
+                                         const WingIdx& w, const WingRec& l)
+{
+    const int32_t run1 = run0 + 255;
+    const bool inside = w.wlo <= run0 && w.whi >= run1 && (run1 < w.clo || run0 > w.chi);
+    const bool out3 = run1 < w.g3lo || run0 > w.g3hi;
+    double num[4], den[4];
+    if (inside && out3 && (w.flags & kGroupSafe)) {  // the window covers the run, on the 1-node rule
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const double dv = x[e] - l.nu0;
+            num[e] = 1.0;
+            den[e] = fma(dv, dv, l.G2);
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int32_t j = j0 + 64 * e;
+            const bool take = j >= w.wlo && j <= w.whi && !(j >= w.clo && j <= w.chi);
+            const bool one = j < w.g3lo || j > w.g3hi;
+            const double dv = x[e] - l.nu0;
+            double nn, mm;
+            gh3_nm(dv, l.X, l.a2, l.c, l.p, l.r, nn, mm);
+            mm = one ? fma(dv, dv, l.G2) : mm;
+            nn = one ? 1.0 : nn;
+            if (!(w.flags & kGroupSafe)) {
+                const double v = qdiv(l.Lg * nn, mm);
+                acc[e] += take ? v : 0.0;
+            }
+            num[e] = take ? nn : 0.0;
+            den[e] = take ? mm : 1.0;
+        }
+        if (!(w.flags & kGroupSafe)) return;
+    }
+    const double P01 = den[0] * den[1], P23 = den[2] * den[3];
+    const double c = qrcp3(P01 * P23) * l.Lg;
+    const double c01 = c * P23, c23 = c * P01;
+    acc[0] = fma(c01 * den[1], num[0], acc[0]);
+    acc[1] = fma(c01 * den[0], num[1], acc[1]);
+    acc[2] = fma(c23 * den[3], num[2], acc[2]);
+    acc[3] = fma(c23 * den[2], num[3], acc[3]);
+}
+
+// The run's sums over every kStep-th of the nl lines from the first on.
+template <int kStep>
+__device__ __forceinline__ void run_lines(double (&acc)[4], int32_t first, int32_t nl, int32_t run0, double nu_min,
+                                          double dnu, const WingRec* __restrict__ wing,
+                                          const WingIdx* __restrict__ idx)
+{
+    const int32_t j0 = run0 + (int32_t)(threadIdx.x & 63);
+    double x[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        x[e] = fma((double)(j0 + 64 * e), dnu, nu_min);
+        acc[e] = 0.0;
+    }
+    if (first >= nl) return;
+    WingIdx w = idx[first];
+    WingRec l = wing[first];
+    for (int32_t i = first; i < nl; i += kStep) {
+        // (the next line's records on their way meanwhile)
+        const int32_t next = min(i + kStep, nl - 1);
+        const WingIdx wn = idx[next];
+        const WingRec ln = wing[next];
+        if (w.whi >= run0 && w.wlo <= run0 + 255) run_eval(acc, x, run0, j0, w, l);
+        w = wn;
+        l = ln;
+    }
+}
+
 // Lines [L0, L1) at the points of block t of one state (record pointers
 // already offset to the state): out[j - obase] = the sum, or += it with
 // accumulate.  Each wavefront takes every fourth batch of 64 lines (one per
@@ -425,10 +504,34 @@ __device__ __forceinline__ void wing_f64_tile(int64_t t, int64_t L0, int64_t L1,
     const int32_t b1 = min(b0 + kBlock, n) - 1, s1 = min(s0 + kSub, n) - 1;
     const double xref = fma((double)b0, dnu, nu_min);  // positions are taken relative to the block's first point
     const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-    far_ok = far_ok && L1 - L0 > kFewLines;
     wing += L0;
     idx += L0;
     const int32_t nl = (int32_t)(L1 - L0);
+    if (nl <= (kThreeLevels ? kFewLines : kFewLinesSmall)) {
+        double acc[4];
+        if constexpr (kThreeLevels) {  // each wavefront its points
+            run_lines<1>(acc, 0, nl, s0, nu_min, dnu, wing, idx);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int32_t j = s0 + 64 * e + lane;
+                if (j < n) out[j - obase] = accumulate ? out[j - obase] + acc[e] : acc[e];
+            }
+        } else {  // each wavefront every fourth line at all points
+            double* part = reinterpret_cast<double*>(&S.near[0][0]);
+            run_lines<kWaves>(acc, wave, nl, b0, nu_min, dnu, wing, idx);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) part[wave * kBlock + 64 * e + lane] = acc[e];
+            __syncthreads();
+            const int32_t j = b0 + (int32_t)threadIdx.x;
+            if (j < n) {
+                double v = 0.0;
+#pragma unroll
+                for (int q = 0; q < kWaves; ++q) v += part[q * kBlock + threadIdx.x];
+                out[j - obase] = accumulate ? out[j - obase] + v : v;
+            }
+        }
+        return;
+    }
 
     for (int k = threadIdx.x; k < kWaves * kFarNodes; k += 64 * kWaves) (&S.sub[0][0])[k] = (&S.block[0][0])[k] = 0.0;
     for (int k = threadIdx.x; k < kLeaves * kWaves * kFarNodes; k += 64 * kWaves) (&S.leaf[0][0])[k] = 0.0;
