@@ -753,7 +753,7 @@ int plan_reserve(hk_ctx* ctx, PlanBufs& pb, int64_t n_points, int64_t n_tiles, i
 // buffers sized here); the tiles' line ranges go to ranges (2 n_tiles per
 // state).  The reach: of the one state, or reach_of ([device] n_states).
 int plan_begin(hk_ctx* ctx, PlanBufs& pb, int64_t* ranges, int64_t n_tiles, int32_t n_states, double reach,
-               const double* reach_of, int32_t tp, int64_t min_seg, int64_t busy_min, const hk_grid* grid,
+               const double* reach_of, int32_t tp, int64_t min_seg, const CutRules& cut, const hk_grid* grid,
                PlanMaking* pm)
 {
     const int64_t n_ref = (grid->n_points + kRefTilePoints - 1) / kRefTilePoints;
@@ -763,10 +763,22 @@ int plan_begin(hk_ctx* ctx, PlanBufs& pb, int64_t* ranges, int64_t n_tiles, int3
     pm->tp = tp;
     pm->tiles = RangeJob{n_tiles, tp, n_states, reach, reach_of, ranges};
     pm->ref = RangeJob{n_ref, kRefTilePoints, n_states, reach, reach_of, ref};
-    pm->job = PlanJob{ref,      ranges,   n_ref,    n_tiles,
-                      min_seg,  busy_min, n_states, static_cast<int64_t*>(pb.seg.p),
-                      static_cast<int64_t*>(pb.first.p), static_cast<int64_t*>(pb.slot.p),
-                      static_cast<int64_t*>(pb.bsum.p),  static_cast<int64_t*>(pb.total.p)};
+    pm->job = PlanJob{ref,
+                      ranges,
+                      n_ref,
+                      n_tiles,
+                      min_seg,
+                      cut.usual,
+                      cut.wide,
+                      cut.wide_points * grid->dnu,
+                      reach,
+                      reach_of,
+                      n_states,
+                      static_cast<int64_t*>(pb.seg.p),
+                      static_cast<int64_t*>(pb.first.p),
+                      static_cast<int64_t*>(pb.slot.p),
+                      static_cast<int64_t*>(pb.bsum.p),
+                      static_cast<int64_t*>(pb.total.p)};
     return HK_OK;
 }
 
@@ -876,7 +888,7 @@ int autotune_wing(hk_ctx* ctx, int32_t n_try, const double* d_reach, const hk_gr
         PlanMaking pm;
         WorkPlan wp;
         // segments of whole 256-line compensation blocks
-        rc = plan_begin(ctx, ctx->ln.wplan, ranges, n_tiles, n_try, 0.0, d_reach, tp, 256, kBusyMin, grid, &pm);
+        rc = plan_begin(ctx, ctx->ln.wplan, ranges, n_tiles, n_try, 0.0, d_reach, tp, 256, kCut32, grid, &pm);
         if (rc != HK_OK) break;
         RangeJobs rj = range_jobs(ctx, grid);
         rj.job[rj.n++] = pm.tiles;
@@ -1351,7 +1363,7 @@ static int launch_f32_pass(hk_ctx* ctx, const PrepParams& pp, const hk_grid* gri
     WorkPlan wwp, cwp;
     PlanMaking wpm;
     // segments of whole 256-line compensation blocks for the wing
-    if (int rc = plan_begin(ctx, ctx->ln.wplan, ranges, n_tiles, 1, reach, nullptr, tp, 256, kBusyMin, grid, &wpm))
+    if (int rc = plan_begin(ctx, ctx->ln.wplan, ranges, n_tiles, 1, reach, nullptr, tp, 256, kCut32, grid, &wpm))
         return rc;
     {
         StageTimer tm(ctx, HK_STAGE_LINE_PREP, s);
@@ -1471,7 +1483,7 @@ static int opacity_launch(hk_ctx* ctx, const hk_state* st, const hk_grid* grid, 
 
     PlanMaking wpm, cpm;
     if (int rc = plan_begin(ctx, ctx->ln.cplan, ranges_c, n_tiles_c, 1, reach_core, nullptr, tpc, 64,
-                            precision == HK_F64 ? kBusyMinCore64 : kBusyMin, grid, &cpm))
+                            precision == HK_F64 ? kCutCore64 : kCut32, grid, &cpm))
         return rc;
     if (precision != HK_F64)
         return launch_f32_pass(ctx, pp, grid, reach, widx, cpm, precision == HK_F32_SURROGATE, f);
@@ -1484,7 +1496,7 @@ static int opacity_launch(hk_ctx* ctx, const hk_state* st, const hk_grid* grid, 
     // and every kind of tile's ranges in one launch, both plans in another.
     HK_HIP(ctx, ctx->ln.kc.ensure((size_t)std::max(np, 1) * sizeof(double)), "allocating the series grid");
     WorkPlan wwp, cwp;
-    if (int rc = plan_begin(ctx, ctx->ln.wplan, ranges, n_tiles, 1, reach, nullptr, tp, 64, kBusyMinWing64, grid, &wpm))
+    if (int rc = plan_begin(ctx, ctx->ln.wplan, ranges, n_tiles, 1, reach, nullptr, tp, 64, kCutWing64, grid, &wpm))
         return rc;
     {
         StageTimer tm(ctx, HK_STAGE_LINE_PREP, s);
@@ -1951,13 +1963,13 @@ int hk_tables(hk_ctx* ctx, const hk_state* states, int32_t n_states, const hk_gr
         // wing's; every state of the batch in one launch per step
         PlanMaking wpm, cpm;
         if (int rc = plan_begin(ctx, ctx->ln.cplan, rc_all, n_tiles_c, nbat, 0.0, d_reach_c, tpc, 64,
-                                f64 ? kBusyMinCore64 : kBusyMin, grid, &cpm))
+                                f64 ? kCutCore64 : kCut32, grid, &cpm))
             return rc;
         int64_t* rw = static_cast<int64_t*>(ctx->tb_ranges.p);
         auto wing_plan = [&]() -> int {
             const int32_t tp = f64 ? tp64 : opacity_f32_tile_points(ppl);
             return plan_begin(ctx, ctx->ln.wplan, rw, ((int64_t)np + tp - 1) / tp, nbat, 0.0, d_reach, tp,
-                              f64 ? 64 : 256, f64 ? kBusyMinWing64 : kBusyMin, grid, &wpm);
+                              f64 ? 64 : 256, f64 ? kCutWing64 : kCut32, grid, &wpm);
         };
         RangeJobs rj = range_jobs(ctx, grid);
         rj.job[rj.n++] = cpm.tiles;

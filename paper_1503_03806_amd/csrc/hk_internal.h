@@ -203,21 +203,36 @@ inline int64_t plan_partial_points_bound(int64_t n_points, int32_t tile_points)
     return 6 * n_points + 2 * (int64_t)tile_points;
 }
 int64_t plan_scratch_count(int64_t n_pairs);  // int64 values of the plan's block sums
-// A state is cut when fewer reference tiles than busy_min hold lines (or very
-// unevenly many).
-constexpr int64_t kBusyMin = 4096;
+// When a state's tiles are cut: fewer than `busy` reference tiles hold lines (or
+// very unevenly many), and the fullest of them at least `lines`.
+struct CutRule {
+    int64_t busy, lines;
+};
+// A kernel's rule, and the one it has where a line reaches wide_points and more.
+struct CutRules {
+    CutRule usual, wide;
+    double wide_points;
+};
+constexpr CutRules kCut32{{4096, 1}, {4096, 1}, __builtin_inf()};
 // The binary64 wing, a wavefront of which holds 64 points on small grids: 256
 // workgroups on whole tiles are better than twice the items, each of which
 // repeats the tiles' reductions and interpolation.  (Whole steps, with 256 /
 // with 128 here: 9e4 lines x 9e4 points 213 / 195 us, 1.2e4 x 1.2e5 87 / 73,
-// 1.2e5 x 1.2e5 239 / 208; with 64 the same but 4e3 x 4e4 67 -> 69.)
-constexpr int64_t kBusyMinWing64 = 128;
+// 1.2e5 x 1.2e5 239 / 208; with 64 the same but 4e3 x 4e4 67 -> 69.)  Tiles of
+// few lines cost about as much in each part as whole: with 1 / with 1024 lines
+// tables of 300 states of 1e3 lines x 6e4 points took 3770 / 2540 us, 1000
+// states of 1e3 x 1e4 3770 / 2730, single states of 500 x 6e3 to 3e4 x 4e4 the
+// same, to 1 us.
+constexpr CutRules kCutWing64{{128, 1024}, {128, 1024}, __builtin_inf()};
 // The binary64 series: a wavefront has work only from the lines near its own
 // 256 points, so the halves of a cut tile's lines leave half its wavefronts
 // idle.  (3e6 lines x 1e6 points 4.9 ms a step with 4096 here, 4.4 with 1024
 // and below; nine states of 1e5 x 4e5 1.33 -> 1.28 with 512; 4e5 lines x 1.2e5
-// points 584 us with 256 and 553 with 128.)
-constexpr int64_t kBusyMinCore64 = 128;
+// points 584 us with 256 and 553 with 128.)  Not so where a line's series covers
+// whole tiles (steps with the usual rule / with the wide one: reach of ~3000
+// points, 1e3 lines x 1e5 points 541 / 278 us, 1e4 x 3e5 2413 / 1638, 3e4 x 1e5
+// 5950 / 3760; but at 1650 points 3e4 x 2e5 1650 / 1877).
+constexpr CutRules kCutCore64{{128, 256}, {1024, 64}, 2048.0};
 // One plan to make: the segment lengths seg[s] of n_states states from their
 // reference ranges (tiles of kRefTilePoints points, 2 n_ref values per state;
 // min_seg: the shortest segment, a power of two -- 256 for the binary32 wing,
@@ -226,7 +241,10 @@ constexpr int64_t kBusyMinCore64 = 128;
 // per state).
 struct PlanJob {
     const int64_t *ref, *ranges;
-    int64_t n_ref, n_tiles, min_seg, busy_min;
+    int64_t n_ref, n_tiles, min_seg;
+    CutRule cut, wide;  // wide: where the state's reach is at least wide_reach
+    double wide_reach, reach;
+    const double* reach_of;
     int32_t n_states;
     int64_t *seg, *first, *slot, *bsum, *total;
 };

@@ -13,8 +13,8 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kPerThread = 4;
 constexpr int64_t kPerBlock = (int64_t)kThreads * kPerThread;
-// A state's tiles are cut when fewer than busy_min reference tiles hold
-// lines, or when the fullest holds more than kUneven times the mean.
+// A state's tiles are uneven when the fullest reference tile holds more than
+// kUneven times the mean (CutRule).
 constexpr int64_t kUneven = 3;
 
 // Segment length of a state from its reference tiles' statistics: the smallest power of two >=
@@ -25,12 +25,13 @@ constexpr int64_t kUneven = 3;
 // <= |A| / tp + 2 tiles of tp points.  So the items stay <= sum_t (c_t / L
 // + 2) <= 6 n_tiles and the partial points <= 6 n_points + 2 tile points.
 __device__ inline int64_t seg_length(int64_t busy, int64_t mx, int64_t sum, int64_t n_points, int64_t n_lines,
-                                     int64_t min_seg, int64_t busy_min)
+                                     const PlanJob& j, int32_t st)
 {
-    if (!(sum > 0 && (busy < busy_min || mx * busy > kUneven * sum))) return kNoSplit;
+    const CutRule& c = (j.reach_of ? j.reach_of[st] : j.reach) >= j.wide_reach ? j.wide : j.cut;
+    if (!(sum > 0 && mx >= c.lines && (busy < c.busy || mx * busy > kUneven * sum))) return kNoSplit;
     const double W = 512.0 * (double)sum + 4096.0 * (double)n_lines;
     const double need = W / (4.0 * (double)n_points);
-    int64_t L = min_seg;
+    int64_t L = j.min_seg;
     while ((double)L < need && L < kNoSplit) L <<= 1;  // kNoSplit: not cut after all
     return L;
 }
@@ -60,7 +61,7 @@ __global__ __launch_bounds__(kThreads) void seg_length_kernel(PlanJob j, int64_t
         __syncthreads();
     }
     if (threadIdx.x == 0)
-        j.seg[blockIdx.x] = seg_length(red[0][0], red[1][0], red[2][0], n_points, n_lines, j.min_seg, j.busy_min);
+        j.seg[blockIdx.x] = seg_length(red[0][0], red[1][0], red[2][0], n_points, n_lines, j, blockIdx.x);
 }
 
 __device__ inline void pair_counts(int64_t p, int64_t n_pairs, const int64_t* __restrict__ ranges,
@@ -216,7 +217,7 @@ __global__ __launch_bounds__(kSmallThreads) void plan_small_kernel(PlanJobs jobs
                 mx = max(mx, part[1][w]);
                 sum += part[2][w];
             }
-            j.seg[st] = seg_length(busy, mx, sum, n_points, n_lines, j.min_seg, j.busy_min);
+            j.seg[st] = seg_length(busy, mx, sum, n_points, n_lines, j, st);
         }
         __syncthreads();
     }
