@@ -162,9 +162,11 @@ const char* hk_last_error(const hk_ctx* ctx);
  * the host for host arrays, by a kernel for device arrays); HK_EINVAL names
  * the first offending line, and a rejected list leaves the context
  * unchanged.  A list not already in non-decreasing nu is ordered on the
- * device by a stable radix sort of nu's bit patterns (temporary device
- * memory of ~24 B per line, released on return; a host list is first copied
- * as it is).  Synchronous: the arrays may be freed or rewritten on return. */
+ * device by a stable sort of nu's bit patterns (sorted chunks that are merged,
+ * above 2^24 lines radix passes over the whole list; device memory of ~24 B
+ * per line, kept by the context for the next list up to 64 MiB and released on
+ * return above; a host list is first copied as it is).  Synchronous: the
+ * arrays may be freed or rewritten on return. */
 int hk_load_lines(hk_ctx* ctx, const hk_lines* lines, const hk_species* species, int lines_on_device);
 
 /* ---- Input (§2.3, §3.5): HITRAN / HITEMP line records -------------------- */
@@ -210,8 +212,8 @@ int hk_read_par(const char* path, int64_t first, int32_t molecule, const hk_line
  * wavenumber-ordered piece of a list, a dense band) the Gauss-Hermite sum is
  * split at fixed line-index segments whose sums are then added in segment
  * order.  In binary64 a line's Gauss-Hermite terms over a tile of points far
- * from it are interpolated from Chebyshev nodes of the tile, to below 4e-17
- * of each term.  Results are bitwise reproducible, do not depend on the
+ * from it are interpolated from Chebyshev nodes of the tile (where more than a
+ * few lines reach it), to below 4e-17 of each term.  Results are bitwise reproducible, do not depend on the
  * tuning options, and agree bit for bit with hk_tables.
  *
  * kappa is [device] double[n_points] for both precisions.  comp must be
@@ -319,7 +321,8 @@ int hk_kdist_noalloc(hk_ctx* ctx, const void* kappa, int precision, int64_t n_po
  * n_lines * 96 B + n_points * 8 B per state in binary32, n_lines * 160 B +
  * n_points * 8 B in binary64, plus up to 6 n_points * 8 B of partial sums per
  * state whose tiles are split); the batch size is "tables_batch" states, or
- * (0, the default) as many as fit in "tables_mem_mib".  Each batch's work
+ * (0, the default) as many as fit in "tables_mem_mib", and at most as many as
+ * one launch holds the work items of.  Each batch's work
  * plan is read back once to size its launches (one stream synchronisation
  * per batch).  On the first call for a (precision, line count, grid size,
  * cutoff/dnu) the binary32 wing tile shape is chosen by timing 2, 4 and 8
@@ -340,8 +343,9 @@ int hk_tables(hk_ctx* ctx, const hk_state* states, int32_t n_states, const hk_gr
 /* Least-squares Chebyshev fit of ln kappa(y) per bin (§2.6), solved by the
  * QR decomposition of the design matrix A[i][c] = T_c(t_i),
  * t_i = 2 y_i - 1, y_i = (i + 1/2)/M for the i-th smallest of the bin's M
- * values (one thin Householder QR per bin size, computed on the host and
- * cached; per bin the kernel forms Q^T d and solves R C = Q^T d).
+ * values (one thin QR per bin size, cached: by Householder reflections on the
+ * host below 512 points, by Cholesky on the device from there on; per bin the
+ * kernels form Q^T d and solve R C = Q^T d).
  *   sorted   [device] the bins sorted ascending, as hk_kdist's sorted_out
  *            (double for HK_F64, float for HK_F32_KAHAN keys)
  *   coef_out [device] double [n_bins][n_coef]
@@ -453,7 +457,8 @@ int hk_gauss_legendre(int32_t n, double* g, double* w);
 
 /* Tuning knobs (results do not depend on them; only speed and memory do):
  *   "f64_points_per_lane"  4 (default) or 8; kept for callers that set it:
- *                          the binary64 kernel has one shape per grid size.
+ *                          the binary64 kernel has its shape from the list
+ *                          and the grid.
  *   "f32_points_per_lane"  2, 4 or 8 for the binary32 kernel (default 4).
  *   "tables_batch"         states per hk_tables launch, 0 = automatic
  *                          (default).
@@ -476,7 +481,8 @@ int hk_gauss_legendre(int32_t n, double* g, double* w);
  * Unknown names or values: HK_EINVAL. */
 int hk_set_option(hk_ctx* ctx, const char* name, int64_t value);
 /* Reads a knob into *value; also, read-only: "tables_points_per_lane", the
- * tile shape the last hk_tables call used (0 before any); "wing_items", the
+ * tile shape the last hk_tables call used (0 before any; binary64: the
+ * "f64_points_per_lane" setting, which its kernel does not read); "wing_items", the
  * work items of the last wing launch (one per grid tile and state unless
  * tiles were split into line segments); "wing_segment_lines", the segment
  * length of that launch's first state (0: not split).  The last two wait

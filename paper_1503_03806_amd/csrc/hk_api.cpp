@@ -183,7 +183,7 @@ struct hk_ctx {
     DevBuf check_part;    // of a list in device memory
     DevBuf line_scratch;  // the last unordered list's sort, up to kKeepSortScratch
     bool have_run = false;
-    int f64_points_per_lane = 4;  // tile shape of the binary64 opacity kernel (4 or 8)
+    int f64_points_per_lane = 4;  // 4 or 8, read by no kernel (the binary64 wing has its shape from the list and the grid)
     int f32_points_per_lane = 4;  // tile shape of the binary32 opacity kernel
     int wing_edge_paths = 1;      // 0: window-edge runs take the general path (same bits)
     int tables_overlap = 0;       // 1: tables run the series beside the wing on the second stream
@@ -196,7 +196,7 @@ struct hk_ctx {
     int64_t tables_mem = (int64_t)32 << 30;
     int tables_autotune = 1;
     int32_t last_tables_states = 0;  // > 0: hk_stats reports that hk_tables call
-    int tables_ppl_used = 0;          // tile shape of the last hk_tables call
+    int tables_ppl_used = 0;          // tile shape of the last hk_tables call (binary64: the setting above)
     struct Tuned {  // binary32
         int64_t n_lines, n_points, cut_steps;
         int ppl;

@@ -65,11 +65,11 @@ __device__ inline double qrcp(double den)
 // are kept per tile, and one polynomial per tile gives the sums at its
 // points.  The tiles form three levels (a work item's block of 4 kSub points,
 // its four wavefronts' kSub, their four kLeaf) or, with kSub = kLeaf, two; a
-// line is taken at the largest
-// tile that admits it (far_at is inherited: a tile inside an admitting one
-// admits the line too), and point by point only in the leaves that do not:
+// line is taken at the largest tile that admits it (a tile inside an admitting
+// one admits the line too), and point by point only in the leaves that do not:
 // those near its centre, or where its window, or its boundary between the
-// two rules or with the series, ends inside the leaf.
+// two rules or with the series, ends inside the leaf.  Items of few lines are
+// taken point by point throughout.
 //
 // The error of interpolating 1/(x - p) at the roots of T_N is
 // T_N(x)/T_N(p) of the value, pointwise.  The rules' poles (nu0 -+ i Gamma_L,
@@ -84,7 +84,9 @@ __device__ inline double qrcp(double den)
 // point evaluations in place of 2e4, and the kernel alone takes 1.22 ms
 // against 6.9 ms with every line at every point; 3e6 lines x 1e6 points with
 // 5e3 points per window 2.6 against 9.7 ms, 1e5 lines x 4e5 points 0.16
-// against 0.49 ms.
+// against 0.49 ms.  More than 128 registers cost a wavefront per SIMD: what is
+// added here is checked against that (131: 3e6 lines x 1e6 points 3590 -> 3690
+// us a step, in 128 with spills).
 constexpr int kFarNodes = kWingNodes;  // 24
 constexpr int kFarRatio = 3;
 constexpr int kLeaf = 64;

@@ -199,8 +199,8 @@ __global__ __launch_bounds__(kThreads) void resample_solve_kernel(BinSet<K> whol
 // ---- the factors of the design matrix ----
 //
 // Cholesky QR: A^T A = R^T R, Q = A R^-1.  For M >= 512 the columns T_c on the
-// equispaced t_i are close to orthogonal (condition number <= 7 for 32
-// coefficients), so forming A^T A loses at most a factor 49; it, its Cholesky
+// equispaced t_i are close to orthogonal (condition number at most 7.01, for 32
+// coefficients), so forming A^T A loses at most a factor 50; it, its Cholesky
 // factor, the inverse and Q's sums are taken in pairs of binary64 numbers
 // (106 bits), so that Q and R are A's factors rounded once.  Below 512 points
 // the condition number rises (it is unbounded as M nears the number of
