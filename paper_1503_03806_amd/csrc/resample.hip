@@ -499,7 +499,7 @@ __global__ __launch_bounds__(kThreads) void transmission_short_kernel(const K* _
 // segments' go to part and are added by transmission_sum_kernel.  Bound: the
 // VALU work of the exponentials left.  (100 bins of 1e4 x 500 masses over 48
 // decades: 680 us with a mass per thread over the whole bin and the library's
-// exp throughout, 240 us; 3 bins of 2.7e4 x 37 masses 1790 -> 29 us.)
+// exp throughout, 230 us; 3 bins of 2.7e4 x 37 masses 1790 -> 29 us.)
 constexpr int kDirectWaves = 8;
 template <typename K>
 __global__ __launch_bounds__(64 * kDirectWaves) void transmission_direct_kernel(const K* __restrict__ sorted,
